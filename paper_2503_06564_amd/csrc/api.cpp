@@ -60,8 +60,7 @@ struct trdq_rotation : trdq::Rotation {};
 struct trdq_layer {
     Table table;
     int K = 0, N = 0, wbits = 0;
-    std::vector<trdq_weights *> w;     // one per group (H_t depends on t)
-    std::vector<float *> diag;         // device copies of the groups' diagonals (null = ones)
+    std::vector<trdq_weights *> w;     // one per group (H_t depends on t), with its copy of the diagonal (null = ones)
     std::vector<char> set;
 };
 
@@ -169,94 +168,99 @@ void trdq_table_destroy(trdq_table *t)
 
 namespace {
 
-// Shared body of the two weight-preparation entry points.  perm_dev == nullptr: H_t(W) of Eq. 10
-// with one rotation; otherwise the full H_t(W) of Eq. 9 (rotation, P^T, rotation).
+// One device allocation per weight set (an allocation and its release cost 50-100 us each, more than the
+// kernels that fill it): codes, their block-tiled copy where the width has one, scales, column sums, the
+// preparation's block maxima, and the diagonal for a handle that keeps a copy.
+trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
+{
+    const int K = w->K, N = w->N, nb = K / trdq::kBlock;
+    const bool w4 = w->wbits == 4;
+    const size_t code_bytes = w4 ? (size_t)K * N / 2 : (size_t)K * N;
+    // widths the block-tiled products take: whole 144-channel tiles (int8), whole 128-channel tiles (int4)
+    const bool tiled = !asym && N % (w4 ? 128 : 144) == 0;
+    size_t total = 0;
+    auto take = [&](size_t bytes) { const size_t at = total; total += (bytes + 255) / 256 * 256; return at; };
+    const size_t at_codes = take(code_bytes), at_tiled = tiled ? take(code_bytes) : 0;
+    const size_t at_scales = take((w4 ? (size_t)nb * N : (size_t)N) * sizeof(float));
+    const size_t at_colsum = take((size_t)N * sizeof(float));          // int32 sums, or the scaled float ones of int4 codes
+    const size_t at_zcw = asym ? take((size_t)N * sizeof(int32_t)) : 0;
+    const size_t at_amax = take((size_t)nb * N * sizeof(float));
+    const size_t at_diag = with_diag ? take((size_t)K * sizeof(float)) : 0;
+    if (hipMalloc(&w->block, total) != hipSuccess) { w->block = nullptr; (void)hipGetLastError(); return TRDQ_ERR_ALLOC; }
+    char *const base = static_cast<char *>(w->block);
+    w->codes = base + at_codes;
+    w->codes_tiled = tiled ? base + at_tiled : nullptr;
+    w->scales = reinterpret_cast<float *>(base + at_scales);
+    if (w4) w->colsumw = reinterpret_cast<float *>(base + at_colsum);
+    else w->colsum = reinterpret_cast<int32_t *>(base + at_colsum);
+    w->zcw = asym ? reinterpret_cast<int32_t *>(base + at_zcw) : nullptr;
+    w->amax = reinterpret_cast<float *>(base + at_amax);
+    w->diag = with_diag ? reinterpret_cast<float *>(base + at_diag) : nullptr;
+    return TRDQ_OK;
+}
+
+// Fills an allocated weight set from W_dev on `st` and waits for it.  perm_dev == nullptr: H_t(W) of Eq. 10 with
+// one rotation; otherwise the full H_t(W) of Eq. 9 (rotation, P^T, rotation).  rot / rot2: dense blocks.
+trdq_status fill_weights(trdq_weights *w, const float *W_dev, const float *diag_dev, const int32_t *perm_dev,
+                         const trdq::Rotation *rot, const trdq::Rotation *rot2, hipStream_t st)
+{
+    const int K = w->K, N = w->N;
+    const float half = 0.08838834764831845f;            // 1 / sqrt(128)
+    const size_t bytes = (size_t)K * N * sizeof(float);
+    float *Wrot = nullptr, *Wrot2 = nullptr;            // rotated weights, where more than one kernel needs them
+    if (((rot || perm_dev) && hipMalloc(reinterpret_cast<void **>(&Wrot), bytes) != hipSuccess) ||
+        (rot2 && hipMalloc(reinterpret_cast<void **>(&Wrot2), bytes) != hipSuccess)) {
+        (void)hipGetLastError();
+        if (Wrot) (void)hipFree(Wrot);
+        return TRDQ_ERR_ALLOC;
+    }
+    hipError_t e;
+    if (rot) {
+        // dense orthonormal blocks (nothing to normalise afterwards); Eq. 10 in full: rows gathered through the
+        // permutation and rotated a second time
+        e = trdq::launch_prepare_rotate_dense(W_dev, K, N, rot->diag, nullptr, rot->R, Wrot, w->amax, st);
+        if (e == hipSuccess && rot2) e = trdq::launch_prepare_rotate_dense(Wrot, K, N, nullptr, perm_dev, rot2->R, Wrot2, w->amax, st);
+        if (e == hipSuccess) e = trdq::launch_prepare_quant(rot2 ? Wrot2 : Wrot, nullptr, nullptr, false, 1.0f, *w, w->amax, nullptr, st);
+    } else if (perm_dev) {
+        // the Hadamard form of Eq. 9: two unnormalised rotations, 1/128
+        e = trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, nullptr, Wrot, st);
+        if (e == hipSuccess) e = trdq::launch_prepare_quant(Wrot, nullptr, perm_dev, true, 0.0078125f, *w, w->amax, nullptr, st);
+    } else {
+        e = trdq::launch_prepare_quant(W_dev, diag_dev, nullptr, true, half, *w, w->amax, w->diag, st);
+    }
+    const bool ok = e == hipSuccess && hipStreamSynchronize(st) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    if (Wrot) (void)hipFree(Wrot);
+    if (Wrot2) (void)hipFree(Wrot2);
+    return ok ? TRDQ_OK : TRDQ_ERR_HIP;
+}
+
+// Shared body of the weight-preparation entry points; with_diag: the set keeps a copy of diag_dev.
 trdq_status prepare_weights_impl(const float *W_dev, int K, int N, const float *diag_dev, const int32_t *perm_dev,
                                  int block, int wbits, void *stream, trdq_weights **out,
-                                 const trdq::Rotation *rot = nullptr, const trdq::Rotation *rot2 = nullptr)
+                                 const trdq::Rotation *rot = nullptr, const trdq::Rotation *rot2 = nullptr,
+                                 bool with_diag = false)
 {
     if (!out) return TRDQ_ERR_NULL;
     *out = nullptr;
     if (!W_dev) return TRDQ_ERR_NULL;
     if (block != trdq::kBlock || (wbits != 8 && wbits != 6 && wbits != 4)) return TRDQ_ERR_UNSUPPORTED;
     if (K <= 0 || N <= 0 || K % trdq::kBlock != 0 || N % 16 != 0) return TRDQ_ERR_SHAPE;
-    const int qbits = wbits;
-    if (wbits == 6) wbits = 8;      // 6-bit codes live in the 8-bit layout; only the quantiser's range differs
-
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    const int nb = K / trdq::kBlock;
     trdq_weights *w = new (std::nothrow) trdq_weights;
     if (!w) return TRDQ_ERR_ALLOC;
-    w->K = K; w->N = N; w->wbits = wbits; w->qbits = qbits;
+    w->K = K; w->N = N; w->qbits = wbits;
+    w->wbits = wbits == 6 ? 8 : wbits;      // 6-bit codes live in the 8-bit layout; only the quantiser's range differs
     w->rotation = rot ? (rot2 ? trdq::kRotDenseRPR : trdq::kRotDense) : (perm_dev ? trdq::kRotHadamardRPR : trdq::kRotHadamard);
-    float *Wrot = nullptr, *Wrot2 = nullptr, *amax = nullptr;
-    const size_t code_bytes = wbits == 8 ? (size_t)K * N : (size_t)K * N / 2;
-    const size_t scale_count = wbits == 8 ? (size_t)N : (size_t)nb * N;
-    trdq_status rc = TRDQ_OK;
-    bool ok = true;
-    if (hipGetDevice(&w->device) != hipSuccess) { rc = TRDQ_ERR_HIP; goto fail; }
-    if (hipMalloc(&w->codes, code_bytes) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&w->scales), scale_count * sizeof(float)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&Wrot), (size_t)K * N * sizeof(float)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&amax), (size_t)nb * N * sizeof(float)) != hipSuccess ||
-        (perm_dev && hipMalloc(reinterpret_cast<void **>(&Wrot2), (size_t)K * N * sizeof(float)) != hipSuccess) ||
-        (wbits == 8 && hipMalloc(reinterpret_cast<void **>(&w->colsum), (size_t)N * sizeof(int32_t)) != hipSuccess) ||
-        (wbits == 4 && hipMalloc(reinterpret_cast<void **>(&w->colsumw), (size_t)N * sizeof(float)) != hipSuccess)) {
-        rc = TRDQ_ERR_ALLOC;
-        goto fail;
+    trdq_status rc = hipGetDevice(&w->device) == hipSuccess ? TRDQ_OK : TRDQ_ERR_HIP;
+    if (rc == TRDQ_OK) rc = alloc_weights(w, with_diag);
+    if (rc == TRDQ_OK) rc = fill_weights(w, W_dev, diag_dev, perm_dev, rot, rot2, static_cast<hipStream_t>(stream));
+    if (rc != TRDQ_OK) {
+        (void)hipGetLastError();
+        trdq_weights_destroy(w);
+        return rc;
     }
-    if (rot && rot2) {
-        // Eq. 10 in full with dense blocks: first rotation, rows gathered through the permutation, second rotation
-        ok = trdq::launch_prepare_rotate_dense(W_dev, K, N, rot->diag, nullptr, rot->R, Wrot, amax, st) == hipSuccess &&
-             trdq::launch_prepare_rotate_dense(Wrot, K, N, nullptr, perm_dev, rot2->R, Wrot2, amax, st) == hipSuccess &&
-             trdq::launch_prepare_quant(Wrot2, amax, K, N, qbits, 1.0f, w->codes, w->scales, st) == hipSuccess;
-    } else if (rot) {
-        // dense orthonormal blocks: nothing to normalise afterwards
-        ok = trdq::launch_prepare_rotate_dense(W_dev, K, N, rot->diag, nullptr, rot->R, Wrot, amax, st) == hipSuccess &&
-             trdq::launch_prepare_quant(Wrot, amax, K, N, qbits, 1.0f, w->codes, w->scales, st) == hipSuccess;
-    } else if (!(ok = trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, nullptr, Wrot, amax, st) == hipSuccess)) {
-    } else if (perm_dev) {
-        // (the Hadamard form of Eq. 9)
-        // rows gathered through the permutation, rotated again; two unnormalised rotations: 1/128
-        ok = trdq::launch_prepare_rotate(Wrot, K, N, nullptr, perm_dev, Wrot2, amax, st) == hipSuccess &&
-             trdq::launch_prepare_quant(Wrot2, amax, K, N, qbits, 0.0078125f, w->codes, w->scales, st) == hipSuccess;
-    } else {
-        ok = trdq::launch_prepare_quant(Wrot, amax, K, N, qbits, 0.08838834764831845f, w->codes, w->scales, st) == hipSuccess;
-    }
-    if (ok && wbits == 8) ok = trdq::launch_weight_colsum(w->codes, K, N, w->colsum, st) == hipSuccess;
-    // widths the block-tiled product takes (whole 144-channel tiles): a second copy of the codes in 1 KB blocks
-    if (ok && wbits == 8 && N % 144 == 0) {
-        if (hipMalloc(&w->codes_tiled, code_bytes) != hipSuccess) { rc = TRDQ_ERR_ALLOC; goto fail; }
-        ok = trdq::launch_retile_rows(static_cast<const int8_t *>(w->codes), static_cast<int8_t *>(w->codes_tiled), N, K,
-                                      true, st) == hipSuccess;
-    }
-    if (ok && wbits == 4) ok = trdq::launch_weight_colsumw4(w->codes, w->scales, K, N, w->colsumw, st) == hipSuccess;
-    // ... and of the packed int4 codes in 512-byte blocks (whole 128-channel tiles)
-    if (ok && wbits == 4 && N % 128 == 0) {
-        if (hipMalloc(&w->codes_tiled, code_bytes) != hipSuccess) { rc = TRDQ_ERR_ALLOC; goto fail; }
-        ok = trdq::launch_retile_w4_codes(w->codes, w->codes_tiled, N, K, st) == hipSuccess;
-    }
-    if (!ok || hipStreamSynchronize(st) != hipSuccess) {
-        rc = TRDQ_ERR_HIP;
-        goto fail;
-    }
-    (void)hipFree(Wrot);
-    if (Wrot2) (void)hipFree(Wrot2);
-    (void)hipFree(amax);
     *out = w;
     return TRDQ_OK;
-fail:
-    (void)hipGetLastError();
-    if (Wrot) (void)hipFree(Wrot);
-    if (Wrot2) (void)hipFree(Wrot2);
-    if (amax) (void)hipFree(amax);
-    if (w->codes) (void)hipFree(w->codes);
-    if (w->codes_tiled) (void)hipFree(w->codes_tiled);
-    if (w->scales) (void)hipFree(w->scales);
-    if (w->colsum) (void)hipFree(w->colsum);
-    if (w->colsumw) (void)hipFree(w->colsumw);
-    delete w;
-    return rc;
 }
 
 }  // namespace
@@ -276,43 +280,34 @@ trdq_status trdq_prepare_weights_asym(const float *W_dev, int K, int N, const fl
     if (block != trdq::kBlock || wbits != 8) return TRDQ_ERR_UNSUPPORTED;
     if (K <= 0 || N <= 0 || K % trdq::kBlock != 0 || N % 16 != 0) return TRDQ_ERR_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int nb = K / trdq::kBlock;
     trdq_weights *w = new (std::nothrow) trdq_weights;
     if (!w) return TRDQ_ERR_ALLOC;
     w->K = K; w->N = N; w->wbits = 8; w->qbits = 8;
     w->rotation = trdq::kRotHadamard;
-    float *Wrot = nullptr, *amax = nullptr, *lohi = nullptr;
-    trdq_status rc = TRDQ_OK;
-    bool ok = true;
-    if (hipGetDevice(&w->device) != hipSuccess) { rc = TRDQ_ERR_HIP; goto fail; }
-    if (hipMalloc(&w->codes, (size_t)K * N) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&w->scales), (size_t)N * sizeof(float)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&w->colsum), (size_t)N * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&w->zcw), (size_t)N * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&Wrot), (size_t)K * N * sizeof(float)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&amax), (size_t)nb * N * sizeof(float)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&lohi), (size_t)2 * N * sizeof(float)) != hipSuccess) {
+    float *Wrot = nullptr, *lohi = nullptr;             // one allocation: the rotated weights and the column ranges
+    trdq_status rc = hipGetDevice(&w->device) == hipSuccess ? TRDQ_OK : TRDQ_ERR_HIP;
+    if (rc == TRDQ_OK) rc = alloc_weights(w, false, true);
+    if (rc == TRDQ_OK && hipMalloc(reinterpret_cast<void **>(&Wrot), ((size_t)K * N + 2 * (size_t)N) * sizeof(float)) != hipSuccess) {
+        Wrot = nullptr;
         rc = TRDQ_ERR_ALLOC;
-        goto fail;
     }
-    ok = trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, nullptr, Wrot, amax, st) == hipSuccess &&
-         trdq::launch_prepare_quant_asym(Wrot, lohi, K, N, 0.08838834764831845f, w->codes, w->scales, w->zcw, st) == hipSuccess &&
-         trdq::launch_weight_colsum(w->codes, K, N, w->colsum, st) == hipSuccess;
-    if (!ok || hipStreamSynchronize(st) != hipSuccess) { rc = TRDQ_ERR_HIP; goto fail; }
-    (void)hipFree(Wrot); (void)hipFree(amax); (void)hipFree(lohi);
+    if (rc == TRDQ_OK) {
+        lohi = Wrot + (size_t)K * N;
+        const bool ok =
+            trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, nullptr, Wrot, st) == hipSuccess &&
+            trdq::launch_prepare_quant_asym(Wrot, lohi, K, N, 0.08838834764831845f, w->codes, w->scales, w->zcw, st) == hipSuccess &&
+            trdq::launch_weight_colsum(w->codes, K, N, w->colsum, st) == hipSuccess &&
+            hipStreamSynchronize(st) == hipSuccess;
+        if (!ok) rc = TRDQ_ERR_HIP;
+    }
+    if (Wrot) (void)hipFree(Wrot);
+    if (rc != TRDQ_OK) {
+        (void)hipGetLastError();
+        trdq_weights_destroy(w);
+        return rc;
+    }
     *out = w;
     return TRDQ_OK;
-fail:
-    (void)hipGetLastError();
-    if (Wrot) (void)hipFree(Wrot);
-    if (amax) (void)hipFree(amax);
-    if (lohi) (void)hipFree(lohi);
-    if (w->codes) (void)hipFree(w->codes);
-    if (w->scales) (void)hipFree(w->scales);
-    if (w->colsum) (void)hipFree(w->colsum);
-    if (w->zcw) (void)hipFree(w->zcw);
-    delete w;
-    return rc;
 }
 
 trdq_status trdq_weights_export_zero_points(const trdq_weights *w, int32_t *zw_host)
@@ -746,12 +741,7 @@ trdq_status trdq_weights_export_packed(const trdq_weights *w, uint8_t *packed_ho
 void trdq_weights_destroy(trdq_weights *w)
 {
     if (!w) return;
-    if (w->codes) (void)hipFree(w->codes);
-    if (w->codes_tiled) (void)hipFree(w->codes_tiled);
-    if (w->scales) (void)hipFree(w->scales);
-    if (w->colsum) (void)hipFree(w->colsum);
-    if (w->zcw) (void)hipFree(w->zcw);
-    if (w->colsumw) (void)hipFree(w->colsumw);
+    if (w->block) (void)hipFree(w->block);
     delete w;
 }
 
@@ -897,7 +887,7 @@ trdq_status trdq_xq_untile(const int8_t *Xt_dev, int64_t M, int K, int8_t *Xq_de
     if (M > 0 && (!Xt_dev || !Xq_dev)) return TRDQ_ERR_NULL;
     if (!aligned(Xt_dev, 16) || !aligned(Xq_dev, 16)) return TRDQ_ERR_SHAPE;
     if (M == 0) return TRDQ_OK;
-    return hip_status(trdq::launch_retile_rows(Xt_dev, Xq_dev, M, K, false, static_cast<hipStream_t>(stream)));
+    return hip_status(trdq::launch_xq_untile(Xt_dev, Xq_dev, M, K, static_cast<hipStream_t>(stream)));
 }
 
 int trdq_qgemm_tiled_supported(const trdq_weights *w, int64_t M)
@@ -1071,7 +1061,6 @@ trdq_status trdq_layer_create(const trdq_table *t, int K, int N, int wbits, trdq
     l->K = K; l->N = N; l->wbits = wbits;
     try {
         l->w.assign((size_t)t->n_groups, nullptr);
-        l->diag.assign((size_t)t->n_groups, nullptr);
         l->set.assign((size_t)t->n_groups, 0);
     } catch (...) {
         std::free(l->table.map);
@@ -1087,25 +1076,25 @@ trdq_status trdq_layer_set_group(trdq_layer *l, int g, const float *diag_dev, co
     if (!l || !W_dev) return TRDQ_ERR_NULL;
     if (g < 0 || g >= l->table.n_groups) return TRDQ_ERR_RANGE;
     if (diag_dev && !aligned(diag_dev, 16)) return TRDQ_ERR_SHAPE;
-    trdq_weights *w = nullptr;
-    trdq_status rc = trdq_prepare_weights(W_dev, l->K, l->N, diag_dev, trdq::kBlock, l->wbits, stream, &w);
-    if (rc != TRDQ_OK) return rc;
-    float *d = nullptr;
-    if (diag_dev) {
-        if (hipMalloc(reinterpret_cast<void **>(&d), sizeof(float) * (size_t)l->K) != hipSuccess) {
-            trdq_weights_destroy(w);
-            return TRDQ_ERR_ALLOC;
-        }
-        if (hipMemcpy(d, diag_dev, sizeof(float) * (size_t)l->K, hipMemcpyDeviceToDevice) != hipSuccess) {
-            (void)hipFree(d);
-            trdq_weights_destroy(w);
-            return TRDQ_ERR_HIP;
-        }
+    trdq_weights *&slot = l->w[(size_t)g];
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return TRDQ_ERR_HIP; }
+    if (slot && slot->device == dev && (slot->diag != nullptr) == (diag_dev != nullptr)) {
+        // Replacing a group by one of the same form: refilled where it is (releasing the old set and allocating
+        // another cost 0.1-0.2 ms).  As the release did, this waits for whatever still reads the old set on
+        // any stream.  A failure leaves the group unset.
+        if (hipDeviceSynchronize() != hipSuccess) { (void)hipGetLastError(); return TRDQ_ERR_HIP; }
+        l->set[(size_t)g] = 0;
+        trdq_status rc = fill_weights(slot, W_dev, diag_dev, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream));
+        if (rc == TRDQ_OK) l->set[(size_t)g] = 1;
+        return rc;
     }
-    if (l->w[(size_t)g]) trdq_weights_destroy(l->w[(size_t)g]);
-    if (l->diag[(size_t)g]) (void)hipFree(l->diag[(size_t)g]);
-    l->w[(size_t)g] = w;
-    l->diag[(size_t)g] = d;
+    trdq_weights *w = nullptr;
+    trdq_status rc = prepare_weights_impl(W_dev, l->K, l->N, diag_dev, nullptr, trdq::kBlock, l->wbits, stream, &w, nullptr,
+                                          nullptr, diag_dev != nullptr);
+    if (rc != TRDQ_OK) return rc;
+    if (slot) trdq_weights_destroy(slot);
+    slot = w;
     l->set[(size_t)g] = 1;
     return TRDQ_OK;
 }
@@ -1119,7 +1108,7 @@ trdq_status trdq_layer_forward(const trdq_layer *l, int step, const void *X_dev,
     const int g = l->table.map[step];
     if (!l->set[(size_t)g]) return TRDQ_ERR_MISMATCH;
     const trdq_weights *w = l->w[(size_t)g];
-    const float *d = l->diag[(size_t)g];
+    const float *d = w->diag;
     if (fused > 0 || (fused < 0 && trdq::fused_pays(M, l->K, l->N, w->wbits)))
         return trdq_linear_fused(X_dev, M, l->K, d, w, bias_dev, Y_dev, l->N, stream);
     if (!Xq_ws_dev || !sx_ws_dev) return TRDQ_ERR_NULL;
@@ -1148,8 +1137,6 @@ void trdq_layer_destroy(trdq_layer *l)
 {
     if (!l) return;
     for (trdq_weights *w : l->w) trdq_weights_destroy(w);
-    for (float *d : l->diag)
-        if (d) (void)hipFree(d);
     std::free(l->table.map);
     delete l;
 }

@@ -1,6 +1,15 @@
 // prepare_weights: H_t(W) = R^T . (Delta_t^-1 . W) of Eq. 10 and the symmetric weight
 // quantiser (per output channel for int8, per 128-row group and output channel for int4).
-// Offline, once per time-step group; two streaming kernels through a float32 scratch matrix.
+// Offline, once per time-step group.
+//
+// What bounds it: W is read (4 bytes an element) and the codes are written twice (row-major and
+// block-tiled), 6 bytes an element, 32 MB for a 1152 x 4608 set; the rest of a set's preparation is the
+// host's: device allocations and the final synchronisation.  So one Hadamard rotation goes without the
+// float32 scratch matrix that used to carry the rotated weights from one kernel to the next: int4 codes
+// need the maximum of their own 128-row block only and take one kernel, int8 codes need the maximum of
+// the whole column, which a first pass finds and a second one, rotating again from W (which the
+// memory-side cache still holds), uses.  The quantising kernel also writes the block-tiled codes and the
+// column sums, which were kernels of their own.
 #include "device_utils.h"
 #include "trdq_internal.h"
 
@@ -11,61 +20,103 @@ namespace {
 constexpr int kCols = 64;          // output channels per workgroup
 constexpr int kPrepThreads = 256;
 
-// Kernel 1: one workgroup rotates one 128-row block of 64 columns.
-//   Wrot[b*128 + j, n] = sum_k H[k][j] * W[row(b*128 + k), n] / d[b*128 + k]      (unnormalised H)
-//   amax[b, n]         = max_j |Wrot[b*128 + j, n]|
-// row(k) = k, or perm[k] (clamped to the matrix) when a permutation is given: the P^T factor of
-// Eq. 9 in front of the second rotation.
-__global__ __launch_bounds__(kPrepThreads) void prepare_rotate_kernel(
-    const float *__restrict__ W, int K, int N, const float *__restrict__ diag,
-    const int32_t *__restrict__ perm, float *__restrict__ Wrot, float *__restrict__ amax)
+// A workgroup holds one 128-row block of 64 columns: wave q the rows 32 q .. 32 q + 31, a lane one column.
+// Loads the block into v, row k through perm (clamped to the matrix) when a permutation is given -- the
+// P^T factor of Eq. 9 in front of the second rotation --, divided by the diagonal.
+__device__ __forceinline__ void load_block(const float *__restrict__ W, int K, int N, const float *__restrict__ diag,
+                                           const int32_t *__restrict__ perm, int b, int q, int n, bool col_ok,
+                                           float (&v)[32])
 {
-    __shared__ float tile[kBlock][kCols + 1];
-    __shared__ float part[4][kCols];
-    const int b = blockIdx.y;
-    const int n0 = blockIdx.x * kCols;
-    const int c = threadIdx.x % kCols;
-    const int q = threadIdx.x / kCols;     // 0..3
-    const int n = n0 + c;
-    const bool col_ok = n < N;
-
-    for (int k = q; k < kBlock; k += 4) {
-        float w = 0.0f;
-        if (col_ok) {
-            int row = b * kBlock + k;
-            if (perm) {
-                row = perm[row];
-                row = row < 0 ? 0 : (row >= K ? K - 1 : row);
-            }
-            w = W[(size_t)row * N + n];
-            if (diag) w = w / diag[b * kBlock + k];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        int row = b * kBlock + 32 * q + i;
+        if (perm) {
+            row = perm[row];
+            row = row < 0 ? 0 : (row >= K ? K - 1 : row);
         }
-        tile[k][c] = w;
+        v[i] = col_ok ? W[(size_t)row * N + n] : 0.0f;
     }
-    __syncthreads();
-    // 7 butterfly stages down the rows; 64 pairs per column per stage, 16 per thread
-    for (int h = 1; h < kBlock; h <<= 1) {
-        for (int pr = q; pr < kBlock / 2; pr += 4) {
-            const int lo = ((pr / h) * 2 * h) + (pr % h);
-            const float a = tile[lo][c], bb = tile[lo + h][c];
-            tile[lo][c] = a + bb;
-            tile[lo + h][c] = a - bb;
-        }
-        __syncthreads();
+    if (diag) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) v[i] = v[i] / diag[b * kBlock + 32 * q + i];
     }
-    float m = 0.0f;
-    for (int k = q; k < kBlock; k += 4) {
-        const float w = tile[k][c];
-        m = fmaxf(m, fabsf(w));
-        if (col_ok) Wrot[(size_t)(b * kBlock + k) * N + n] = w;
-    }
-    part[q][c] = m;
-    __syncthreads();
-    if (q == 0 && col_ok)
-        amax[(size_t)b * N + n] = fmaxf(fmaxf(part[0][c], part[1][c]), fmaxf(part[2][c], part[3][c]));
 }
 
-// Kernel 1 with a dense rotation block in place of the butterflies (H_t(W) = R^T (Delta^-1 W) with
+// Unnormalised H_128 down the column: five butterfly stages inside the lane, the last two across the four
+// waves through LDS (one exchange: a lane reads the other waves' values of its row numbers and forms its
+// own of the four results).
+__device__ __forceinline__ void rotate_block(float (&v)[32], int q, int c, float (&tile)[kBlock][kCols])
+{
+#pragma unroll
+    for (int h = 1; h < 32; h <<= 1) {
+#pragma unroll
+        for (int i0 = 0; i0 < 32; i0 += 2 * h) {
+#pragma unroll
+            for (int i = i0; i < i0 + h; ++i) {
+                const float a = v[i], bb = v[i + h];
+                v[i] = a + bb;
+                v[i + h] = a - bb;
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 32; ++i) tile[32 * q + i][c] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        const float t0 = tile[i][c], t1 = tile[32 + i][c], t2 = tile[64 + i][c], t3 = tile[96 + i][c];
+        const float lo = (q & 1) ? t0 - t1 : t0 + t1, hi = (q & 1) ? t2 - t3 : t2 + t3;
+        v[i] = (q & 2) ? lo - hi : lo + hi;
+    }
+}
+
+// Rotation of the whole matrix into a scratch matrix (in front of a permutation, or of the asymmetric quantiser):
+//   Wrot[b*128 + j, n] = sum_k H[k][j] * W[row(b*128 + k), n] / d[b*128 + k]      (unnormalised H)
+__global__ __launch_bounds__(kPrepThreads) void prepare_rotate_kernel(
+    const float *__restrict__ W, int K, int N, const float *__restrict__ diag,
+    const int32_t *__restrict__ perm, float *__restrict__ Wrot)
+{
+    __shared__ float tile[kBlock][kCols];
+    const int b = blockIdx.y, c = threadIdx.x % kCols, q = __builtin_amdgcn_readfirstlane(threadIdx.x / kCols);
+    const int n = blockIdx.x * kCols + c;
+    const bool col_ok = n < N;
+    float v[32];
+    load_block(W, K, N, diag, perm, b, q, n, col_ok, v);
+    rotate_block(v, q, c, tile);
+    if (!col_ok) return;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) Wrot[(size_t)(b * kBlock + 32 * q + i) * N + n] = v[i];
+}
+
+// First pass of the int8 quantiser: amax[b, n] = the largest magnitude of the rotated block.  Also clears the
+// column sums that the second pass adds to, and copies the diagonal for a handle that keeps one.
+__global__ __launch_bounds__(kPrepThreads) void prepare_absmax_kernel(
+    const float *__restrict__ W, int K, int N, const float *__restrict__ diag,
+    const int32_t *__restrict__ perm, float *__restrict__ amax, int32_t *__restrict__ colsum,
+    float *__restrict__ diag_copy)
+{
+    __shared__ float tile[kBlock][kCols];
+    __shared__ float part[4][kCols];
+    const int b = blockIdx.y, c = threadIdx.x % kCols, q = __builtin_amdgcn_readfirstlane(threadIdx.x / kCols);
+    const int n = blockIdx.x * kCols + c;
+    const bool col_ok = n < N;
+    float v[32];
+    load_block(W, K, N, diag, perm, b, q, n, col_ok, v);
+    if (diag_copy && blockIdx.x == 0 && threadIdx.x < kBlock)
+        diag_copy[b * kBlock + threadIdx.x] = diag[b * kBlock + threadIdx.x];
+    rotate_block(v, q, c, tile);
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) m = fmaxf(m, fabsf(v[i]));
+    part[q][c] = m;
+    __syncthreads();
+    if (q == 0 && col_ok) {
+        amax[(size_t)b * N + n] = fmaxf(fmaxf(part[0][c], part[1][c]), fmaxf(part[2][c], part[3][c]));
+        if (b == 0) colsum[n] = 0;
+    }
+}
+
+// The rotation with a dense block in place of the butterflies (H_t(W) = R^T (Delta^-1 W) with
 // the blocks of the BlockDiag equation as arbitrary orthogonal matrices):
 //   Wrot[b*128 + j, n] = sum_k R_b[k][j] * W[b*128 + k, n] / d[b*128 + k]
 // Wave q of the workgroup produces rows j = 32 q .. 32 q + 31 of 64 columns; the row of R_b it
@@ -117,69 +168,102 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_rotate_dense_kernel(
         amax[(size_t)b * N + n] = fmaxf(fmaxf(part[0][c], part[1][c]), fmaxf(part[2][c], part[3][c]));
 }
 
-// Kernel 2: quantise and transpose one 128-row block of 64 columns into the K-contiguous
-// layouts the product kernels read (see Weights in trdq_internal.h).
+// Quantises one 128-row block of 64 columns into the layouts the product kernels read (see Weights in
+// trdq_internal.h): K-contiguous rows, and where `tiled` is given the block-tiled copy.
 //   wbits 8: scale[n]    = max_b amax[b, n] * norm / 127   (qmax = 31 in the same layout: 6-bit codes)
-//   wbits 4: scale[b, n] = amax[b, n]       * norm / 7
+//   wbits 4: scale[b, n] = max over the block * norm / 7
 // norm undoes the unnormalised butterflies: 1/sqrt(128) after one rotation, 1/128 after two.
-//   code = rint(Wrot * qmax / amax)   (ties to even; amax == 0 -> 0)
-template <int WBITS>
+//   code = rint(w * qmax / amax)   (ties to even; amax == 0 -> 0)
+// ROTATE: W is rotated here (int4 codes then find their maximum here, too); otherwise W holds rotated
+// values and amax their block maxima.  A lane ends with 32 consecutive codes of one channel: two
+// 16-byte pieces of its row (a 128-byte line per channel from the four waves), 256 consecutive bytes
+// over 16 lanes in the tiled form.  Measured, average over the four int8 linears of a block of width 1152: 9 us
+// for the maxima and 10 us here, against 34 + 17 + 7 + 6 us for rotation, quantiser, column sums and
+// second copy as kernels of their own with float32 values between them.
+template <int WBITS, bool ROTATE>
 __global__ __launch_bounds__(kPrepThreads) void prepare_quant_kernel(
-    const float *__restrict__ Wrot, const float *__restrict__ amax, int K, int N, float norm, float qmax,
-    void *__restrict__ codes, float *__restrict__ scales)
+    const float *__restrict__ W, int K, int N, const float *__restrict__ diag, const int32_t *__restrict__ perm,
+    const float *__restrict__ amax, float norm, float qmax, void *__restrict__ codes, void *__restrict__ tiled,
+    float *__restrict__ scales, int32_t *__restrict__ colsum, float *__restrict__ diag_copy)
 {
-    __shared__ int8_t q8[kCols][kBlock + 16];
-    __shared__ float inv_s[kCols];
+    __shared__ float tile[kBlock][kCols];
+    __shared__ float part[4][kCols];
     const int nb = K / kBlock;
-    const int b = blockIdx.y;
-    const int n0 = blockIdx.x * kCols;
-
-    if (threadIdx.x < kCols) {
-        const int n = n0 + threadIdx.x;
-        float a = 0.0f;
-        if (n < N) {
-            if (WBITS == 8) {
-                for (int bb = 0; bb < nb; ++bb) a = fmaxf(a, amax[(size_t)bb * N + n]);
-                if (b == 0) scales[n] = a * (norm / qmax);
-            } else {
-                a = amax[(size_t)b * N + n];
-                scales[(size_t)b * N + n] = a * (norm / qmax);
-            }
-        }
-        inv_s[threadIdx.x] = a > 0.0f ? qmax / a : 0.0f;
-    }
-    __syncthreads();
-    const int c = threadIdx.x % kCols;
-    const int q = threadIdx.x / kCols;
-    const int n = n0 + c;
-    for (int k = q; k < kBlock; k += 4) {
-        float w = n < N ? Wrot[(size_t)(b * kBlock + k) * N + n] : 0.0f;
-        q8[c][k] = (int8_t)(quant_bits(w, inv_s[c]) & 0xFF);
-    }
-    __syncthreads();
+    const int b = blockIdx.y, c = threadIdx.x % kCols, q = __builtin_amdgcn_readfirstlane(threadIdx.x / kCols);
+    const int n = blockIdx.x * kCols + c;
+    const bool col_ok = n < N;
+    float v[32];
+    load_block(W, K, N, ROTATE ? diag : nullptr, ROTATE ? perm : nullptr, b, q, n, col_ok, v);
+    float a = 0.0f;
     if (WBITS == 8) {
-        // 64 columns x 128 bytes -> 16-byte chunks, K contiguous
-        int8_t *out = static_cast<int8_t *>(codes);
-        for (int ch = threadIdx.x; ch < kCols * (kBlock / 16); ch += kPrepThreads) {
-            const int cc = ch / (kBlock / 16), kk = (ch % (kBlock / 16)) * 16;
-            if (n0 + cc < N)
-                *reinterpret_cast<uint4 *>(out + (size_t)(n0 + cc) * K + b * kBlock + kk) =
-                    *reinterpret_cast<const uint4 *>(&q8[cc][kk]);
+        if (col_ok)
+            for (int bb = q; bb < nb; bb += 4) a = fmaxf(a, amax[(size_t)bb * N + n]);
+    } else {
+        if (diag_copy && blockIdx.x == 0 && threadIdx.x < kBlock)
+            diag_copy[b * kBlock + threadIdx.x] = diag[b * kBlock + threadIdx.x];
+        if (!ROTATE && col_ok) a = amax[(size_t)b * N + n];
+    }
+    if (ROTATE) rotate_block(v, q, c, tile);
+    if (WBITS == 4 && ROTATE) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) a = fmaxf(a, fabsf(v[i]));
+    }
+    part[q][c] = a;
+    __syncthreads();
+    a = fmaxf(fmaxf(part[0][c], part[1][c]), fmaxf(part[2][c], part[3][c]));
+    if (q == 0 && col_ok) {
+        if (WBITS == 4) scales[(size_t)b * N + n] = a * (norm / qmax);
+        else if (b == 0) scales[n] = a * (norm / qmax);
+    }
+    const float inv = a > 0.0f ? qmax / a : 0.0f;
+    uint32_t u[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) u[i] = quant_bits(v[i], inv);
+    const int k0 = b * kBlock + 32 * q;                // the lane's first input channel
+    if (WBITS == 8) {
+        if (colsum) {
+            int t = 0;
+#pragma unroll
+            for (int i = 0; i < 32; ++i) t += (int)(int8_t)(u[i] & 0xFF);
+            __syncthreads();
+            part[q][c] = __int_as_float(t);
+            __syncthreads();
+            if (q == 0 && col_ok)
+                atomicAdd(colsum + n, __float_as_int(part[0][c]) + __float_as_int(part[1][c]) +
+                                          __float_as_int(part[2][c]) + __float_as_int(part[3][c]));
+        }
+        if (!col_ok) return;
+        int8_t *const out = static_cast<int8_t *>(codes) + (size_t)n * K + k0;
+        int8_t *const blk = static_cast<int8_t *>(tiled) + ((size_t)(n >> 4) * (K >> 6) + (k0 >> 6)) * 1024 +
+                            ((k0 & 63) >> 4) * 256 + (n & 15) * 16;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            uint32_t w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                w[j] = pack4_low_bytes(u[16 * p + 4 * j], u[16 * p + 4 * j + 1], u[16 * p + 4 * j + 2], u[16 * p + 4 * j + 3]);
+            const uint4 piece = make_uint4(w[0], w[1], w[2], w[3]);
+            *reinterpret_cast<uint4 *>(out + 16 * p) = piece;
+            if (tiled) *reinterpret_cast<uint4 *>(blk + 256 * p) = piece;
         }
     } else {
+        if (!col_ok) return;
         // 8 consecutive k -> 4 bytes: byte j = code(k0+j) & 0xF | (code(k0+4+j) & 0xF) << 4
-        uint8_t *out = static_cast<uint8_t *>(codes);
-        for (int u = threadIdx.x; u < kCols * (kBlock / 8); u += kPrepThreads) {
-            const int cc = u / (kBlock / 8), k0 = (u % (kBlock / 8)) * 8;
-            if (n0 + cc < N) {
-                uint32_t word = 0;
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t lo = (uint8_t)q8[cc][k0 + j] & 0xFu;
-                    const uint32_t hi = (uint8_t)q8[cc][k0 + 4 + j] & 0xFu;
-                    word |= (lo | (hi << 4)) << (8 * j);
-                }
-                *reinterpret_cast<uint32_t *>(out + (size_t)(n0 + cc) * (K / 2) + (b * kBlock + k0) / 2) = word;
-            }
+        uint32_t w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t lo = pack4_low_bytes(u[8 * j], u[8 * j + 1], u[8 * j + 2], u[8 * j + 3]);
+            const uint32_t hi = pack4_low_bytes(u[8 * j + 4], u[8 * j + 5], u[8 * j + 6], u[8 * j + 7]);
+            w[j] = (lo & 0x0F0F0F0Fu) | ((hi << 4) & 0xF0F0F0F0u);
+        }
+        *reinterpret_cast<uint4 *>(static_cast<uint8_t *>(codes) + (size_t)n * (K / 2) + k0 / 2) =
+            make_uint4(w[0], w[1], w[2], w[3]);
+        if (tiled) {
+            // units of 16 input channels (8 bytes), see qgemm_tiled.hip
+            uint8_t *const blk = static_cast<uint8_t *>(tiled) + ((size_t)(n >> 4) * (K >> 6) + (k0 >> 6)) * 512 +
+                                 ((k0 & 63) >> 4) * 128 + (n & 15) * 8;
+            *reinterpret_cast<uint2 *>(blk) = make_uint2(w[0], w[1]);
+            *reinterpret_cast<uint2 *>(blk + 128) = make_uint2(w[2], w[3]);
         }
     }
 }
@@ -316,10 +400,10 @@ hipError_t launch_weight_colsum(const void *codes, int K, int N, int32_t *colsum
 }
 
 hipError_t launch_prepare_rotate(const float *W, int K, int N, const float *diag, const int32_t *perm,
-                                 float *Wrot, float *amax, hipStream_t st)
+                                 float *Wrot, hipStream_t st)
 {
     dim3 grid((N + kCols - 1) / kCols, K / kBlock);
-    hipLaunchKernelGGL(prepare_rotate_kernel, grid, dim3(kPrepThreads), 0, st, W, K, N, diag, perm, Wrot, amax);
+    hipLaunchKernelGGL(prepare_rotate_kernel, grid, dim3(kPrepThreads), 0, st, W, K, N, diag, perm, Wrot);
     return hipGetLastError();
 }
 
@@ -342,13 +426,6 @@ __global__ __launch_bounds__(64) void weight_colsumw4_kernel(const uint8_t *__re
     if (lane == 0) colsumw[n] = 16.0f * t;
 }
 
-hipError_t launch_weight_colsumw4(const void *codes, const float *scales, int K, int N, float *colsumw, hipStream_t st)
-{
-    hipLaunchKernelGGL(weight_colsumw4_kernel, dim3(N), dim3(64), 0, st, static_cast<const uint8_t *>(codes), scales, K, N,
-                       colsumw);
-    return hipGetLastError();
-}
-
 hipError_t launch_prepare_rotate_dense(const float *W, int K, int N, const float *diag, const int32_t *perm,
                                        const float *R, float *Wrot, float *amax, hipStream_t st)
 {
@@ -357,16 +434,33 @@ hipError_t launch_prepare_rotate_dense(const float *W, int K, int N, const float
     return hipGetLastError();
 }
 
-hipError_t launch_prepare_quant(const float *Wrot, const float *amax, int K, int N, int wbits, float norm,
-                                void *codes, float *scales, hipStream_t st)
+hipError_t launch_prepare_quant(const float *W, const float *diag, const int32_t *perm, bool rotate, float norm,
+                                const Weights &w, float *amax, float *diag_copy, hipStream_t st)
 {
-    dim3 grid((N + kCols - 1) / kCols, K / kBlock);
-    if (wbits == 8 || wbits == 6)
-        hipLaunchKernelGGL(prepare_quant_kernel<8>, grid, dim3(kPrepThreads), 0, st, Wrot, amax, K, N, norm,
-                           wbits == 8 ? 127.0f : 31.0f, codes, scales);
-    else
-        hipLaunchKernelGGL(prepare_quant_kernel<4>, grid, dim3(kPrepThreads), 0, st, Wrot, amax, K, N, norm, 7.0f, codes, scales);
-    return hipGetLastError();
+    const int K = w.K, N = w.N;
+    const dim3 grid((N + kCols - 1) / kCols, K / kBlock), threads(kPrepThreads);
+    if (!diag) diag_copy = nullptr;
+    if (w.wbits == 4) {
+        auto kern = rotate ? prepare_quant_kernel<4, true> : prepare_quant_kernel<4, false>;
+        hipLaunchKernelGGL(kern, grid, threads, 0, st, W, K, N, diag, perm, amax, norm, 7.0f, w.codes, w.codes_tiled,
+                           w.scales, nullptr, diag_copy);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        hipLaunchKernelGGL(weight_colsumw4_kernel, dim3(N), dim3(64), 0, st, static_cast<const uint8_t *>(w.codes), w.scales,
+                           K, N, w.colsumw);
+        return hipGetLastError();
+    }
+    const float qmax = w.qbits == 6 ? 31.0f : 127.0f;
+    if (rotate) {
+        hipLaunchKernelGGL(prepare_absmax_kernel, grid, threads, 0, st, W, K, N, diag, perm, amax, w.colsum, diag_copy);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        hipLaunchKernelGGL((prepare_quant_kernel<8, true>), grid, threads, 0, st, W, K, N, diag, perm, amax, norm, qmax,
+                           w.codes, w.codes_tiled, w.scales, w.colsum, nullptr);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((prepare_quant_kernel<8, false>), grid, threads, 0, st, W, K, N, diag, perm, amax, norm, qmax,
+                       w.codes, w.codes_tiled, w.scales, nullptr, nullptr);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    return launch_weight_colsum(w.codes, K, N, w.colsum, st);
 }
 
 }  // namespace trdq

@@ -386,14 +386,9 @@ bool qgemm_tiled_pays(int64_t M, int K, int N)
     return !(K >= 2304 && tiles <= 2 * (int64_t)num_cus());
 }
 
-hipError_t launch_retile_w4_codes(const void *src, void *dst, int64_t N, int K, hipStream_t st)
+hipError_t launch_xq_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st)
 {
-    return launch_retile_w4(src, dst, N, K, st);
-}
-
-hipError_t launch_retile_rows(const int8_t *src, int8_t *dst, int64_t R, int K, bool to_tiled, hipStream_t st)
-{
-    return launch_retile(src, dst, R, K, to_tiled, st);
+    return launch_untile(Xt, Xq, M, K, st);
 }
 
 }  // namespace trdq

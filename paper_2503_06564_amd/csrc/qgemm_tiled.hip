@@ -792,31 +792,16 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
 #endif
 }
 
-// 8-byte units between the row-major packed form [N, K / 2] and the block form above
-__global__ void retile_w4_kernel(const uint2 *__restrict__ src, uint2 *__restrict__ dst, int64_t N, int K)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int upr = K >> 4;                           // units per channel
-    if (idx >= N * upr) return;
-    const int64_t n = idx / upr;
-    const int q = (int)(idx - n * upr);
-    const int64_t t = ((n >> 4) * (K >> 6) + (q >> 2)) * 64 + (q & 3) * 16 + (n & 15);
-    dst[t] = src[idx];
-}
-
-// 16 bytes per thread between the row-major form [R, K] and the block form
-template <bool TO_TILED>
-__global__ void retile_kernel(const int8_t *__restrict__ src, int8_t *__restrict__ dst, int64_t R, int K)
+// 16 bytes per thread from the block form to the row-major form [M, K]
+__global__ void untile_kernel(const int8_t *__restrict__ Xt, int8_t *__restrict__ Xq, int64_t M, int K)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int cpr = K >> 4;                           // 16-byte pieces per row
-    if (idx >= R * cpr) return;
+    if (idx >= M * cpr) return;
     const int64_t row = idx / cpr;
     const int c = (int)(idx - row * cpr);
     const int64_t t = ((row >> 4) * (K >> 6) + (c >> 2)) * 1024 + (c & 3) * 256 + (row & 15) * 16;
-    const int64_t r = row * K + (int64_t)c * 16;
-    if (TO_TILED) *reinterpret_cast<uint4 *>(dst + t) = *reinterpret_cast<const uint4 *>(src + r);
-    else *reinterpret_cast<uint4 *>(dst + r) = *reinterpret_cast<const uint4 *>(src + t);
+    *reinterpret_cast<uint4 *>(Xq + row * K + (int64_t)c * 16) = *reinterpret_cast<const uint4 *>(Xt + t);
 }
 
 }  // namespace
@@ -906,22 +891,11 @@ hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st)
     return debug ? go(qgemm4_tiled_kernel<true>) : go(qgemm4_tiled_kernel<false>);
 }
 
-hipError_t launch_retile_w4(const void *src, void *dst, int64_t N, int K, hipStream_t st)
+hipError_t launch_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st)
 {
-    const int64_t n = N * (K / 16);
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(retile_w4_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                       static_cast<const uint2 *>(src), static_cast<uint2 *>(dst), N, K);
-    return hipGetLastError();
-}
-
-hipError_t launch_retile(const int8_t *src, int8_t *dst, int64_t R, int K, bool to_tiled, hipStream_t st)
-{
-    if (R <= 0) return hipSuccess;
-    const int64_t n = R * (K / 16);
-    const unsigned grid = (unsigned)((n + 255) / 256);
-    if (to_tiled) hipLaunchKernelGGL(retile_kernel<true>, dim3(grid), dim3(256), 0, st, src, dst, R, K);
-    else hipLaunchKernelGGL(retile_kernel<false>, dim3(grid), dim3(256), 0, st, src, dst, R, K);
+    if (M <= 0) return hipSuccess;
+    const int64_t n = M * (K / 16);
+    hipLaunchKernelGGL(untile_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, Xt, Xq, M, K);
     return hipGetLastError();
 }
 

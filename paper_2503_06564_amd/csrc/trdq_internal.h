@@ -30,6 +30,9 @@ struct Weights {
     int32_t *colsum = nullptr;   // int8 weights: sum over k of the codes of every output channel [N]
     int32_t *zcw = nullptr;      // asymmetric int8 weights (Eq. 1-3 per output channel): 128 - z_w [N]; codes hold q - 128
     float *colsumw = nullptr;    // int4 weights: 16 * sum_g s_w[g][n] * (sum of the codes of group g) [N]
+    float *diag = nullptr;       // the handle's copy of the diagonal [K], if it keeps one
+    float *amax = nullptr;       // scratch of the preparation: block maxima [K/128, N]
+    void *block = nullptr;       // the one device allocation that holds all of the above
     int device = 0;
 };
 
@@ -59,14 +62,13 @@ hipError_t launch_rotate_quant(const uint16_t *X, int64_t M, int K, int64_t ldx,
                                int8_t *Xq, float *sx, int32_t *zc, const void *warm, int64_t warm_bytes, hipStream_t st,
                                int abits = 8,    // symmetric codes in +-(2^(abits-1) - 1); K <= 4608 unless 8
                                bool tiled = false);
-// the product on block-tiled operands, and the conversion between the two forms of an int8 matrix [R, K]
+// the product on block-tiled operands, and the conversion of block-tiled codes to rows
 bool qgemm_tiled_supports(const Weights &w, int64_t M, const void *Y, int64_t ldy);
 hipError_t launch_qgemm_tiled(const Weights &w, const int8_t *Xt, const float *sx, int64_t M, const float *bias,
                               uint16_t *Y, int64_t ldy, int32_t *acc_debug, hipStream_t st);
 // measured choice between the two products for a layer object (true: the tiled pair is the faster one)
 bool qgemm_tiled_pays(int64_t M, int K, int N);
-hipError_t launch_retile_rows(const int8_t *src, int8_t *dst, int64_t R, int K, bool to_tiled, hipStream_t st);
-hipError_t launch_retile_w4_codes(const void *src, void *dst, int64_t N, int K, hipStream_t st);
+hipError_t launch_xq_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st);
 hipError_t launch_rotate_quant_wide(const uint16_t *X, int64_t M, int K, int64_t ldx, const float *diag,
                                     int8_t *Xq, float *sx, hipStream_t st);
 
@@ -77,16 +79,17 @@ hipError_t launch_rotate_quant_rpr(const uint16_t *X, int64_t M, int K, int64_t 
                                    hipStream_t st, int32_t *zc = nullptr);   // zc: asymmetric codes, as launch_rotate_quant
 
 // perm (optional): rows are read through it (row k of the input to the rotation = row perm[k]).
-// norm: what undoes the unnormalised butterflies (1/sqrt(128) per rotation applied).
 hipError_t launch_prepare_rotate(const float *W, int K, int N, const float *diag, const int32_t *perm,
-                                 float *Wrot, float *amax, hipStream_t st);
+                                 float *Wrot, hipStream_t st);
+// Codes (both forms), scales and column sums of w from W: rotated on the way (rotate: diag and perm as above; amax:
+// scratch of K / 128 * N floats), or already rotated with its block maxima in amax.  norm: what undoes the
+// unnormalised butterflies (1/sqrt(128) per rotation applied).  diag_copy (optional) receives diag.
+hipError_t launch_prepare_quant(const float *W, const float *diag, const int32_t *perm, bool rotate, float norm,
+                                const Weights &w, float *amax, float *diag_copy, hipStream_t st);
 // asymmetric weight quantiser: lohi = scratch of 2 N floats; codes [N, K] = q - 128, scales [N], zcw [N] = 128 - z
 hipError_t launch_prepare_quant_asym(const float *Wrot, float *lohi, int K, int N, float norm, void *codes, float *scales,
                                      int32_t *zcw, hipStream_t st);
 hipError_t launch_xq_rowsum(const int8_t *Xq, int64_t M, int K, int32_t *rowsum, hipStream_t st);
-hipError_t launch_weight_colsumw4(const void *codes, const float *scales, int K, int N, float *colsumw, hipStream_t st);
-hipError_t launch_prepare_quant(const float *Wrot, const float *amax, int K, int N, int wbits, float norm,
-                                void *codes, float *scales, hipStream_t st);   // wbits 8, 6 (8-bit layout) or 4
 
 // Calibration-side reductions (calibrate.hip).  mag / wmax / d are device arrays of K floats.
 hipError_t launch_channel_absmax(const uint16_t *X, int64_t M, int K, int64_t ldx, const float *diag,
