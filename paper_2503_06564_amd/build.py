@@ -25,6 +25,7 @@ SOURCE_FLAGS = {"qgemm_dma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                 # ... and have the first kernel arguments delivered in registers at wave launch instead
                 # of fetched by the kernel's first instructions (a fraction of a microsecond per launch)
                 "rotate_quant.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-kernarg-preload-count=16"],
+                "fused.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
                 "rotate_quant_rpr.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                 "calibrate.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 

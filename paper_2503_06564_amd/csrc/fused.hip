@@ -18,7 +18,6 @@ constexpr int kThreads = 256;
 constexpr int kPad = 16;
 constexpr int kBN = 128;   // output channels per weight tile
 constexpr int kBK = 128;   // input channels per weight tile = one rotation block / scale group
-constexpr int64_t kSmallMaxWorkgroups = 512;    // few-token kernel: at most two rounds of workgroups
 
 struct FusedArgs {
     const uint16_t *X;     // bf16 [M, ldx]
@@ -258,226 +257,342 @@ __global__ __launch_bounds__(kThreads) void linear_fused_kernel(FusedArgs g)
     }
 }
 
-// ---- few tokens: one 16-token panel per workgroup, K split over eight waves ---------------------
-// With a few hundred tokens the unfused pair is bound by two launches and two chains of memory
-// latency, not by arithmetic.  Here a workgroup of eight waves owns 16 tokens and BN = 16 * TN
-// output channels.  Every weight byte of its slab meets exactly one matrix instruction (there is
-// one token tile), so staging weights in LDS would buy nothing: wave w loads the fragments of
-// its k-steps (64 input channels each; steps w, w + 8, w + 16) straight from global memory into
-// registers, all of them up front, right after the loads of the activations, so that they are
-// in flight while the panel is rotated and quantised into LDS.  Then each wave multiplies its
-// k-steps, the eight partial sums meet in LDS, and wave w finishes channel tiles w and w + 8.
-// K <= 1536 (three k-steps per wave, 108 fragment registers), int8 weights.
-constexpr int kSmallThreads = 512;
-constexpr int kSmallSteps = 3;
+// ---- few tokens: one 16-token panel per workgroup, a wave per rotation block -----------------------
+// With up to a few hundred tokens the unfused pair is bound by two launches and two chains of memory
+// latency, not by arithmetic, and so is this kernel: what counts is the length of the one chain that is
+// left.  A workgroup owns 16 tokens and 16 * TN output channels for the whole K; a wave owns BPW rotation
+// blocks (128 input channels each; one up to K = 1536, three at K = 4608), and does everything for them:
+//
+//   loads       X, the diagonal, and the weight fragments straight into registers (every weight byte meets
+//               exactly one matrix instruction: LDS would buy nothing), all requested up front;
+//   rotation    lane (token r, q) starts with the 8-channel chunks 32 c + 8 q, c = 0..3: index bits 6, 5
+//               and 2..0 are butterflies inside the lane, bits 4 and 3 sit in the lane number; a swap of two
+//               registers between lane halves (rows) turns such a bit into a register bit and a register bit
+//               into the lane bit, so that afterwards the lane holds the 32 consecutive channels 32 q ..;
+//   codes       after the token maxima have met in LDS, the lane's 32 codes are its operands of the two
+//               matrix instructions of the block as they are: the instruction does not care which input
+//               channels a lane supplies as long as both operands agree, so the weights are loaded for the
+//               same 32 channels (32 consecutive bytes of a channel's row) and no code crosses a lane;
+//   product     2 TN matrix instructions per block; the waves' partial sums (int8 weights: one per wave, int4:
+//               one per block, i.e. per scale group) meet in LDS, wave w finishes channel tiles w, w + waves, ...
+//
+// The launcher takes the narrowest tile whose grid is one round of workgroups: repeating the rotation on
+// idle compute units is free, and fewer weight bytes per compute unit arrive sooner.  The arguments that the
+// first loads need are the ones delivered in registers at wave launch.
+//
+// Measured, back-to-back launches (an empty kernel: 2.5-3 us): 1152 -> 1152 int8 at 16 / 128 / 256 / 512 tokens
+// 4.9 / 5.5 / 6.9 / 9.1 us, against 9.8 / 10.0 / 10.2 / 11.1 for a form that split K over eight waves, rotated
+// with lane exchanges (630 vector instructions per wave instead of 290) and passed the codes through LDS, and
+// 13.3-14.1 for the pair; int4 5.2 / 5.9 / 6.7 / 7.6 against 15.4-16.5 for the pair; 4608 -> 1152 at 16 tokens
+// 12.5 (int8) and 13.5 us (int4) against 35.4 and 40.9 for the pair.
+constexpr int64_t kSmallMaxWorkgroups = 512;    // at most two rounds of workgroups
+constexpr int kSmallMaxBlocks = 36;
 
-template <int TN, int T, bool ASYM = false>
-__global__ __launch_bounds__(kSmallThreads) void linear_fused_small_kernel(FusedArgs g)
+// butterfly over an index bit that sits in lane bit 5 (HALF = 32) or 4 (16) of registers x (register bit 0)
+// and y (register bit 1): the two bits trade places, x becomes the sum and y the difference
+template <int HALF>
+__device__ __forceinline__ void butterfly_swap(float &x, float &y)
 {
-    constexpr int BN = TN * 16;
+    uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
+    if constexpr (HALF == 32) {
+        const auto t = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        a = t[0]; b = t[1];
+    } else {
+        const auto t = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = t[0]; b = t[1];
+    }
+    x = __uint_as_float(a) + __uint_as_float(b);
+    y = __uint_as_float(a) - __uint_as_float(b);
+}
+
+// v[8 c + j] = element 32 c + 8 q + j of the block in lane q (= lane / 16) -> the unnormalised H_128 of the
+// block, element 32 q + 8 c + j in v[8 c + j]
+__device__ __forceinline__ void fwht128_quarters(float (&v)[32])
+{
+    auto bf = [](float &a, float &b) { const float s = a + b; b = a - b; a = s; };
+#pragma unroll
+    for (int h = 1; h < 8; h <<= 1)
+#pragma unroll
+        for (int i = 0; i < 32; ++i)
+            if (!(i & h)) bf(v[i], v[i + h]);
+#pragma unroll
+    for (int h = 8; h < 32; h <<= 1)
+#pragma unroll
+        for (int i = 0; i < 32; ++i)
+            if (!(i & h)) bf(v[i], v[i + h]);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) butterfly_swap<32>(v[i], v[i + 16]);
+#pragma unroll
+    for (int i = 0; i < 32; ++i)
+        if (!(i & 8)) butterfly_swap<16>(v[i], v[i + 8]);
+}
+
+template <int TN, int BPW, bool W4, bool ASYM>
+__global__ __launch_bounds__(768) void linear_fused_small_kernel(
+    const uint16_t *__restrict__ X, const float *__restrict__ diag, const uint8_t *__restrict__ Wc, int64_t ldx, int M,
+    int K, int N, const float *__restrict__ sw, const float *__restrict__ bias, const int32_t *__restrict__ colsum,
+    uint16_t *__restrict__ Y, int64_t ldy)
+{
+    static_assert(!(W4 && ASYM), "zero points are carried for int8 weights only");
     extern __shared__ __align__(16) int8_t smem[];
-    const int K = g.K;
-    const int nb = K / kBlock;
-    const int LDX = K + kPad;
-    int8_t *const Xp = smem;                                              // [16][K + 16] int8 panel
-    float *const sxs = reinterpret_cast<float *>(smem + 16 * LDX);       // [16]
-    int *const zcs = reinterpret_cast<int *>(smem + 16 * LDX + 64);      // [16] 128 - z (ASYM)
-    v4i *const part = reinterpret_cast<v4i *>(smem + 16 * LDX + 128);    // [8][TN][64] partial sums
-    float *const dl = reinterpret_cast<float *>(part);                   // [K] diagonal (before the sums need the space)
+    float *const ext_s = reinterpret_cast<float *>(smem);                 // [waves][32]: token maxima (and minima)
+    v4i *const part = reinterpret_cast<v4i *>(smem + 12 * 32 * 4);        // [waves or blocks][TN][64] partial sums
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, lg = lane >> 4;
-    const int tile = blockIdx.x % g.tiles_n, panel = blockIdx.x / g.tiles_n;
-    const int64_t m0 = (int64_t)panel * 16;
-    const int n0 = tile * BN;
-    const int KS = K / 64;
+    const int nw = blockDim.x >> 6;
+    const int nb = K / kBlock;
+    const int r = lane & 15, q = lane >> 4;
+    const int n0 = blockIdx.x * (TN * 16);
+    const int m = blockIdx.y * 16 + r;
+    const bool tok_ok = m < M;
+    const int b0 = wave * BPW;                                           // the wave's first block
 
-    // Loads return in order, so the order of issue is the order of need: the diagonal (one 16-byte
-    // piece per thread, shared through LDS), the activations, then the weight fragments.
-    float4 dpiece = make_float4(1.f, 1.f, 1.f, 1.f);
-    if (g.diag && tid * 4 < K) dpiece = *reinterpret_cast<const float4 *>(g.diag + tid * 4);
-    const int r = wave * 2 + (lg >> 1), s = lg & 1;     // token of this lane row, and which half of its blocks
-    const int64_t token = m0 + r;
-    const bool tok_ok = token < g.M;
-    uint4 raw[T];
+    // Loads return in order, so the order of issue is the order of need.  Tokens past the end and a last
+    // wave's blocks past the row are clamped: loaded and rotated like the others, their sums are not used.
+    uint4 raw[BPW][4];
+    float4 dv[8];
+    auto load_d = [&](int i) {
+        const int b = b0 + i < nb ? b0 + i : nb - 1;
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-        const int b = t * 2 + s;
-        raw[t] = make_uint4(0, 0, 0, 0);
-        if (tok_ok && b < nb)
-            raw[t] = *reinterpret_cast<const uint4 *>(g.X + token * g.ldx + (int64_t)b * kBlock + l16 * 8);
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                dv[2 * c + h] = diag ? *reinterpret_cast<const float4 *>(diag + b * kBlock + c * 32 + q * 8 + h * 4)
+                                     : make_float4(1.f, 1.f, 1.f, 1.f);
+    };
+    {
+        const uint16_t *const xt = X + (int64_t)(tok_ok ? m : M - 1) * ldx + q * 8;
+#pragma unroll
+        for (int i = 0; i < BPW; ++i) {
+            const int b = b0 + i < nb ? b0 + i : nb - 1;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) raw[i][c] = *reinterpret_cast<const uint4 *>(xt + b * kBlock + c * 32);
+            if (i == 0) load_d(0);
+        }
     }
-
-    // this wave's weight fragments: channel n0 + 16a + l16, input channels 64 * step + 16 * lg .. + 15
-    v4i wf[kSmallSteps][TN];
-    auto load_w = [&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        const int step = wave + 8 * i;
-        if (step < KS) {
+    // weights of channel n0 + 16 a + r, the lane's 32 input channels of each of the wave's blocks
+    constexpr int WR = W4 ? 1 : 2;                   // 16-byte pieces of them
+    // (six blocks' worth of int8 fragments do not fit beside the activations: they follow the rotation)
+    constexpr bool kLateW = !W4 && BPW == 3 && TN > 1;
+    uint4 wf[BPW][TN][WR];
+    auto load_w = [&]() {
+#pragma unroll
+        for (int i = 0; i < BPW; ++i) {
+            const int b = b0 + i < nb ? b0 + i : nb - 1;
 #pragma unroll
             for (int a = 0; a < TN; ++a) {
-                int n = n0 + a * 16 + l16;
-                if (n >= g.N) n = g.N - 1;
-                wf[i][a] = *reinterpret_cast<const v4i *>(static_cast<const int8_t *>(g.Wc) + (size_t)n * K + step * 64 + lg * 16);
-            }
-        } else {
+                int n = n0 + a * 16 + r;
+                if (n >= N) n = N - 1;
+                const uint8_t *src = Wc + (W4 ? (size_t)n * (K >> 1) + b * 64 + q * 16 : (size_t)n * K + b * kBlock + q * 32);
 #pragma unroll
-            for (int a = 0; a < TN; ++a) wf[i][a] = v4i{0, 0, 0, 0};
+                for (int h = 0; h < WR; ++h) wf[i][a][h] = *reinterpret_cast<const uint4 *>(src + 16 * h);
+            }
         }
     };
-    load_w(std::integral_constant<int, 0>{});
-    load_w(std::integral_constant<int, 1>{});
-    if (tid * 4 < K) *reinterpret_cast<float4 *>(dl + tid * 4) = dpiece;
-    __syncthreads();
+    if constexpr (!kLateW) load_w();
 
-    // rotate and quantise the panel into LDS
-    {
-        const LaneSigns sg(l16);
-        float v[T][8];
-        float amax = 0.0f, amin = 0.0f;
+    float v[BPW][32];
+    float amax = 0.0f, amin = 0.0f;
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int b = t * 2 + s < nb ? t * 2 + s : nb - 1;
-            const float4 d0 = *reinterpret_cast<const float4 *>(dl + b * kBlock + l16 * 8);
-            const float4 d1 = *reinterpret_cast<const float4 *>(dl + b * kBlock + l16 * 8 + 4);
-            v[t][0] = bf16_lo(raw[t].x) * d0.x;
-            v[t][1] = bf16_hi(raw[t].x) * d0.y;
-            v[t][2] = bf16_lo(raw[t].y) * d0.z;
-            v[t][3] = bf16_hi(raw[t].y) * d0.w;
-            v[t][4] = bf16_lo(raw[t].z) * d1.x;
-            v[t][5] = bf16_hi(raw[t].z) * d1.y;
-            v[t][6] = bf16_lo(raw[t].w) * d1.z;
-            v[t][7] = bf16_hi(raw[t].w) * d1.w;
-            fwht128_rows16(v[t], sg);
+    for (int i = 0; i < BPW; ++i) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if constexpr (ASYM) {
-                    amax = fmaxf(amax, v[t][j]);
-                    amin = fminf(amin, v[t][j]);
-                } else {
-                    amax = fmaxf(amax, fabsf(v[t][j]));
-                }
-            }
-            if (t == 0) {
-                // the last k-step's fragments go out once the first block is done (the queue has drained by then)
-                __builtin_amdgcn_sched_barrier(0);
-                load_w(std::integral_constant<int, 2>{});
-                __builtin_amdgcn_sched_barrier(0);
-            }
+        for (int c = 0; c < 4; ++c) {
+            const uint4 x = raw[i][c];
+            const float4 d0 = dv[2 * c], d1 = dv[2 * c + 1];
+            v[i][8 * c + 0] = bf16_lo(x.x) * d0.x; v[i][8 * c + 1] = bf16_hi(x.x) * d0.y;
+            v[i][8 * c + 2] = bf16_lo(x.y) * d0.z; v[i][8 * c + 3] = bf16_hi(x.y) * d0.w;
+            v[i][8 * c + 4] = bf16_lo(x.z) * d1.x; v[i][8 * c + 5] = bf16_hi(x.z) * d1.y;
+            v[i][8 * c + 6] = bf16_lo(x.w) * d1.z; v[i][8 * c + 7] = bf16_hi(x.w) * d1.w;
         }
-        amax = row16_max(amax);
-        amax = fmaxf(amax, __shfl_xor(amax, 16));
-        if constexpr (ASYM) {
-            amin = -row16_max(-amin);
-            amin = fminf(amin, __shfl_xor(amin, 16));
-            const TokenRangeQuant q(amin, amax);
-            if (s == 0 && l16 == 0) {
-                sxs[r] = tok_ok ? q.scale : 0.0f;
-                zcs[r] = tok_ok ? q.zc : 0;
-            }
+        if (i + 1 < BPW) load_d(i + 1);
+        fwht128_quarters(v[i]);
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int b = t * 2 + s;
-                if (b < nb) *reinterpret_cast<uint2 *>(Xp + r * LDX + b * kBlock + l16 * 8) = q.pack8(v[t]);
-            }
-        } else {
-            const float inv = token_inv_scale(amax);
-            if (s == 0 && l16 == 0) sxs[r] = tok_ok ? token_scale(amax) : 0.0f;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int b = t * 2 + s;
-                if (b < nb) *reinterpret_cast<uint2 *>(Xp + r * LDX + b * kBlock + l16 * 8) = quant_pack8(v[t], inv);
+        for (int j = 0; j < 32; j += 2) {
+            if constexpr (ASYM) {
+                amax = fmaxf(fmaxf(amax, v[i][j]), v[i][j + 1]);
+                amin = fminf(fminf(amin, v[i][j]), v[i][j + 1]);
+            } else {
+                amax = fmaxf(fmaxf(amax, fabsf(v[i][j])), fabsf(v[i][j + 1]));
             }
         }
     }
-    __syncthreads();        // panel and scales published; every wave is done with the diagonal
+    if constexpr (kLateW) {
+        __builtin_amdgcn_sched_barrier(0);
+        load_w();
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // token extremes: over the lane's four quarters, then over the waves (a clamped block repeats the row's
+    // last one and changes nothing)
+    amax = fmaxf(amax, __shfl_xor(amax, 16));
+    amax = fmaxf(amax, __shfl_xor(amax, 32));
+    if constexpr (ASYM) {
+        amin = fminf(amin, __shfl_xor(amin, 16));
+        amin = fminf(amin, __shfl_xor(amin, 32));
+    }
+    if (q == 0) {
+        ext_s[wave * 32 + r] = amax;
+        if constexpr (ASYM) ext_s[wave * 32 + 16 + r] = amin;
+    }
+    // operands of the epilogue for the wave's first channel tile: requested here, used after the last barrier
+    const int a_own = wave < TN ? wave : 0;
+    const int n_own = n0 + a_own * 16 + q * 4 < N ? n0 + a_own * 16 + q * 4 : N - 4;
+    float4 sw_own = make_float4(1.f, 1.f, 1.f, 1.f), bi_own = make_float4(0.f, 0.f, 0.f, 0.f);
+    if constexpr (!W4) sw_own = *reinterpret_cast<const float4 *>(sw + n_own);
+    if (bias) bi_own = *reinterpret_cast<const float4 *>(bias + n_own);
+    __syncthreads();
+    for (int w = 0; w < nw; ++w) {
+        amax = fmaxf(amax, ext_s[w * 32 + r]);
+        if constexpr (ASYM) amin = fminf(amin, ext_s[w * 32 + 16 + r]);
+    }
+    const TokenRangeQuant rq(amin, amax);            // ASYM
+    const float inv = token_inv_scale(amax);
+    auto code_bits = [&](float x) -> uint32_t {
+        if constexpr (ASYM) return rq.bits(x);
+        else return quant_bits(x, inv);
+    };
 
     v4i acc[TN];
 #pragma unroll
     for (int a = 0; a < TN; ++a) acc[a] = v4i{0, 0, 0, 0};
 #pragma unroll
-    for (int i = 0; i < kSmallSteps; ++i) {
-        const int step = wave + 8 * i;
-        if (step < KS) {
-            const v4i xf = *reinterpret_cast<const v4i *>(Xp + l16 * LDX + step * 64 + lg * 16);
+    for (int i = 0; i < BPW; ++i) {
+        if (b0 + i < nb) {                           // wave-uniform
+            v4i xf[2];
 #pragma unroll
-            for (int a = 0; a < TN; ++a)
-                acc[a] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[i][a], xf, acc[a], 0, 0, 0);
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const float *p = v[i] + 16 * h + 4 * w;
+                    xf[h][w] = (int)pack4_low_bytes(code_bits(p[0]), code_bits(p[1]), code_bits(p[2]), code_bits(p[3]));
+                }
+#pragma unroll
+            for (int a = 0; a < TN; ++a) {
+                v4i wl, wh;
+                if constexpr (W4) {
+                    const uint4 p = wf[i][a][0];     // 16 * code, see Weights
+                    wl = v4i{(int)((p.x << 4) & 0xF0F0F0F0u), (int)(p.x & 0xF0F0F0F0u),
+                             (int)((p.y << 4) & 0xF0F0F0F0u), (int)(p.y & 0xF0F0F0F0u)};
+                    wh = v4i{(int)((p.z << 4) & 0xF0F0F0F0u), (int)(p.z & 0xF0F0F0F0u),
+                             (int)((p.w << 4) & 0xF0F0F0F0u), (int)(p.w & 0xF0F0F0F0u)};
+                } else {
+                    wl = __builtin_bit_cast(v4i, wf[i][a][0]);
+                    wh = __builtin_bit_cast(v4i, wf[i][a][1]);
+                }
+                acc[a] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wl, xf[0], W4 ? v4i{0, 0, 0, 0} : acc[a], 0, 0, 0);
+                acc[a] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wh, xf[1], acc[a], 0, 0, 0);
+                if constexpr (W4) part[((b0 + i) * TN + a) * 64 + lane] = acc[a];
+            }
         }
     }
+    if constexpr (!W4) {
 #pragma unroll
-    for (int a = 0; a < TN; ++a) part[(wave * TN + a) * 64 + lane] = acc[a];
+        for (int a = 0; a < TN; ++a) part[(wave * TN + a) * 64 + lane] = acc[a];
+    }
     __syncthreads();
 
-    // wave w finishes channel tiles w, w + 8: lane holds channels n .. n + 3 of token m0 + l16
-    for (int a = wave; a < TN; a += 8) {
-        v4i sum = part[a * 64 + lane];
-#pragma unroll
-        for (int w = 1; w < 8; ++w) sum += part[(w * TN + a) * 64 + lane];
-        const int n = n0 + a * 16 + lg * 4;
-        const int64_t m = m0 + l16;
-        if (n < g.N && m < g.M) {
-            const float4 sw = *reinterpret_cast<const float4 *>(g.sw + n);
-            float4 bi = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (g.bias) bi = *reinterpret_cast<const float4 *>(g.bias + n);
-            const float sxm = sxs[l16];
-            if constexpr (ASYM) {
-                const int4 cs = *reinterpret_cast<const int4 *>(g.colsum + n);
-                const int zc = zcs[l16];
-                sum += v4i{zc * cs.x, zc * cs.y, zc * cs.z, zc * cs.w};
-            }
-            uint2 o;
-            o.x = pack_bf16x2((float)sum[0] * sxm * sw.x + bi.x, (float)sum[1] * sxm * sw.y + bi.y);
-            o.y = pack_bf16x2((float)sum[2] * sxm * sw.z + bi.z, (float)sum[3] * sxm * sw.w + bi.w);
-            *reinterpret_cast<uint2 *>(g.Y + m * g.ldy + n) = o;
+    // wave w finishes channel tiles w, w + waves, ...: lane holds channels n .. n + 3 of token r
+    for (int a = wave; a < TN; a += nw) {
+        const int n = n0 + a * 16 + q * 4;
+        if (n >= N || !tok_ok) continue;
+        float4 s = sw_own, bi = bi_own;
+        if (a != wave) {
+            if constexpr (!W4) s = *reinterpret_cast<const float4 *>(sw + n);
+            if (bias) bi = *reinterpret_cast<const float4 *>(bias + n);
         }
+        v4f f;
+        if constexpr (W4) {
+            // the groups' sums in ascending order, each with its scale, as the other int4 products add them
+            f = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int g = 0; g < nb; ++g) {
+                const float4 sg = *reinterpret_cast<const float4 *>(sw + (size_t)g * N + n);
+                const v4i t = part[(g * TN + a) * 64 + lane];
+                f[0] += sg.x * (float)t[0]; f[1] += sg.y * (float)t[1];
+                f[2] += sg.z * (float)t[2]; f[3] += sg.w * (float)t[3];
+            }
+            const float sxm = token_scale(amax) * 0.0625f;
+            f = v4f{sxm * f[0] + bi.x, sxm * f[1] + bi.y, sxm * f[2] + bi.z, sxm * f[3] + bi.w};
+        } else {
+            v4i sum = part[a * 64 + lane];
+            for (int w = 1; w < nw; ++w) sum += part[(w * TN + a) * 64 + lane];
+            float sxm;
+            if constexpr (ASYM) {
+                const int4 cs = *reinterpret_cast<const int4 *>(colsum + n);
+                sum += v4i{rq.zc * cs.x, rq.zc * cs.y, rq.zc * cs.z, rq.zc * cs.w};
+                sxm = rq.scale;
+            } else {
+                sxm = token_scale(amax);
+            }
+            f = v4f{(float)sum[0] * sxm * s.x + bi.x, (float)sum[1] * sxm * s.y + bi.y,
+                    (float)sum[2] * sxm * s.z + bi.z, (float)sum[3] * sxm * s.w + bi.w};
+        }
+        uint2 o;
+        o.x = pack_bf16x2(f[0], f[1]);
+        o.y = pack_bf16x2(f[2], f[3]);
+        *reinterpret_cast<uint2 *>(Y + (int64_t)m * ldy + n) = o;
     }
 }
 
-template <int TN, int T, bool ASYM>
+int small_blocks_per_wave(int K) { return (K / kBlock + 11) / 12; }
+
+// Channel tiles (of 16) per workgroup: the narrowest of the built ones whose grid is one round of workgroups,
+// else the widest.  Several blocks per wave leave registers for one or two tiles only.
+int small_tiles(int64_t M, int K, int N)
+{
+    const int64_t panels = (M + 15) / 16;
+    static constexpr int opts[] = {1, 2, 3, 5, 9};
+    const int bpw = small_blocks_per_wave(K);
+    const int n_opts = bpw == 1 ? 5 : 2;
+    for (int i = 0; i < n_opts; ++i)
+        if (panels * ((N + opts[i] * 16 - 1) / (opts[i] * 16)) <= num_cus()) return opts[i];
+    return opts[n_opts - 1];
+}
+
+int64_t small_workgroups(int64_t M, int K, int N)
+{
+    const int tn = small_tiles(M, K, N);
+    return ((M + 15) / 16) * ((N + tn * 16 - 1) / (tn * 16));
+}
+
+template <int TN, int BPW, bool W4, bool ASYM>
 hipError_t launch_small(const FusedArgs &a, hipStream_t st)
 {
-    FusedArgs g = a;
-    const int64_t panels = (g.M + 15) / 16;
-    g.tiles_n = (g.N + TN * 16 - 1) / (TN * 16);
-    const size_t smem = (size_t)16 * (g.K + kPad) + 128 + (size_t)8 * TN * 1024;
-    auto kern = linear_fused_small_kernel<TN, T, ASYM>;
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem); e != hipSuccess) return e;
-    // consecutive workgroups take the channel tiles of one panel: with eight tiles (1152 = 8 x 144)
-    // each of the eight dies keeps seeing the same weight slab
-    hipLaunchKernelGGL(kern, dim3((unsigned)(panels * g.tiles_n)), dim3(kSmallThreads), smem, st, g);
+    const int nb = a.K / kBlock, nw = (nb + BPW - 1) / BPW;
+    const size_t smem = 12 * 32 * 4 + (size_t)(W4 ? nb : nw) * TN * 1024;
+    auto kern = linear_fused_small_kernel<TN, BPW, W4, ASYM>;
+    if (smem > 64 * 1024)
+        if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem); e != hipSuccess) return e;
+    // consecutive workgroups take the channel tiles of one panel
+    const dim3 grid((unsigned)((a.N + TN * 16 - 1) / (TN * 16)), (unsigned)((a.M + 15) / 16));
+    hipLaunchKernelGGL(kern, grid, dim3(64 * nw), smem, st, a.X, a.diag, static_cast<const uint8_t *>(a.Wc), a.ldx,
+                       (int)a.M, a.K, a.N, a.sw, a.bias, a.colsum, a.Y, a.ldy);
     return hipGetLastError();
 }
 
-// few-token kernel: int8 weights, K <= 1536, and few enough workgroups that repeating the
-// rotation per channel tile costs less than a second launch
-bool small_applies(const FusedArgs &a, int wbits)
+// few-token kernel: few enough workgroups that repeating the rotation per channel tile costs less than a
+// second launch
+bool small_applies(const FusedArgs &a)
 {
-    if (wbits != 8 || a.K > 1536) return false;
-    const int bn = a.N % 144 == 0 ? 144 : 128;
-    const int64_t wgs = ((a.M + 15) / 16) * ((a.N + bn - 1) / bn);
-    return wgs <= kSmallMaxWorkgroups;
+    return a.K <= kSmallMaxBlocks * kBlock && small_workgroups(a.M, a.K, a.N) <= kSmallMaxWorkgroups;
 }
 
-template <int TN, bool ASYM>
-hipError_t launch_small_tn(const FusedArgs &a, hipStream_t st)
-{
-    switch ((a.K / kBlock + 1) / 2) {       // blocks per lane row (two lane rows share a token)
-        case 1: return launch_small<TN, 1, ASYM>(a, st);
-        case 2: return launch_small<TN, 2, ASYM>(a, st);
-        case 3: return launch_small<TN, 3, ASYM>(a, st);
-        case 4: return launch_small<TN, 4, ASYM>(a, st);
-        case 5: return launch_small<TN, 5, ASYM>(a, st);
-        default: return launch_small<TN, 6, ASYM>(a, st);
-    }
-}
-
-template <bool ASYM>
+template <bool W4, bool ASYM>
 hipError_t launch_small_any(const FusedArgs &a, hipStream_t st)
 {
-    return a.N % 144 == 0 ? launch_small_tn<9, ASYM>(a, st) : launch_small_tn<8, ASYM>(a, st);
+    const int tn = small_tiles(a.M, a.K, a.N);
+    switch (small_blocks_per_wave(a.K)) {
+        case 1:
+            switch (tn) {
+                case 1: return launch_small<1, 1, W4, ASYM>(a, st);
+                case 2: return launch_small<2, 1, W4, ASYM>(a, st);
+                case 3: return launch_small<3, 1, W4, ASYM>(a, st);
+                case 5: return launch_small<5, 1, W4, ASYM>(a, st);
+                default: return launch_small<9, 1, W4, ASYM>(a, st);
+            }
+        case 2: return tn == 1 ? launch_small<1, 2, W4, ASYM>(a, st) : launch_small<2, 2, W4, ASYM>(a, st);
+        default: return tn == 1 ? launch_small<1, 3, W4, ASYM>(a, st) : launch_small<2, 3, W4, ASYM>(a, st);
+    }
 }
 
 template <int BM, int T, int S, bool W4, bool ASYM>
@@ -520,13 +635,12 @@ hipError_t launch_w(const FusedArgs &a, hipStream_t st)
 
 bool fused_supports(int K) { return K % kBlock == 0 && K / kBlock <= 48; }
 
-// True where the fused kernel is the faster path: the few-token kernel in a single round of
-// workgroups (measured on 1152-wide layers: 10-11.5 us against 14-15 us for the pair up to 512 tokens).
+// True where the fused kernel is the faster path: the few-token kernel in a single round of workgroups.  In a
+// second round the repeated rotation costs more than the pair's second launch: 1152 -> 1152 at 1024 tokens 17.4
+// against 15.0 us, 1152 -> 4608 at 256 tokens 17.0 against 14.8 us (at half of those 9.1 / 14.1 and 9.0 / 13.9).
 bool fused_pays(int64_t M, int K, int N, int wbits)
 {
-    if (wbits != 8 || K > 1536 || K % kBlock != 0 || M <= 0) return false;
-    const int bn = N % 144 == 0 ? 144 : 128;
-    return ((M + 15) / 16) * ((N + bn - 1) / bn) <= num_cus();
+    return M > 0 && K % kBlock == 0 && K <= kSmallMaxBlocks * kBlock && small_workgroups(M, K, N) <= num_cus();
 }
 
 hipError_t launch_linear_fused(const Weights &w, const uint16_t *X, int64_t M, int64_t ldx,
@@ -538,7 +652,10 @@ hipError_t launch_linear_fused(const Weights &w, const uint16_t *X, int64_t M, i
     FusedArgs a;
     a.X = X; a.diag = diag; a.Wc = w.codes; a.sw = w.scales; a.bias = bias; a.colsum = w.colsum; a.Y = Y;
     a.M = M; a.ldx = ldx; a.ldy = ldy; a.K = w.K; a.N = w.N; a.tiles_n = 0; a.nsplit = 1;
-    if (small_applies(a, w.wbits)) return asym ? launch_small_any<true>(a, st) : launch_small_any<false>(a, st);
+    if (small_applies(a)) {
+        if (asym) return launch_small_any<false, true>(a, st);
+        return w.wbits == 4 ? launch_small_any<true, false>(a, st) : launch_small_any<false, false>(a, st);
+    }
     if (asym) return launch_w<false, true>(a, st);
     return w.wbits == 4 ? launch_w<true>(a, st) : launch_w<false>(a, st);
 }

@@ -145,11 +145,20 @@ def _ptr(t):
     return t.ctypes.data
 
 
+_raw_stream = None      # device index -> the current stream's hipStream_t, once torch is there
+
+
 def _stream(stream):
-    if stream is None:
+    """hipStream_t of `stream`, or of the current stream (looked up as a plain number: building a Stream object
+    for it costs 2.7 us of the 8 us that the host spends on a small call)."""
+    global _raw_stream
+    if stream is not None:
+        return getattr(stream, "cuda_stream", stream)
+    if _raw_stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
-    return getattr(stream, "cuda_stream", stream)
+        torch.cuda.current_stream()                     # initialises torch's side, or raises its error
+        _raw_stream = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+    return _raw_stream[0](_raw_stream[1]())
 
 
 # ------------------------------------------------------------------ table
@@ -719,6 +728,7 @@ class Layer:
         _check(lib().trdq_layer_create(table.handle, K, N, wbits, C.byref(h)), "trdq_layer_create")
         self.handle = h
         self.K, self.N, self.wbits = K, N, wbits
+        self._forward = lib().trdq_layer_forward
 
     def set_group(self, g, diag, W, stream=None):
         _check(lib().trdq_layer_set_group(self.handle, g, _ptr(diag), _ptr(W), _stream(stream)),
@@ -726,10 +736,10 @@ class Layer:
 
     def forward(self, step, X, Y, bias=None, fused=False, Xq_ws=None, sx_ws=None, stream=None):
         """fused: True / False, or None to let the library choose (fused for few tokens)."""
-        _check(lib().trdq_layer_forward(self.handle, step, _ptr(X), X.shape[0], _ptr(bias), _ptr(Y),
-                                        -1 if fused is None else (1 if fused else 0), _ptr(Xq_ws), _ptr(sx_ws),
-                                        _stream(stream)),
-               "trdq_layer_forward")
+        st = self._forward(self.handle, step, _ptr(X), X.shape[0], _ptr(bias), _ptr(Y),
+                           -1 if fused is None else (1 if fused else 0), _ptr(Xq_ws), _ptr(sx_ws), _stream(stream))
+        if st != OK:
+            raise TrdqError(st, "trdq_layer_forward")
 
     def weights(self, g):
         h = C.c_void_p()
