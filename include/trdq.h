@@ -114,9 +114,8 @@ trdq_status trdq_weights_export(const trdq_weights *w, int8_t *codes_host, float
 trdq_status trdq_weights_export_packed(const trdq_weights *w, uint8_t *packed_host);
 
 /* Bytes of the weight format (codes + scales): K*N + 4N for wbits 8, K*N/2 + 4*(K/128)*N for wbits 4.
- * An int8 set whose N is a multiple of 144, and an int4 set whose N is a multiple of 128, holds
- * its codes a second time, block-tiled for trdq_qgemm_tiled (another K*N resp. K*N/2 bytes of
- * device memory, not part of this figure). */
+ * A symmetric set holds its codes a second time, block-tiled (another K*N resp. K*N/2 bytes of device
+ * memory, not part of this figure): the form of trdq_qgemm_tiled, and what the kernels for few tokens read. */
 trdq_status trdq_weights_nbytes(const trdq_weights *w, int64_t *nbytes_out);
 
 void trdq_weights_destroy(trdq_weights *w);
@@ -422,18 +421,17 @@ trdq_status trdq_qgemm(const trdq_weights *w, const int8_t *Xq_dev, const float 
  *   The integer sums are those of trdq_qgemm (exact; acc_debug_dev as there, [K/128, M, N] for
  *   int4 weights), the epilogue is the same arithmetic, and so are the float folds of the int4
  *   scale groups, in the same order: the outputs are those of trdq_qgemm bit for bit.
- *   Such weight sets keep a second copy of their codes in the block form (K * N more bytes for
- *   int8, K * N / 2 for int4). */
+ *   The weights are read from the block-tiled copy of their codes that every symmetric set keeps. */
 int64_t trdq_xq_tiled_nbytes(int64_t M, int K);      /* -1 for M < 0, K <= 0 or K % 128 != 0 */
 trdq_status trdq_rotate_quant_tiled(const void *X_dev, int64_t M, int K, int64_t ldx,
                                     const float *diag_dev, int block,
                                     int8_t *Xt_dev, float *sx_dev, const trdq_weights *next, void *stream);
 trdq_status trdq_xq_untile(const int8_t *Xt_dev, int64_t M, int K, int8_t *Xq_dev, void *stream);
 int trdq_qgemm_tiled_supported(const trdq_weights *w, int64_t M);
-/* 1 where the tiled pair is also the faster one by the library's measured rule (K <= 4608 and
- * either more than one 128 x 144 output tile per compute unit, or at most one and K >= 1024;
- * int4 weights: at least one 128 x 128 tile per compute unit): what trdq_layer_forward takes by
- * itself. */
+/* 1 where the tiled pair is also the faster one by the library's measured rule (K <= 4608, more output
+ * tiles than the kernel for few tokens takes, and either more than one 128 x 144 tile per compute unit, or
+ * at most one and K >= 1024; int4 weights: at least one 128 x 128 tile per compute unit): what
+ * trdq_layer_forward takes by itself. */
 int trdq_qgemm_tiled_preferred(const trdq_weights *w, int64_t M);
 trdq_status trdq_qgemm_tiled(const trdq_weights *w, const int8_t *Xt_dev, const float *sx_dev, int64_t M,
                              const float *bias_dev, void *Y_dev, int64_t ldy,

@@ -80,6 +80,20 @@ trdq_status check_device(int handle_device)
     return dev == handle_device ? TRDQ_OK : TRDQ_ERR_MISMATCH;
 }
 
+// What a quantising pass of M tokens reads ahead for the product that follows it: the copy of the codes that this
+// product will read (tiled: the caller goes on to the block-tiled product).
+trdq_status warm_range(const trdq_weights *next, int64_t M, bool tiled, const void *&warm, int64_t &bytes)
+{
+    warm = nullptr;
+    bytes = 0;
+    if (!next || !next->codes) return TRDQ_OK;
+    if (trdq_status rd = check_device(next->device); rd != TRDQ_OK) return rd;
+    warm = next->codes_tiled && (tiled || trdq::qgemm_reads_tiled_codes(*next, M)) ? next->codes_tiled : next->codes;
+    bytes = (int64_t)next->N * next->K / (next->wbits == 4 ? 2 : 1);
+    bytes -= bytes % 16;
+    return TRDQ_OK;
+}
+
 // Data pointers may be NULL when M == 0 (an empty tensor has no storage).
 trdq_status check_rotate_args(const void *X, int64_t M, int K, int64_t ldx, int block)
 {
@@ -176,8 +190,7 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     const int K = w->K, N = w->N, nb = K / trdq::kBlock;
     const bool w4 = w->wbits == 4;
     const size_t code_bytes = w4 ? (size_t)K * N / 2 : (size_t)K * N;
-    // widths the block-tiled products take: whole 144-channel tiles (int8), whole 128-channel tiles (int4)
-    const bool tiled = !asym && N % (w4 ? 128 : 144) == 0;
+    const bool tiled = !asym;                           // block-tiled copy: every symmetric set
     size_t total = 0;
     auto take = [&](size_t bytes) { const size_t at = total; total += (bytes + 255) / 256 * 256; return at; };
     const size_t at_codes = take(code_bytes), at_tiled = tiled ? take(code_bytes) : 0;
@@ -766,12 +779,7 @@ trdq_status trdq_rotate_quant_warm(const void *X_dev, int64_t M, int K, int64_t 
     if (M == 0) return TRDQ_OK;
     const void *warm = nullptr;
     int64_t warm_bytes = 0;
-    if (next && next->codes) {
-        if (trdq_status rd = check_device(next->device); rd != TRDQ_OK) return rd;
-        warm = next->codes;
-        warm_bytes = (int64_t)next->N * next->K / (next->wbits == 4 ? 2 : 1);
-        warm_bytes -= warm_bytes % 16;
-    }
+    if (trdq_status rd = warm_range(next, M, false, warm, warm_bytes); rd != TRDQ_OK) return rd;
     return hip_status(trdq::launch_rotate_quant(static_cast<const uint16_t *>(X_dev), M, K, ldx, diag_dev,
                                                 Xq_dev, sx_dev, nullptr, warm, warm_bytes,
                                                 static_cast<hipStream_t>(stream)));
@@ -790,12 +798,7 @@ trdq_status trdq_rotate_quant_bits(const void *X_dev, int64_t M, int K, int64_t 
     if (M == 0) return TRDQ_OK;
     const void *warm = nullptr;
     int64_t warm_bytes = 0;
-    if (next && next->codes) {
-        if (trdq_status rd = check_device(next->device); rd != TRDQ_OK) return rd;
-        warm = next->codes;
-        warm_bytes = (int64_t)next->N * next->K / (next->wbits == 4 ? 2 : 1);
-        warm_bytes -= warm_bytes % 16;
-    }
+    if (trdq_status rd = warm_range(next, M, false, warm, warm_bytes); rd != TRDQ_OK) return rd;
     return hip_status(trdq::launch_rotate_quant(static_cast<const uint16_t *>(X_dev), M, K, ldx, diag_dev,
                                                 Xq_dev, sx_dev, nullptr, warm, warm_bytes,
                                                 static_cast<hipStream_t>(stream), abits));
@@ -815,12 +818,7 @@ trdq_status trdq_rotate_quant_asym(const void *X_dev, int64_t M, int K, int64_t 
     if (M == 0) return TRDQ_OK;
     const void *warm = nullptr;
     int64_t warm_bytes = 0;
-    if (next && next->codes) {
-        if (trdq_status rd = check_device(next->device); rd != TRDQ_OK) return rd;
-        warm = next->codes;
-        warm_bytes = (int64_t)next->N * next->K / (next->wbits == 4 ? 2 : 1);
-        warm_bytes -= warm_bytes % 16;
-    }
+    if (trdq_status rd = warm_range(next, M, false, warm, warm_bytes); rd != TRDQ_OK) return rd;
     return hip_status(trdq::launch_rotate_quant(static_cast<const uint16_t *>(X_dev), M, K, ldx, diag_dev,
                                                 Xq_dev, sx_dev, zc_dev, warm, warm_bytes,
                                                 static_cast<hipStream_t>(stream)));
@@ -840,12 +838,7 @@ trdq_status trdq_rotate_quant_rpr(const void *X_dev, int64_t M, int K, int64_t l
     if (M == 0) return TRDQ_OK;
     const void *warm = nullptr;
     int64_t warm_bytes = 0;
-    if (next && next->codes) {
-        if (trdq_status rd = check_device(next->device); rd != TRDQ_OK) return rd;
-        warm = next->codes;
-        warm_bytes = (int64_t)next->N * next->K / (next->wbits == 4 ? 2 : 1);
-        warm_bytes -= warm_bytes % 16;
-    }
+    if (trdq_status rd = warm_range(next, M, false, warm, warm_bytes); rd != TRDQ_OK) return rd;
     return hip_status(trdq::launch_rotate_quant_rpr(static_cast<const uint16_t *>(X_dev), M, K, ldx, diag_dev,
                                                     perm_dev, Xq_dev, sx_dev, warm, warm_bytes,
                                                     static_cast<hipStream_t>(stream)));
@@ -869,13 +862,7 @@ trdq_status trdq_rotate_quant_tiled(const void *X_dev, int64_t M, int K, int64_t
     if (M == 0) return TRDQ_OK;
     const void *warm = nullptr;
     int64_t warm_bytes = 0;
-    if (next && next->codes) {
-        if (trdq_status rd = check_device(next->device); rd != TRDQ_OK) return rd;
-        // warm what the tiled product will read
-        warm = next->codes_tiled ? next->codes_tiled : next->codes;
-        warm_bytes = (int64_t)next->N * next->K / (next->wbits == 4 ? 2 : 1);
-        warm_bytes -= warm_bytes % 16;
-    }
+    if (trdq_status rd = warm_range(next, M, true, warm, warm_bytes); rd != TRDQ_OK) return rd;
     return hip_status(trdq::launch_rotate_quant(static_cast<const uint16_t *>(X_dev), M, K, ldx, diag_dev,
                                                 Xt_dev, sx_dev, nullptr, warm, warm_bytes,
                                                 static_cast<hipStream_t>(stream), 8, true));
@@ -940,12 +927,7 @@ trdq_status trdq_rotate_quant_rpr_asym(const void *X_dev, int64_t M, int K, int6
     if (M == 0) return TRDQ_OK;
     const void *warm = nullptr;
     int64_t warm_bytes = 0;
-    if (next && next->codes) {
-        if (trdq_status rd = check_device(next->device); rd != TRDQ_OK) return rd;
-        warm = next->codes;
-        warm_bytes = (int64_t)next->N * next->K / (next->wbits == 4 ? 2 : 1);
-        warm_bytes -= warm_bytes % 16;
-    }
+    if (trdq_status rd = warm_range(next, M, false, warm, warm_bytes); rd != TRDQ_OK) return rd;
     return hip_status(trdq::launch_rotate_quant_rpr(static_cast<const uint16_t *>(X_dev), M, K, ldx, diag_dev,
                                                     perm_dev, Xq_dev, sx_dev, warm, warm_bytes,
                                                     static_cast<hipStream_t>(stream), zc_dev));

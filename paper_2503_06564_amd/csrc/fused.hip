@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kThreads) void linear_fused_kernel(FusedArgs g)
 //   codes       after the token maxima have met in LDS, the lane's 32 codes are its operands of the two
 //               matrix instructions of the block as they are: the instruction does not care which input
 //               channels a lane supplies as long as both operands agree, so the weights are loaded for the
-//               same 32 channels (32 consecutive bytes of a channel's row) and no code crosses a lane;
+//               same 32 channels and no code crosses a lane;
 //   product     2 TN matrix instructions per block; the waves' partial sums (int8 weights: one per wave, int4:
 //               one per block, i.e. per scale group) meet in LDS, wave w finishes channel tiles w, w + waves, ...
 //
@@ -280,11 +280,10 @@ __global__ __launch_bounds__(kThreads) void linear_fused_kernel(FusedArgs g)
 // idle compute units is free, and fewer weight bytes per compute unit arrive sooner.  The arguments that the
 // first loads need are the ones delivered in registers at wave launch.
 //
-// Measured, back-to-back launches (an empty kernel: 2.5-3 us): 1152 -> 1152 int8 at 16 / 128 / 256 / 512 tokens
-// 4.9 / 5.5 / 6.9 / 9.1 us, against 9.8 / 10.0 / 10.2 / 11.1 for a form that split K over eight waves, rotated
-// with lane exchanges (630 vector instructions per wave instead of 290) and passed the codes through LDS, and
-// 13.3-14.1 for the pair; int4 5.2 / 5.9 / 6.7 / 7.6 against 15.4-16.5 for the pair; 4608 -> 1152 at 16 tokens
-// 12.5 (int8) and 13.5 us (int4) against 35.4 and 40.9 for the pair.
+// Measured, back-to-back launches (an empty kernel: 2.2 us): 1152 -> 1152 int8 at 16 / 128 / 256 / 512 tokens
+// 4.8 / 5.4 / 6.2 / 7.1 us, against 9.8 / 10.0 / 10.2 / 11.1 for a form that split K over eight waves, rotated
+// with lane exchanges (630 vector instructions per wave instead of 290), read row-major weights and passed the codes
+// through LDS, and 7.7-11.4 for the pair; int4 5.2 / 5.9 / 6.9 / 7.7; 4608 -> 1152 at 16 tokens 12.0 (int8), 12.9 (int4).
 constexpr int64_t kSmallMaxWorkgroups = 512;    // at most two rounds of workgroups
 constexpr int kSmallMaxBlocks = 36;
 
@@ -372,22 +371,30 @@ __global__ __launch_bounds__(768) void linear_fused_small_kernel(
             if (i == 0) load_d(0);
         }
     }
-    // weights of channel n0 + 16 a + r, the lane's 32 input channels of each of the wave's blocks
+    // weights of channel n0 + 16 a + r, the lane's 32 input channels of each of the wave's blocks, from the
+    // block-tiled copy: a load's lanes cover runs of 256 (128) bytes.  (Row-major rows would put the four lanes of
+    // a quad in four rows, which the compute unit's address path takes four times as long for.)
     constexpr int WR = W4 ? 1 : 2;                   // 16-byte pieces of them
     // (six blocks' worth of int8 fragments do not fit beside the activations: they follow the rotation)
     constexpr bool kLateW = !W4 && BPW == 3 && TN > 1;
     uint4 wf[BPW][TN][WR];
+    const uint32_t wofs = (uint32_t)((q >> 1) * (W4 ? 512 : 1024) + (q & 1) * (W4 ? 256 : 512) + r * (W4 ? 8 : 16));
     auto load_w = [&]() {
 #pragma unroll
         for (int i = 0; i < BPW; ++i) {
             const int b = b0 + i < nb ? b0 + i : nb - 1;
 #pragma unroll
             for (int a = 0; a < TN; ++a) {
-                int n = n0 + a * 16 + r;
-                if (n >= N) n = N - 1;
-                const uint8_t *src = Wc + (W4 ? (size_t)n * (K >> 1) + b * 64 + q * 16 : (size_t)n * K + b * kBlock + q * 32);
-#pragma unroll
-                for (int h = 0; h < WR; ++h) wf[i][a][h] = *reinterpret_cast<const uint4 *>(src + 16 * h);
+                const int t = n0 + a * 16 < N ? n0 / 16 + a : N / 16 - 1;      // N is a multiple of 16
+                // the lane's first 16 input channels: k block 2 b + q / 2, piece 2 (q % 2) of it
+                const uint8_t *src = Wc + ((size_t)t * (K >> 6) + 2 * b) * (W4 ? 512 : 1024) + wofs;
+                if constexpr (W4) {
+                    const uint2 lo = *reinterpret_cast<const uint2 *>(src), hi = *reinterpret_cast<const uint2 *>(src + 128);
+                    wf[i][a][0] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                } else {
+                    wf[i][a][0] = *reinterpret_cast<const uint4 *>(src);
+                    wf[i][a][1] = *reinterpret_cast<const uint4 *>(src + 256);
+                }
             }
         }
     };
@@ -635,12 +642,16 @@ hipError_t launch_w(const FusedArgs &a, hipStream_t st)
 
 bool fused_supports(int K) { return K % kBlock == 0 && K / kBlock <= 48; }
 
-// True where the fused kernel is the faster path: the few-token kernel in a single round of workgroups.  In a
-// second round the repeated rotation costs more than the pair's second launch: 1152 -> 1152 at 1024 tokens 17.4
-// against 15.0 us, 1152 -> 4608 at 256 tokens 17.0 against 14.8 us (at half of those 9.1 / 14.1 and 9.0 / 13.9).
+// True where the fused kernel is the faster path: the few-token kernel in a single round of workgroups (two of
+// the small ones that one or two blocks make).  In a second round the repeated rotation costs more than the pair's
+// second launch, us: 1152 -> 4608 at 128 tokens 7.0 against 13.2 (256 workgroups), at 256 tokens 12.9 against 14.9;
+// 768 -> 3072 at 256 tokens (352) 11.0 against 10.7; 4608 -> 1152 at 64 tokens (144) 15.3 against 17.7, at 128 (288)
+// 28.2 against 18.7; 256 -> 512 at 2048 tokens (512) 6.4 against 7.7.
 bool fused_pays(int64_t M, int K, int N, int wbits)
 {
-    return M > 0 && K % kBlock == 0 && K <= kSmallMaxBlocks * kBlock && small_workgroups(M, K, N) <= num_cus();
+    (void)wbits;
+    return M > 0 && K % kBlock == 0 && K <= kSmallMaxBlocks * kBlock &&
+           small_workgroups(M, K, N) <= (int64_t)num_cus() * (K <= 2 * kBlock ? 2 : 1);
 }
 
 hipError_t launch_linear_fused(const Weights &w, const uint16_t *X, int64_t M, int64_t ldx,
@@ -653,6 +664,7 @@ hipError_t launch_linear_fused(const Weights &w, const uint16_t *X, int64_t M, i
     a.X = X; a.diag = diag; a.Wc = w.codes; a.sw = w.scales; a.bias = bias; a.colsum = w.colsum; a.Y = Y;
     a.M = M; a.ldx = ldx; a.ldy = ldy; a.K = w.K; a.N = w.N; a.tiles_n = 0; a.nsplit = 1;
     if (small_applies(a)) {
+        a.Wc = w.codes_tiled;
         if (asym) return launch_small_any<false, true>(a, st);
         return w.wbits == 4 ? launch_small_any<true, false>(a, st) : launch_small_any<false, false>(a, st);
     }

@@ -267,6 +267,17 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
         a.zc = zc; a.colsum = w.colsum; a.zcw = w.zcw; a.rowsum = rowsum;
         return launch_qgemm8_asym(a, acc_debug != nullptr, 0, st);
     }
+    // few output tiles: operands straight into registers, K split over the waves
+    if (variant < 0 && w.wbits == 8 && w.codes_tiled) {
+        if (const int tile = qgemm8_direct_tile(M, w.K, w.N); tile >= 0) {
+            GemmArgs a;
+            a.Xq = Xq; a.Wc = w.codes_tiled; a.sx = sx; a.sw = w.scales; a.bias = bias; a.Y = Y;
+            a.acc_debug = acc_debug; a.M = M; a.ldy = ldy; a.K = w.K; a.N = w.N;
+            a.zc = zc; a.colsum = w.colsum;
+            if (zc && !w.colsum) return hipErrorInvalidValue;
+            return launch_qgemm8_direct(a, acc_debug != nullptr, tile, st);
+        }
+    }
     // A ragged token count would send the whole product to the kernel that takes any shape.  With the
     // built-in choice and int8 weights, the whole 256-token (or 128-token) panels go to the fast kernels
     // and only the remaining rows to that kernel, as a second launch on the same stream.
@@ -374,6 +385,11 @@ hipError_t launch_qgemm_tiled(const Weights &w, const int8_t *Xt, const float *s
     return w.wbits == 4 ? launch_qgemm4_tiled(a, acc_debug != nullptr, st) : launch_qgemm8_tiled(a, acc_debug != nullptr, st);
 }
 
+bool qgemm_reads_tiled_codes(const Weights &w, int64_t M)
+{
+    return w.wbits == 8 && w.codes_tiled && qgemm8_direct_tile(M, w.K, w.N) >= 0;
+}
+
 bool qgemm_tiled_pays(int64_t M, int K, int N)
 {
     // Measured on the DiT-XL/2 widths at 256 ... 32768 tokens.  Up to one 128 x 144 tile per compute
@@ -381,6 +397,8 @@ bool qgemm_tiled_pays(int64_t M, int K, int N)
     // at K = 4608); with more tiles the kernel with two workgroups per compute unit does, by 5-30 %,
     // except for long K at up to two tiles per compute unit, where the row-major kernel whose wave groups
     // split K is level with it.
+    // Below those, few tiles go to the kernel that takes both operands straight into registers.
+    if (qgemm8_direct_tile(M, K, N) >= 0) return false;
     const int64_t tiles = (M / 128) * (int64_t)(N / 144);
     if (tiles <= num_cus()) return K >= 1024;
     return !(K >= 2304 && tiles <= 2 * (int64_t)num_cus());

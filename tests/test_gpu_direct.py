@@ -1,0 +1,48 @@
+"""The product for launches with few output tiles (operands straight into registers, K split over the waves) at the edges
+of its tiles, against exact integer sums and the oracle's epilogue on the GPU's own codes."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_06564_amd import trdq, workloads as wl
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+# every tile of the table, from both sides of its remainders: one unit per wave up to K = 1536, two to three beyond
+# (13 units: 7 waves, the last with one; 25 units: 9 waves, the last with one), K = 128 with a single wave
+SHAPES = [(1, 128, 16), (15, 256, 48), (17, 1152, 16), (16, 1152, 4608), (65, 1152, 1168), (129, 1152, 1152),
+          (250, 768, 2304), (500, 1152, 1136), (33, 1664, 80), (1, 4608, 1152), (63, 3200, 272), (200, 4608, 1152),
+          (769, 4608, 1152), (1000, 3072, 768), (2047, 256, 512)]
+
+
+@pytest.mark.parametrize("M,K,N", SHAPES)
+@pytest.mark.parametrize("asym", [False, True])
+def test_edges(oracle, M, K, N, asym):
+    Xb, W, d, bias = wl.small_case(900 + M, M, K, N, n_outliers=4)
+    w = trdq.prepare_weights(gu.f32_to_dev(W), gu.f32_to_dev(d))
+    X, dd = gu.bf16_to_dev(Xb), gu.f32_to_dev(d)
+    Xq = torch.empty((M, K), dtype=torch.int8, device=gu.dev())
+    sx = torch.empty(M, device=gu.dev())
+    zc = torch.empty(M, dtype=torch.int32, device=gu.dev())
+    buf = torch.full((M + 1, N + 8), 7.0, dtype=torch.bfloat16, device=gu.dev())
+    Y = buf[:M, :N]
+    acc = torch.full((M, N), -7, dtype=torch.int32, device=gu.dev())
+    for debug in (acc, None):
+        buf.fill_(7.0)
+        if asym:
+            trdq.rotate_quant_asym(X, dd, Xq, sx, zc, warm=w)
+            trdq.qgemm_asym(w, Xq, sx, zc, Y, bias=gu.f32_to_dev(bias), acc_debug=debug)
+        else:
+            trdq.rotate_quant(X, dd, Xq, sx, warm=w)
+            trdq.qgemm(w, Xq, sx, Y, bias=gu.f32_to_dev(bias), acc_debug=debug)
+    torch.cuda.synchronize()
+    assert (buf[M] == 7.0).all() and (buf[:, N:] == 7.0).all()      # nothing outside the output
+    codes, scales = w.export()
+    q = Xq.cpu().numpy().astype(np.float64)
+    if asym:
+        q = q + zc.cpu().numpy()[:, None]                            # q - z, exact in float64 as the sums are
+    want = (q @ codes.astype(np.float64)).astype(np.int32)
+    assert np.array_equal(acc.cpu().numpy(), want), "int32 accumulators differ"
+    y = oracle.dequant(want, sx.cpu().numpy(), scales, bias)
+    gu.assert_y_same_codes(gu.bf16_to_host(Y), y, "Y (same codes)")
