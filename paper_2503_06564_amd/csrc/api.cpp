@@ -1091,9 +1091,11 @@ trdq_status trdq_layer_forward(const trdq_layer *l, int step, const void *X_dev,
     if (!l->set[(size_t)g]) return TRDQ_ERR_MISMATCH;
     const trdq_weights *w = l->w[(size_t)g];
     const float *d = w->diag;
-    if (fused > 0 || (fused < 0 && trdq::fused_pays(M, l->K, l->N, w->wbits)))
+    const bool have_ws = Xq_ws_dev && sx_ws_dev;
+    if (fused > 0 || (fused < 0 && (have_ws ? trdq::fused_pays(M, l->K, l->N, w->wbits)
+                                            : trdq::fused_needs_no_workspace(M, l->K, l->N, w->wbits))))
         return trdq_linear_fused(X_dev, M, l->K, d, w, bias_dev, Y_dev, l->N, stream);
-    if (!Xq_ws_dev || !sx_ws_dev) return TRDQ_ERR_NULL;
+    if (!have_ws) return TRDQ_ERR_NULL;
     // the workspace is private to the layer: block-tiled codes where the tiled product takes the shape
     // (M % 128 == 0 there, so the workspace size M * K is the same)
     if (trdq_qgemm_tiled_preferred(w, M) && aligned(Y_dev, 16)) {

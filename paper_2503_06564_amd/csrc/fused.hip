@@ -654,6 +654,15 @@ bool fused_pays(int64_t M, int K, int N, int wbits)
            small_workgroups(M, K, N) <= (int64_t)num_cus() * (K <= 2 * kBlock ? 2 : 1);
 }
 
+// Where trdq_layer_forward takes the fused kernel for a caller that gave no workspace: a fixed range of shapes, so that
+// which calls need one does not move with the measured choice above.
+bool fused_needs_no_workspace(int64_t M, int K, int N, int wbits)
+{
+    if (wbits != 8 || K > 1536 || K % kBlock != 0 || M <= 0) return false;
+    const int bn = N % 144 == 0 ? 144 : 128;
+    return ((M + 15) / 16) * ((N + bn - 1) / bn) <= num_cus();
+}
+
 hipError_t launch_linear_fused(const Weights &w, const uint16_t *X, int64_t M, int64_t ldx,
                                const float *diag, const float *bias, uint16_t *Y, int64_t ldy,
                                hipStream_t st, bool asym)
