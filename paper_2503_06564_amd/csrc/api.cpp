@@ -81,14 +81,14 @@ trdq_status check_device(int handle_device)
 }
 
 // What a quantising pass of M tokens reads ahead for the product that follows it: the copy of the codes that this
-// product will read (tiled: the caller goes on to the block-tiled product).
-trdq_status warm_range(const trdq_weights *next, int64_t M, bool tiled, const void *&warm, int64_t &bytes)
+// product will read (tiled: the caller goes on to the block-tiled product; asym: codes with zero points).
+trdq_status warm_range(const trdq_weights *next, int64_t M, bool tiled, const void *&warm, int64_t &bytes, bool asym = false)
 {
     warm = nullptr;
     bytes = 0;
     if (!next || !next->codes) return TRDQ_OK;
     if (trdq_status rd = check_device(next->device); rd != TRDQ_OK) return rd;
-    warm = next->codes_tiled && (tiled || trdq::qgemm_reads_tiled_codes(*next, M)) ? next->codes_tiled : next->codes;
+    warm = next->codes_tiled && (tiled || trdq::qgemm_reads_tiled_codes(*next, M, asym)) ? next->codes_tiled : next->codes;
     bytes = (int64_t)next->N * next->K / (next->wbits == 4 ? 2 : 1);
     bytes -= bytes % 16;
     return TRDQ_OK;
@@ -818,7 +818,7 @@ trdq_status trdq_rotate_quant_asym(const void *X_dev, int64_t M, int K, int64_t 
     if (M == 0) return TRDQ_OK;
     const void *warm = nullptr;
     int64_t warm_bytes = 0;
-    if (trdq_status rd = warm_range(next, M, false, warm, warm_bytes); rd != TRDQ_OK) return rd;
+    if (trdq_status rd = warm_range(next, M, false, warm, warm_bytes, true); rd != TRDQ_OK) return rd;
     return hip_status(trdq::launch_rotate_quant(static_cast<const uint16_t *>(X_dev), M, K, ldx, diag_dev,
                                                 Xq_dev, sx_dev, zc_dev, warm, warm_bytes,
                                                 static_cast<hipStream_t>(stream)));
@@ -927,7 +927,7 @@ trdq_status trdq_rotate_quant_rpr_asym(const void *X_dev, int64_t M, int K, int6
     if (M == 0) return TRDQ_OK;
     const void *warm = nullptr;
     int64_t warm_bytes = 0;
-    if (trdq_status rd = warm_range(next, M, false, warm, warm_bytes); rd != TRDQ_OK) return rd;
+    if (trdq_status rd = warm_range(next, M, false, warm, warm_bytes, true); rd != TRDQ_OK) return rd;
     return hip_status(trdq::launch_rotate_quant_rpr(static_cast<const uint16_t *>(X_dev), M, K, ldx, diag_dev,
                                                     perm_dev, Xq_dev, sx_dev, warm, warm_bytes,
                                                     static_cast<hipStream_t>(stream), zc_dev));

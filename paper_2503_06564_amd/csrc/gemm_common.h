@@ -118,6 +118,11 @@ hipError_t launch_qgemm4_dma(const GemmArgs &a, bool debug, int variant, hipStre
 // Kernel on block-tiled operands (qgemm_tiled.hip): a.Xq and a.Wc point at the tiled forms.
 bool tiled_supports(const GemmArgs &a);
 hipError_t launch_qgemm8_tiled(const GemmArgs &a, bool debug, hipStream_t st);
+// the same kernels on row-major activation codes, any M >= 128 and N >= 144; a.Wc points at the tiled form, a.zc / a.colsum
+// (optional): asymmetric activations
+bool tiled_rows_supports(const GemmArgs &a);
+bool tiled_rows_pays(int64_t M, int K, int N, bool asym);
+hipError_t launch_qgemm8_tiled_rows(const GemmArgs &a, bool debug, hipStream_t st);
 hipError_t launch_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st);
 // int4 weights on block-tiled operands (qgemm_tiled.hip): a.Wc holds the block form of the packed codes
 bool tiled4_supports(const GemmArgs &a);

@@ -247,9 +247,11 @@ hipError_t launch_cfg(const GemmArgs &a, bool debug, hipStream_t st)
 
 // Tile variants.  0-5: register-staged double buffer {BM, BN, BK} (also the int4 path):
 //   0: 128x128x64   1: 128x128x128   2: 256x128x64   3: 128x256x64   4: 256x128x128   5: 64x128x128
-// 6 and up: the direct-to-LDS int8 kernels of qgemm_dma.hip (variant - 6 indexes its table).
+// 6 and up: the direct-to-LDS int8 kernels of qgemm_dma.hip (variant - 6 indexes its table).  The last two: the tiled
+// kernels on row-major activations (qgemm_tiled.hip; shapes they do not take go to the built-in choice), and the
+// 256 x 256 kernel.
 constexpr int kRegVariants = 6;
-int qgemm_num_variants() { return kRegVariants + dma_num_variants() + 1; }
+int qgemm_num_variants() { return kRegVariants + dma_num_variants() + 2; }
 
 hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, const int32_t *zc, int64_t M,
                         const float *bias, uint16_t *Y, int64_t ldy, int32_t *acc_debug,
@@ -278,7 +280,18 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
             return launch_qgemm8_direct(a, acc_debug != nullptr, tile, st);
         }
     }
-    // A ragged token count would send the whole product to the kernel that takes any shape.  With the
+    const int rows_variant = kRegVariants + dma_num_variants(), wide_variant = rows_variant + 1;
+    if (w.wbits == 8 && w.codes_tiled &&
+        (variant == rows_variant || (variant < 0 && tiled_rows_pays(M, w.K, w.N, zc != nullptr)))) {
+        GemmArgs a;
+        a.Xq = Xq; a.Wc = w.codes_tiled; a.sx = sx; a.sw = w.scales; a.bias = bias; a.Y = Y;
+        a.acc_debug = acc_debug; a.M = M; a.ldy = ldy; a.K = w.K; a.N = w.N;
+        a.zc = zc; a.colsum = w.colsum;
+        if (tiled_rows_supports(a)) return launch_qgemm8_tiled_rows(a, acc_debug != nullptr, st);
+    }
+    if (variant == rows_variant) variant = -1;
+    // A ragged token count that the rows form did not take (many tokens, see tiled_rows_pays, or rows of Y that are
+    // not 16-byte aligned) would send the whole product to the kernel that takes any shape.  With the
     // built-in choice and int8 weights, the whole 256-token (or 128-token) panels go to the fast kernels
     // and only the remaining rows to that kernel, as a second launch on the same stream.
     if (variant < 0 && w.wbits == 8 && M >= 1024 && M % 128 != 0) {
@@ -343,7 +356,7 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
         if (tiles144 > 0 && tiles144 <= num_cus())
             variant = a.K >= 2304 ? kRegVariants + 18 : kRegVariants + 14;
         else if (tiles256 >= 400 && wide_supports(a))
-            variant = kRegVariants + dma_num_variants();
+            variant = wide_variant;
         else if (tiles144 > 0)
             variant = kRegVariants + 15;
     }
@@ -357,7 +370,7 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
         default:
             // last variant: 256 x 256 tiles, hand-scheduled loop; shapes it does not take go to the
             // ring kernel
-            if (variant == kRegVariants + dma_num_variants())
+            if (variant == wide_variant)
                 return wide_supports(a) ? launch_qgemm8_wide(a, dbg, st) : launch_qgemm8_dma(a, dbg, 0, st);
             return launch_qgemm8_dma(a, dbg, variant - kRegVariants, st);
     }
@@ -385,9 +398,10 @@ hipError_t launch_qgemm_tiled(const Weights &w, const int8_t *Xt, const float *s
     return w.wbits == 4 ? launch_qgemm4_tiled(a, acc_debug != nullptr, st) : launch_qgemm8_tiled(a, acc_debug != nullptr, st);
 }
 
-bool qgemm_reads_tiled_codes(const Weights &w, int64_t M)
+bool qgemm_reads_tiled_codes(const Weights &w, int64_t M, bool asym)
 {
-    return w.wbits == 8 && w.codes_tiled && qgemm8_direct_tile(M, w.K, w.N) >= 0;
+    return w.wbits == 8 && w.codes_tiled &&
+           (qgemm8_direct_tile(M, w.K, w.N) >= 0 || tiled_rows_pays(M, w.K, w.N, asym));
 }
 
 bool qgemm_tiled_pays(int64_t M, int K, int N)

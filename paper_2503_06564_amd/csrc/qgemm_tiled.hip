@@ -38,7 +38,13 @@ constexpr int kNS = 3;                       // stages of the ring
 constexpr int kStageBig = (256 / 16 + kTN) * 1024;
 constexpr int kParOff = 3 * kStageBig;     // epilogue operands: [144 s_w][pad][144 bias][pad][256 s_x]
 constexpr int kParSw = 0, kParBias = 1024, kParSx = 2048;
-constexpr int kTiledLds = kParOff + 3072;    // 79872 B: two workgroups per compute unit
+constexpr int kParCs = 3072, kParZc = 4096;  // asymmetric activations: [144 column sums][pad][256 zero-point terms]
+constexpr int par_bytes(bool asym) { return asym ? 5120 : 3072; }
+constexpr int tiled_lds(bool asym) { return kParOff + par_bytes(asym); }   // 79872 or 81920 B: two workgroups per compute unit
+
+// Where the activations are: kBlocks: the block-tiled form, whole tiles.  kRows: row-major [M, K], any M and N from one
+// tile on.  kRowsAsym: the same with zero points.
+enum { kBlocks = 0, kRows = 1, kRowsAsym = 2 };
 
 template <int... Is, class F>
 __device__ __forceinline__ void static_for_seq(std::integer_sequence<int, Is...>, F &&f)
@@ -65,6 +71,46 @@ __device__ __forceinline__ void copy_1k_if(int on, uint32_t voff, const void *sb
                  : "memory", "scc");
 }
 
+__device__ __forceinline__ void copy_256_if(int on, uint32_t voff, const void *sbase, uint32_t lds_addr)
+{
+    asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lskip%=\n\t"
+                 "s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1\n"
+                 ".Lskip%=:"
+                 :: "v"(voff), "s"(sbase), "s"(lds_addr), "s"(__builtin_amdgcn_readfirstlane(on))
+                 : "memory", "scc");
+}
+
+// First token and channel of a tile.  M need not be a multiple of the tile's height (with row-major activations neither
+// of 128, and N not of the width): the last tile then starts early enough to end at the last token or channel.  What it shares with its neighbour is computed twice
+// and stored twice, the same values.
+__device__ __forceinline__ int64_t tile_m0(const GemmArgs &g, int tm, int bm)
+{
+    const int64_t m0 = (int64_t)tm * bm;
+    return m0 > g.M - bm ? g.M - bm : m0;
+}
+template <int FORM>
+__device__ __forceinline__ int tile_n0(const GemmArgs &g, int tn)
+{
+    const int n0 = tn * kBN;
+    return FORM != kBlocks && n0 > g.N - kBN ? g.N - kBN : n0;
+}
+
+// Row-major activations: a copy instruction moves 16 rows x 64 bytes, four lanes to a row (lanes of a quad in four
+// rows take four times as long at the compute unit's address path), so the rows lie 64 bytes apart in LDS, their
+// 16-byte pieces XOR-swizzled for the fragment reads.
+template <int FORM>
+__device__ __forceinline__ uint32_t x_copy_off(int lane, int K)
+{
+    if constexpr (FORM == kBlocks) return (uint32_t)(lane * 16);
+    else return (uint32_t)((lane >> 2) * K + ((lane & 3) ^ chunk_swizzle<64>(lane >> 2)) * 16);
+}
+template <int FORM>
+__device__ __forceinline__ int x_frag_off(int r, int p)
+{
+    if constexpr (FORM == kBlocks) return blk_off(r, p);
+    else return r * 64 + (p ^ chunk_swizzle<64>(r)) * 16;
+}
+
 // One output tile of BM tokens x 144 channels.  Wave w owns token rows w * BM/4 .. of the tile
 // and all 144 channels: TM = BM / 64 activation fragments (its own, which only it reads) and the
 // nine weight fragments (shared) per k-step; the lane ends with channels n .. n+3 of one token per
@@ -73,7 +119,7 @@ __device__ __forceinline__ void copy_1k_if(int on, uint32_t voff, const void *sb
 // ahead, then 9 x TM matrix instructions on the fragments in registers while the next step's
 // fragments are read: a weight fragment's registers are refilled as soon as its TM instructions
 // have issued, the activation fragments alternate between two sets.
-template <int BM, bool DEBUG>
+template <int BM, bool DEBUG, int FORM>
 __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8_t *smem)
 {
     constexpr int TM = BM / 64;
@@ -93,13 +139,15 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
     const int KT = g.K >> 6;                          // k-steps
-    const int64_t m0 = (int64_t)tm * BM;
-    const int n0 = tn * kBN;
+    const int64_t m0 = tile_m0(g, tm, BM);
+    const int n0 = tile_n0<FORM>(g, tn);
 
     const int64_t gstride = (int64_t)KT * 1024;      // bytes from one 16-row group to the next
-    const int8_t *const xsrc = g.Xq + (m0 / 16 + wave * TM) * gstride;
+    const int8_t *const xsrc = g.Xq + (m0 + wave * TM * 16) * g.K;
     const int8_t *const wsrc = static_cast<const int8_t *>(g.Wc) + (int64_t)(n0 / 16) * gstride;
     const uint32_t voff = (uint32_t)(lane * 16);        // copies keep the block's order
+    const uint32_t voffx = x_copy_off<FORM>(lane, g.K);
+    constexpr int XSTEP = FORM == kBlocks ? 1024 : 64;  // bytes from one k-step of the activations to the next
 
     const int8_t *xs[TM], *ws[2];
 #pragma unroll
@@ -113,7 +161,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
         constexpr int c = decltype(c_tag)::value;
         const uint32_t sbase = lds0 + st * STAGE;
         const int64_t so = (int64_t)s * 1024;
-        if constexpr (c < TM) dma_1k(voff, xs[c] + so, sbase + (wave * TM + c) * 1024);
+        if constexpr (c < TM) dma_1k(voffx, xs[c] + (int64_t)s * XSTEP, sbase + (wave * TM + c) * 1024);
         else if constexpr (c < TM + 2) dma_1k(voff, ws[c - TM] + so, sbase + (XB + wave + 4 * (c - TM)) * 1024);
         else copy_1k_if(wave == 0, voff, ws8 + so, sbase + (XB + 8) * 1024);
     };
@@ -131,7 +179,15 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
         copy_1k_if(wave == 1 && g.bias != nullptr, v36, g.bias ? g.bias + n0 : g.sw, par + kParBias);
         if (wave == 1 && g.bias == nullptr)           // no bias: zeros, so that the epilogue needs no branch
             *reinterpret_cast<uint4 *>(smem + kParOff + kParBias + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
-        copy_1k_if(wave == 2, vsx, g.sx + m0, par + kParSx);
+        if constexpr (FORM == kBlocks) {
+            copy_1k_if(wave == 2, vsx, g.sx + m0, par + kParSx);
+        } else {                                      // any token may be the tile's first: four-byte pieces
+            copy_256_if(wave < BM / 64, (uint32_t)(lane * 4), g.sx + m0 + wave * 64, par + kParSx + wave * 256);
+            if constexpr (FORM == kRowsAsym) {
+                copy_256_if(wave < BM / 64, (uint32_t)(lane * 4), g.zc + m0 + wave * 64, par + kParZc + wave * 256);
+                copy_1k_if(wave == 3, v36, g.colsum + n0, par + kParCs);
+            }
+        }
     }
     // KT is even and at least 2 (K is a multiple of 128)
     issue(0, 0);
@@ -149,6 +205,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
     const uint64_t clk_t1 = wall_clock64();
 #endif
     const int fro = blk_off(l16, lg);                 // the lane's piece of a fragment block
+    const int frox = x_frag_off<FORM>(l16, lg);       // ... of an activation block
     v4i acc[kTN][TM];
 #pragma unroll
     for (int a = 0; a < kTN; ++a)
@@ -158,7 +215,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
 #pragma unroll
     for (int a = 0; a < kTN; ++a) af[a] = *reinterpret_cast<const v4i *>(smem + (XB + a) * 1024 + fro);
 #pragma unroll
-    for (int b = 0; b < TM; ++b) bf[0][b] = *reinterpret_cast<const v4i *>(smem + (wave * TM + b) * 1024 + fro);
+    for (int b = 0; b < TM; ++b) bf[0][b] = *reinterpret_cast<const v4i *>(smem + (wave * TM + b) * 1024 + frox);
 
     int st = 0;
     // One k-step on activation fragment set PAR.  REFILL: the next step exists; its fragments are read
@@ -173,12 +230,13 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
         constexpr int WAITN = decltype(wait_tag)::value;
         const int nst = (st + 1 == kNS) ? 0 : st + 1;
         const int8_t *const nxt = smem + nst * STAGE + fro;
+        const int8_t *const nxtx = smem + nst * STAGE + frox;
         if constexpr (REFILL) {
             wait_vmcnt<WAITN>();                               // step kt+1 has landed (this wave's share)
             __syncthreads();                                   // ... everyone's; step kt's stage is retired
 #pragma unroll
             for (int b = 0; b < TM; ++b)
-                bf[1 - PAR][b] = *reinterpret_cast<const v4i *>(nxt + (wave * TM + b) * 1024);
+                bf[1 - PAR][b] = *reinterpret_cast<const v4i *>(nxtx + (wave * TM + b) * 1024);
             __builtin_amdgcn_sched_barrier(0);
         }
         static_for_n<kTN>([&](auto a_tag) {
@@ -232,9 +290,15 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
 #pragma unroll
     for (int b = 0; b < TM; ++b) {
         const float sxm = par[kParSx / 4 + wave * (BM / 4) + b * 16 + l16];
+        int zc = 0;
+        if constexpr (FORM == kRowsAsym) zc = reinterpret_cast<const int *>(par)[kParZc / 4 + wave * (BM / 4) + b * 16 + l16];
 #pragma unroll
         for (int a = 0; a < kTN; ++a) {
             const float4 s = s_nxt, bi = bi_nxt;
+            if constexpr (FORM == kRowsAsym) {
+                if (a == 0) asm volatile("" ::: "memory");            // re-read per token tile: 36 registers if kept
+                acc[a][b] += zc * *reinterpret_cast<const v4i *>(par + kParCs / 4 + a * 16 + lg * 4);
+            }
             {
                 const int an = (a + 1) % kTN;         // wraps to the first tile for the next token tile
                 s_nxt = *reinterpret_cast<const float4 *>(psw + an * 16);
@@ -277,19 +341,19 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
 #endif
 }
 
-template <bool DEBUG>
+template <bool DEBUG, int FORM>
 __global__ __launch_bounds__(kThreads, 2) void qgemm8_tiled_kernel(GemmArgs g, int n_big, int nbn)
 {
     extern __shared__ __align__(16) int8_t smem[];
     const int id = blockIdx.x;
-    const int tiles_n = g.N / kBN;
+    const int tiles_n = (g.N + kBN - 1) / kBN;        // kBlocks: whole tiles
     int tm, tn;
     if (id < n_big) {
-        tile_map(id, (int)(g.M / 256), nbn, tm, tn);
-        run_tile<256, DEBUG>(g, tm, tn, smem);
+        tile_map(id, (int)((g.M + 255) / 256), nbn, tm, tn);
+        run_tile<256, DEBUG, FORM>(g, tm, tn, smem);
     } else {
-        tile_map(id - n_big, (int)(g.M / 128), tiles_n - nbn, tm, tn);
-        run_tile<128, DEBUG>(g, tm, tn + nbn, smem);
+        tile_map(id - n_big, (int)((g.M + 127) / 128), tiles_n - nbn, tm, tn);
+        run_tile<128, DEBUG, FORM>(g, tm, tn + nbn, smem);
     }
 }
 
@@ -313,9 +377,9 @@ constexpr int kKsStage = (8 + kTN) * 1024;
 constexpr int kKsCopies = 9;                         // per wave and k-step
 constexpr int kKsPairs = 2;
 template <int NS> constexpr int ks_par_off() { return kKsPairs * NS * kKsStage; }
-template <int NS> constexpr int ks_lds() { return ks_par_off<NS>() + 3072; }
+template <int NS> constexpr int ks_lds(bool asym) { return ks_par_off<NS>() + par_bytes(asym); }
 
-template <int NS, bool DEBUG>
+template <int NS, bool DEBUG, int FORM>
 __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(GemmArgs g)
 {
     constexpr int NG = kKsPairs;
@@ -336,17 +400,19 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
     const int mw = wave & 1, kg = wave >> 1;         // token half, part of K
     const int l16 = lane & 15, lg = lane >> 4;
     int tm, tn;
-    tile_map(blockIdx.x, (int)(g.M / 128), g.N / kBN, tm, tn);
+    tile_map(blockIdx.x, (int)((g.M + 127) / 128), (g.N + kBN - 1) / kBN, tm, tn);
     const int KT = g.K >> 6;                          // k-steps of the product
     const int KTg = KT / NG;                          // of one pair: even, at least NS
-    const int64_t m0 = (int64_t)tm * 128;
-    const int n0 = tn * kBN;
+    const int64_t m0 = tile_m0(g, tm, 128);
+    const int n0 = tile_n0<FORM>(g, tn);
 
     const int64_t gstride = (int64_t)KT * 1024;      // bytes from one 16-row group to the next
     const int64_t kofs = (int64_t)kg * KTg * 1024;   // this pair's first k-step
-    const int8_t *const xsrc = g.Xq + (m0 / 16 + mw * TM) * gstride + kofs;
+    constexpr int XSTEP = FORM == kBlocks ? 1024 : 64;  // bytes from one k-step of the activations to the next
+    const int8_t *const xsrc = g.Xq + (m0 + mw * TM * 16) * g.K + (int64_t)kg * KTg * XSTEP;
     const int8_t *const wsrc = static_cast<const int8_t *>(g.Wc) + (int64_t)(n0 / 16) * gstride + kofs;
     const uint32_t voff = (uint32_t)(lane * 16);        // copies keep the block's order
+    const uint32_t voffx = x_copy_off<FORM>(lane, g.K);
     int8_t *const ring = smem + kg * RING;
     const uint32_t ring0 = lds0 + kg * RING;
 
@@ -367,7 +433,8 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
     }
     auto issue_one = [&](auto c_tag, int s, int st) {
         constexpr int c = decltype(c_tag)::value;
-        dma_1k(voff, src[c] + (int64_t)s * 1024, ring0 + st * kKsStage + dst[c]);
+        if constexpr (c < TM) dma_1k(voffx, src[c] + (int64_t)s * XSTEP, ring0 + st * kKsStage + dst[c]);
+        else dma_1k(voff, src[c] + (int64_t)s * 1024, ring0 + st * kKsStage + dst[c]);
     };
     auto issue = [&](int s, int st) {
         static_for_n<P>([&](auto c) { issue_one(c, s, st); });
@@ -382,7 +449,15 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
         copy_1k_if(wave == 1 && g.bias != nullptr, v36, g.bias ? g.bias + n0 : g.sw, par + kParBias);
         if (wave == 1 && g.bias == nullptr)
             *reinterpret_cast<uint4 *>(smem + PAROFF + kParBias + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
-        copy_1k_if(wave == 2, vsx, g.sx + m0, par + kParSx);
+        if constexpr (FORM == kBlocks) {
+            copy_1k_if(wave == 2, vsx, g.sx + m0, par + kParSx);
+        } else {
+            copy_256_if(wave < 2, (uint32_t)(lane * 4), g.sx + m0 + mw * 64, par + kParSx + mw * 256);
+            if constexpr (FORM == kRowsAsym) {
+                copy_256_if(wave < 2, (uint32_t)(lane * 4), g.zc + m0 + mw * 64, par + kParZc + mw * 256);
+                copy_1k_if(wave == 3, v36, g.colsum + n0, par + kParCs);
+            }
+        }
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) issue(s, s);
@@ -393,7 +468,7 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
     const uint64_t clk_t1 = wall_clock64();
 #endif
 
-    const int fro = blk_off(l16, lg);
+    const int fro = blk_off(l16, lg), frox = x_frag_off<FORM>(l16, lg);
     v4i acc[kTN][TM];
 #pragma unroll
     for (int a = 0; a < kTN; ++a)
@@ -403,7 +478,7 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
 #pragma unroll
     for (int a = 0; a < kTN; ++a) af[a] = *reinterpret_cast<const v4i *>(ring + (8 + a) * 1024 + fro);
 #pragma unroll
-    for (int b = 0; b < TM; ++b) bf[0][b] = *reinterpret_cast<const v4i *>(ring + (mw * TM + b) * 1024 + fro);
+    for (int b = 0; b < TM; ++b) bf[0][b] = *reinterpret_cast<const v4i *>(ring + (mw * TM + b) * 1024 + frox);
 
     int st = 0;
     // One k-step on activation fragment set PAR.  REFILL: the next step exists: wait until at most
@@ -417,12 +492,13 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
         constexpr int WAITN = decltype(wait_tag)::value;
         const int nst = (st + 1 == NS) ? 0 : st + 1;
         const int8_t *const nxt = ring + nst * kKsStage + fro;
+        const int8_t *const nxtx = ring + nst * kKsStage + frox;
         if constexpr (REFILL) {
             wait_vmcnt<WAITN>();
             __syncthreads();
 #pragma unroll
             for (int b = 0; b < TM; ++b)
-                bf[1 - PAR][b] = *reinterpret_cast<const v4i *>(nxt + (mw * TM + b) * 1024);
+                bf[1 - PAR][b] = *reinterpret_cast<const v4i *>(nxtx + (mw * TM + b) * 1024);
             __builtin_amdgcn_sched_barrier(0);
         }
         static_for_n<kTN>([&](auto a_tag) {
@@ -500,10 +576,14 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
         if (b * NG / TM == kg) {                      // wave-uniform
             const int64_t m_own = m0 + mw * 64 + b * 16;
             const float sxm = par[kParSx / 4 + mw * 64 + b * 16 + l16];
+            int zc = 0;
+            if constexpr (FORM == kRowsAsym) zc = reinterpret_cast<const int *>(par)[kParZc / 4 + mw * 64 + b * 16 + l16];
 #pragma unroll
             for (int a = 0; a < kTN; ++a) {
                 const float4 s = sw_r[a];
                 const float4 bi = bi_r[a];
+                if constexpr (FORM == kRowsAsym)
+                    acc[a][b] += zc * *reinterpret_cast<const v4i *>(par + kParCs / 4 + a * 16 + lg * 4);
                 if constexpr (DEBUG) {
                     *reinterpret_cast<int4 *>(g.acc_debug + (m_own + l16) * g.N + n0 + a * 16 + lg * 4) =
                         make_int4(acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]);
@@ -568,15 +648,6 @@ constexpr int kW4Stage = 13312;
 constexpr int kW4ParOff = kW4NS * kW4Stage;          // epilogue operands: [128 bias][128 s_x]
 constexpr int kW4Lds = kW4ParOff + 2048;             // 68608 B
 constexpr int kW4Copies = 4;
-
-__device__ __forceinline__ void copy_256_if(int on, uint32_t voff, const void *sbase, uint32_t lds_addr)
-{
-    asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lskip%=\n\t"
-                 "s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1\n"
-                 ".Lskip%=:"
-                 :: "v"(voff), "s"(sbase), "s"(lds_addr), "s"(__builtin_amdgcn_readfirstlane(on))
-                 : "memory", "scc");
-}
 
 template <bool DEBUG>
 __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
@@ -817,57 +888,103 @@ bool tiled_supports(const GemmArgs &a)
 // short tiles alone would need more; all tall tiles when even those need more than one round.
 void tiled_split(int64_t M, int N, int &n_big, int &nbn)
 {
-    const int T = N / kBN;
+    const int T = (N + kBN - 1) / kBN;
     const int64_t slots = 2 * (int64_t)num_cus();
-    const int64_t p128 = M / 128;
+    const int64_t p128 = (M + 127) / 128, p256 = (M + 255) / 256;
     n_big = 0; nbn = 0;
-    if (M % 256 != 0 || p128 * T <= slots) return;
-    // tiles(nbn) = (M / 256) * nbn + (M / 128) * (T - nbn) <= slots
-    int64_t need = (p128 * T - slots + (p128 / 2) - 1) / (p128 / 2);
+    if (M < 256 || p128 * T <= slots) return;
+    // tiles(nbn) = p256 * nbn + p128 * (T - nbn) <= slots
+    const int64_t need = p128 > p256 ? (p128 * T - slots + (p128 - p256) - 1) / (p128 - p256) : T;
     nbn = (int)(need > T ? T : need);
-    n_big = (int)((M / 256) * nbn);
+    n_big = (int)(p256 * nbn);
 }
 
 // The kernel that splits K inside the workgroup: two pairs, four stages for an even number of
 // k-steps per pair and three for an odd one (the main loop takes the steps two at a time).
 bool tiled_ksplit_applies(const GemmArgs &a)
 {
-    return a.K % 128 == 0 && a.K >= 1024 && (a.M / 128) * (int64_t)(a.N / kBN) <= num_cus();
+    return a.K % 128 == 0 && a.K >= 1024 && ((a.M + 127) / 128) * (int64_t)((a.N + kBN - 1) / kBN) <= num_cus();
 }
 
-template <int NS>
+template <int NS, int FORM>
 hipError_t launch_ksplit(const GemmArgs &a, bool debug, hipStream_t st)
 {
     GemmArgs g = a;
-    constexpr int lds = ks_lds<NS>();
+    constexpr int lds = ks_lds<NS>(FORM == kRowsAsym);
     auto go = [&](auto kern) -> hipError_t {
         if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)((a.M / 128) * (a.N / kBN))), dim3(256), lds, st, g);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(((a.M + 127) / 128) * ((a.N + kBN - 1) / kBN))), dim3(256), lds, st, g);
         return hipGetLastError();
     };
 #ifdef TRDQ_PROBE_PHASES
     debug = false;                                    // the debug pointer receives time stamps instead
 #endif
-    return debug ? go(qgemm8_tiled_ksplit_kernel<NS, true>) : go(qgemm8_tiled_ksplit_kernel<NS, false>);
+    return debug ? go(qgemm8_tiled_ksplit_kernel<NS, true, FORM>) : go(qgemm8_tiled_ksplit_kernel<NS, false, FORM>);
+}
+
+template <int FORM>
+hipError_t launch_form(const GemmArgs &a, bool debug, hipStream_t st)
+{
+    if (tiled_ksplit_applies(a)) return ((a.K / 128) & 1) ? launch_ksplit<3, FORM>(a, debug, st) : launch_ksplit<4, FORM>(a, debug, st);
+    int n_big, nbn;
+    tiled_split(a.M, a.N, n_big, nbn);
+    const int64_t total = n_big + ((a.M + 127) / 128) * ((a.N + kBN - 1) / kBN - nbn);
+    GemmArgs g = a;
+    constexpr int lds = tiled_lds(FORM == kRowsAsym);
+    auto go = [&](auto kern) -> hipError_t {
+        if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(kThreads), lds, st, g, n_big, nbn);
+        return hipGetLastError();
+    };
+#ifdef TRDQ_PROBE_PHASES
+    debug = false;                                    // the debug pointer receives time stamps instead
+#endif
+    return debug ? go(qgemm8_tiled_kernel<true, FORM>) : go(qgemm8_tiled_kernel<false, FORM>);
 }
 
 hipError_t launch_qgemm8_tiled(const GemmArgs &a, bool debug, hipStream_t st)
 {
-    if (!tiled_supports(a)) return hipErrorInvalidValue;
-    if (tiled_ksplit_applies(a)) return ((a.K / 128) & 1) ? launch_ksplit<3>(a, debug, st) : launch_ksplit<4>(a, debug, st);
-    int n_big, nbn;
-    tiled_split(a.M, a.N, n_big, nbn);
-    const int64_t total = n_big + (a.M / 128) * (a.N / kBN - nbn);
-    GemmArgs g = a;
-    auto go = [&](auto kern) -> hipError_t {
-        if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), kTiledLds); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(kThreads), kTiledLds, st, g, n_big, nbn);
-        return hipGetLastError();
-    };
-#ifdef TRDQ_PROBE_PHASES
-    debug = false;                                    // the debug pointer receives time stamps instead
-#endif
-    return debug ? go(qgemm8_tiled_kernel<true>) : go(qgemm8_tiled_kernel<false>);
+    return tiled_supports(a) ? launch_form<kBlocks>(a, debug, st) : hipErrorInvalidValue;
+}
+
+bool tiled_rows_supports(const GemmArgs &a)
+{
+    return a.M >= 128 && a.M <= (1 << 30) && a.N >= kBN && a.N % 16 == 0 && a.K % 128 == 0 && a.K >= 128 && a.ldy % 8 == 0 &&
+           reinterpret_cast<uintptr_t>(a.Y) % 16 == 0 && !a.zcw && (!a.zc || a.colsum);
+}
+
+// Where this form is the faster one for row-major codes that the kernel for few tiles leaves (qgemm8_direct_tile < 0);
+// both sides measured on ten shapes from 256 -> 512 to 4608 -> 1152 at 130 ... 32768 tokens.  Against the tiled form the
+// half-line copies cost 12 % from 4096 tokens on (1152 -> 3456: 21.4 against 18.7 us), which puts it level with
+// the 128 x 144 and 256 x 256 kernels where tokens and channels are whole tiles; it wins where they are not, because the
+// others leave the remainder to the any-shape kernel, a second launch (or the whole product, below 1024 tokens or with
+// zero points), us, before and after: 1152 -> 3456 at 500 / 1500 / 5000 tokens 11.1 / 18.6 / 30.2 -> 8.4 / 12.6 / 26.3,
+// 768 -> 3072 at 1000 tokens 9.6 -> 6.8, 4608 -> 1152 at 3000 tokens 29.3 -> 22.9.
+//   - Remainder of tokens: up to where the second launch is a small part: 1100 tiles of 256 x 256 (1152 -> 4608 at 12000
+//     tokens, 846 tiles: 82.1 -> 74.9, at 16000, 1134 tiles: 95.3 -> 98.3), and with a width of which the last tile
+//     repeats a part 14000 tokens (1024 -> 2048 at 12000 34.6 -> 33.5, at 16000 39.7 -> 42.7).
+//   - Whole tiles: at most one per compute unit, where K is split inside the workgroup (768 -> 2304 at 1024 tokens
+//     7.9 -> 6.8, 4608 -> 1152 at 1024 19.6 -> 17.8); for long K half of that (4096 tokens: 24.4 -> 25.0).
+//   - Zero points: the only other kernel that takes them at any shape is the any-shape one (768 -> 3072 at 4096 tokens
+//     23.2 -> 16.2, 1152 -> 4608 at 32700 tokens 268 -> 190).
+bool tiled_rows_pays(int64_t M, int K, int N, bool asym)
+{
+    if (M < 128 || N < kBN) return false;
+    const bool whole_n = N % kBN == 0;
+    if (M % 128 == 0 && whole_n) {
+        if (asym && K < 512) return true;
+        const int64_t tiles = (M / 128) * (int64_t)(N / kBN);
+        return tiles <= num_cus() / (K >= 2304 ? 2 : 1);
+    }
+    if (asym) return true;
+    if (M % 128 == 0) return false;
+    return whole_n ? ((M + 255) / 256) * ((N + 255) / 256) < 1100 : M < 14000;
+}
+
+hipError_t launch_qgemm8_tiled_rows(const GemmArgs &a, bool debug, hipStream_t st)
+{
+    if (!tiled_rows_supports(a)) return hipErrorInvalidValue;
+    return a.zc ? launch_form<kRowsAsym>(a, debug, st) : launch_form<kRows>(a, debug, st);
 }
 
 bool tiled4_supports(const GemmArgs &a)

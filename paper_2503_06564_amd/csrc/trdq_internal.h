@@ -67,7 +67,7 @@ bool qgemm_tiled_supports(const Weights &w, int64_t M, const void *Y, int64_t ld
 hipError_t launch_qgemm_tiled(const Weights &w, const int8_t *Xt, const float *sx, int64_t M, const float *bias,
                               uint16_t *Y, int64_t ldy, int32_t *acc_debug, hipStream_t st);
 // whether the product of row-major codes reads the block-tiled copy of the weights for M tokens (built-in choice)
-bool qgemm_reads_tiled_codes(const Weights &w, int64_t M);
+bool qgemm_reads_tiled_codes(const Weights &w, int64_t M, bool asym = false);
 // measured choice between the two products for a layer object (true: the tiled pair is the faster one)
 bool qgemm_tiled_pays(int64_t M, int K, int N);
 hipError_t launch_xq_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st);
