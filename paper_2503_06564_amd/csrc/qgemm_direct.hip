@@ -197,6 +197,9 @@ constexpr int kDirectTiles[5][2] = {{1, 1}, {1, 2}, {2, 2}, {2, 4}, {4, 4}};
 // 256 tokens 4.0 (32 x 64), 768 tokens 5.8 (432 of 32 x 64; 64 x 64 7.3); at 4608 -> 1152: 64 tokens 6.4 (16 x 32),
 // 256 tokens 9.0 (32 x 64), 768 tokens 13.4 (64 x 64; 32 x 64 15.8).  One unit per wave leaves registers for two rounds
 // of 32 x 64 tiles, and 64 x 64 never pays there.
+// Two (2.5) workgroups per compute unit is the most that pays for few units too, however many would fit: the kernels with
+// tiles in LDS have little K to walk there (128 -> 512 at 8192 tokens 8.0 in 2048 workgroups against 5.2 us, 256 -> 1024
+// at 4096 7.9 / 5.7, 640 -> 512 at 4096 7.2 / 6.1, at 2048 in 512 workgroups 5.6 both ways, 768 -> 2304 at 700 8.3 / 6.3).
 // Beyond that the kernels with tiles in LDS are ahead: 1152 -> 1152 at 1024 tokens 8.0 both ways, at 1536 11.2 against
 // 8.7 us; 4608 -> 1152 at 1024 tokens 20.7 against 17.6 us.  Shapes that those kernels take only in part (ragged token
 // counts, widths that are no multiple of 144) stay here longer: 4608 -> 1152 at 1000 tokens 20.5 against 27.2 us.
@@ -205,13 +208,18 @@ int qgemm8_direct_tile(int64_t M, int K, int N)
     const int nu = K / 128;
     if (M <= 0 || nu <= 0 || (int64_t)M > (1 << 20)) return -1;
     const int per = (nu + 11) / 12, nw = (nu + per - 1) / per;
-    const int64_t round = (int64_t)num_cus() * 9 / (per == 1 ? nw : 9);
     const bool whole = M % 128 == 0 && N % 144 == 0;
+    const int64_t cus = num_cus(), most_wide = whole ? 2 * cus : 5 * cus / 2;
+    int64_t round = cus * 9 / (per == 1 ? nw : 9);
+    if (round > 2 * cus) round = 2 * cus;
     for (int i = 0; i < 5; ++i) {
         const int tm = 16 * kDirectTiles[i][0], tn = 16 * kDirectTiles[i][1];
         const int64_t wgs = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
         int64_t most = round;
-        if (i == 3 && per == 1) most = whole ? 2 * round : 5 * round / 2;
+        if (i == 3 && per == 1) {
+            most = whole ? 2 * round : 5 * round / 2;
+            if (most > most_wide) most = most_wide;
+        }
         if (i == 4) most = per == 1 ? 0 : (whole ? round : 7 * round / 4);
         if (wgs <= most) return i;
     }
