@@ -430,7 +430,7 @@ trdq_status trdq_xq_untile(const int8_t *Xt_dev, int64_t M, int K, int8_t *Xq_de
 int trdq_qgemm_tiled_supported(const trdq_weights *w, int64_t M);
 /* 1 where the tiled pair is also the faster one by the library's measured rule (K <= 4608, more output
  * tiles than the kernel for few tokens takes, and either more than one 128 x 144 tile per compute unit, or
- * at most one and K >= 1024; int4 weights: at least one 128 x 128 tile per compute unit): what
+ * at most one and K >= 1024; int4 weights: more than three tiles of 64 x 128 per compute unit): what
  * trdq_layer_forward takes by itself. */
 int trdq_qgemm_tiled_preferred(const trdq_weights *w, int64_t M);
 trdq_status trdq_qgemm_tiled(const trdq_weights *w, const int8_t *Xt_dev, const float *sx_dev, int64_t M,

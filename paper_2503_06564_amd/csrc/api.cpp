@@ -889,8 +889,8 @@ int trdq_qgemm_tiled_supported(const trdq_weights *w, int64_t M)
 int trdq_qgemm_tiled_preferred(const trdq_weights *w, int64_t M)
 {
     if (!trdq_qgemm_tiled_supported(w, M) || w->K / trdq::kBlock > 36) return 0;
-    // int4 weights: measured 5-15 % ahead of the row-major kernel from one 128 x 128 tile per compute unit on
-    if (w->wbits == 4) return (M / 128) * (int64_t)(w->N / 128) >= trdq::num_cus() ? 1 : 0;
+    // int4 weights: measured 5-15 % ahead of the row-major kernel wherever those for fewer tiles are not ahead of both
+    if (w->wbits == 4) return trdq::qgemm4_tiled_pays(M, w->K, w->N) ? 1 : 0;
     return trdq::qgemm_tiled_pays(M, w->K, w->N) ? 1 : 0;
 }
 

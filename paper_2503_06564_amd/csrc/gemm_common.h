@@ -127,11 +127,18 @@ hipError_t launch_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStre
 // int4 weights on block-tiled operands (qgemm_tiled.hip): a.Wc holds the block form of the packed codes
 bool tiled4_supports(const GemmArgs &a);
 hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st);
+// 64-token tiles on row-major activation codes, any M >= 64 and N >= 128
+bool tiled4_rows_supports(const GemmArgs &a);
+bool tiled4_rows_pays(int64_t M, int K, int N);
+hipError_t launch_qgemm4_tiled_rows(const GemmArgs &a, bool debug, hipStream_t st);
 
 // Small launches, both operands straight into registers (qgemm_direct.hip); tile indexes the table there.
 // qgemm8_direct_tile: the tile for int8 weights where this form is the fastest, else -1.
 int qgemm8_direct_tile(int64_t M, int K, int N);
 hipError_t launch_qgemm8_direct(const GemmArgs &a, bool debug, int tile, hipStream_t st);
+// the same for int4 weights (a.Wc: the block form of the packed codes)
+int qgemm4_direct_tile(int64_t M, int K, int N);
+hipError_t launch_qgemm4_direct(const GemmArgs &a, bool debug, int tile, hipStream_t st);
 
 // 256 x 256 tile kernel with a hand-scheduled main loop (qgemm_wide.hip).
 bool wide_supports(const GemmArgs &a);

@@ -280,6 +280,18 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
             return launch_qgemm8_direct(a, acc_debug != nullptr, tile, st);
         }
     }
+    // int4 weights: the same, or the tiled kernel's 64-token form (variants 8 ... 10 and 11 ask for them)
+    if (w.wbits == 4 && w.codes_tiled && (variant < 0 || (variant >= 8 && variant < 12))) {
+        GemmArgs a;
+        a.Xq = Xq; a.Wc = w.codes_tiled; a.sx = sx; a.sw = w.scales; a.bias = bias; a.Y = Y;
+        a.acc_debug = acc_debug; a.M = M; a.ldy = ldy; a.K = w.K; a.N = w.N;
+        a.zc = zc; a.colsumw = w.colsumw;
+        if (zc && !w.colsumw) return hipErrorInvalidValue;
+        const int tile = variant < 0 ? qgemm4_direct_tile(M, w.K, w.N) : (variant < 11 ? variant - 8 : -1);
+        if (tile >= 0) return launch_qgemm4_direct(a, acc_debug != nullptr, tile, st);
+        if ((variant == 11 || tiled4_rows_pays(M, w.K, w.N)) && tiled4_rows_supports(a))
+            return launch_qgemm4_tiled_rows(a, acc_debug != nullptr, st);
+    }
     const int rows_variant = kRegVariants + dma_num_variants(), wide_variant = rows_variant + 1;
     if (w.wbits == 8 && w.codes_tiled &&
         (variant == rows_variant || (variant < 0 && tiled_rows_pays(M, w.K, w.N, zc != nullptr)))) {
@@ -400,8 +412,15 @@ hipError_t launch_qgemm_tiled(const Weights &w, const int8_t *Xt, const float *s
 
 bool qgemm_reads_tiled_codes(const Weights &w, int64_t M, bool asym)
 {
-    return w.wbits == 8 && w.codes_tiled &&
+    if (!w.codes_tiled) return false;
+    if (w.wbits == 4) return qgemm4_direct_tile(M, w.K, w.N) >= 0 || (!asym && tiled4_rows_pays(M, w.K, w.N));
+    return w.wbits == 8 &&
            (qgemm8_direct_tile(M, w.K, w.N) >= 0 || tiled_rows_pays(M, w.K, w.N, asym));
+}
+
+bool qgemm4_tiled_pays(int64_t M, int K, int N)
+{
+    return qgemm4_direct_tile(M, K, N) < 0 && !tiled4_rows_pays(M, K, N);
 }
 
 bool qgemm_tiled_pays(int64_t M, int K, int N)

@@ -9,6 +9,8 @@
 // end.  Integer sums are exact, so the split changes nothing.  Back-to-back launches, before and after: 1152 -> 1152
 // at 16 / 128 / 512 tokens 8.4 / 8.4 / 8.6 -> 2.8 / 3.3 / 5.7 us, 4608 -> 1152 at 16 / 512 tokens 24 / 22.6 -> 3.7 / 11.5 us.
 // Rows and channels past the edges are clamped on load and not stored.
+#include <type_traits>
+
 #include "gemm_common.h"
 
 namespace trdq {
@@ -187,6 +189,195 @@ hipError_t launch8(const GemmArgs &a, bool debug, hipStream_t st)
     return hipGetLastError();
 }
 
+// int4 weights: the same tiles, units (= scale groups) and copies.  A lane's weight fragment is the eight packed bytes of
+// its unit in the block-tiled copy, widened in registers.  The float sums over the groups keep the order of the other int4
+// kernels (one group after the other, so that the outputs are theirs bit for bit): the waves leave the int32 sums of
+// their groups in LDS and the wave that finishes a tile folds them in turn.  Up to 12 groups that is one round of
+// waves; with more the waves walk K together, a round of up to nine groups at a time, each round folded before the next one's
+// sums are laid down (the requests of a unit go out a round ahead).
+template <int TM, int TN, bool ONE>
+__global__ __launch_bounds__(768) void qgemm4_direct_kernel(GemmArgs g, int debug)
+{
+    extern __shared__ __align__(16) int8_t smem[];
+    constexpr int XB = TM * 2048;                    // a unit's activations
+    constexpr int PER = 2 * TM + 2 * TN;             // requests of a unit
+    constexpr int MW = ONE ? 12 : 9;                 // most waves
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nw = blockDim.x >> 6;
+    const int r = lane & 15, q = lane >> 4;
+    int tm, tn;
+    tile_map(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+    const int64_t m0 = (int64_t)tm * (16 * TM);
+    const int n0 = tn * (16 * TN);
+    const int K = g.K, nu = K >> 7;
+    // [waves][TM * TN][64]: with one round in the place of the activations, once these are consumed
+    v4i *const part = reinterpret_cast<v4i *>(smem + (ONE ? 0 : nw * 2 * XB));
+
+    int8_t *const mine = smem + wave * ((ONE ? 1 : 2) * XB);
+    const uint32_t mine0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)mine;
+    const int8_t *const xbase = g.Xq + m0 * K;
+    uint32_t vx[2 * TM];                             // copy i: rows 8 i .. 8 i + 7 of the tile
+#pragma unroll
+    for (int i = 0; i < 2 * TM; ++i) {
+        const int row = 8 * i + (lane >> 3), c = (lane & 7) ^ chunk_swizzle<128>(row);
+        const int64_t left = g.M - 1 - m0;           // rows past the last token repeat it
+        vx[i] = (uint32_t)((row < left ? row : (int)left) * K + c * 16);
+    }
+    const uint8_t *wp[TN];
+#pragma unroll
+    for (int a = 0; a < TN; ++a) {
+        int t = n0 / 16 + a;                         // N is a multiple of 16
+        if (t * 16 >= g.N) t = g.N / 16 - 1;
+        wp[a] = static_cast<const uint8_t *>(g.Wc) + (int64_t)t * (K >> 6) * 512 + lane * 8;
+    }
+    uint2 w[ONE ? 1 : 2][TN][2];
+    auto request = [&](auto buf_tag, int u) {
+        constexpr int buf = decltype(buf_tag)::value;
+#pragma unroll
+        for (int i = 0; i < 2 * TM; ++i) dma_1k(vx[i], xbase + u * 128, mine0 + buf * XB + i * 1024);
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                w[buf][a][h] = *reinterpret_cast<const uint2 *>(wp[a] + (2 * u + h) * 512);
+    };
+    int fro[2];                                      // the lane's piece of a 16-row fragment, per half of the unit
+#pragma unroll
+    for (int h = 0; h < 2; ++h) fro[h] = r * 128 + ((4 * h + q) ^ chunk_swizzle<128>(r)) * 16;
+
+    // the tiles this wave finishes are wave, wave + waves, ...; with several rounds there are at most two
+    auto tile_m = [&](int t) { return m0 + (t % TM) * 16 + r; };
+    auto tile_n = [&](int t) {
+        const int n = n0 + (t / TM) * 16 + q * 4;
+        return n < g.N ? n : g.N - 4;                // loads only: such a tile is not stored
+    };
+    auto load_scales = [&](int t, int u0, float4 (&sc)[MW]) {
+        const float *const p = g.sw + tile_n(t);
+#pragma unroll
+        for (int v = 0; v < MW; ++v) sc[v] = *reinterpret_cast<const float4 *>(p + (int64_t)(u0 + v < nu ? u0 + v : nu - 1) * g.N);
+    };
+    auto fold = [&](int t, int u0, const float4 (&sc)[MW], v4f &f) {
+#pragma unroll
+        for (int v = 0; v < MW; ++v) {
+            if (v < nw && u0 + v < nu) {
+                const v4i p = part[(v * TM * TN + t) * 64 + lane];
+                if (debug && tile_m(t) < g.M && n0 + (t / TM) * 16 + q * 4 < g.N)
+                    *reinterpret_cast<int4 *>(g.acc_debug + ((int64_t)(u0 + v) * g.M + tile_m(t)) * g.N + tile_n(t)) =
+                        make_int4(p[0] >> 4, p[1] >> 4, p[2] >> 4, p[3] >> 4);
+                f[0] += sc[v].x * (float)p[0];
+                f[1] += sc[v].y * (float)p[1];
+                f[2] += sc[v].z * (float)p[2];
+                f[3] += sc[v].w * (float)p[3];
+            }
+        }
+    };
+    auto finish = [&](int t, v4f f) {                // y = (s_x / 16) * f + bias, the codes having been 16 * code
+        const int64_t m = tile_m(t);
+        const int n = n0 + (t / TM) * 16 + q * 4;
+        if (m >= g.M || n >= g.N) return;
+        if (g.zc) {
+            const float zc = (float)g.zc[m];
+            const float4 cw = *reinterpret_cast<const float4 *>(g.colsumw + n);
+            f += v4f{zc * cw.x, zc * cw.y, zc * cw.z, zc * cw.w};
+        }
+        const float sxm = g.sx[m] * 0.0625f;
+        const float4 bi = g.bias ? *reinterpret_cast<const float4 *>(g.bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+        uint2 o;
+        o.x = pack_bf16x2(sxm * f[0] + bi.x, sxm * f[1] + bi.y);
+        o.y = pack_bf16x2(sxm * f[2] + bi.z, sxm * f[3] + bi.w);
+        *reinterpret_cast<uint2 *>(g.Y + m * g.ldy + n) = o;
+    };
+    v4f f[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+    // one round: this wave's unit u0 + wave (past the last one the last is requested again and its sums are not used)
+    auto round = [&](auto buf_tag, int u0) {
+        constexpr int buf = decltype(buf_tag)::value;
+        if constexpr (ONE) {
+            wait_vmcnt<0>();
+        } else {
+            const int nxt = u0 + nw + wave;
+            request(std::integral_constant<int, 1 - buf>{}, nxt < nu ? nxt : nu - 1);
+            wait_vmcnt<PER>();                       // everything but the requests just made
+        }
+        v4i acc[TN][TM];
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b) acc[a][b] = v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            v4i x[TM];
+#pragma unroll
+            for (int b = 0; b < TM; ++b) x[b] = *reinterpret_cast<const v4i *>(mine + buf * XB + b * 2048 + fro[h]);
+#pragma unroll
+            for (int a = 0; a < TN; ++a) {
+                const uint2 p = w[buf][a][h];
+                const v4i wa = v4i{(int)((p.x << 4) & 0xF0F0F0F0u), (int)(p.x & 0xF0F0F0F0u),
+                                   (int)((p.y << 4) & 0xF0F0F0F0u), (int)(p.y & 0xF0F0F0F0u)};
+#pragma unroll
+                for (int b = 0; b < TM; ++b) acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wa, x[b], acc[a][b], 0, 0, 0);
+            }
+        }
+        float4 sc[MW];
+        if (wave < TM * TN) load_scales(wave, u0, sc);
+        __syncthreads();                             // ONE: the activations' areas are free; else the last round is folded
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b) part[((wave * TN + a) * TM + b) * 64 + lane] = acc[a][b];
+        __syncthreads();
+        if constexpr (ONE) {
+            for (int t = wave; t < TM * TN; t += nw) {
+                if (t != wave) load_scales(t, u0, sc);
+                f[0] = v4f{0.f, 0.f, 0.f, 0.f};
+                fold(t, u0, sc, f[0]);
+                finish(t, f[0]);
+            }
+        } else {
+            if (wave < TM * TN) fold(wave, u0, sc, f[0]);
+            if (wave + nw < TM * TN) {
+                load_scales(wave + nw, u0, sc);
+                fold(wave + nw, u0, sc, f[1]);
+            }
+        }
+    };
+    request(std::integral_constant<int, 0>{}, wave < nu ? wave : nu - 1);
+    if constexpr (ONE) {
+        round(std::integral_constant<int, 0>{}, 0);
+    } else {
+        for (int u0 = 0;; u0 += 2 * nw) {
+            round(std::integral_constant<int, 0>{}, u0);
+            if (u0 + nw >= nu) break;
+            round(std::integral_constant<int, 1>{}, u0 + nw);
+            if (u0 + 2 * nw >= nu) break;
+        }
+        wait_vmcnt<0>();                             // the repeated request
+        if (wave < TM * TN) finish(wave, f[0]);
+        if (wave + nw < TM * TN) finish(wave + nw, f[1]);
+    }
+}
+
+template <int TM, int TN>
+hipError_t launch4(const GemmArgs &a, bool debug, hipStream_t st)
+{
+    GemmArgs g = a;
+    g.tiles_m = (int)((g.M + 16 * TM - 1) / (16 * TM));
+    g.tiles_n = (g.N + 16 * TN - 1) / (16 * TN);
+    const int nu = g.K / 128;
+    const bool one = nu <= 12;
+    const int per = one ? 1 : (nu + 8) / 9, nw = (nu + per - 1) / per;
+    if (!one && TM * TN > 2 * nw) return hipErrorInvalidValue;    // two tiles to finish per wave
+    const size_t area = (size_t)nw * (one ? 1 : 2) * TM * 2048, sums = (size_t)nw * TM * TN * 1024;
+    const size_t smem = one ? (area > sums ? area : sums) : area + sums;
+    const dim3 grid((unsigned)(g.tiles_m * g.tiles_n)), threads(64 * nw);
+    auto kern = one ? qgemm4_direct_kernel<TM, TN, true> : qgemm4_direct_kernel<TM, TN, false>;
+    if (smem > 64 * 1024)
+        if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, grid, threads, smem, st, g, (int)debug);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 // Tiles in the order they are tried: {16-token tiles, 16-channel tiles}.
@@ -234,6 +425,35 @@ hipError_t launch_qgemm8_direct(const GemmArgs &a, bool debug, int tile, hipStre
         case 2: return launch8<2, 2>(a, debug, st);
         case 3: return launch8<2, 4>(a, debug, st);
         case 4: return launch8<4, 4>(a, debug, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+// int4 tiles, in the order they are tried: 16 x 32, 32 x 32, 32 x 64.  One workgroup per compute unit, with one
+// round of groups two of 32 x 32 (us: 1152 -> 1152 at 64 / 250 / 384 tokens 10.9 / 11.3 / 10.6 -> 5.2 / 5.9 / 6.1, in 576
+// workgroups at 500 tokens 8.2 against 7.9 of the 64-token tiles in LDS; 4608 -> 1152 at 64 / 192 / 250 tokens
+// 30.3 / 30.6 / 31.1 -> 7.5 / 9.4 / 14.0, those take 22.8).  One or two groups, which those do not take: four (256 -> 512
+// at 1000 tokens 6.1 -> 4.9, at 2048 6.0 -> 5.6, in 1504 workgroups at 3000 7.0 against 6.2).
+int qgemm4_direct_tile(int64_t M, int K, int N)
+{
+    const int nu = K / 128;
+    if (M <= 0 || nu <= 0 || nu > 72 || M > (1 << 20)) return -1;
+    const int64_t cus = num_cus();
+    const int64_t most[3] = {nu < 3 ? 4 * cus : cus, nu < 3 ? 4 * cus : (nu <= 12 ? 2 * cus : cus), cus};
+    constexpr int tiles[3][2] = {{1, 2}, {2, 2}, {2, 4}};
+    for (int i = 0; i < 3; ++i) {
+        const int tm = 16 * tiles[i][0], tn = 16 * tiles[i][1];
+        if (((M + tm - 1) / tm) * ((N + tn - 1) / tn) <= most[i]) return i;
+    }
+    return -1;
+}
+
+hipError_t launch_qgemm4_direct(const GemmArgs &a, bool debug, int tile, hipStream_t st)
+{
+    switch (tile) {
+        case 0: return launch4<1, 2>(a, debug, st);
+        case 1: return launch4<2, 2>(a, debug, st);
+        case 2: return launch4<2, 4>(a, debug, st);
     }
     return hipErrorInvalidValue;
 }

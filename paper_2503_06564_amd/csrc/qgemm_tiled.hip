@@ -89,10 +89,10 @@ __device__ __forceinline__ int64_t tile_m0(const GemmArgs &g, int tm, int bm)
     return m0 > g.M - bm ? g.M - bm : m0;
 }
 template <int FORM>
-__device__ __forceinline__ int tile_n0(const GemmArgs &g, int tn)
+__device__ __forceinline__ int tile_n0(const GemmArgs &g, int tn, int bn = kBN)
 {
-    const int n0 = tn * kBN;
-    return FORM != kBlocks && n0 > g.N - kBN ? g.N - kBN : n0;
+    const int n0 = tn * bn;
+    return FORM != kBlocks && n0 > g.N - bn ? g.N - bn : n0;
 }
 
 // Row-major activations: a copy instruction moves 16 rows x 64 bytes, four lanes to a row (lanes of a quad in four
@@ -643,17 +643,21 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
 // zero, so that they run under the matrix instructions of the tiles before.
 constexpr int kW4BM = 128, kW4BN = 128;
 constexpr int kW4NS = 5;
-constexpr int kW4XOff = 0, kW4WOff = 8192, kW4SOff = 12288;
-constexpr int kW4Stage = 13312;
-constexpr int kW4ParOff = kW4NS * kW4Stage;          // epilogue operands: [128 bias][128 s_x]
-constexpr int kW4Lds = kW4ParOff + 2048;             // 68608 B
-constexpr int kW4Copies = 4;
+constexpr int kW4XOff = 0;
+constexpr int w4_woff(int bm) { return bm * 64; }
+constexpr int w4_soff(int bm) { return bm * 64 + 4096; }
+constexpr int w4_stage(int bm) { return bm * 64 + 5120; }
+constexpr int w4_par_off(int bm) { return kW4NS * w4_stage(bm); }   // epilogue operands: [128 bias][pad][BM s_x]
+constexpr int w4_lds(int bm) { return w4_par_off(bm) + 2048; }      // 68608 B, with 64 tokens 48128 B
 
-template <bool DEBUG>
-__global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
+template <int BM, bool DEBUG, int FORM>
+__global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kernel(GemmArgs g)
 {
     extern __shared__ __align__(16) int8_t smem[];
-    constexpr int TM = 4, TN = 4, NS = kW4NS, P = kW4Copies;
+    constexpr int TM = BM / 32, TN = 4, NS = kW4NS;
+    constexpr int XC = BM / 64;                       // activation blocks a wave copies per k-step
+    constexpr int P = XC + 2;                         // copies per wave and k-step
+    constexpr int kW4WOff = w4_woff(BM), kW4SOff = w4_soff(BM), kW4Stage = w4_stage(BM), kW4ParOff = w4_par_off(BM);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)smem;
 #ifdef TRDQ_PROBE_PHASES
     const uint64_t clk_c0 = __builtin_readcyclecounter();
@@ -665,16 +669,17 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
     const int wm = wave & 1, wn = wave >> 1;
     const int l16 = lane & 15, lg = lane >> 4;
     int tm, tn;
-    tile_map(blockIdx.x, (int)(g.M / kW4BM), g.N / kW4BN, tm, tn);
+    tile_map(blockIdx.x, (int)((g.M + BM - 1) / BM), (g.N + kW4BN - 1) / kW4BN, tm, tn);
     const int KT = g.K >> 6;                          // k-steps: even, at least NS
-    const int64_t m0 = (int64_t)tm * kW4BM;
-    const int n0 = tn * kW4BN;
+    const int64_t m0 = tile_m0(g, tm, BM);
+    const int n0 = tile_n0<FORM>(g, tn, kW4BN);
 
     const int64_t xstride = (int64_t)KT * 1024;      // bytes from one 16-token group to the next
     const int64_t wstride = (int64_t)KT * 512;       // ... one 16-channel group to the next
-    const int8_t *const xsrc = g.Xq + (m0 / 16 + 2 * wave) * xstride;
+    constexpr int XSTEP = FORM == kBlocks ? 1024 : 64;  // bytes from one k-step of the activations to the next
+    const int8_t *const xsrc = g.Xq + (m0 + 16 * XC * wave) * g.K;
     const uint8_t *const wsrc = static_cast<const uint8_t *>(g.Wc) + (int64_t)(n0 / 16 + 2 * wave) * wstride;
-    const uint32_t voff = (uint32_t)(lane * 16);
+    const uint32_t voffx = x_copy_off<FORM>(lane, g.K);
     // the weight copy moves two blocks: lanes 0-31 the first, lanes 32-63 the one a channel group further
     const uint32_t voffw = (uint32_t)((lane & 31) * 16) + (lane >= 32 ? (uint32_t)wstride : 0u);
     const float *const ssrc = g.sw + n0 + (wave & 1) * 64;
@@ -682,8 +687,8 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
     auto issue_one = [&](auto c_tag, int s, int st) {
         constexpr int c = decltype(c_tag)::value;
         const uint32_t sbase = lds0 + st * kW4Stage;
-        if constexpr (c < 2) dma_1k(voff, xsrc + c * xstride + (int64_t)s * 1024, sbase + kW4XOff + (2 * wave + c) * 1024);
-        else if constexpr (c == 2) dma_1k(voffw, wsrc + (int64_t)s * 512, sbase + kW4WOff + wave * 1024);
+        if constexpr (c < XC) dma_1k(voffx, xsrc + c * xstride + (int64_t)s * XSTEP, sbase + kW4XOff + (XC * wave + c) * 1024);
+        else if constexpr (c == XC) dma_1k(voffw, wsrc + (int64_t)s * 512, sbase + kW4WOff + wave * 1024);
         else copy_256_if(1, voffs, ssrc + (int64_t)(s >> 1) * g.N, sbase + kW4SOff + wave * 256);
     };
     auto issue = [&](int s, int st) {
@@ -697,7 +702,8 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
         copy_1k_if(wave == 0 && g.bias != nullptr, v32, g.bias ? g.bias + n0 : g.sw, par);
         if (wave == 0 && g.bias == nullptr)
             *reinterpret_cast<uint4 *>(smem + kW4ParOff + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
-        copy_1k_if(wave == 1, v32, g.sx + m0, par + 1024);
+        if constexpr (FORM == kBlocks) copy_1k_if(wave == 1, v32, g.sx + m0, par + 1024);
+        else copy_256_if(wave < BM / 64, (uint32_t)(lane * 4), g.sx + m0 + wave * 64, par + 1024 + wave * 256);
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) issue(s, s);
@@ -708,7 +714,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
     const uint64_t clk_t1 = wall_clock64();
 #endif
 
-    const int xfr = kW4XOff + (wm * TM) * 1024 + lane * 16;
+    const int xfr = kW4XOff + (wm * TM) * 1024 + (FORM == kBlocks ? lane * 16 : x_frag_off<FORM>(l16, lg));
     const int wfr = kW4WOff + (wn * TN) * 512 + lane * 8;
     const int sfr = kW4SOff + (wn * 64 + lg * 4) * 4;
     auto widen = [](uint2 p) {
@@ -733,7 +739,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
     for (int b = 0; b < TM; ++b) bf[0][b] = *reinterpret_cast<const v4i *>(smem + xfr + b * 1024);
 
     const int n_lane = n0 + wn * 64 + lg * 4;
-    const int64_t m_lane0 = m0 + wm * 64 + l16;
+    const int64_t m_lane0 = m0 + wm * (BM / 2) + l16;
     int st = 0;
     // One k-step.  HALF 0 starts the sums of a scale group (folding the group before, tile by tile, with
     // the scales read one group earlier) and ends by reading the new group's scales; HALF 1 continues the sums.
@@ -774,7 +780,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
                 }
             }
             if constexpr (has_next) af[a] = widen(raw[a]);
-            issue_one(std::integral_constant<int, a>{}, kt + NS < KT ? kt + NS : KT - 1, st);
+            if constexpr (a < P) issue_one(std::integral_constant<int, a>{}, kt + NS < KT ? kt + NS : KT - 1, st);
             __builtin_amdgcn_sched_barrier(0);
         });
         // The group's scales, once the fold of the group before is done, from the NEXT step's stage (they
@@ -830,7 +836,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
     for (int a = 0; a < TN; ++a) bi_r[a] = *reinterpret_cast<const float4 *>(par + wn * 64 + a * 16 + lg * 4);
 #pragma unroll
     for (int b = 0; b < TM; ++b) {
-        const float sxm = par[256 + wm * 64 + b * 16 + l16] * 0.0625f;
+        const float sxm = par[256 + wm * (BM / 2) + b * 16 + l16] * 0.0625f;
 #pragma unroll
         for (int a = 0; a < TN; ++a) {
             uint2 o;
@@ -845,7 +851,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
             const int id = i * 64 + lane;
             const int row = id >> 3, c = id & 7;
             const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * ROWB + c * 16);
-            store_out16(g.Y + (m0 + wm * 64 + b * 16 + row) * g.ldy + n0 + wn * 64 + c * 8, v);
+            store_out16(g.Y + (m0 + wm * (BM / 2) + b * 16 + row) * g.ldy + n0 + wn * 64 + c * 8, v);
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -858,7 +864,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_tiled_kernel(GemmArgs g)
         uint64_t *o = reinterpret_cast<uint64_t *>(g.acc_debug) + (int64_t)blockIdx.x * 16;
         o[0] = clk_t0; o[1] = clk_t1; o[2] = clk_t2; o[3] = wall_clock64();
         o[4] = clk_c0; o[5] = clk_c1; o[6] = clk_c2; o[7] = clk_c3;
-        o[8] = hw; o[9] = xcc; o[10] = 128; o[11] = 4;                 // 4: the int4 kernel
+        o[8] = hw; o[9] = xcc; o[10] = BM; o[11] = 4;                 // 4: the int4 kernel
     }
 #endif
 }
@@ -993,19 +999,52 @@ bool tiled4_supports(const GemmArgs &a)
            reinterpret_cast<uintptr_t>(a.Y) % 16 == 0 && !a.zc;
 }
 
-hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st)
+namespace {
+
+template <int BM, int FORM>
+hipError_t launch_w4(const GemmArgs &a, bool debug, hipStream_t st)
 {
-    if (!tiled4_supports(a)) return hipErrorInvalidValue;
     GemmArgs g = a;
     auto go = [&](auto kern) -> hipError_t {
-        if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), kW4Lds); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)((a.M / kW4BM) * (a.N / kW4BN))), dim3(kThreads), kW4Lds, st, g);
+        if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), w4_lds(BM)); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(((a.M + BM - 1) / BM) * ((a.N + kW4BN - 1) / kW4BN))), dim3(kThreads), w4_lds(BM),
+                           st, g);
         return hipGetLastError();
     };
 #ifdef TRDQ_PROBE_PHASES
     debug = false;                                    // the debug pointer receives time stamps instead
 #endif
-    return debug ? go(qgemm4_tiled_kernel<true>) : go(qgemm4_tiled_kernel<false>);
+    return debug ? go(qgemm4_tiled_kernel<BM, true, FORM>) : go(qgemm4_tiled_kernel<BM, false, FORM>);
+}
+
+}  // namespace
+
+hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st)
+{
+    return tiled4_supports(a) ? launch_w4<kW4BM, kBlocks>(a, debug, st) : hipErrorInvalidValue;
+}
+
+bool tiled4_rows_supports(const GemmArgs &a)
+{
+    return a.M >= 64 && a.M <= (1 << 30) && a.N >= kW4BN && a.N % 16 == 0 && a.K % 128 == 0 && a.K >= 64 * kW4NS + 64 &&
+           a.ldy % 8 == 0 && reinterpret_cast<uintptr_t>(a.Y) % 16 == 0 && !a.zc;
+}
+
+hipError_t launch_qgemm4_tiled_rows(const GemmArgs &a, bool debug, hipStream_t st)
+{
+    return tiled4_rows_supports(a) ? launch_w4<64, kRows>(a, debug, st) : hipErrorInvalidValue;
+}
+
+// Where the 64-token tiles on row-major codes are the fastest int4 product: up to three workgroups per compute unit, one
+// round (beyond, 128-token tiles do less widening and folding per product: 1152 -> 1152 at 6000 tokens, 846 tiles, 18.0
+// against 16.6 us).  With one 128 x 128 tile per compute unit and one wave per SIMD every k-step waits for its barrier,
+// its LDS reads and its fold in turn; two or three workgroups of half the height fill those waits.  us, before and
+// after: 1024 -> 2048 at 1232 / 2048 / 3000 tokens 10.5 / 10.6 / 15.2 -> 9.1 / 10.2 / 12.9, 1152 -> 4608 at 1000 16.0 -> 13.5,
+// 4608 -> 1152 at 1000 31.0 -> 23.2, 768 -> 768 at 3000 9.2 -> 7.8.  Half-line copies of the activations cost
+// nothing here, the product being bound by its vector instructions.
+bool tiled4_rows_pays(int64_t M, int K, int N)
+{
+    return M >= 64 && N >= kW4BN && K >= 64 * kW4NS + 64 && ((M + 63) / 64) * ((N + kW4BN - 1) / kW4BN) <= 3 * (int64_t)num_cus();
 }
 
 hipError_t launch_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st)

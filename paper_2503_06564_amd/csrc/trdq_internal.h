@@ -70,6 +70,7 @@ hipError_t launch_qgemm_tiled(const Weights &w, const int8_t *Xt, const float *s
 bool qgemm_reads_tiled_codes(const Weights &w, int64_t M, bool asym = false);
 // measured choice between the two products for a layer object (true: the tiled pair is the faster one)
 bool qgemm_tiled_pays(int64_t M, int K, int N);
+bool qgemm4_tiled_pays(int64_t M, int K, int N);   // int4 weights
 hipError_t launch_xq_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st);
 hipError_t launch_rotate_quant_wide(const uint16_t *X, int64_t M, int K, int64_t ldx, const float *diag,
                                     int8_t *Xq, float *sx, hipStream_t st);

@@ -46,3 +46,58 @@ def test_edges(oracle, M, K, N, asym):
     assert np.array_equal(acc.cpu().numpy(), want), "int32 accumulators differ"
     y = oracle.dequant(want, sx.cpu().numpy(), scales, bias)
     gu.assert_y_same_codes(gu.bf16_to_host(Y), y, "Y (same codes)")
+
+
+# int4: one and two groups (no other tiled kernel takes them), one round of waves, several with a last round that is full
+# (18, 36 groups), short (13, 25: some waves without a group), and the 64-token tiles from one tile on
+SHAPES4 = [(1, 128, 16), (33, 256, 48), (17, 1152, 80), (31, 1536, 64), (40, 1664, 96), (65, 2304, 32), (50, 3200, 144),
+           (1, 4608, 1152), (64, 384, 128), (129, 1152, 304), (250, 4608, 144), (1000, 512, 272)]
+
+
+@pytest.mark.parametrize("M,K,N", SHAPES4)
+@pytest.mark.parametrize("variant", [8, 9, 10, 11, "asym"])
+def test_int4_edges(oracle, M, K, N, variant):
+    """Group sums exact, outputs bit for bit those of the ring kernel (the folds keep its order)."""
+    asym = variant == "asym"
+    Xb, W, d, bias = wl.small_case(950 + M, M, K, N, n_outliers=4)
+    w = trdq.prepare_weights(gu.f32_to_dev(W), gu.f32_to_dev(d), wbits=4)
+    X, dd, bd = gu.bf16_to_dev(Xb), gu.f32_to_dev(d), gu.f32_to_dev(bias)
+    Xq = torch.empty((M, K), dtype=torch.int8, device=gu.dev())
+    sx = torch.empty(M, device=gu.dev())
+    zc = torch.empty(M, dtype=torch.int32, device=gu.dev())
+    if asym:
+        trdq.rotate_quant_asym(X, dd, Xq, sx, zc, warm=w)
+    else:
+        trdq.rotate_quant(X, dd, Xq, sx, warm=w)
+    buf = torch.full((M + 1, N + 8), 7.0, dtype=torch.bfloat16, device=gu.dev())
+    Y, ring = buf[:M, :N], torch.empty((M, N), dtype=torch.bfloat16, device=gu.dev())
+    acc = torch.full((K // 128, M, N), -7, dtype=torch.int32, device=gu.dev())
+    try:
+        if asym:                         # takes the library's choice
+            trdq.qgemm_asym(w, Xq, sx, zc, Y, bias=bd, acc_debug=acc)
+            buf.fill_(7.0)
+            trdq.qgemm_asym(w, Xq, sx, zc, Y, bias=bd)
+        else:
+            trdq.qgemm_set_variant(6)
+            trdq.qgemm(w, Xq, sx, ring, bias=bd)
+            trdq.qgemm_set_variant(variant)
+            trdq.qgemm(w, Xq, sx, Y, bias=bd, acc_debug=acc)
+            buf.fill_(7.0)
+            trdq.qgemm(w, Xq, sx, Y, bias=bd)
+    finally:
+        trdq.qgemm_set_variant(-1)
+    torch.cuda.synchronize()
+    assert (buf[M] == 7.0).all() and (buf[:, N:] == 7.0).all()      # nothing outside the output
+    codes, scales = w.export()
+    q = Xq.cpu().numpy().astype(np.float64)
+    want = np.stack([q[:, g:g + 128] @ codes[g:g + 128].astype(np.float64) for g in range(0, K, 128)]).astype(np.int32)
+    assert np.array_equal(acc.cpu().numpy(), want), "int32 group sums differ"
+    if not asym:
+        assert torch.equal(Y, ring)
+        return
+    z = zc.cpu().numpy().astype(np.float64)
+    sums = want.astype(np.float64) + z[None, :, None] * codes.reshape(K // 128, 128, N).sum(axis=1)[:, None, :]
+    y = (sums * scales[:, None, :]).sum(axis=0) * sx.cpu().numpy().astype(np.float64)[:, None] + bias
+    got = Y.float().cpu().numpy().astype(np.float64)
+    # one bf16 step of the value, and the float32 sums' part that the zero-point term cancels (up to 255 / range)
+    assert (np.abs(got - y) <= 2.0 ** -8 * np.abs(y) + 1e-4 * np.abs(y).max(axis=1, keepdims=True)).all()
