@@ -53,3 +53,17 @@ def test_cosine_similarity_attention_sized(oracle):
     want = oracle.cosine_similarity(ab, bb)
     assert abs(got[0] - want[0]) <= TOL
     assert 0.99 < got[0] < 1.0
+
+
+# a workgroup per segment up to 8192 pieces of 8 elements (64, 256 or 1024 lanes), chunks beyond; pieces past the end of a
+# step, elements past the last piece
+@pytest.mark.parametrize("n,L", [(2, 8 * 256), (2, 8 * 257 + 3), (2, 8 * 1024 + 7), (2, 8 * 1025), (2, 8 * 8192 + 1),
+                                 (2, 8 * 8193), (2, 8 * 9216 + 5), (1, 8 * 100001 + 2), (700, 8 * 8200)])
+def test_cosine_similarity_work_split(oracle, n, L):
+    Lp = (L + 7) // 8 * 8
+    rng = np.random.default_rng(n + L)
+    a = rng.standard_normal((n, Lp)).astype(np.float32)
+    b = (0.7 * a + 0.3 * rng.standard_normal((n, Lp)).astype(np.float32)).astype(np.float32)
+    ab, bb = wl.f32_to_bf16_bits(a), wl.f32_to_bf16_bits(b)
+    got, want = _run(ab, bb, L), oracle.cosine_similarity(ab[:, :L], bb[:, :L])
+    assert np.abs(got - want).max() <= TOL, f"max error {np.abs(got - want).max():.2e}"
