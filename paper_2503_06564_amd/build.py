@@ -27,7 +27,6 @@ SOURCE_FLAGS = {"qgemm_dma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                 # of fetched by the kernel's first instructions (a fraction of a microsecond per launch)
                 "rotate_quant.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-kernarg-preload-count=16"],
                 "fused.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=16"],
-                "rotate_quant_rpr.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
                 "calibrate.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 

@@ -1,24 +1,25 @@
 // rotate_quant_rpr: the full activation transform of Eq. 9,
 //   G_t(X) = (X . Delta_t) . R^(1) . P . R^(2),
 // first block rotation, zigzag permutation P (Sec. 3.2), second block rotation, followed by the
-// per-token dynamic int8 quantiser (Eq. 1-2, symmetric form).  Both rotations use the same
+// per-token dynamic int8 quantiser (Eq. 1-2 symmetric, Eq. 1-3 with zero points).  Both rotations use the same
 // block-diagonal Hadamard blocks as rotate_quant; (U P)[k'] = U[perm[k']].
 //
-// The permutation moves channels between blocks, so a token's whole rotated row has to exist
-// before the second rotation starts: a workgroup owns TOK tokens and keeps their first-rotation
-// output in LDS as fp32 (TOK x K x 4 bytes: 16 tokens up to K = 2304, 8 tokens up to K = 4608).
-//   stage 1: each wave rotates its blocks of the row (H_128 = H_16 (x) H_8: the H_8 factor and the
-//            diagonal on the vector ALU inside a lane, the H_16 factor over the 16 chunks of a
-//            block as an exact fp32 product with a +-1 matrix, v_mfma_f32_16x16x4_f32) and
-//            writes the result to LDS by channel;
-//   stage 2: each wave gathers the channels perm[k'] of its output blocks from LDS, rotates them
-//            the same way and keeps the results in registers until the token maxima are known
-//            (exchanged through LDS), then quantises and stores like rotate_quant.
-// The matrix instruction has 16 columns: 16 tokens of one block, or, with TOK = 8, 8 tokens of
-// two blocks at once (lanes r >= 8 hold token r - 8 of the wave's second block; the +-1 operand
-// is the same for every column).  Both rotations are unnormalised; the factor 1/128 goes into
-// the scale.  Entries of perm are clamped to [0, K) on the way in, so a bad table gives wrong
-// numbers, never an access outside the row.
+// The permutation moves channels between blocks, so a token's whole rotated row has to exist before the second rotation
+// starts: a workgroup owns 4 QUADS tokens and keeps their first-rotation output in LDS as fp32.
+//   stage 1: a wave rotates its blocks, four tokens at a time (16 lanes to a token's block, 8 channels to a lane), and
+//            writes them to LDS by channel;
+//   stage 2: it gathers the channels perm[k'] of its output blocks from LDS, rotates them the same way, keeps them in
+//            registers until the token maxima are known (exchanged through LDS), then quantises and stores.
+// What bounds it is vector issue: 128 channels of 16 tokens cost about 650 vector instructions.  The rotation is butterflies
+// on the vector ALU: three stages in the lane and four across the 16 lanes, each of the latter one multiply-add whose
+// operand comes from the other lane (the form that multiplied by H_16 on the fp32 matrix instruction held the vector
+// ALU for 1024 cycles per 16-token block and rotation, twice the cost, and its 16 columns asked for workgroups of 16 or
+// 8 tokens: at K = 4608 one per compute unit, each phase of which waited for the one before).
+// us at 4096 / 32768 tokens, that form and this one: 1152 channels 10.0 / 65.6 -> 6.7 / 34.6 (3.3 TB/s), 4608 channels
+// 31.7 / 231 -> 17.8 / 122 (3.7 TB/s).  Relative error against float64 1.3e-7 -> 1.0e-7 (sums by pairs, and the diagonal
+// inside the first stage's multiply-add).
+// Both rotations are unnormalised; the factor 1/128 goes into the scale.  Entries of perm are clamped to [0, K) on the
+// way in, so a bad table gives wrong numbers, never an access outside the row.
 #include "device_utils.h"
 #include "trdq_internal.h"
 
@@ -26,94 +27,157 @@ namespace trdq {
 
 namespace {
 
-constexpr int kRowPad = 4;     // floats of padding per LDS row: tokens land in different banks
+constexpr int kRowPad = 4;     // floats of padding per LDS row
 
-// in-lane H_8 over 8 values (three add stages)
-__device__ __forceinline__ void h8(float (&v)[8])
+// Walsh-Hadamard transform of 128 values held by 16 lanes, 8 to a lane.  The lanes are paired by the exchanges that cost
+// one operand each: lane ^ 1, ^ 2, ^ 7 (half-row mirror) and ^ 8.  In the basis {1, 2, 7, 8} lane p has the
+// coordinates (b0 ^ b2, b1 ^ b2, b2, b3) of its bits; chunk(p) is the 8-channel chunk with these index bits.  A stage
+// is own + s * other with s = -1 in the lane whose coordinate is 1: that lane gets other - own negated, so that
+// after all four stages lane p holds (-1)^(sum of its coordinates) times its coefficient.  Flipping all index bits of the
+// input has the same effect on the transform, so the input is taken with chunk 15 - chunk(p) in lane p and the signs
+// cancel: coefficients of chunk(p) come out.
+struct Lane16 {
+    float s1, s2, s7, s8;
+    int chunk;
+    __device__ __forceinline__ explicit Lane16(int p)
+    {
+        const int c1 = (p ^ (p >> 2)) & 1, c2 = ((p >> 1) ^ (p >> 2)) & 1, c7 = (p >> 2) & 1, c8 = p >> 3;
+        chunk = c1 | c2 << 1 | c7 << 2 | c8 << 3;
+        s1 = c1 ? -1.0f : 1.0f;
+        s2 = c2 ? -1.0f : 1.0f;
+        s7 = c7 ? -1.0f : 1.0f;
+        s8 = c8 ? -1.0f : 1.0f;
+    }
+};
+
+__device__ __forceinline__ void cross16(float (&v)[8], const Lane16 &ln)
 {
-    const float b0 = v[0] + v[1], b1 = v[0] - v[1], b2 = v[2] + v[3], b3 = v[2] - v[3];
-    const float b4 = v[4] + v[5], b5 = v[4] - v[5], b6 = v[6] + v[7], b7 = v[6] - v[7];
-    const float a0 = b0 + b2, a2 = b0 - b2, a1 = b1 + b3, a3 = b1 - b3;
-    const float a4 = b4 + b6, a6 = b4 - b6, a5 = b5 + b7, a7 = b5 - b7;
-    v[0] = a0 + a4; v[4] = a0 - a4;
-    v[1] = a1 + a5; v[5] = a1 - a5;
-    v[2] = a2 + a6; v[6] = a2 - a6;
-    v[3] = a3 + a7; v[7] = a3 - a7;
+    // v += s * (v of the paired lane), four stages.  A lane-crossing read needs two wait states after the write of its
+    // register: the s_nop for what came before, the eight values in turn within the block.  (The compiler makes a move, its
+    // own wait states and a multiply-add of each.)
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %0, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %6, %6, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %7, %7, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %0, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %6, %6, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %7, %7, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %0, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %6, %6, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %7, %7, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %0, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %6, %6, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %7, %7, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
+        : "v"(ln.s1), "v"(ln.s2), "v"(ln.s7), "v"(ln.s8));
 }
 
-template <int TOK, int SPW>
-__global__ __launch_bounds__(768) void rotate_quant_rpr_kernel(
+// sum and difference of a bf16 pair times its two factors
+__device__ __forceinline__ void scaled_pair(uint32_t x, float d0, float d1, float &sum, float &diff)
+{
+    const float b = bf16_hi(x) * d1;
+    sum = __builtin_fmaf(bf16_lo(x), d0, b);
+    diff = __builtin_fmaf(bf16_lo(x), d0, -b);
+}
+
+// the second and third of the transform's three in-lane stages
+__device__ __forceinline__ void stages_2_4(float (&v)[8])
+{
+#pragma unroll
+    for (int h = 2; h < 8; h <<= 1)
+#pragma unroll
+        for (int i = 0; i < 8; i += 2 * h)
+#pragma unroll
+            for (int j = i; j < i + h; ++j) {
+                const float a = v[j], b = v[j + h];
+                v[j] = a + b;
+                v[j + h] = a - b;
+            }
+}
+
+// QUADS: groups of four tokens per workgroup; SPW: most blocks per wave; ASYM: zero points (codes stored as q - 128,
+// zc[i] = 128 - z_i), as in rotate_quant.
+template <int QUADS, int SPW, bool ASYM>
+__global__ __launch_bounds__(768, 6) void rotate_quant_rpr_kernel(
     const uint16_t *__restrict__ X, int64_t M, int nb, int64_t ldx,
     const float *__restrict__ diag, const int32_t *__restrict__ perm,
     int8_t *__restrict__ Xq, float *__restrict__ sx, int32_t *__restrict__ zc,
     const uint4 *__restrict__ warm, int64_t warm_chunks)
 {
-    // zc != null: the asymmetric quantiser of Eq. 1-3 (codes stored as q - 128, zc[i] = 128 - z_i), as in rotate_quant
-    static_assert(TOK == 16 || TOK == 8, "16 or 8 tokens per workgroup");
-    const bool asym = zc != nullptr;
+    constexpr int TOK = 4 * QUADS;
     extern __shared__ __align__(16) float lds[];
     const int K = nb * kBlock;
     const int nw = blockDim.x >> 6;
     const int rowf = K + kRowPad;                    // floats per LDS row
     float *const T = lds;                            // [TOK][rowf]: first-rotation output
-    float *const amax_s = lds + (size_t)TOK * rowf;  // [2][nw][16] (maxima, minima); after it a 1 KB dump area for the weight copies
+    float *const ext_s = lds + (size_t)TOK * rowf;   // [2][nw][TOK] (maxima, minima); after it a 1 KB dump area for the weight copies
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, r = lane & 15;
-    constexpr int BPI = 16 / TOK;                    // blocks a wave rotates per matrix instruction
-    const int rt = r & (TOK - 1);                    // token slot of this lane
-    const int bsel = r / TOK;                        // which of the item's blocks this lane holds
-    const int64_t tg = blockIdx.x;
-    int64_t token = tg * TOK + rt;
-    const bool token_ok = token < M;
-    if (token >= M) token = M - 1;                   // clamped: rotated like the others, never stored
+    const int t4 = lane >> 4;                        // token of the quad
+    const Lane16 ln(lane & 15);
+    const int c_in = (15 - ln.chunk) * 8, c_out = ln.chunk * 8;
+    const int64_t m0 = (int64_t)blockIdx.x * TOK;
 
-    // ---- stage 1: T[token][.] = (x * d) H_128 per block (natural row order of H_16) -----------
-    float hn[4];                                     // A operand: H_16[q = r][p = 4s + g]
-#pragma unroll
-    for (int s = 0; s < 4; ++s) hn[s] = (__builtin_popcount(r & (4 * s + g)) & 1) ? -1.0f : 1.0f;
+    // ---- stage 1: T[token][.] = (x * d) H_128 per block ------------------------------------------
+    // everything is requested first; a block past the row is clamped (a redundant, cached read)
+    uint4 raw[SPW][QUADS];
+    float4 dg[SPW][2];
 #pragma unroll
     for (int i = 0; i < SPW; ++i) {
-        const int b0 = (wave + nw * i) * BPI;        // wave-uniform: first block of the item
-        if (b0 < nb) {
-            const int bl = b0 + bsel;                // this lane's block (may be one past the end)
-            const bool b_ok = bl < nb;
-            const int b = b_ok ? bl : nb - 1;        // clamped: rotated, not written
-            float w[4][8];
-            const uint16_t *src = X + token * ldx + b * kBlock + g * 8;
+        const int b = wave + nw * i < nb ? wave + nw * i : nb - 1;    // wave-uniform
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const uint4 q = *reinterpret_cast<const uint4 *>(src + s * 32);
-                float4 d0 = make_float4(1.f, 1.f, 1.f, 1.f), d1 = d0;
-                if (diag) {
-                    const float *dp = diag + b * kBlock + (4 * s + g) * 8;
-                    d0 = *reinterpret_cast<const float4 *>(dp);
-                    d1 = *reinterpret_cast<const float4 *>(dp + 4);
-                }
-                w[s][0] = bf16_lo(q.x) * d0.x; w[s][1] = bf16_hi(q.x) * d0.y;
-                w[s][2] = bf16_lo(q.y) * d0.z; w[s][3] = bf16_hi(q.y) * d0.w;
-                w[s][4] = bf16_lo(q.z) * d1.x; w[s][5] = bf16_hi(q.z) * d1.y;
-                w[s][6] = bf16_lo(q.w) * d1.z; w[s][7] = bf16_hi(q.w) * d1.w;
-                h8(w[s]);
-            }
-            // D[q][token] = sum_p H_16[q][p] * w[p][token]; lane (g, r) receives q = 4g .. 4g+3
-            v4f acc[8];
+        for (int q = 0; q < QUADS; ++q) {
+            int64_t token = m0 + q * 4 + t4;
+            if (token >= M) token = M - 1;           // clamped: rotated like the others, never stored
+            raw[i][q] = *reinterpret_cast<const uint4 *>(X + token * ldx + b * kBlock + c_in);
+        }
+        dg[i][0] = dg[i][1] = make_float4(1.f, 1.f, 1.f, 1.f);
+        if (diag) {
+            dg[i][0] = *reinterpret_cast<const float4 *>(diag + b * kBlock + c_in);
+            dg[i][1] = *reinterpret_cast<const float4 *>(diag + b * kBlock + c_in + 4);
+        }
+    }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < SPW; ++i) {
+        const int b = wave + nw * i;
+        if (b < nb) {
+            const float4 d0 = dg[i][0], d1 = dg[i][1];
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(hn[s], w[s][j], acc[j], 0, 0, 0);
-            }
-            if (b_ok) {
-                float *dst = T + (size_t)rt * rowf + b * kBlock + g * 32;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    *reinterpret_cast<float4 *>(dst + q * 8) = make_float4(acc[0][q], acc[1][q], acc[2][q], acc[3][q]);
-                    *reinterpret_cast<float4 *>(dst + q * 8 + 4) = make_float4(acc[4][q], acc[5][q], acc[6][q], acc[7][q]);
-                }
+            for (int q = 0; q < QUADS; ++q) {
+                const uint4 x = raw[i][q];
+                // the diagonal rides in the first stage of the transform
+                float v[8];
+                scaled_pair(x.x, d0.x, d0.y, v[0], v[1]);
+                scaled_pair(x.y, d0.z, d0.w, v[2], v[3]);
+                scaled_pair(x.z, d1.x, d1.y, v[4], v[5]);
+                scaled_pair(x.w, d1.z, d1.w, v[6], v[7]);
+                stages_2_4(v);
+                cross16(v, ln);
+                float *dst = T + (size_t)(q * 4 + t4) * rowf + b * kBlock + c_out;
+                *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+                *reinterpret_cast<float4 *>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
             }
         }
     }
@@ -121,7 +185,7 @@ __global__ __launch_bounds__(768) void rotate_quant_rpr_kernel(
     // rotate_quant): up to four direct-to-LDS copies per wave into a dump area nobody reads.
     if (warm_chunks > 0) {
         const uint32_t dump = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)lds +
-                              (uint32_t)(sizeof(float) * ((size_t)TOK * rowf + (size_t)nw * 32));
+                              (uint32_t)(sizeof(float) * ((size_t)TOK * rowf + (size_t)nw * 2 * TOK));
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int64_t c0 = ((int64_t)t * gridDim.x + blockIdx.x) * blockDim.x + (wave << 6);   // wave-uniform
@@ -133,131 +197,119 @@ __global__ __launch_bounds__(768) void rotate_quant_rpr_kernel(
             }
         }
     }
-    __syncthreads();
-
-    // ---- stage 2: gather by perm, rotate again, keep in registers -----------------------------------
-    // Rows of H_16 permuted as in rotate_quant: lane group g' receives chunks 2g', 2g'+1 (i = 0, 1)
-    // and 8 + 2g', 9 + 2g' (i = 2, 3), so each 16-byte store covers 64 consecutive bytes of a token.
-    const int qrow = (r & 2) ? 8 + 2 * (r >> 2) + (r & 1) : 2 * (r >> 2) + (r & 1);
-    float hs[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) hs[s] = (__builtin_popcount(qrow & (4 * s + g)) & 1) ? -1.0f : 1.0f;
-
-    v4f out[SPW][8];
-    float amax = 0.0f;
-    float amin = 0.0f;                               // asymmetric: the token minimum (<= 0); amax is then the maximum (>= 0)
-    const float *Trow = T + (size_t)rt * rowf;
+    // the channels this lane gathers, requested before the barrier
+    int4 idx[SPW][2];
 #pragma unroll
     for (int i = 0; i < SPW; ++i) {
-        const int b0 = (wave + nw * i) * BPI;
-        if (b0 < nb) {
-            const int b = (b0 + bsel < nb) ? b0 + bsel : nb - 1;
-            float w[4][8];
+        const int b = wave + nw * i < nb ? wave + nw * i : nb - 1;
+        idx[i][0] = *reinterpret_cast<const int4 *>(perm + b * kBlock + c_in);
+        idx[i][1] = *reinterpret_cast<const int4 *>(perm + b * kBlock + c_in + 4);
+    }
+    __syncthreads();
+
+    // ---- stage 2: gather by perm, rotate again, keep in registers ---------------------------------
+    float out[SPW][QUADS][8];
+    float amax[QUADS], amin[QUADS];                  // ASYM: maximum (>= 0) and minimum (<= 0); else the absolute maximum
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int32_t *pp = perm + b * kBlock + (4 * s + g) * 8;
-                const int4 i0 = *reinterpret_cast<const int4 *>(pp);
-                const int4 i1 = *reinterpret_cast<const int4 *>(pp + 4);
-                const int idx[8] = {i0.x, i0.y, i0.z, i0.w, i1.x, i1.y, i1.z, i1.w};
+    for (int q = 0; q < QUADS; ++q) amax[q] = amin[q] = 0.0f;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    int k = idx[j];
-                    k = k < 0 ? 0 : (k >= K ? K - 1 : k);
-                    w[s][j] = Trow[k];
-                }
-                h8(w[s]);
-            }
+    for (int i = 0; i < SPW; ++i) {
+        const int b = wave + nw * i;
+        if (b < nb) {
+            int k[8] = {idx[i][0].x, idx[i][0].y, idx[i][0].z, idx[i][0].w, idx[i][1].x, idx[i][1].y, idx[i][1].z, idx[i][1].w};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < 8; ++j) k[j] = max(0, min(k[j], K - 1)) + t4 * rowf;
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(hs[s], w[s][j], acc, 0, 0, 0);
-                out[i][j] = acc;
-                if (asym) {
-                    amax = fmaxf(fmaxf(amax, fmaxf(acc[0], acc[1])), fmaxf(acc[2], acc[3]));
-                    amin = fminf(fminf(amin, fminf(acc[0], acc[1])), fminf(acc[2], acc[3]));
-                } else {
-                    amax = fmaxf(fmaxf(amax, fabsf(acc[0])), fabsf(acc[1]));
-                    amax = fmaxf(fmaxf(amax, fabsf(acc[2])), fabsf(acc[3]));
+            for (int q = 0; q < QUADS; ++q) {
+                float v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[j] = T[k[j] + q * 4 * rowf];
+                cross16(v, ln);
+                fwht8_inlane(v);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) out[i][q][j] = v[j];
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) {
+                    if constexpr (ASYM) {
+                        amax[q] = fmaxf(fmaxf(amax[q], v[j]), v[j + 1]);
+                        amin[q] = fminf(fminf(amin[q], v[j]), v[j + 1]);
+                    } else {
+                        amax[q] = fmaxf(fmaxf(amax[q], fabsf(v[j])), fabsf(v[j + 1]));
+                    }
                 }
             }
         }
     }
 
-    // token absmax: over the four lane-rows of this wave, then over the waves through LDS
-    amax = fmaxf(amax, __shfl_xor(amax, 16));
-    amax = fmaxf(amax, __shfl_xor(amax, 32));
-    if (BPI == 2) amax = fmaxf(amax, __shfl_xor(amax, 8));       // the token's other block in this wave
-    amin = fminf(amin, __shfl_xor(amin, 16));
-    amin = fminf(amin, __shfl_xor(amin, 32));
-    if (BPI == 2) amin = fminf(amin, __shfl_xor(amin, 8));
-    if (g == 0) {
-        amax_s[wave * 16 + r] = amax;
-        amax_s[(nw + wave) * 16 + r] = amin;
+    // token extremes: over the 16 lanes, then over the waves through LDS
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+        amax[q] = row16_max(amax[q]);
+        if constexpr (ASYM) amin[q] = -row16_max(-amin[q]);
+        if ((lane & 15) == 0) {
+            ext_s[wave * TOK + q * 4 + t4] = amax[q];
+            if constexpr (ASYM) ext_s[(nw + wave) * TOK + q * 4 + t4] = amin[q];
+        }
     }
     __syncthreads();
-    for (int wv = 0; wv < nw; ++wv) {
-        amax = fmaxf(amax, amax_s[wv * 16 + r]);
-        amin = fminf(amin, amax_s[(nw + wv) * 16 + r]);
-    }
 
     // out holds 128 * V.  Symmetric: s_x = max|V| / 127; codes = rint(V / s_x) = rint(out * 127 / max|out|).
     // Asymmetric (range [lo, hi] with lo <= 0 <= hi): s_x = (hi - lo) / 255, z = -rint(lo / s_x), stored code =
     // clamp(rint(V / s_x) + z, 0, 255) - 128; the integer offset rides in the rounding constant of the same FMA.
-    float inv, magic = kRoundMagic;
-    if (asym) {
-        const float range = amax - amin;
-        inv = range > 0.0f ? 255.0f / range : 0.0f;
-        const float z = -rintf(amin * inv);
-        magic = kRoundMagic + (z - 128.0f);
-        if (wave == 0 && g == 0 && r < TOK && token_ok) {
-            sx[token] = range * (0.0078125f / 255.0f);
-            zc[token] = 128 - (int)z;
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+        for (int wv = 0; wv < nw; ++wv) {
+            amax[q] = fmaxf(amax[q], ext_s[wv * TOK + q * 4 + t4]);
+            if constexpr (ASYM) amin[q] = fminf(amin[q], ext_s[(nw + wv) * TOK + q * 4 + t4]);
         }
-    } else {
-        inv = amax > 0.0f ? 127.0f / amax : 0.0f;
-        if (wave == 0 && g == 0 && r < TOK && token_ok) sx[token] = amax * (0.0078125f / 127.0f);
-    }
-    auto code_bits = [&](float v) -> uint32_t {
-        const float t = __builtin_fmaf(v, inv, magic);
-        // symmetric codes cannot leave +-127; the clamp only acts on the asymmetric range ends
-        return __float_as_uint(__builtin_amdgcn_fmed3f(t, kRoundMagic - 128.0f, kRoundMagic + 127.0f));
-    };
-
-#pragma unroll
-    for (int i = 0; i < SPW; ++i) {
-        const int b = (wave + nw * i) * BPI + bsel;
-        if (b < nb && token_ok) {
-            uint32_t c[8];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                c[2 * q] = pack4_low_bytes(code_bits(out[i][0][q]), code_bits(out[i][1][q]),
-                                           code_bits(out[i][2][q]), code_bits(out[i][3][q]));
-                c[2 * q + 1] = pack4_low_bytes(code_bits(out[i][4][q]), code_bits(out[i][5][q]),
-                                               code_bits(out[i][6][q]), code_bits(out[i][7][q]));
+        const int64_t token = m0 + q * 4 + t4;
+        const bool token_ok = token < M;
+        float inv, magic = kRoundMagic;
+        if constexpr (ASYM) {
+            const float range = amax[q] - amin[q];
+            inv = range > 0.0f ? 255.0f / range : 0.0f;
+            const float z = -rintf(amin[q] * inv);
+            magic = kRoundMagic + (z - 128.0f);
+            if (wave == 0 && (lane & 15) == 0 && token_ok) {
+                sx[token] = range * (0.0078125f / 255.0f);
+                zc[token] = 128 - (int)z;
             }
-            int8_t *dst = Xq + token * (int64_t)K + b * kBlock + g * 16;
-            *reinterpret_cast<uint4 *>(dst) = make_uint4(c[0], c[1], c[2], c[3]);
-            *reinterpret_cast<uint4 *>(dst + 64) = make_uint4(c[4], c[5], c[6], c[7]);
+        } else {
+            inv = amax[q] > 0.0f ? 127.0f / amax[q] : 0.0f;
+            if (wave == 0 && (lane & 15) == 0 && token_ok) sx[token] = amax[q] * (0.0078125f / 127.0f);
+        }
+        auto code_bits = [&](float v) -> uint32_t {
+            const float t = __builtin_fmaf(v, inv, magic);
+            // symmetric codes cannot leave +-127; the clamp only acts on the asymmetric range ends
+            return __float_as_uint(ASYM ? __builtin_amdgcn_fmed3f(t, kRoundMagic - 128.0f, kRoundMagic + 127.0f) : t);
+        };
+#pragma unroll
+        for (int i = 0; i < SPW; ++i) {
+            const int b = wave + nw * i;
+            if (b < nb && token_ok) {
+                const float (&v)[8] = out[i][q];
+                uint2 c;
+                c.x = pack4_low_bytes(code_bits(v[0]), code_bits(v[1]), code_bits(v[2]), code_bits(v[3]));
+                c.y = pack4_low_bytes(code_bits(v[4]), code_bits(v[5]), code_bits(v[6]), code_bits(v[7]));
+                *reinterpret_cast<uint2 *>(Xq + token * (int64_t)K + b * kBlock + c_out) = c;
+            }
         }
     }
     // the copies to the dump area must have landed before the workgroup's LDS is given away
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-template <int TOK, int SPW>
-hipError_t launch_rpr(const uint16_t *X, int64_t M, int nb, int nw, int64_t ldx, const float *diag,
+template <int QUADS, int SPW>
+hipError_t launch_rpr(const uint16_t *X, int64_t M, int nb, int64_t ldx, const float *diag,
                       const int32_t *perm, int8_t *Xq, float *sx, int32_t *zc, const void *warm, int64_t warm_bytes,
                       hipStream_t st)
 {
-    const int K = nb * kBlock;
-    const size_t smem = sizeof(float) * ((size_t)TOK * (K + kRowPad) + (size_t)nw * 32) + 1024;
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(rotate_quant_rpr_kernel<TOK, SPW>), 160 * 1024);
-        e != hipSuccess)
-        return e;
-    const int64_t groups = (M + TOK - 1) / TOK;
-    hipLaunchKernelGGL((rotate_quant_rpr_kernel<TOK, SPW>), dim3((unsigned)groups), dim3(64 * nw), smem, st,
+    constexpr int TOK = 4 * QUADS;
+    const int K = nb * kBlock, nw = (nb + SPW - 1) / SPW;
+    const size_t smem = sizeof(float) * ((size_t)TOK * (K + kRowPad) + (size_t)nw * 2 * TOK) + 1024;
+    auto kern = zc ? rotate_quant_rpr_kernel<QUADS, SPW, true> : rotate_quant_rpr_kernel<QUADS, SPW, false>;
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), 160 * 1024); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((M + TOK - 1) / TOK)), dim3(64 * nw), smem, st,
                        X, M, nb, ldx, diag, perm, Xq, sx, zc, static_cast<const uint4 *>(warm),
                        (warm && warm_bytes < ((int64_t)1 << 32)) ? warm_bytes / 16 : 0);
     return hipGetLastError();
@@ -265,7 +317,7 @@ hipError_t launch_rpr(const uint16_t *X, int64_t M, int nb, int nw, int64_t ldx,
 
 }  // namespace
 
-// K up to 4608 (36 blocks): 12 waves x 3 blocks; LDS holds 8 tokens x 4608 floats.
+// K up to 4608 (36 blocks): 12 waves x 3 blocks.
 bool rotate_quant_rpr_supports(int K) { return K > 0 && K % kBlock == 0 && K / kBlock <= 36; }
 
 hipError_t launch_rotate_quant_rpr(const uint16_t *X, int64_t M, int K, int64_t ldx, const float *diag,
@@ -275,23 +327,12 @@ hipError_t launch_rotate_quant_rpr(const uint16_t *X, int64_t M, int K, int64_t 
     if (M == 0) return hipSuccess;
     if (!rotate_quant_rpr_supports(K)) return hipErrorInvalidValue;
     const int nb = K / kBlock;
-    // 16 tokens per workgroup while their rows fit LDS, else 8 tokens and two blocks per item
-    const bool tok16 = (size_t)16 * (K + kRowPad) * 4 + (size_t)12 * 128 + 1024 <= 150 * 1024;
-    const int items = tok16 ? nb : (nb + 1) / 2;
-    const int spw = items <= 12 ? 1 : (items <= 24 ? 2 : 3);
-    const int nw = (items + spw - 1) / spw;
-    if (tok16) {
-        switch (spw) {
-            case 1: return launch_rpr<16, 1>(X, M, nb, nw, ldx, diag, perm, Xq, sx, zc, warm, warm_bytes, st);
-            case 2: return launch_rpr<16, 2>(X, M, nb, nw, ldx, diag, perm, Xq, sx, zc, warm, warm_bytes, st);
-            default: return launch_rpr<16, 3>(X, M, nb, nw, ldx, diag, perm, Xq, sx, zc, warm, warm_bytes, st);
-        }
-    }
-    switch (spw) {
-        case 1: return launch_rpr<8, 1>(X, M, nb, nw, ldx, diag, perm, Xq, sx, zc, warm, warm_bytes, st);
-        case 2: return launch_rpr<8, 2>(X, M, nb, nw, ldx, diag, perm, Xq, sx, zc, warm, warm_bytes, st);
-        default: return launch_rpr<8, 3>(X, M, nb, nw, ldx, diag, perm, Xq, sx, zc, warm, warm_bytes, st);
-    }
+    // Eight tokens per workgroup while a wave has one block: the indices and the diagonal serve two quads (us at 4096 /
+    // 32768 tokens, eight against four: 1152 channels 6.7 / 34.6, 6.8 / 39.2; 1536 7.7 / 45.5, 8.4 / 49.6).  Four beyond, where
+    // eight leave room for one or two workgroups per compute unit (2304 10.9 / 61.1, 10.2 / 58.8; 4608 20.8 / 141, 17.8 / 122).
+    if (nb <= 12) return launch_rpr<2, 1>(X, M, nb, ldx, diag, perm, Xq, sx, zc, warm, warm_bytes, st);
+    if (nb <= 24) return launch_rpr<1, 2>(X, M, nb, ldx, diag, perm, Xq, sx, zc, warm, warm_bytes, st);
+    return launch_rpr<1, 3>(X, M, nb, ldx, diag, perm, Xq, sx, zc, warm, warm_bytes, st);
 }
 
 }  // namespace trdq

@@ -42,7 +42,7 @@ def _gpu_rotate_quant_rpr(Xbits, d, perm, ldx=None):
     return Xq, sx
 
 
-# (M, K): one block, the DiT widths (16 tokens per workgroup up to K = 2304, 8 above), ragged M
+# (M, K): one block, the DiT widths, ragged M
 RPR_SHAPES = [(16, 128), (37, 256), (64, 1152), (21, 2304), (40, 2432), (19, 4608), (1, 1152), (0, 1152)]
 
 
@@ -242,3 +242,34 @@ def test_rpr_with_asymmetric_activation_codes(oracle, M, K, N):
     Xq_o, sx_o = oracle.rotate_quant_rpr(Xb, d, perm, 128)
     assert_codes_close(Xq2.cpu().numpy(), Xq_o, "Xq (R P R, symmetric)")
     w.close()
+
+
+# the edges of the work split: one block per wave up to 12 (workgroups of eight tokens), two up to 24, three beyond (of four),
+# the last wave with fewer; token counts on both sides of a workgroup
+@pytest.mark.parametrize("M,K", [(7, 1536), (9, 384), (8, 128), (5, 1664), (3, 3072), (4, 3200), (6, 4480)])
+@pytest.mark.parametrize("asym", [False, True])
+def test_rotate_quant_rpr_work_split(oracle, M, K, asym):
+    Xb, _, d, _ = wl.small_case(41, M, K, 16, n_outliers=max(1, K // 144), outlier=40.0)
+    perm = np.random.default_rng(K).permutation(K).astype(np.int32)
+    # float32 moves a value by some 1e-7 of the row maximum, 1e-5 .. 3e-5 of a step: up to 2 * 3e-5 of the codes lie close
+    # enough to a rounding tie, half a code of the 9 thousand here (the fraction the larger tests allow): at most two, by one
+    few = lambda diff: diff.max() <= 1 and np.count_nonzero(diff) <= 2
+    if not asym:
+        Xq, sx = _gpu_rotate_quant_rpr(Xb, d, perm, ldx=K + 8)
+        Xq_o, sx_o = oracle.rotate_quant_rpr(Xb, d, perm, 128)
+        assert few(np.abs(Xq.cpu().numpy().astype(np.int16) - Xq_o.astype(np.int16)))
+        assert_scales_close(sx.cpu().numpy(), sx_o, "s_x (R P R)")
+        return
+    W = np.zeros((K, 16), dtype=np.float32)
+    W[0, :] = 1.0
+    ref = oracle.linear_rpr_asym(Xb, W, d, perm, None, exact_blas=True)
+    buf = torch.full((M + 1, K), 99, dtype=torch.int8, device=dev())
+    sx = torch.full((M,), -1.0, dtype=torch.float32, device=dev())
+    zc = torch.full((M,), -999, dtype=torch.int32, device=dev())
+    trdq.rotate_quant_rpr_asym(bf16_to_dev(Xb), f32_to_dev(d), torch.from_numpy(perm).to(dev()), buf[:M], sx, zc)
+    torch.cuda.synchronize()
+    assert (buf[M] == 99).all()
+    q, z = buf[:M].cpu().numpy().astype(np.int32) + 128, 128 - zc.cpu().numpy()
+    assert np.array_equal(z, ref["zx"])
+    assert few(np.abs(q - np.asarray(ref["Xq"], dtype=np.int32)))
+    assert_scales_close(sx.cpu().numpy(), ref["sx"], "s_x (R P R, asymmetric)")
