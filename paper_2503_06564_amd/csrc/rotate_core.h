@@ -1,5 +1,5 @@
-// Per-token rotation core shared by the streaming rotate_quant kernel and the fused
-// linear kernel: a row of 16 lanes rotates T blocks of one token and keeps them in registers.
+// Per-token rotation core of the fused linear kernel: a row of 16 lanes rotates T blocks of one token and keeps them
+// in registers.
 #pragma once
 
 #include "device_utils.h"

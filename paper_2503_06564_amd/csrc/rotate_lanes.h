@@ -1,0 +1,96 @@
+// Block-128 Walsh-Hadamard transform with 16 lanes to a block and 8 channels to a lane, one vector instruction per value
+// and stage: shared by the passes that are bound by vector issue or by registers.
+#pragma once
+
+#include "device_utils.h"
+
+namespace trdq {
+
+// Walsh-Hadamard transform of 128 values held by 16 lanes, 8 to a lane.  The lanes are paired by the exchanges that cost
+// one operand each: lane ^ 1, ^ 2, ^ 7 (half-row mirror) and ^ 8.  In the basis {1, 2, 7, 8} lane p has the
+// coordinates (b0 ^ b2, b1 ^ b2, b2, b3) of its bits; chunk(p) is the 8-channel chunk with these index bits.  A stage
+// is own + s * other with s = -1 in the lane whose coordinate is 1: that lane gets other - own negated, so that
+// after all four stages lane p holds (-1)^(sum of its coordinates) times its coefficient.  Flipping all index bits of the
+// input has the same effect on the transform, so the input is taken with chunk 15 - chunk(p) in lane p and the signs
+// cancel: coefficients of chunk(p) come out.
+struct Lane16 {
+    float s1, s2, s7, s8;
+    int chunk;
+    __device__ __forceinline__ explicit Lane16(int p)
+    {
+        const int c1 = (p ^ (p >> 2)) & 1, c2 = ((p >> 1) ^ (p >> 2)) & 1, c7 = (p >> 2) & 1, c8 = p >> 3;
+        chunk = c1 | c2 << 1 | c7 << 2 | c8 << 3;
+        s1 = c1 ? -1.0f : 1.0f;
+        s2 = c2 ? -1.0f : 1.0f;
+        s7 = c7 ? -1.0f : 1.0f;
+        s8 = c8 ? -1.0f : 1.0f;
+    }
+};
+
+__device__ __forceinline__ void cross16(float (&v)[8], const Lane16 &ln)
+{
+    // v += s * (v of the paired lane), four stages.  A lane-crossing read needs two wait states after the write of its
+    // register: the s_nop for what came before, the eight values in turn within the block.  (The compiler makes a move, its
+    // own wait states and a multiply-add of each.)
+    asm("s_nop 1\n\t"
+        "v_fmac_f32_dpp %0, %0, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %6, %6, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %7, %7, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %0, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %6, %6, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %7, %7, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %0, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %6, %6, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %7, %7, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %0, %0, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %1, %1, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %2, %2, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %3, %3, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %4, %4, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %5, %5, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %6, %6, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f32_dpp %7, %7, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
+        : "v"(ln.s1), "v"(ln.s2), "v"(ln.s7), "v"(ln.s8));
+}
+
+// The in-lane part for eight bf16 values times eight factors: the products ride in the first stage's multiply-adds (one
+// rounding for a pair of products instead of two).
+__device__ __forceinline__ void scaled_h8(const uint4 &x, const float4 &d0, const float4 &d1, float (&v)[8])
+{
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+    const float d[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float a = bf16_lo(w[j]), b = bf16_hi(w[j]) * d[2 * j + 1];
+        v[2 * j] = __builtin_fmaf(a, d[2 * j], b);
+        v[2 * j + 1] = __builtin_fmaf(a, d[2 * j], -b);
+    }
+#pragma unroll
+    for (int h = 2; h < 8; h <<= 1)
+#pragma unroll
+        for (int i = 0; i < 8; i += 2 * h)
+#pragma unroll
+            for (int j = i; j < i + h; ++j) {
+                const float a = v[j], b = v[j + h];
+                v[j] = a + b;
+                v[j + h] = a - b;
+            }
+}
+
+}  // namespace trdq

@@ -21,6 +21,7 @@
 // Both rotations are unnormalised; the factor 1/128 goes into the scale.  Entries of perm are clamped to [0, K) on the
 // way in, so a bad table gives wrong numbers, never an access outside the row.
 #include "device_utils.h"
+#include "rotate_lanes.h"
 #include "trdq_internal.h"
 
 namespace trdq {
@@ -28,92 +29,6 @@ namespace trdq {
 namespace {
 
 constexpr int kRowPad = 4;     // floats of padding per LDS row
-
-// Walsh-Hadamard transform of 128 values held by 16 lanes, 8 to a lane.  The lanes are paired by the exchanges that cost
-// one operand each: lane ^ 1, ^ 2, ^ 7 (half-row mirror) and ^ 8.  In the basis {1, 2, 7, 8} lane p has the
-// coordinates (b0 ^ b2, b1 ^ b2, b2, b3) of its bits; chunk(p) is the 8-channel chunk with these index bits.  A stage
-// is own + s * other with s = -1 in the lane whose coordinate is 1: that lane gets other - own negated, so that
-// after all four stages lane p holds (-1)^(sum of its coordinates) times its coefficient.  Flipping all index bits of the
-// input has the same effect on the transform, so the input is taken with chunk 15 - chunk(p) in lane p and the signs
-// cancel: coefficients of chunk(p) come out.
-struct Lane16 {
-    float s1, s2, s7, s8;
-    int chunk;
-    __device__ __forceinline__ explicit Lane16(int p)
-    {
-        const int c1 = (p ^ (p >> 2)) & 1, c2 = ((p >> 1) ^ (p >> 2)) & 1, c7 = (p >> 2) & 1, c8 = p >> 3;
-        chunk = c1 | c2 << 1 | c7 << 2 | c8 << 3;
-        s1 = c1 ? -1.0f : 1.0f;
-        s2 = c2 ? -1.0f : 1.0f;
-        s7 = c7 ? -1.0f : 1.0f;
-        s8 = c8 ? -1.0f : 1.0f;
-    }
-};
-
-__device__ __forceinline__ void cross16(float (&v)[8], const Lane16 &ln)
-{
-    // v += s * (v of the paired lane), four stages.  A lane-crossing read needs two wait states after the write of its
-    // register: the s_nop for what came before, the eight values in turn within the block.  (The compiler makes a move, its
-    // own wait states and a multiply-add of each.)
-    asm("s_nop 1\n\t"
-        "v_fmac_f32_dpp %0, %0, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %1, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %2, %2, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %3, %3, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %4, %4, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %5, %5, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %6, %6, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %7, %7, %8 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %0, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %1, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %2, %2, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %3, %3, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %4, %4, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %5, %5, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %6, %6, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %7, %7, %9 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %0, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %1, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %2, %2, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %3, %3, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %4, %4, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %5, %5, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %6, %6, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %7, %7, %10 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %0, %0, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %1, %1, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %2, %2, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %3, %3, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %4, %4, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %5, %5, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %6, %6, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f32_dpp %7, %7, %11 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
-        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
-        : "v"(ln.s1), "v"(ln.s2), "v"(ln.s7), "v"(ln.s8));
-}
-
-// sum and difference of a bf16 pair times its two factors
-__device__ __forceinline__ void scaled_pair(uint32_t x, float d0, float d1, float &sum, float &diff)
-{
-    const float b = bf16_hi(x) * d1;
-    sum = __builtin_fmaf(bf16_lo(x), d0, b);
-    diff = __builtin_fmaf(bf16_lo(x), d0, -b);
-}
-
-// the second and third of the transform's three in-lane stages
-__device__ __forceinline__ void stages_2_4(float (&v)[8])
-{
-#pragma unroll
-    for (int h = 2; h < 8; h <<= 1)
-#pragma unroll
-        for (int i = 0; i < 8; i += 2 * h)
-#pragma unroll
-            for (int j = i; j < i + h; ++j) {
-                const float a = v[j], b = v[j + h];
-                v[j] = a + b;
-                v[j + h] = a - b;
-            }
-}
 
 // QUADS: groups of four tokens per workgroup; SPW: most blocks per wave; ASYM: zero points (codes stored as q - 128,
 // zc[i] = 128 - z_i), as in rotate_quant.
@@ -167,13 +82,8 @@ __global__ __launch_bounds__(768, 6) void rotate_quant_rpr_kernel(
 #pragma unroll
             for (int q = 0; q < QUADS; ++q) {
                 const uint4 x = raw[i][q];
-                // the diagonal rides in the first stage of the transform
                 float v[8];
-                scaled_pair(x.x, d0.x, d0.y, v[0], v[1]);
-                scaled_pair(x.y, d0.z, d0.w, v[2], v[3]);
-                scaled_pair(x.z, d1.x, d1.y, v[4], v[5]);
-                scaled_pair(x.w, d1.z, d1.w, v[6], v[7]);
-                stages_2_4(v);
+                scaled_h8(x, d0, d1, v);
                 cross16(v, ln);
                 float *dst = T + (size_t)(q * 4 + t4) * rowf + b * kBlock + c_out;
                 *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
@@ -327,6 +237,13 @@ hipError_t launch_rotate_quant_rpr(const uint16_t *X, int64_t M, int K, int64_t 
     if (M == 0) return hipSuccess;
     if (!rotate_quant_rpr_supports(K)) return hipErrorInvalidValue;
     const int nb = K / kBlock;
+    constexpr int64_t most = (int64_t)1 << 24;       // tokens per launch: a grid holds fewer than 2^32 threads
+    if (M > most) {
+        hipError_t e = launch_rotate_quant_rpr(X, most, K, ldx, diag, perm, Xq, sx, warm, warm_bytes, st, zc);
+        if (e != hipSuccess) return e;
+        return launch_rotate_quant_rpr(X + most * ldx, M - most, K, ldx, diag, perm, Xq + most * K, sx + most, nullptr, 0, st,
+                                       zc ? zc + most : nullptr);
+    }
     // Eight tokens per workgroup while a wave has one block: the indices and the diagonal serve two quads (us at 4096 /
     // 32768 tokens, eight against four: 1152 channels 6.7 / 34.6, 6.8 / 39.2; 1536 7.7 / 45.5, 8.4 / 49.6).  Four beyond, where
     // eight leave room for one or two workgroups per compute unit (2304 10.9 / 61.1, 10.2 / 58.8; 4608 20.8 / 141, 17.8 / 122).

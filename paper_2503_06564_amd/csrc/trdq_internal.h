@@ -72,9 +72,6 @@ bool qgemm_reads_tiled_codes(const Weights &w, int64_t M, bool asym = false);
 bool qgemm_tiled_pays(int64_t M, int K, int N);
 bool qgemm4_tiled_pays(int64_t M, int K, int N);   // int4 weights
 hipError_t launch_xq_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st);
-hipError_t launch_rotate_quant_wide(const uint16_t *X, int64_t M, int K, int64_t ldx, const float *diag,
-                                    int8_t *Xq, float *sx, hipStream_t st);
-
 // Full transform of Eq. 9 (rotation, permutation, rotation) and per-token quantisation.
 bool rotate_quant_rpr_supports(int K);
 hipError_t launch_rotate_quant_rpr(const uint16_t *X, int64_t M, int K, int64_t ldx, const float *diag,

@@ -1,0 +1,61 @@
+"""The rotate + quantise pass at the edges of its work split, in each of its forms (rows, block-tiled, other widths, zero
+points), against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_06564_amd import trdq, workloads as wl
+from gpu_util import CODE_FRAC, assert_scales_close, bf16_to_dev, dev, f32_to_dev
+
+pytestmark = pytest.mark.gpu
+
+# one block (workgroups of eight tokens) and more (of four), token counts on both sides; three blocks per wave with a last
+# wave of one and two; nine blocks per wave: beyond 36 blocks, and from 8192 tokens beyond 24
+SHAPES = [(1, 128), (7, 128), (9, 128), (17, 512), (5, 640), (3, 1152), (16, 4608), (4, 4736), (6, 6144), (3, 8192), (8195, 3200)]
+
+
+def _close(got, want):
+    # a float32 value lies up to 3e-5 of a step off: half a code in 10^4 may sit close enough to a rounding tie, and a small
+    # array may hold one or two of them
+    diff = np.abs(got.astype(np.int16) - np.asarray(want, dtype=np.int16))
+    assert diff.max() <= 1 and np.count_nonzero(diff) <= max(2, CODE_FRAC * diff.size)
+
+
+@pytest.mark.parametrize("M,K", SHAPES)
+def test_forms_match_oracle(oracle, M, K):
+    Xb, _, d, _ = wl.small_case(61, M, K, 16, n_outliers=max(1, K // 144), outlier=40.0)
+    X, dd = bf16_to_dev(Xb), f32_to_dev(d)
+    buf = torch.full((M + 1, K), 99, dtype=torch.int8, device=dev())
+    sx = torch.full((M + 1,), -1.0, device=dev())
+    trdq.rotate_quant(X, dd, buf[:M], sx[:M])
+    torch.cuda.synchronize()
+    want, want_s = oracle.rotate_quant(Xb, d)
+    rows = buf[:M].cpu().numpy()
+    _close(rows, want)
+    assert_scales_close(sx[:M].cpu().numpy(), want_s, "s_x")
+    assert (buf[M] == 99).all() and sx[M].item() == -1.0
+    if K > 4608:
+        return
+    Xt = torch.zeros(trdq.xq_tiled_nbytes(M, K), dtype=torch.int8, device=dev())
+    back, st = torch.empty_like(buf[:M]), torch.empty(M, device=dev())
+    trdq.rotate_quant_tiled(X, dd, Xt, st)
+    trdq.xq_untile(Xt, M, K, back)
+    torch.cuda.synchronize()
+    assert np.array_equal(back.cpu().numpy(), rows) and torch.equal(st, sx[:M])
+    trdq.rotate_quant_bits(X, dd, back, st, 6)
+    torch.cuda.synchronize()
+    want6, want_s6 = oracle.rotate_quant(Xb, d, 128, abits=6)
+    _close(back.cpu().numpy(), want6)
+    assert_scales_close(st.cpu().numpy(), want_s6, "s_x (6 bits)")
+    if M > 100:
+        return
+    zc = torch.empty(M, dtype=torch.int32, device=dev())
+    trdq.rotate_quant_asym(X, dd, back, st, zc)
+    torch.cuda.synchronize()
+    V = oracle.rotate(Xb, d, 128)
+    lo, hi = np.minimum(V.min(axis=1), 0), np.maximum(V.max(axis=1), 0)
+    s = (hi - lo) / 255
+    z = -np.rint(lo / s)
+    assert np.array_equal(128 - zc.cpu().numpy(), z)
+    _close(back.cpu().numpy().astype(np.int16) + 128, np.clip(np.rint(V / s[:, None]) + z[:, None], 0, 255))
+    assert_scales_close(st.cpu().numpy(), s, "s_x (zero points)")
