@@ -507,7 +507,7 @@ trdq_status rotate_quant_dense_rpr_impl(const void *X_dev, int64_t M, int64_t ld
                                                                  static_cast<float *>(ws_dev),
                                                                  static_cast<hipStream_t>(stream)));
     return hip_status(trdq::launch_rotate_quant_dense_rpr(static_cast<const uint16_t *>(X_dev), M, rot1->K, ldx,
-                                                          rot1->pieces, perm_dev, rot2->frags32, Xq_dev, sx_dev,
+                                                          rot1->pieces, perm_dev, rot2->frags32, rot2->pieces, Xq_dev, sx_dev,
                                                           static_cast<hipStream_t>(stream)));
 }
 

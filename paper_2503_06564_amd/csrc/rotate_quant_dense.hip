@@ -551,7 +551,7 @@ hipError_t launch_dense_blocks(const uint16_t *X, int64_t M, int nb, int64_t ldx
 // ---- Eq. 10 in full with dense blocks: (X . Delta) . BlockDiag(R1) . P . BlockDiag(R2) -----------
 // frags32[((b * 8 + t) * 8 + s4) * 64 + lane] = four floats: R_b[4 s + g][c(t, r)] for the k-steps
 // s = 4 s4 .. 4 s4 + 3 of v_mfma_f32_16x16x4_f32 (lane = 16 g + r, c(t, r) as for the bf16 pieces):
-// the A operand of the SECOND rotation, whose B operand is fp32 (first-rotation results).
+// the A operand of the SECOND rotation in the form for wide rows without a workspace, whose B operand is fp32.
 __global__ __launch_bounds__(256) void rotation_frags32_kernel(const float *__restrict__ R, float *__restrict__ frags)
 {
     const int b = blockIdx.y;
@@ -564,12 +564,16 @@ __global__ __launch_bounds__(256) void rotation_frags32_kernel(const float *__re
 }
 
 // One workgroup (a wave per block, at most 12) per group of 16 tokens.  Stage 1 is the dense
-// first rotation (bf16 pieces, as above) into an fp32 row buffer T in LDS; stage 2 gathers
-// T[perm[.]] as the B operand of fp32 matrix instructions against the second rotation's
-// fragments; then the token maximum, the codes and the stores as in the one-rotation kernel.
+// first rotation (bf16 pieces, as above) into an fp32 row buffer T in LDS; stage 2 gathers T[perm[.]], splits it exactly
+// into three bf16 pieces and takes the six piece pairs down to 2^-24 against the second rotation's pieces; then
+// the token maximum, the codes and the stores as in the one-rotation kernel.  Both stages are bound by their fragments,
+// 96 KB per block and 16 tokens from L2; with the second one's product on the fp32 matrix instruction (64 KB of float
+// fragments, but 8192 cycles of it per block against 3072) the matrix pipe was: 4096 tokens x 1152 31.4 -> 24.5 us,
+// x 1536 37.9 -> 30.7, and codes off float64's 6.9e-6 -> 3.4e-6 of them (sums of 32 products at a time, in two chains,
+// instead of a chain of 128).
 __global__ __launch_bounds__(768) void rotate_quant_dense_rpr_kernel(
     const uint16_t *__restrict__ X, int64_t M, int nb, int64_t ldx, const uint4 *__restrict__ pieces1,
-    const int32_t *__restrict__ perm, const float4 *__restrict__ frags2, int8_t *__restrict__ Xq, float *__restrict__ sx)
+    const int32_t *__restrict__ perm, const uint4 *__restrict__ pieces2, int8_t *__restrict__ Xq, float *__restrict__ sx)
 {
     extern __shared__ __align__(16) float lds_f[];
     const int K = nb * kBlock;
@@ -601,37 +605,49 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_rpr_kernel(
             *reinterpret_cast<float4 *>(T + l16 * LDT + b * kBlock + 32 * g + 4 * t) =
                 make_float4(out[0][t][0], out[0][t][1], out[0][t][2], out[0][t][3]);
         __syncthreads();
-        float bv[32];
+        // the second rotation's operands: element e of k-step s is input channel 32 s + 8 g + e of the block
+        v8bf xh[4], xm[4], xl[4];
 #pragma unroll
-        for (int s = 0; s < 32; ++s) bv[s] = T[l16 * LDT + srcs[b * kBlock + 4 * s + g]];      // k-step s: k = 4 s + g
+        for (int s = 0; s < 4; ++s) {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = T[l16 * LDT + srcs[b * kBlock + 32 * s + 8 * g + e]];
+            split3_bf16(v, xh[s], xm[s], xl[s]);
+        }
         float amax = 0.0f;
         int lane_off = lane;                 // as in rotate_block_dense: keep the loads inside the group loop
         asm volatile("" : "+v"(lane_off));
-        const float4 *fb = frags2 + (size_t)b * (kBlock * kBlock / 4) + lane_off;
-        float4 fa2[2][8];
-        auto request2 = [&](float4 (&f)[8], int t) {
+        const uint4 *fb = pieces2 + (size_t)b * kPiecesPerBlock + lane_off;
+        // the fragments as in rotate_block_dense: chunks of six (half a tile), smallest piece first, one chunk ahead
+        constexpr int CH = 6;
+        uint4 fa2[2][CH];
+        auto request2 = [&](uint4 (&f)[CH], int i) {
 #pragma unroll
-            for (int s4 = 0; s4 < 8; ++s4) f[s4] = fb[(t * 8 + s4) * 64];
+            for (int e = 0; e < CH; ++e) f[e] = fb[((11 - CH * (i & 1) - e) * 8 + (i >> 1)) * 64];
         };
         request2(fa2[0], 0);
-        __builtin_amdgcn_sched_barrier(0);
+        v4f acc[2];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            if (t + 1 < 8) request2(fa2[(t + 1) & 1], t + 1);
+        for (int i = 0; i < 16; ++i) {
+            if (i + 1 < 16) request2(fa2[(i + 1) & 1], i + 1);
             __builtin_amdgcn_sched_barrier(0);
-            v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+            if ((i & 1) == 0) acc[0] = acc[1] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s4 = 0; s4 < 8; ++s4) {
-                const float4 a4 = fa2[t & 1][s4];
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.x, bv[4 * s4 + 0], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.y, bv[4 * s4 + 1], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.z, bv[4 * s4 + 2], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.w, bv[4 * s4 + 3], acc, 0, 0, 0);
+            for (int e = 0; e < CH; ++e) {
+                const int q = 11 - CH * (i & 1) - e, piece = q >> 2, s = q & 3;
+                union { uint4 u; v8bf v; } f;
+                f.u = fa2[i & 1][e];
+                // the piece pairs down to 2^-24 of |r||t|, two chains of sums
+                if (piece == 0) acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, xl[s], acc[s & 1], 0, 0, 0);
+                if (piece <= 1) acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, xm[s], acc[s & 1], 0, 0, 0);
+                acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, xh[s], acc[s & 1], 0, 0, 0);
             }
+            if (i & 1) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                out[0][t][j] = acc[j];
-                amax = fmaxf(amax, fabsf(acc[j]));
+                for (int j = 0; j < 4; ++j) {
+                    out[0][i >> 1][j] = acc[0][j] + acc[1][j];
+                    amax = fmaxf(amax, fabsf(out[0][i >> 1][j]));
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -892,7 +908,8 @@ hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K,
 }
 
 hipError_t launch_rotate_quant_dense_rpr(const uint16_t *X, int64_t M, int K, int64_t ldx, const void *pieces1,
-                                         const int32_t *perm, const void *frags2, int8_t *Xq, float *sx, hipStream_t st)
+                                         const int32_t *perm, const void *frags2, const void *pieces2, int8_t *Xq, float *sx,
+                                         hipStream_t st)
 {
     if (M == 0) return hipSuccess;
     const int nb = K / kBlock;
@@ -915,7 +932,7 @@ hipError_t launch_rotate_quant_dense_rpr(const uint16_t *X, int64_t M, int K, in
         e != hipSuccess)
         return e;
     hipLaunchKernelGGL(rotate_quant_dense_rpr_kernel, dim3((unsigned)grid), dim3(64 * nb), smem, st, X, M, nb, ldx,
-                       static_cast<const uint4 *>(pieces1), perm, static_cast<const float4 *>(frags2), Xq, sx);
+                       static_cast<const uint4 *>(pieces1), perm, static_cast<const uint4 *>(pieces2), Xq, sx);
     return hipGetLastError();
 }
 

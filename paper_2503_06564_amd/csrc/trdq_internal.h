@@ -44,7 +44,7 @@ struct Rotation {
     float *R = nullptr;          // [K/128][128][128]
     float *diag = nullptr;       // [K] or null (ones)
     void *pieces = nullptr;      // diag . R_b as bf16 pieces (operand of a first or only rotation)
-    void *frags32 = nullptr;     // R_b as float fragments (operand of a second rotation)
+    void *frags32 = nullptr;     // R_b as float fragments (second rotation of wide rows without a workspace)
     int device = 0;
 };
 
@@ -141,7 +141,8 @@ size_t rotation_frags32_bytes(int K);
 hipError_t launch_rotation_frags32(const float *R, int K, void *frags, hipStream_t st);
 bool rotate_quant_dense_rpr_supports(int K);
 hipError_t launch_rotate_quant_dense_rpr(const uint16_t *X, int64_t M, int K, int64_t ldx, const void *pieces1,
-                                         const int32_t *perm, const void *frags2, int8_t *Xq, float *sx, hipStream_t st);
+                                         const int32_t *perm, const void *frags2, const void *pieces2, int8_t *Xq, float *sx,
+                                         hipStream_t st);
 // wide rows (more than 12 blocks) through a workspace of once-rotated values; pieces2: the second rotation's bf16 pieces
 size_t rotate_quant_dense_rpr_workspace_bytes(int64_t M, int K);
 hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K, int64_t ldx, const void *pieces1,
