@@ -969,18 +969,21 @@ bool tiled_rows_supports(const GemmArgs &a)
 //   - Remainder of tokens: up to where the second launch is a small part: 1100 tiles of 256 x 256 (1152 -> 4608 at 12000
 //     tokens, 846 tiles: 82.1 -> 74.9, at 16000, 1134 tiles: 95.3 -> 98.3), and with a width of which the last tile
 //     repeats a part 14000 tokens (1024 -> 2048 at 12000 34.6 -> 33.5, at 16000 39.7 -> 42.7).
-//   - Whole tiles: at most one per compute unit, where K is split inside the workgroup (768 -> 2304 at 1024 tokens
-//     7.9 -> 6.8, 4608 -> 1152 at 1024 19.6 -> 17.8); for long K half of that (4096 tokens: 24.4 -> 25.0).
+//   - Whole tiles: up to three quarters of the compute units have one (1152 -> 3456 at 1024 tokens 9.9 -> 9.5, 768 -> 2304 at
+//     1024 7.9 -> 6.8; 1152 -> 1152 at 4096, one each, 11.3 -> 11.6 with cold weights), for K < 1024 all of them, for long K
+//     half (4608 -> 1152 at 1024 19.6 -> 17.8, at 4096 24.4 -> 25.0).  With zero points K < 1024 only (768 -> 2304 at 1024
+//     8.0 -> 7.5, 1152 -> 3456 9.9 -> 10.6).
 //   - Zero points: the only other kernel that takes them at any shape is the any-shape one (768 -> 3072 at 4096 tokens
-//     23.2 -> 16.2, 1152 -> 4608 at 32700 tokens 268 -> 190).
+//     23.2 -> 19.1, 1152 -> 4608 at 32700 tokens 268 -> 215).
 bool tiled_rows_pays(int64_t M, int K, int N, bool asym)
 {
     if (M < 128 || N < kBN) return false;
     const bool whole_n = N % kBN == 0;
     if (M % 128 == 0 && whole_n) {
         if (asym && K < 512) return true;
-        const int64_t tiles = (M / 128) * (int64_t)(N / kBN);
-        return tiles <= num_cus() / (K >= 2304 ? 2 : 1);
+        if (asym && K >= 1024) return false;
+        const int64_t tiles = (M / 128) * (int64_t)(N / kBN), cus = num_cus();
+        return tiles <= (K < 1024 ? cus : K < 2304 ? cus * 3 / 4 : cus / 2);
     }
     if (asym) return true;
     if (M % 128 == 0) return false;
