@@ -13,7 +13,7 @@ namespace trdq {
 // exchanges, which need the whole wave).
 // RANGE: track the signed extremes instead (amax = max(0, max v), amin = min(0, min v)), which is
 // what the asymmetric quantiser of Eq. 1-3 needs.
-template <int T, int S, bool RANGE = false>
+template <int T, int S, bool RANGE>
 __device__ __forceinline__ void rotate_token(const uint16_t *__restrict__ xtok, bool token_ok, int nb,
                                              int s, int p, const float *__restrict__ diag,
                                              const LaneSigns &sg, float (&v)[T][8], float &amax, float &amin)
@@ -60,15 +60,6 @@ __device__ __forceinline__ void rotate_token(const uint16_t *__restrict__ xtok, 
         if constexpr (S >= 2) amin = fminf(amin, __shfl_xor(amin, 16));
         if constexpr (S >= 4) amin = fminf(amin, __shfl_xor(amin, 32));
     }
-}
-
-template <int T, int S>
-__device__ __forceinline__ void rotate_token(const uint16_t *__restrict__ xtok, bool token_ok, int nb,
-                                             int s, int p, const float *__restrict__ diag,
-                                             const LaneSigns &sg, float (&v)[T][8], float &amax)
-{
-    float unused;
-    rotate_token<T, S, false>(xtok, token_ok, nb, s, p, diag, sg, v, amax, unused);
 }
 
 // v holds sqrt(128) * V.  s_x = max|V| / 127; codes = rint(V / s_x) = rint(v * 127 / max|v|).
