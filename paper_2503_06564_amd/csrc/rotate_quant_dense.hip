@@ -565,12 +565,16 @@ __global__ __launch_bounds__(256) void rotation_frags32_kernel(const float *__re
 
 // One workgroup (a wave per block, at most 12) per group of 16 tokens.  Stage 1 is the dense
 // first rotation (bf16 pieces, as above) into an fp32 row buffer T in LDS; stage 2 gathers T[perm[.]], splits it exactly
-// into three bf16 pieces and takes the six piece pairs down to 2^-24 against the second rotation's pieces; then
-// the token maximum, the codes and the stores as in the one-rotation kernel.  Both stages are bound by their fragments,
-// 96 KB per block and 16 tokens from L2; with the second one's product on the fp32 matrix instruction (64 KB of float
-// fragments, but 8192 cycles of it per block against 3072) the matrix pipe was: 4096 tokens x 1152 31.4 -> 24.5 us,
-// x 1536 37.9 -> 30.7, and codes off float64's 6.9e-6 -> 3.4e-6 of them (sums of 32 products at a time, in two chains,
-// instead of a chain of 128).
+// into three bf16 pieces and takes all nine piece products with the second rotation's pieces; then
+// the token maximum, the codes and the stores as in the one-rotation kernel.
+// Both stages wait for their fragments, 96 KB per block and 16 tokens from L2, and for the matrix pipe (1536 and 4608
+// cycles per block; with the second product on the fp32 matrix instruction, 64 KB of float fragments, 8192 cycles):
+// 4096 tokens x 1152 31.6 -> 26.8 us, x 1536 38.2 -> 33.4.
+// Why nine products: the six down to 2^-24 of |r||t| take 25.6 and 32.2 us, but the split truncates, so what they leave out has the
+// sign of the result: row maxima came out 3e-8 ... 8e-8 too small on average, and for blocks of few entries further off
+// than the fp32 instruction's.  Error of the row maximum against float64 (root mean square, 6144 tokens x 1152, first
+// rotation the identity), fp32 instruction / six products / nine: full blocks 2.0e-7 / 1.0e-7 / 8.0e-8, blocks of 2 x 2
+// rotations 5.2e-8 / 6.7e-8 / 5.1e-8, of 4 x 4 6.0e-8 / 8.1e-8 / 5.5e-8; codes off with full blocks 6.1e-6 / 3.5e-6 / 2.7e-6.
 __global__ __launch_bounds__(768) void rotate_quant_dense_rpr_kernel(
     const uint16_t *__restrict__ X, int64_t M, int nb, int64_t ldx, const uint4 *__restrict__ pieces1,
     const int32_t *__restrict__ perm, const uint4 *__restrict__ pieces2, int8_t *__restrict__ Xq, float *__restrict__ sx)
@@ -626,26 +630,30 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_rpr_kernel(
             for (int e = 0; e < CH; ++e) f[e] = fb[((11 - CH * (i & 1) - e) * 8 + (i >> 1)) * 64];
         };
         request2(fa2[0], 0);
-        v4f acc[2];
+        v4f acc[4];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             if (i + 1 < 16) request2(fa2[(i + 1) & 1], i + 1);
             __builtin_amdgcn_sched_barrier(0);
-            if ((i & 1) == 0) acc[0] = acc[1] = v4f{0.f, 0.f, 0.f, 0.f};
+            if ((i & 1) == 0) acc[0] = acc[1] = acc[2] = acc[3] = v4f{0.f, 0.f, 0.f, 0.f};
+            // Every piece product, in four chains by k-step: those of the high pieces, which have 16 bits and whose sums are
+            // nearly exact, and the others, smallest first, 2^-8 their size.
+            auto multiply = [&](const v8bf (&x)[4], bool high) {
 #pragma unroll
-            for (int e = 0; e < CH; ++e) {
-                const int q = 11 - CH * (i & 1) - e, piece = q >> 2, s = q & 3;
-                union { uint4 u; v8bf v; } f;
-                f.u = fa2[i & 1][e];
-                // the piece pairs down to 2^-24 of |r||t|, two chains of sums
-                if (piece == 0) acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, xl[s], acc[s & 1], 0, 0, 0);
-                if (piece <= 1) acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, xm[s], acc[s & 1], 0, 0, 0);
-                acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, xh[s], acc[s & 1], 0, 0, 0);
-            }
+                for (int e = 0; e < CH; ++e) {
+                    const int q = 11 - CH * (i & 1) - e, s = q & 3, c = (high && q < 4 ? 2 : 0) + (s & 1);
+                    union { uint4 u; v8bf v; } f;
+                    f.u = fa2[i & 1][e];
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, x[s], acc[c], 0, 0, 0);
+                }
+            };
+            multiply(xl, false);
+            multiply(xm, false);
+            multiply(xh, true);
             if (i & 1) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    out[0][i >> 1][j] = acc[0][j] + acc[1][j];
+                    out[0][i >> 1][j] = (acc[2][j] + acc[3][j]) + (acc[0][j] + acc[1][j]);
                     amax = fmaxf(amax, fabsf(out[0][i >> 1][j]));
                 }
             }

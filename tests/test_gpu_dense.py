@@ -346,3 +346,41 @@ def test_time_rotation_calibration_chain(oracle, Mc, K, steps):
     err_plain = np.abs(oracle.linear_dense(Xb, W, d, eye, bias)["Yd"] - exact).mean()
     assert err < 0.5 * err_plain, (err, err_plain)
     w.close(); rot1.close(); rot2.close()
+
+
+@pytest.mark.parametrize("K", [128, 1152, 1536])
+def test_second_rotation_keeps_float32_precision_for_sparse_blocks(K):
+    """Rows up to 12 blocks, first rotation the identity, second of 2 x 2 rotations whose float32 entries have all their
+    low bits set: nothing may be left out of a product, and nothing may lean to one side.
+
+    A row maximum passes five roundings to nearest (the scaled activation, the sums of the high and of the low piece
+    products, their sum, the division by 127), each within 2^-24 of the result, so |relative error| <= 5 * 2^-24 = c.
+    Being unbiased, their mean over M tokens stays within c * sqrt(2 ln(2e9) / M) except once in 10^9 (Hoeffding)."""
+    M, nb = 2043, K // 128
+    g = torch.Generator().manual_seed(K)
+    R2 = torch.zeros(nb, 128, 128)
+    for b in range(nb):
+        rows, cols = torch.randperm(128, generator=g).view(-1, 2), torch.randperm(128, generator=g).view(-1, 2)
+        phi = 0.3 + 0.9 * torch.rand(64, generator=g)
+        c, s = phi.cos(), phi.sin()
+        R2[b, rows[:, 0], cols[:, 0]], R2[b, rows[:, 1], cols[:, 1]] = c, c
+        R2[b, rows[:, 0], cols[:, 1]], R2[b, rows[:, 1], cols[:, 0]] = s, -s
+    bits = R2.view(torch.int32)
+    R2 = torch.where(R2 != 0, bits | 0xFFFF, bits).view(torch.float32)
+    d = torch.exp(0.3 * torch.randn(K, generator=g))
+    X = torch.randn(M, K, generator=g).bfloat16()
+    perm = torch.randperm(K, generator=g)
+    rot1 = trdq.Rotation(torch.eye(128).expand(nb, 128, 128).contiguous().to(dev()), d.to(dev()))
+    rot2 = trdq.Rotation(R2.to(dev()))
+    Xq = torch.empty((M, K), dtype=torch.int8, device=dev())
+    sx = torch.empty(M, device=dev())
+    trdq.rotate_quant_dense_rpr(X.to(dev()), rot1, perm.int().to(dev()), rot2, Xq, sx)
+    torch.cuda.synchronize()
+    T = (X.double() * d.double())[:, perm].view(M, nb, 128)
+    V = torch.stack([T[:, b] @ R2[b].double() for b in range(nb)], dim=1).view(M, K)
+    want = V.abs().amax(dim=1) / 127.0
+    err = ((sx.cpu().double() - want) / want).numpy()
+    bound = 5 * 2.0 ** -24
+    assert np.abs(err).max() <= bound
+    assert abs(err.mean()) <= bound * np.sqrt(2 * np.log(2e9) / M)
+    rot1.close(); rot2.close()
