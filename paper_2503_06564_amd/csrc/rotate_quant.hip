@@ -222,17 +222,35 @@ hipError_t launch_rotate_quant(const uint16_t *X, int64_t M, int K, int64_t ldx,
         return launch_rotate_quant(X + kRQMostTokens * ldx, M - kRQMostTokens, K, ldx, diag, Xq + kRQMostTokens * K,
                                    sx + kRQMostTokens, zc ? zc + kRQMostTokens : nullptr, nullptr, 0, st, abits, tiled);
     }
+    auto go = [&](auto kern) { return kern(X, M, nb, ldx, diag, Xq, sx, zc, warm, warm_bytes, st, abits, tiled); };
     // Three blocks per wave (us at 4096 / 32768 tokens x 1152 with two 4.6 / 21.8, three 4.6 / 20.7, six 5.0 / 20.1); one block and
     // a wave per workgroup would leave a quad too little (128 channels at 32768 tokens: four tokens 5.0, eight 4.5); nine where
     // twelve waves leave two workgroups per compute unit and there are tokens for several rounds (4608 at 16384 / 32768
     // tokens: three 38.6 / 88.2, nine 36.4 / 79.8, at 4096 12.5 / 12.6), and beyond twelve waves of three.
-    if (nb == 1) return launch_spw<2, 1>(X, M, nb, ldx, diag, Xq, sx, zc, warm, warm_bytes, st, abits, tiled);
+    if (nb == 1) return go(launch_spw<2, 1>);
+    // Four and six blocks with tokens for many rounds: a wave per quad, nobody to wait for (three per wave, a wave per quad: 512 at
+    // 24576 / 32768 tokens 9.2 / 11.2, 8.5 / 10.1; 768 12.0 / 15.1, 11.1 / 13.9; 16384 tokens 8.5, 8.6; five blocks level).
+    if (M >= 24576 && nb == 4) return go(launch_spw<1, 4>);
+    if (M >= 24576 && nb == 6) return go(launch_spw<1, 6>);
     // Block-tiled codes of wide rows: eight tokens, so that a piece's stores are 128 consecutive bytes (4608 at 32768 tokens: four
-    // 92, eight 84; 3072 61 / 53; up to 2304 channels no difference).
-    if (tiled && nb > 18 && M >= 8192) return launch_spw<2, 3>(X, M, nb, ldx, diag, Xq, sx, zc, warm, warm_bytes, st, abits, tiled);
-    if (nb > kRQMaxBlocks || (nb > 24 && M >= 8192))
-        return launch_spw<1, 9>(X, M, nb, ldx, diag, Xq, sx, zc, warm, warm_bytes, st, abits, tiled);
-    return launch_spw<1, 3>(X, M, nb, ldx, diag, Xq, sx, zc, warm, warm_bytes, st, abits, tiled);
+    // 92, eight 84; 3072 61 / 53; up to 2304 channels no difference), and as many blocks per wave as leave four or eight
+    // waves (three per wave make nine to eleven, of which a compute unit holds one workgroup and the last wave little
+    // work).  us, three per wave against this, inputs in the memory-side cache / behind it:
+    //   five:  2560 at 8192 tokens 14.2 / 16.8, 13.3 / 16.1, at 20480 29.7 / 34.3, 28.4 / 31.5
+    //   seven: 3328 at 8192 19.6 / 22.1, 16.6 / 20.3, 3584 at 6144 15.7 / 19.4, 14.3 / 16.6, at 16384 35.0 / 40.0, 30.8 / 36.1
+    //   four:  3840 at 8192 22.2 / 25.0, 19.1 / 22.4, 4096 at 16384 37.5 / 40.6, 34.8 / 39.1
+    // With fewer tokens four per wave and four tokens (three, four: 3584 at 4096 11.0 / 14.3, 9.9 / 11.9; 4096 at 6144 17.1 /
+    // 20.5, 14.5 / 18.4; at 2048 level).  Three per wave stay ahead at 22 ... 24 blocks (3072 at 8192: three 14.7 / 17.8, six
+    // 15.2 / 17.6) and from 33 on, where twelve waves are even (eight tokens from 4096: 4480 there 12.4 / 16.1, 12.2 / 14.5).
+    if (tiled && nb > 18) {
+        if (nb <= 20 && M >= 8192) return go(launch_spw<2, 5>);
+        if ((nb == 21 && M >= 8192) || (nb >= 25 && nb <= 28 && M >= 6144)) return go(launch_spw<2, 7>);
+        if (nb >= 28 && nb <= 32 && M >= 3072) return M >= 8192 ? go(launch_spw<2, 4>) : go(launch_spw<1, 4>);
+        if ((nb <= 24 && M >= 8192) || (nb > 32 && M >= 4096)) return go(launch_spw<2, 3>);
+        return go(launch_spw<1, 3>);
+    }
+    if (nb > kRQMaxBlocks || (nb > 24 && M >= 8192)) return go(launch_spw<1, 9>);
+    return go(launch_spw<1, 3>);
 }
 
 }  // namespace trdq

@@ -59,3 +59,36 @@ def test_forms_match_oracle(oracle, M, K):
     assert np.array_equal(128 - zc.cpu().numpy(), z)
     _close(back.cpu().numpy().astype(np.int16) + 128, np.clip(np.rint(V / s[:, None]) + z[:, None], 0, 255))
     assert_scales_close(st.cpu().numpy(), s, "s_x (zero points)")
+
+
+# from each launch shape's smallest token count on: a wave per quad (4 and 6 blocks); block-tiled: five blocks per wave, seven,
+# four (eight and four tokens per workgroup), three; the last workgroup incomplete, blocks that do not fill the last wave
+@pytest.mark.parametrize("M,K", [(24577, 512), (24583, 768), (8193, 2432), (8198, 2560), (8193, 2688), (6145, 3200), (6150, 3584),
+                                 (3077, 3584), (3073, 3712), (8197, 3712), (8192, 4096), (4097, 4224), (3075, 4608)])
+def test_many_tokens_like_few(M, K):
+    """A token's codes do not depend on how many there are: bit for bit those of calls on 512 tokens."""
+    g = torch.Generator(device="cuda").manual_seed(K)
+    X = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    d = torch.exp(0.3 * torch.randn(K, generator=g, device="cuda"))
+    want = torch.empty((M, K), dtype=torch.int8, device="cuda")
+    want_s = torch.empty(M, device="cuda")
+    for m in range(0, M, 512):
+        trdq.rotate_quant(X[m:m + 512], d, want[m:m + 512], want_s[m:m + 512])
+    buf = torch.full((M + 1, K), 99, dtype=torch.int8, device="cuda")
+    sx = torch.full((M + 1,), -1.0, device="cuda")
+    trdq.rotate_quant(X, d, buf[:M], sx[:M])
+    assert torch.equal(buf[:M], want) and torch.equal(sx[:M], want_s)
+    assert (buf[M] == 99).all() and sx[M].item() == -1.0
+    n = trdq.xq_tiled_nbytes(M, K)
+    Xt = torch.full((n + 64,), 99, dtype=torch.int8, device="cuda")
+    sx.fill_(-1.0)
+    trdq.rotate_quant_tiled(X, d, Xt[:n], sx[:M])
+    back = torch.empty_like(want)
+    trdq.xq_untile(Xt[:n], M, K, back)
+    assert torch.equal(back, want) and torch.equal(sx[:M], want_s)
+    assert (Xt[n:] == 99).all() and sx[M].item() == -1.0
+    zc, zc_all = torch.empty(512, dtype=torch.int32, device="cuda"), torch.empty(M, dtype=torch.int32, device="cuda")
+    trdq.rotate_quant_asym(X, d, buf[:M], sx[:M], zc_all)
+    m = M - 300
+    trdq.rotate_quant_asym(X[m:], d, back[m:], want_s[m:], zc[:300])
+    assert torch.equal(buf[m:M], back[m:]) and torch.equal(sx[m:M], want_s[m:]) and torch.equal(zc_all[m:], zc[:300])
