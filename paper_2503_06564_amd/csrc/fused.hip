@@ -276,15 +276,15 @@ __global__ __launch_bounds__(kThreads) void linear_fused_kernel(FusedArgs g)
 //   product     2 TN matrix instructions per block; the waves' partial sums (int8 weights: one per wave, int4:
 //               one per block, i.e. per scale group) meet in LDS, wave w finishes channel tiles w, w + waves, ...
 //
-// The launcher takes the narrowest tile whose grid is one round of workgroups: repeating the rotation on
-// idle compute units is free, and fewer weight bytes per compute unit arrive sooner.  The arguments that the
+// The launcher takes the narrowest tile whose grid is one round of workgroups (see small_tiles): repeating the rotation
+// on idle compute units is free, and fewer weight bytes per compute unit arrive sooner.  The arguments that the
 // first loads need are the ones delivered in registers at wave launch.
 //
 // Measured, back-to-back launches (an empty kernel: 2.2 us): 1152 -> 1152 int8 at 16 / 128 / 256 / 512 tokens
 // 4.8 / 5.4 / 6.2 / 7.1 us, against 9.8 / 10.0 / 10.2 / 11.1 for a form that split K over eight waves, rotated
 // with lane exchanges (630 vector instructions per wave instead of 290), read row-major weights and passed the codes
 // through LDS, and 7.7-11.4 for the pair; int4 5.2 / 5.9 / 6.9 / 7.7; 4608 -> 1152 at 16 tokens 12.0 (int8), 12.9 (int4).
-constexpr int64_t kSmallMaxWorkgroups = 512;    // at most two rounds of workgroups
+constexpr int64_t kSmallMaxWorkgroups = 512;    // of the widest tile: at most two rounds
 constexpr int kSmallMaxBlocks = 36;
 
 // butterfly over an index bit that sits in lane bit 5 (HALF = 32) or 4 (16) of registers x (register bit 0)
@@ -545,21 +545,30 @@ int small_blocks_per_wave(int K) { return (K / kBlock + 11) / 12; }
 
 // Channel tiles (of 16) per workgroup: the narrowest of the built ones whose grid is one round of workgroups,
 // else the widest.  Several blocks per wave leave registers for one or two tiles only.
+// A round is one workgroup per compute unit, but a workgroup of one or two blocks is one or two waves: it finishes its
+// tiles one after the other, and a compute unit has room for more of them: four.  With two blocks that is for where three
+// tiles do not make one round, and from two tiles on (with one a wave rotates more than it multiplies).  us, one workgroup
+// per compute unit against this (int8; with zero points): 128 -> 512 at 700 / 1024 tokens 5.8 / 5.9, 4.0 / 4.3 (6.4 / 6.5,
+// 4.2 / 4.5); 256 -> 512 at 700 / 1024 5.4 / 5.4, 4.5 / 4.9 (6.0 / 6.1, 4.8 / 5.3); three blocks gain nothing (384 -> 512 at
+// 1024 5.4, in 704 workgroups 5.6).
 int small_tiles(int64_t M, int K, int N)
 {
-    const int64_t panels = (M + 15) / 16;
+    const int64_t panels = (M + 15) / 16, cus = num_cus();
     static constexpr int opts[] = {1, 2, 3, 5, 9};
-    const int bpw = small_blocks_per_wave(K);
+    const int bpw = small_blocks_per_wave(K), nb = K / kBlock;
     const int n_opts = bpw == 1 ? 5 : 2;
+    auto grid = [&](int tn) { return panels * ((N + tn * 16 - 1) / (tn * 16)); };
+    const bool several = nb == 1 || (nb == 2 && grid(3) > cus);
     for (int i = 0; i < n_opts; ++i)
-        if (panels * ((N + opts[i] * 16 - 1) / (opts[i] * 16)) <= num_cus()) return opts[i];
+        if (grid(opts[i]) <= (several && (nb == 1 || i > 0) ? 4 * cus : cus)) return opts[i];
     return opts[n_opts - 1];
 }
 
+// Workgroups of the widest tile: what tells how many rounds a shape needs at least.
 int64_t small_workgroups(int64_t M, int K, int N)
 {
-    const int tn = small_tiles(M, K, N);
-    return ((M + 15) / 16) * ((N + tn * 16 - 1) / (tn * 16));
+    const int bn = small_blocks_per_wave(K) == 1 ? 144 : 32;
+    return ((M + 15) / 16) * ((N + bn - 1) / bn);
 }
 
 template <int TN, int BPW, bool W4, bool ASYM>

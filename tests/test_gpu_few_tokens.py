@@ -49,3 +49,29 @@ def test_edges_asym(M, K, N):
     trdq.rotate_quant_asym(X, dd, Xq, sx, zc)
     trdq.qgemm_asym(w, Xq, sx, zc, Yp, bias=bd)
     gu.assert_y_close(gu.bf16_to_host(Y), gu.bf16_to_host(Yp), "fused asymmetric against the pair")
+
+
+# one and two blocks with workgroups for several per compute unit: each number of channel tiles that such a grid takes
+# (1, 2, 3, 5), token panels and channel tiles incomplete
+@pytest.mark.parametrize("M,K,N", [(497, 128, 496), (700, 128, 528), (1000, 128, 528), (1300, 128, 816),
+                                   (700, 256, 528), (1001, 256, 528), (1300, 256, 816)])
+@pytest.mark.parametrize("form", ["w8", "w4", "asym"])
+def test_narrow_rows_many_workgroups(M, K, N, form):
+    Xb, W, d, bias = wl.small_case(850 + M, M, K, N, n_outliers=4)
+    X, dd, bd = gu.bf16_to_dev(Xb), gu.f32_to_dev(d), gu.f32_to_dev(bias)
+    w = trdq.prepare_weights(gu.f32_to_dev(W), dd, wbits=4 if form == "w4" else 8)
+    buf = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device=gu.dev())
+    Y, Yp = buf[:M], torch.empty((M, N), dtype=torch.bfloat16, device=gu.dev())
+    Xq = torch.empty((M, K), dtype=torch.int8, device=gu.dev())
+    sx, zc = torch.empty(M, device=gu.dev()), torch.empty(M, dtype=torch.int32, device=gu.dev())
+    if form == "asym":
+        trdq.linear_fused_asym(X, dd, w, Y, bias=bd)
+        trdq.rotate_quant_asym(X, dd, Xq, sx, zc)
+        trdq.qgemm_asym(w, Xq, sx, zc, Yp, bias=bd)
+    else:
+        trdq.linear_fused(X, dd, w, Y, bias=bd)
+        trdq.rotate_quant(X, dd, Xq, sx)
+        trdq.qgemm(w, Xq, sx, Yp, bias=bd)
+    torch.cuda.synchronize()
+    assert (buf[M] == 7.0).all()
+    gu.assert_y_close(gu.bf16_to_host(Y), gu.bf16_to_host(Yp), "fused against the pair")
