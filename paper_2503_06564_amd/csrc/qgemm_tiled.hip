@@ -971,8 +971,10 @@ bool tiled_rows_supports(const GemmArgs &a)
 //     repeats a part 14000 tokens (1024 -> 2048 at 12000 34.6 -> 33.5, at 16000 39.7 -> 42.7).
 //   - Whole tiles: up to three quarters of the compute units have one (1152 -> 3456 at 1024 tokens 9.9 -> 9.5, 768 -> 2304 at
 //     1024 7.9 -> 6.8; 1152 -> 1152 at 4096, one each, 11.3 -> 11.6 with cold weights), for K < 1024 all of them, for long K
-//     half (4608 -> 1152 at 1024 19.6 -> 17.8, at 4096 24.4 -> 25.0).  With zero points K < 1024 only (768 -> 2304 at 1024
-//     8.0 -> 7.5, 1152 -> 3456 9.9 -> 10.6).
+//     half (4608 -> 1152 at 1024 19.6 -> 17.8, at 4096 24.4 -> 25.0).  Below K = 512, where the width is whole 128-channel
+//     tiles too, the 128 x 128 kernel is the other one and has no K to walk: only at nearly one tile each (256 -> 2304 at
+//     512 / 1536 / 2048 tokens 4.5 / 5.4 / 6.3 -> 4.7 / 5.5 / 6.0; 128 -> 1152 at 1024 4.1 -> 4.5).  With zero points K < 1024
+//     only (768 -> 2304 at 1024 8.0 -> 7.5, 1152 -> 3456 9.9 -> 10.6).
 //   - Zero points: the only other kernel that takes them at any shape is the any-shape one (768 -> 3072 at 4096 tokens
 //     23.2 -> 19.1, 1152 -> 4608 at 32700 tokens 268 -> 215).
 bool tiled_rows_pays(int64_t M, int K, int N, bool asym)
@@ -983,6 +985,7 @@ bool tiled_rows_pays(int64_t M, int K, int N, bool asym)
         if (asym && K < 512) return true;
         if (asym && K >= 1024) return false;
         const int64_t tiles = (M / 128) * (int64_t)(N / kBN), cus = num_cus();
+        if (K < 512 && N % 128 == 0) return K >= 256 && tiles > cus * 7 / 8 && tiles <= cus;
         return tiles <= (K < 1024 ? cus : K < 2304 ? cus * 3 / 4 : cus / 2);
     }
     if (asym) return true;
