@@ -134,7 +134,7 @@ hipError_t launch_qgemm4_tiled_rows(const GemmArgs &a, bool debug, hipStream_t s
 
 // Small launches, both operands straight into registers (qgemm_direct.hip); tile indexes the table there.
 // qgemm8_direct_tile: the tile for int8 weights where this form is the fastest, else -1.
-int qgemm8_direct_tile(int64_t M, int K, int N);
+int qgemm8_direct_tile(int64_t M, int K, int N, bool asym = false);
 hipError_t launch_qgemm8_direct(const GemmArgs &a, bool debug, int tile, hipStream_t st);
 // the same for int4 weights (a.Wc: the block form of the packed codes)
 int qgemm4_direct_tile(int64_t M, int K, int N);

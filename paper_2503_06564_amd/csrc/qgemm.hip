@@ -271,7 +271,7 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
     }
     // few output tiles: operands straight into registers, K split over the waves
     if (variant < 0 && w.wbits == 8 && w.codes_tiled) {
-        if (const int tile = qgemm8_direct_tile(M, w.K, w.N); tile >= 0) {
+        if (const int tile = qgemm8_direct_tile(M, w.K, w.N, zc != nullptr); tile >= 0) {
             GemmArgs a;
             a.Xq = Xq; a.Wc = w.codes_tiled; a.sx = sx; a.sw = w.scales; a.bias = bias; a.Y = Y;
             a.acc_debug = acc_debug; a.M = M; a.ldy = ldy; a.K = w.K; a.N = w.N;
@@ -415,7 +415,7 @@ bool qgemm_reads_tiled_codes(const Weights &w, int64_t M, bool asym)
     if (!w.codes_tiled) return false;
     if (w.wbits == 4) return qgemm4_direct_tile(M, w.K, w.N) >= 0 || (!asym && tiled4_rows_pays(M, w.K, w.N));
     return w.wbits == 8 &&
-           (qgemm8_direct_tile(M, w.K, w.N) >= 0 || tiled_rows_pays(M, w.K, w.N, asym));
+           (qgemm8_direct_tile(M, w.K, w.N, asym) >= 0 || tiled_rows_pays(M, w.K, w.N, asym));
 }
 
 bool qgemm4_tiled_pays(int64_t M, int K, int N)

@@ -389,30 +389,47 @@ constexpr int kDirectTiles[5][2] = {{1, 1}, {1, 2}, {2, 2}, {2, 4}, {4, 4}};
 // 256 tokens 9.0 (32 x 64), 768 tokens 13.4 (64 x 64; 32 x 64 15.8).  One unit per wave leaves registers for two rounds
 // of 32 x 64 tiles, and 64 x 64 never pays there.
 // Two (2.5) workgroups per compute unit is the most that pays for few units too, however many would fit: the kernels with
-// tiles in LDS have little K to walk there (128 -> 512 at 8192 tokens 8.0 in 2048 workgroups against 5.2 us, 256 -> 1024
-// at 4096 7.9 / 5.7, 640 -> 512 at 4096 7.2 / 6.1, at 2048 in 512 workgroups 5.6 both ways, 768 -> 2304 at 700 8.3 / 6.3).
+// tiles in LDS have little K to walk there (640 -> 512 at 4096 7.2 / 6.1, at 2048 in 512 workgroups 5.6 both ways, 768 -> 2304
+// at 700 8.3 / 6.3).  One or two units are workgroups of one or two waves, which finish their tiles one after the other:
+// small tiles in many workgroups.  us, with a wave of 32 x 64 / now / tiles in LDS: 128 -> 512 at 2048 tokens (16 x 16, 16 per
+// compute unit) 6.0 / 3.8 / 4.0, 128 -> 2304 at 256 5.9 / 3.3 / 3.8, 128 -> 512 at 4096 (32 per) 5.1 against 4.4; 256 -> 512 at
+// 2048 (16 x 32, 8 per) 5.1 / 4.1 / 4.5, 256 -> 768 at 2048 (12 per) 4.9 against 4.7; widths that no other kernel takes in
+// whole tiles a quarter more (256 -> 1168 at 1024 4.2, 6.6).
 // Beyond that the kernels with tiles in LDS are ahead: 1152 -> 1152 at 1024 tokens 8.0 both ways, at 1536 11.2 against
-// 8.7 us; 4608 -> 1152 at 1024 tokens 20.7 against 17.6 us.  Shapes that those kernels take only in part (ragged token
-// counts, widths that are no multiple of 144) stay here longer: 4608 -> 1152 at 1000 tokens 20.5 against 27.2 us.
-int qgemm8_direct_tile(int64_t M, int K, int N)
+// 8.7 us; 4608 -> 1152 at 1024 tokens 20.7 against 17.6 us.  Of shapes that those kernels take only in part (ragged token
+// counts, odd widths) 64 x 64 tiles take more: 4608 -> 1168 at 1000 tokens 21.6 against 22.3 us, 3072 -> 1168 at 1024 16.1 / 19.8.
+// Widths of whole 128-channel tiles they take as they are, until K is long: 1664 -> 1536 at 1024 tokens (384 workgroups) 13.4
+// against 9.3 us, 3072 -> 768 at 1536 15.7 / 13.7, 3584 -> 768 at 2048 17.8 / 16.3 but -> 1024 at 1536 17.2 / 20.0, 4096 -> 768 at
+// 2048 18.5 / 20.1.  With ragged tokens (2304 -> 3072 at 400 17.7 / 11.9, 2688 -> 3072 at 400 19.6 / 14.8, 3072 -> 1536 at 1000
+// 15.8 / 17.8) and with zero points (3072 -> 1536 at 1024 15.7 / 18.4) the other kernels are slower ones, and the line lies lower.
+int qgemm8_direct_tile(int64_t M, int K, int N, bool asym)
 {
     const int nu = K / 128;
     if (M <= 0 || nu <= 0 || (int64_t)M > (1 << 20)) return -1;
+    auto grid = [&](int i) {
+        const int tm = 16 * kDirectTiles[i][0], tn = 16 * kDirectTiles[i][1];
+        return ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
+    };
+    const int64_t cus = num_cus();
+    if (nu <= 2) {
+        const int64_t most = (nu == 1 ? 16 : 8) * cus * (N % 128 != 0 && N % 144 != 0 ? 5 : 4) / 4;
+        if (nu == 2 && grid(0) <= 2 * cus) return 0;
+        return grid(nu - 1) <= most ? nu - 1 : -1;
+    }
     const int per = (nu + 11) / 12, nw = (nu + per - 1) / per;
     const bool whole = M % 128 == 0 && N % 144 == 0;
-    const int64_t cus = num_cus(), most_wide = whole ? 2 * cus : 5 * cus / 2;
+    const bool whole128 = N % 128 == 0 && K < (asym || M % 128 != 0 ? 2816 : (M % 1024 != 0 ? 3200 : 4096));
+    const int64_t most_wide = whole ? 2 * cus : 5 * cus / 2;
     int64_t round = cus * 9 / (per == 1 ? nw : 9);
     if (round > 2 * cus) round = 2 * cus;
     for (int i = 0; i < 5; ++i) {
-        const int tm = 16 * kDirectTiles[i][0], tn = 16 * kDirectTiles[i][1];
-        const int64_t wgs = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
         int64_t most = round;
         if (i == 3 && per == 1) {
             most = whole ? 2 * round : 5 * round / 2;
             if (most > most_wide) most = most_wide;
         }
-        if (i == 4) most = per == 1 ? 0 : (whole ? round : 7 * round / 4);
-        if (wgs <= most) return i;
+        if (i == 4) most = per == 1 ? 0 : (whole || whole128 ? round : 7 * round / 4);
+        if (grid(i) <= most) return i;
     }
     return -1;
 }
@@ -432,14 +449,17 @@ hipError_t launch_qgemm8_direct(const GemmArgs &a, bool debug, int tile, hipStre
 // int4 tiles, in the order they are tried: 16 x 32, 32 x 32, 32 x 64.  One workgroup per compute unit, with one
 // round of groups two of 32 x 32 (us: 1152 -> 1152 at 64 / 250 / 384 tokens 10.9 / 11.3 / 10.6 -> 5.2 / 5.9 / 6.1, in 576
 // workgroups at 500 tokens 8.2 against 7.9 of the 64-token tiles in LDS; 4608 -> 1152 at 64 / 192 / 250 tokens
-// 30.3 / 30.6 / 31.1 -> 7.5 / 9.4 / 14.0, those take 22.8).  One or two groups, which those do not take: four (256 -> 512
-// at 1000 tokens 6.1 -> 4.9, at 2048 6.0 -> 5.6, in 1504 workgroups at 3000 7.0 against 6.2).
+// 30.3 / 30.6 / 31.1 -> 7.5 / 9.4 / 14.0, those take 22.8).  One or two groups, which those do not take: two, four (256 -> 512
+// at 1000 tokens 6.1 -> 4.2, at 2048 5.8 -> 5.5, in 1504 workgroups at 3000 7.0 against 6.2); one, whose workgroup is one wave: six,
+// of the smallest tile only (128 -> 512 at 1024 tokens 5.0 -> 4.3, -> 768 at 1024 5.0 -> 4.8, -> 512 at 2048 in eight 5.3 against
+// 5.1; 32 x 32 there 5.8).
 int qgemm4_direct_tile(int64_t M, int K, int N)
 {
     const int nu = K / 128;
     if (M <= 0 || nu <= 0 || nu > 72 || M > (1 << 20)) return -1;
     const int64_t cus = num_cus();
-    const int64_t most[3] = {nu < 3 ? 4 * cus : cus, nu < 3 ? 4 * cus : (nu <= 12 ? 2 * cus : cus), cus};
+    const int64_t most[3] = {nu == 1 ? 6 * cus : (nu == 2 ? 4 * cus : cus), nu == 1 ? 0 : (nu == 2 ? 4 * cus : (nu <= 12 ? 2 * cus : cus)),
+                             nu == 1 ? 0 : cus};
     constexpr int tiles[3][2] = {{1, 2}, {2, 2}, {2, 4}};
     for (int i = 0; i < 3; ++i) {
         const int tm = 16 * tiles[i][0], tn = 16 * tiles[i][1];

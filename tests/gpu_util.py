@@ -6,6 +6,8 @@ Tolerances (stated by the benchmark spec, derived in the design notes):
   scales    rtol 1e-5
   bf16 Y    within 1e-2 x row absmax of the oracle's quantised output
 """
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -163,3 +165,11 @@ def assert_y_close(got_bits, want_bits, what, skip_rows=None, skip_cols=None):
     worst = float((np.where(ok, 0.0, err) / np.maximum(row, 1e-30)).max())
     assert np.all(ok), f"{what}: max err / row absmax = {worst}"
     return float((err / np.maximum(row, 1e-30)).max())
+
+
+def library_rule(symbol, M, K, N, *flags):
+    """What one of the library's dispatch rules, a C++ function (int64 M, int K, int N, bool ...), answers: a test that is meant
+    for one kernel asserts it, so that a change of the rule cannot send its shapes elsewhere unseen."""
+    f = getattr(trdq.lib(), symbol)
+    f.restype, f.argtypes = C.c_int, [C.c_int64, C.c_int, C.c_int] + [C.c_bool] * len(flags)
+    return f(M, K, N, *flags)

@@ -48,6 +48,18 @@ def test_edges(oracle, M, K, N, asym):
     gu.assert_y_same_codes(gu.bf16_to_host(Y), y, "Y (same codes)")
 
 
+# one and two units with workgroups for many per compute unit (the largest grids that this kernel takes), and widths of
+# whole 128-channel tiles on both sides of the line to the kernels with tiles in LDS
+@pytest.mark.parametrize("M,K,N,tile", [(4090, 128, 256, 0), (2040, 128, 496, 0), (2040, 256, 512, 1), (1010, 256, 1168, 1),
+                                        (512, 1664, 1536, 4), (640, 1664, 1536, 4), (1024, 1664, 1536, -1), (1024, 3072, 1536, -1)])
+@pytest.mark.parametrize("asym", [False, True])
+def test_edges_of_the_choice(oracle, M, K, N, tile, asym):
+    if asym and K == 3072:
+        tile = 4                         # with zero points the line lies lower
+    assert gu.library_rule("_ZN4trdq4gemm18qgemm8_direct_tileEliib", M, K, N, asym) == tile
+    test_edges(oracle, M, K, N, asym)
+
+
 # int4: one and two groups (no other tiled kernel takes them), one round of waves, several with a last round that is full
 # (18, 36 groups), short (13, 25: some waves without a group), and the 64-token tiles from one tile on
 SHAPES4 = [(1, 128, 16), (33, 256, 48), (17, 1152, 80), (31, 1536, 64), (40, 1664, 96), (65, 2304, 32), (50, 3200, 144),
