@@ -36,8 +36,9 @@
  *     Nothing is printed and nothing aborts.  M == 0 is a valid no-op, for which the
  *     data pointers may be NULL (an empty tensor has no storage).
  *   - NaN / Inf in X or W are not detected; the result is then unspecified.
- *   - Handles are immutable after creation: concurrent forward calls on
- *     different streams may share them.  A handle's buffers live on the device
+ *   - Handles are immutable after creation, layers between two calls of
+ *     trdq_layer_set_group: concurrent forward calls on different streams may
+ *     share them.  A handle's buffers live on the device
  *     that was current when it was created; a launch that is given a handle
  *     while another device is current returns ERR_MISMATCH.
  */
@@ -468,7 +469,11 @@ typedef struct trdq_layer trdq_layer;
 trdq_status trdq_layer_create(const trdq_table *t, int K, int N, int wbits, trdq_layer **out);
 
 /* Prepare group g from W_dev [K, N] and diag_dev [K] (or NULL = ones; the diagonal is copied
- * to a device buffer the layer owns).  Replaces an earlier setting of the same group. */
+ * to a device buffer the layer owns).  Replaces an earlier setting of the same group; if it fails, that
+ * setting stays.  Returns when the weights are ready.  Calls that were enqueued before go on with the set they
+ * were given: a replaced set is left as it is, and the next replacement in this layer, of whichever group,
+ * waits for the device and fills its memory (so a layer that has replaced a group holds one set more).
+ * No other call may run on the same layer object during this one. */
 trdq_status trdq_layer_set_group(trdq_layer *l, int g, const float *diag_dev, const float *W_dev,
                                  void *stream);
 
@@ -484,6 +489,7 @@ trdq_status trdq_layer_forward(const trdq_layer *l, int step, const void *X_dev,
                                const float *bias_dev, void *Y_dev, int fused,
                                int8_t *Xq_ws_dev, float *sx_ws_dev, void *stream);
 
+/* The set of group g, owned by the layer: valid until the group is set again or the layer destroyed. */
 trdq_status trdq_layer_weights(const trdq_layer *l, int g, const trdq_weights **w_out);
 void trdq_layer_destroy(trdq_layer *l);
 

@@ -61,6 +61,7 @@ struct trdq_layer {
     Table table;
     int K = 0, N = 0, wbits = 0;
     std::vector<trdq_weights *> w;     // one per group (H_t depends on t), with its copy of the diagonal (null = ones)
+    trdq_weights *spare = nullptr;     // the set that was replaced last: what the next replacement fills
     std::vector<char> set;
 };
 
@@ -1058,24 +1059,29 @@ trdq_status trdq_layer_set_group(trdq_layer *l, int g, const float *diag_dev, co
     if (!l || !W_dev) return TRDQ_ERR_NULL;
     if (g < 0 || g >= l->table.n_groups) return TRDQ_ERR_RANGE;
     if (diag_dev && !aligned(diag_dev, 16)) return TRDQ_ERR_SHAPE;
-    trdq_weights *&slot = l->w[(size_t)g];
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return TRDQ_ERR_HIP; }
-    if (slot && slot->device == dev && (slot->diag != nullptr) == (diag_dev != nullptr)) {
-        // Replacing a group by one of the same form: refilled where it is (releasing the old set and allocating
-        // another cost 0.1-0.2 ms).  As the release did, this waits for whatever still reads the old set on
-        // any stream.  A failure leaves the group unset.
-        if (hipDeviceSynchronize() != hipSuccess) { (void)hipGetLastError(); return TRDQ_ERR_HIP; }
-        l->set[(size_t)g] = 0;
-        trdq_status rc = fill_weights(slot, W_dev, diag_dev, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream));
-        if (rc == TRDQ_OK) l->set[(size_t)g] = 1;
-        return rc;
-    }
+    trdq_weights *&slot = l->w[(size_t)g];
     trdq_weights *w = nullptr;
-    trdq_status rc = prepare_weights_impl(W_dev, l->K, l->N, diag_dev, nullptr, trdq::kBlock, l->wbits, stream, &w, nullptr,
-                                          nullptr, diag_dev != nullptr);
-    if (rc != TRDQ_OK) return rc;
-    if (slot) trdq_weights_destroy(slot);
+    trdq_status rc;
+    if (l->spare && l->spare->device == dev && (l->spare->diag != nullptr) == (diag_dev != nullptr)) {
+        // A set replaced earlier is filled (releasing one and allocating another cost 0.1-0.2 ms), once nothing reads it any
+        // more on any stream.  The group's own set is never written: launches made before go on with it, and it stays
+        // the group's set if this fails.
+        if (hipDeviceSynchronize() != hipSuccess) { (void)hipGetLastError(); return TRDQ_ERR_HIP; }
+        rc = fill_weights(l->spare, W_dev, diag_dev, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream));
+        if (rc != TRDQ_OK) return rc;
+        w = l->spare;
+        l->spare = nullptr;
+    } else {
+        rc = prepare_weights_impl(W_dev, l->K, l->N, diag_dev, nullptr, trdq::kBlock, l->wbits, stream, &w, nullptr, nullptr,
+                                  diag_dev != nullptr);
+        if (rc != TRDQ_OK) return rc;
+    }
+    if (slot) {
+        trdq_weights_destroy(l->spare);      // (of another form: one spare set is kept)
+        l->spare = slot;
+    }
     slot = w;
     l->set[(size_t)g] = 1;
     return TRDQ_OK;
@@ -1121,6 +1127,7 @@ void trdq_layer_destroy(trdq_layer *l)
 {
     if (!l) return;
     for (trdq_weights *w : l->w) trdq_weights_destroy(w);
+    trdq_weights_destroy(l->spare);
     std::free(l->table.map);
     delete l;
 }

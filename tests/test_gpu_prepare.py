@@ -1,5 +1,5 @@
 """Weight preparation at the edges of its kernels (widths that are no multiple of a workgroup's 64 columns, one and
-many blocks) against the oracle, and groups of a layer that are set again in place."""
+many blocks) against the oracle, and groups of a layer that are set again."""
 import numpy as np
 import pytest
 
@@ -32,8 +32,8 @@ def test_codes_and_scales(trdq, oracle, wbits, K, N, with_diag):
 
 @pytest.mark.parametrize("wbits", [8, 4])
 def test_group_set_again(trdq, wbits):
-    """A group that is replaced holds what a fresh layer would hold: same diagonal form (refilled in place),
-    then the diagonal dropped, then brought back."""
+    """A group that is replaced holds what a fresh layer would hold: same diagonal form, then the diagonal dropped, then
+    brought back."""
     import torch
     M, K, N = 40, 384, 144
     table = trdq.Table(4, 2)
@@ -55,3 +55,59 @@ def test_group_set_again(trdq, wbits):
         assert torch.isfinite(out[0].float()).all() and torch.equal(out[0], out[1])
         for a, b in zip(layer.weights(1).export(), fresh.weights(1).export()):
             assert np.array_equal(a, b)
+
+
+def test_replaced_set_is_left_alone(trdq):
+    """Replacing a group writes another set than the one that calls may still be reading, the first time and when it
+    fills a set that was replaced before."""
+    K, N = 384, 144
+    layer = trdq.Layer(trdq.Table(4, 2), K, N, 8)
+    held = []
+    for seed in range(5):
+        _, W, d, _ = wl.small_case(seed, 4, K, N)
+        layer.set_group(1, f32_to_dev(d), f32_to_dev(W))
+        w = layer.weights(1)
+        if held:
+            before, codes, scales = held[-1]
+            assert w.handle.value != before.handle.value
+            got = before.export()            # the set just replaced, not yet filled again
+            assert np.array_equal(got[0], codes) and np.array_equal(got[1], scales)
+        held.append((w, *w.export()))
+    assert held[0][0].handle.value == held[2][0].handle.value == held[4][0].handle.value     # two sets take turns
+
+
+@pytest.mark.parametrize("replaced_before", [0, 1, 2])
+def test_failed_replacement_keeps_the_group(trdq, replaced_before):
+    """The preparation of a group ends with a wait for its stream, which a capturing stream refuses."""
+    import ctypes as C
+
+    import torch
+    hip = trdq.lib()                     # finds the runtime that the library itself is linked to
+    M, K, N = 8, 384, 144
+    layer = trdq.Layer(trdq.Table(4, 2), K, N, 8)
+    xb, W, d, _ = wl.small_case(1, M, K, N)
+    X, dd, Wd = bf16_to_dev(xb), f32_to_dev(d), f32_to_dev(W)
+    other = f32_to_dev(2.0 * W)
+    for _ in range(replaced_before):
+        layer.set_group(1, dd, other)
+    layer.set_group(1, dd, Wd)
+    ws = dict(Xq_ws=torch.empty((M, K), dtype=torch.int8, device="cuda"), sx_ws=torch.empty(M, device="cuda"))
+    want, got = (torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    layer.forward(3, X, want, **ws)
+    torch.cuda.synchronize()
+    stream, graph = C.c_void_p(), C.c_void_p()
+    assert hip.hipStreamCreate(C.byref(stream)) == 0
+    assert hip.hipStreamBeginCapture(stream, 2) == 0                    # relaxed: allocations stay allowed
+    with pytest.raises(trdq.TrdqError) as e:
+        layer.set_group(1, dd, other, stream=stream.value)
+    assert e.value.status == trdq.ERR_HIP
+    hip.hipStreamEndCapture(stream, C.byref(graph))                     # an invalidated capture: no graph comes out
+    hip.hipGetLastError()
+    assert hip.hipStreamDestroy(stream) == 0
+    layer.forward(3, X, got, **ws)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    layer.set_group(1, dd, other)                                       # and it can be replaced afterwards
+    layer.forward(3, X, got, **ws)
+    torch.cuda.synchronize()
+    assert not torch.equal(got, want) and torch.isfinite(got.float()).all()
