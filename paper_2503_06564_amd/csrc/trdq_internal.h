@@ -31,7 +31,7 @@ struct Weights {
     int32_t *zcw = nullptr;      // asymmetric int8 weights (Eq. 1-3 per output channel): 128 - z_w [N]; codes hold q - 128
     float *colsumw = nullptr;    // int4 weights: 16 * sum_g s_w[g][n] * (sum of the codes of group g) [N]
     float *diag = nullptr;       // the handle's copy of the diagonal [K], if it keeps one
-    float *amax = nullptr;       // scratch of the preparation: block maxima [K/128, N]
+    float *amax = nullptr;       // scratch of the preparation of 8-bit codes after one Hadamard rotation: block maxima [K/128, N]
     void *block = nullptr;       // the one device allocation that holds all of the above
     int device = 0;
 };
