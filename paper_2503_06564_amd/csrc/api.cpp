@@ -354,11 +354,12 @@ trdq_status trdq_rotation_create(const float *R_dev, const float *diag_dev, int 
     if (!r) return TRDQ_ERR_ALLOC;
     r->K = K;
     const size_t r_bytes = (size_t)K * trdq::kBlock * sizeof(float);
+    const bool wide = trdq::rotate_quant_dense_rpr_reads_frags32(K);     // 64 KB per block that narrower rows never read
     trdq_status rc = TRDQ_OK;
     if (hipGetDevice(&r->device) != hipSuccess) { rc = TRDQ_ERR_HIP; goto fail; }
     if (hipMalloc(reinterpret_cast<void **>(&r->R), r_bytes) != hipSuccess ||
         hipMalloc(&r->pieces, trdq::rotation_pieces_bytes(K)) != hipSuccess ||
-        hipMalloc(&r->frags32, trdq::rotation_frags32_bytes(K)) != hipSuccess ||
+        (wide && hipMalloc(&r->frags32, trdq::rotation_frags32_bytes(K)) != hipSuccess) ||
         (diag_dev && hipMalloc(reinterpret_cast<void **>(&r->diag), (size_t)K * sizeof(float)) != hipSuccess)) {
         rc = TRDQ_ERR_ALLOC;
         goto fail;
@@ -366,7 +367,7 @@ trdq_status trdq_rotation_create(const float *R_dev, const float *diag_dev, int 
     if (hipMemcpyAsync(r->R, R_dev, r_bytes, hipMemcpyDeviceToDevice, st) != hipSuccess ||
         (diag_dev && hipMemcpyAsync(r->diag, diag_dev, (size_t)K * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess) ||
         trdq::launch_rotation_pieces(r->R, r->diag, K, r->pieces, st) != hipSuccess ||
-        trdq::launch_rotation_frags32(r->R, K, r->frags32, st) != hipSuccess ||
+        (wide && trdq::launch_rotation_frags32(r->R, K, r->frags32, st) != hipSuccess) ||
         hipStreamSynchronize(st) != hipSuccess) {
         rc = TRDQ_ERR_HIP;
         goto fail;

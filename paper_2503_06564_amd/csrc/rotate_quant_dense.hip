@@ -871,6 +871,7 @@ hipError_t launch_channel_absmax_dense(const uint16_t *X, int64_t M, int K, int6
 
 bool rotate_quant_dense_supports(int K) { return K % kBlock == 0 && K / kBlock <= 36; }
 bool rotate_quant_dense_rpr_supports(int K) { return K % kBlock == 0 && K / kBlock <= 36; }
+bool rotate_quant_dense_rpr_reads_frags32(int K) { return K / kBlock > 12; }
 
 // Rows wider than 12 blocks have a second form that goes through a workspace: the once-rotated values,
 // float32, channel-major, tokens rounded up to 32 (the first rotation writes whole groups of 32 tokens),
@@ -921,7 +922,7 @@ hipError_t launch_rotate_quant_dense_rpr(const uint16_t *X, int64_t M, int K, in
 {
     if (M == 0) return hipSuccess;
     const int nb = K / kBlock;
-    if (nb > 12) {
+    if (rotate_quant_dense_rpr_reads_frags32(K)) {
         // wide rows: 8 tokens per workgroup of 12 waves
         const int64_t groups8 = (M + 7) / 8;
         const int64_t grid8 = groups8 < num_cus() ? groups8 : num_cus();

@@ -44,7 +44,7 @@ struct Rotation {
     float *R = nullptr;          // [K/128][128][128]
     float *diag = nullptr;       // [K] or null (ones)
     void *pieces = nullptr;      // diag . R_b as bf16 pieces (operand of a first or only rotation)
-    void *frags32 = nullptr;     // R_b as float fragments (second rotation of wide rows without a workspace)
+    void *frags32 = nullptr;     // R_b as float fragments (second rotation of wide rows without a workspace), else null
     int device = 0;
 };
 
@@ -138,6 +138,7 @@ hipError_t launch_rotate_quant_dense(const uint16_t *X, int64_t M, int K, int64_
 hipError_t launch_prepare_rotate_dense(const float *W, int K, int N, const float *diag, const int32_t *perm,
                                        const float *R, float *Wrot, float *amax, hipStream_t st);
 size_t rotation_frags32_bytes(int K);
+bool rotate_quant_dense_rpr_reads_frags32(int K);    // whether the form without a workspace reads them for such rows
 hipError_t launch_rotation_frags32(const float *R, int K, void *frags, hipStream_t st);
 bool rotate_quant_dense_rpr_supports(int K);
 hipError_t launch_rotate_quant_dense_rpr(const uint16_t *X, int64_t M, int K, int64_t ldx, const void *pieces1,
