@@ -314,3 +314,16 @@ def test_asym_weight_calls_check_arguments_before_any_gpu_call():
 def test_fused_asym_checks_arguments_before_any_gpu_call():
     L = trdq.lib()
     assert L.trdq_linear_fused_asym(0x1000, 4, 256, None, None, None, 0x2000, 16, None) == trdq.ERR_NULL
+
+
+def test_current_stream_without_the_private_lookup(monkeypatch):
+    """A torch without its private raw-stream function: the public one answers, for the stream that is current then."""
+    import types
+
+    import torch
+    streams = iter([5, 77, 78])
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=next(streams)))
+    monkeypatch.setattr(torch, "_C", types.SimpleNamespace())
+    monkeypatch.setattr(trdq, "_raw_stream", None)
+    assert trdq._stream(None) == 77 and trdq._stream(None) == 78
+    assert trdq._stream(9) == 9 and trdq._stream(types.SimpleNamespace(cuda_stream=11)) == 11
