@@ -241,7 +241,7 @@ trdq_status fill_weights(trdq_weights *w, const float *W_dev, const float *diag_
         if (e == hipSuccess) e = trdq::launch_prepare_quant(rot2 ? Wrot2 : Wrot, nullptr, nullptr, false, 1.0f, *w, amax, nullptr, st);
     } else if (perm_dev) {
         // the Hadamard form of Eq. 9: two unnormalised rotations, 1/128
-        e = trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, nullptr, Wrot, st);
+        e = trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, Wrot, st);
         if (e == hipSuccess) e = trdq::launch_prepare_quant(Wrot, nullptr, perm_dev, true, 0.0078125f, *w, amax, nullptr, st);
     } else {
         e = trdq::launch_prepare_quant(W_dev, diag_dev, nullptr, true, half, *w, amax, w->diag, st);
@@ -312,7 +312,7 @@ trdq_status trdq_prepare_weights_asym(const float *W_dev, int K, int N, const fl
     if (rc == TRDQ_OK) {
         lohi = Wrot + (size_t)K * N;
         const bool ok =
-            trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, nullptr, Wrot, st) == hipSuccess &&
+            trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, Wrot, st) == hipSuccess &&
             trdq::launch_prepare_quant_asym(Wrot, lohi, K, N, 0.08838834764831845f, w->codes, w->scales, w->zcw, st) == hipSuccess &&
             trdq::launch_weight_colsum(w->codes, K, N, w->colsum, st) == hipSuccess &&
             hipStreamSynchronize(st) == hipSuccess;
@@ -1103,7 +1103,7 @@ trdq_status trdq_layer_forward(const trdq_layer *l, int step, const void *X_dev,
     const trdq_weights *w = l->w[(size_t)g];
     const float *d = w->diag;
     const bool have_ws = Xq_ws_dev && sx_ws_dev;
-    if (fused > 0 || (fused < 0 && (have_ws ? trdq::fused_pays(M, l->K, l->N, w->wbits)
+    if (fused > 0 || (fused < 0 && (have_ws ? trdq::fused_pays(M, l->K, l->N)
                                             : trdq::fused_needs_no_workspace(M, l->K, l->N, w->wbits))))
         return trdq_linear_fused(X_dev, M, l->K, d, w, bias_dev, Y_dev, l->N, stream);
     if (!have_ws) return TRDQ_ERR_NULL;

@@ -586,13 +586,6 @@ hipError_t launch_small(const FusedArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-// few-token kernel: few enough workgroups that repeating the rotation per channel tile costs less than a
-// second launch
-bool small_applies(const FusedArgs &a)
-{
-    return a.K <= kSmallMaxBlocks * kBlock && small_workgroups(a.M, a.K, a.N) <= kSmallMaxWorkgroups;
-}
-
 template <bool W4, bool ASYM>
 hipError_t launch_small_any(const FusedArgs &a, hipStream_t st)
 {
@@ -651,14 +644,19 @@ hipError_t launch_w(const FusedArgs &a, hipStream_t st)
 
 bool fused_supports(int K) { return K % kBlock == 0 && K / kBlock <= 48; }
 
+// The few-token kernel: few enough workgroups that repeating the rotation per channel tile costs less than a second launch.
+bool fused_takes_few_tokens(int64_t M, int K, int N)
+{
+    return K <= kSmallMaxBlocks * kBlock && small_workgroups(M, K, N) <= kSmallMaxWorkgroups;
+}
+
 // True where the fused kernel is the faster path: the few-token kernel in a single round of workgroups (two of
 // the small ones that one or two blocks make).  In a second round the repeated rotation costs more than the pair's
 // second launch, us: 1152 -> 4608 at 128 tokens 7.0 against 13.2 (256 workgroups), at 256 tokens 12.9 against 14.9;
 // 768 -> 3072 at 256 tokens (352) 11.0 against 10.7; 4608 -> 1152 at 64 tokens (144) 15.3 against 17.7, at 128 (288)
 // 28.2 against 18.7; 256 -> 512 at 2048 tokens (512) 6.4 against 7.7.
-bool fused_pays(int64_t M, int K, int N, int wbits)
+bool fused_pays(int64_t M, int K, int N)
 {
-    (void)wbits;
     return M > 0 && K % kBlock == 0 && K <= kSmallMaxBlocks * kBlock &&
            small_workgroups(M, K, N) <= (int64_t)num_cus() * (K <= 2 * kBlock ? 2 : 1);
 }
@@ -681,7 +679,7 @@ hipError_t launch_linear_fused(const Weights &w, const uint16_t *X, int64_t M, i
     FusedArgs a;
     a.X = X; a.diag = diag; a.Wc = w.codes; a.sw = w.scales; a.bias = bias; a.colsum = w.colsum; a.Y = Y;
     a.M = M; a.ldx = ldx; a.ldy = ldy; a.K = w.K; a.N = w.N; a.tiles_n = 0; a.nsplit = 1;
-    if (small_applies(a)) {
+    if (fused_takes_few_tokens(a.M, a.K, a.N)) {
         a.Wc = w.codes_tiled;
         if (asym) return launch_small_any<false, true>(a, st);
         return w.wbits == 4 ? launch_small_any<true, false>(a, st) : launch_small_any<false, false>(a, st);

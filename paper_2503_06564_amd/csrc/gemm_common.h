@@ -132,7 +132,8 @@ bool tiled4_rows_supports(const GemmArgs &a);
 bool tiled4_rows_pays(int64_t M, int K, int N);
 hipError_t launch_qgemm4_tiled_rows(const GemmArgs &a, bool debug, hipStream_t st);
 
-// Small launches, both operands straight into registers (qgemm_direct.hip); tile indexes the table there.
+// Small launches, weights straight into registers, activations through LDS areas of the waves' own (qgemm_direct.hip); tile
+// indexes the table there.
 // qgemm8_direct_tile: the tile for int8 weights where this form is the fastest, else -1.
 int qgemm8_direct_tile(int64_t M, int K, int N, bool asym = false);
 hipError_t launch_qgemm8_direct(const GemmArgs &a, bool debug, int tile, hipStream_t st);

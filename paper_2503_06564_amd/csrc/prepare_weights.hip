@@ -71,17 +71,16 @@ __device__ __forceinline__ void rotate_block(float (&v)[32], int q, int c, float
 }
 
 // Rotation of the whole matrix into a scratch matrix (in front of a permutation, or of the asymmetric quantiser):
-//   Wrot[b*128 + j, n] = sum_k H[k][j] * W[row(b*128 + k), n] / d[b*128 + k]      (unnormalised H)
+//   Wrot[b*128 + j, n] = sum_k H[k][j] * W[b*128 + k, n] / d[b*128 + k]      (unnormalised H)
 __global__ __launch_bounds__(kPrepThreads) void prepare_rotate_kernel(
-    const float *__restrict__ W, int K, int N, const float *__restrict__ diag,
-    const int32_t *__restrict__ perm, float *__restrict__ Wrot)
+    const float *__restrict__ W, int K, int N, const float *__restrict__ diag, float *__restrict__ Wrot)
 {
     __shared__ float tile[kBlock][kCols];
     const int b = blockIdx.y, c = threadIdx.x % kCols, q = __builtin_amdgcn_readfirstlane(threadIdx.x / kCols);
     const int n = blockIdx.x * kCols + c;
     const bool col_ok = n < N;
     float v[32];
-    load_block(W, K, N, diag, perm, b, q, n, col_ok, v);
+    load_block(W, K, N, diag, nullptr, b, q, n, col_ok, v);
     rotate_block(v, q, c, tile);
     if (!col_ok) return;
 #pragma unroll
@@ -399,11 +398,10 @@ hipError_t launch_weight_colsum(const void *codes, int K, int N, int32_t *colsum
     return hipGetLastError();
 }
 
-hipError_t launch_prepare_rotate(const float *W, int K, int N, const float *diag, const int32_t *perm,
-                                 float *Wrot, hipStream_t st)
+hipError_t launch_prepare_rotate(const float *W, int K, int N, const float *diag, float *Wrot, hipStream_t st)
 {
     dim3 grid((N + kCols - 1) / kCols, K / kBlock);
-    hipLaunchKernelGGL(prepare_rotate_kernel, grid, dim3(kPrepThreads), 0, st, W, K, N, diag, perm, Wrot);
+    hipLaunchKernelGGL(prepare_rotate_kernel, grid, dim3(kPrepThreads), 0, st, W, K, N, diag, Wrot);
     return hipGetLastError();
 }
 

@@ -269,7 +269,7 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
         a.zc = zc; a.colsum = w.colsum; a.zcw = w.zcw; a.rowsum = rowsum;
         return launch_qgemm8_asym(a, acc_debug != nullptr, 0, st);
     }
-    // few output tiles: operands straight into registers, K split over the waves
+    // few output tiles: weights straight into registers, K split over the waves
     if (variant < 0 && w.wbits == 8 && w.codes_tiled) {
         if (const int tile = qgemm8_direct_tile(M, w.K, w.N, zc != nullptr); tile >= 0) {
             GemmArgs a;
@@ -337,7 +337,6 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
             const int64_t tiles144 = (M / 128) * (a.N / 144);
             kind = tiles144 > num_cus() ? 15 : (a.K >= 2304 ? 18 : 14);
         }
-        if (variant >= 0) kind = variant;     // tests: 0, 14, 15 or 18
         return launch_qgemm8_asym(a, dbg, kind, st);
     }
     // the row-wise epilogues store 16 bytes per lane: an output whose rows are only 8-byte aligned
@@ -430,7 +429,7 @@ bool qgemm_tiled_pays(int64_t M, int K, int N)
     // at K = 4608); with more tiles the kernel with two workgroups per compute unit does, by 5-30 %,
     // except for long K at up to two tiles per compute unit, where the row-major kernel whose wave groups
     // split K is level with it.
-    // Below those, few tiles go to the kernel that takes both operands straight into registers.
+    // Below those, few tiles go to the kernel that splits K over the waves of small workgroups.
     if (qgemm8_direct_tile(M, K, N) >= 0) return false;
     const int64_t tiles = (M / 128) * (int64_t)(N / 144);
     if (tiles <= num_cus()) return K >= 1024;

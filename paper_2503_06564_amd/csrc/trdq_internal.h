@@ -78,11 +78,9 @@ hipError_t launch_rotate_quant_rpr(const uint16_t *X, int64_t M, int K, int64_t 
                                    const int32_t *perm, int8_t *Xq, float *sx, const void *warm, int64_t warm_bytes,
                                    hipStream_t st, int32_t *zc = nullptr);   // zc: asymmetric codes, as launch_rotate_quant
 
-// perm (optional): rows are read through it (row k of the input to the rotation = row perm[k]).
-hipError_t launch_prepare_rotate(const float *W, int K, int N, const float *diag, const int32_t *perm,
-                                 float *Wrot, hipStream_t st);
-// Codes (both forms), scales and column sums of w from W: rotated on the way (rotate: diag and perm as above; amax:
-// scratch of K / 128 * N floats), or already rotated with its block maxima in amax.  norm: what undoes the
+hipError_t launch_prepare_rotate(const float *W, int K, int N, const float *diag, float *Wrot, hipStream_t st);
+// Codes (both forms), scales and column sums of w from W: rotated on the way (rotate: divided by diag, rows read through
+// perm, row k of the input to the rotation = row perm[k], both optional; amax: scratch of K / 128 * N floats), or already rotated with its block maxima in amax.  norm: what undoes the
 // unnormalised butterflies (1/sqrt(128) per rotation applied).  diag_copy (optional) receives diag.
 hipError_t launch_prepare_quant(const float *W, const float *diag, const int32_t *perm, bool rotate, float norm,
                                 const Weights &w, float *amax, float *diag_copy, hipStream_t st);
@@ -150,7 +148,8 @@ hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K,
                                             const int32_t *perm, const void *pieces2, int8_t *Xq, float *sx,
                                             float *T, hipStream_t st);
 bool fused_supports(int K);
-bool fused_pays(int64_t M, int K, int N, int wbits);
+bool fused_takes_few_tokens(int64_t M, int K, int N);    // which of the two fused kernels
+bool fused_pays(int64_t M, int K, int N);
 bool fused_needs_no_workspace(int64_t M, int K, int N, int wbits);
 hipError_t launch_linear_fused(const Weights &w, const uint16_t *X, int64_t M, int64_t ldx,
                                const float *diag, const float *bias, uint16_t *Y, int64_t ldy,
