@@ -60,8 +60,8 @@ def test_rotate_quant_asym_one_sided_and_zero_rows(oracle):
     assert sx[1].item() == 0.0 and zx_o[2] == 0 and zx_o[3] == 255
 
 
-# the last five shapes reach the 128 x 144 kernels: one workgroup per tile (K < 2304), two wave groups
-# splitting K (even and odd numbers of k-tiles), two workgroups per compute unit (more than 256 tiles)
+# 1024 x 1152 x 1152 and 4224 x 512 x 1152 run the 128 x 144 kernels (one workgroup per tile; two per compute unit), the others
+# the kernels for few tiles; those shapes that the 128 x 144 kernels split K for are in test_gpu_routes.py
 @pytest.mark.parametrize("M,K,N", [(1, 128, 16), (17, 256, 144), (300, 4608, 272), (513, 384, 400), (1024, 1152, 1152),
                                    (256, 1152, 288), (256, 2304, 144), (384, 4608, 144), (256, 2432, 144),
                                    (4224, 512, 1152), (1100, 1152, 1152), (1407, 2304, 144)])
@@ -117,8 +117,8 @@ def test_linear_asym_int4_weights(oracle, M, K, N):
     w.close()
 
 
-# both fused kernels: few tokens (one 16-token panel per workgroup, K <= 1536) and the general one
-# (panels of 64, 32 and 16 tokens as K grows); ragged token and channel counts, with and without a diagonal
+# ragged token and channel counts, one to three blocks per wave of the few-token kernel, and (1100 x 1152 x 1152, 1024 x 1152 x 3456)
+# the general one's panels of 64 tokens; its other panels are in test_gpu_routes.py
 @pytest.mark.parametrize("M,K,N,wbits", [(1, 128, 16, 8), (17, 256, 144, 8), (256, 1152, 1152, 8), (100, 1152, 272, 6),
                                          (1100, 1152, 1152, 8), (513, 384, 400, 8), (300, 2304, 272, 8),
                                          (200, 4608, 144, 8), (1024, 1152, 3456, 6)])

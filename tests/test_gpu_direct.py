@@ -1,5 +1,5 @@
-"""The product for launches with few output tiles (operands straight into registers, K split over the waves) at the edges
-of its tiles, against exact integer sums and the oracle's epilogue on the GPU's own codes."""
+"""The product for launches with few output tiles (weights straight into registers, activations through areas of the waves'
+own, K split over the waves) at the edges of its tiles, against exact integer sums and the oracle's epilogue on the GPU's own codes."""
 import numpy as np
 import pytest
 import torch

@@ -171,8 +171,8 @@ def test_qgemm_w8_pipelined_full_tiles(oracle, M, K, N, variant):
     _linear_case(oracle, 13, M, K, N, 8, variant)
 
 
-# ragged token counts with the built-in choice: whole panels on the fast kernels, the remaining rows on the
-# kernel that takes any shape (two launches); tails shorter and longer than 128 rows, 144- and 128-wide tiles
+# ragged token counts with the built-in choice: few tiles, and the tiled kernel on row-major codes (4100 x 512 x 1152); the
+# two-launch form, whole panels and the remaining rows, is in test_gpu_routes.py
 @pytest.mark.parametrize("M,K,N", [(1100, 1152, 1152), (1025, 256, 288), (2180, 384, 400), (1407, 2304, 144),
                                    (4100, 512, 1152)])
 def test_qgemm_w8_ragged_tokens_split(oracle, M, K, N):
@@ -270,7 +270,7 @@ def test_fused_matches_unfused_and_oracle(oracle, M, K, N, wbits):
     Y = torch.zeros((M, N), dtype=torch.bfloat16, device="cuda")
     trdq.linear_fused(X, gu.f32_to_dev(d), w, Y, bias=gu.f32_to_dev(bias))
     torch.cuda.synchronize()
-    # The fused kernel rotates with vector-ALU butterflies, rotate_quant with the matrix cores:
+    # The fused kernels and rotate_quant take the stages of the butterflies in different orders:
     # the same fp32 accuracy but another rounding order, so a code may differ by one LSB on a
     # rare element (the tolerance of both against the oracle); everything else is identical.
     same = (Y == Y_unfused).float().mean().item()
@@ -284,8 +284,7 @@ def test_fused_matches_unfused_and_oracle(oracle, M, K, N, wbits):
 @pytest.mark.parametrize("K", [128, 256, 384, 640, 896, 1152, 1408, 1536])
 @pytest.mark.parametrize("M,N", [(40, 144), (512, 288), (19, 160)])
 def test_fused_few_token_kernel(oracle, M, K, N):
-    """The 16-token-panel kernel (int8 weights, K <= 1536): every count of blocks per lane row,
-    144- and 128-channel tiles, ragged token and channel counts."""
+    """The 16-token-panel kernel with one block per wave: one to twelve waves, ragged token and channel counts."""
     say(f"fused few tokens M={M} K={K} N={N}")
     Xb, W, d, bias = wl.small_case(31, M, K, N, n_outliers=max(1, K // 144), outlier=40.0)
     w = trdq.prepare_weights(gu.f32_to_dev(W), gu.f32_to_dev(d), wbits=8)

@@ -1,0 +1,81 @@
+"""Kernels that the library's choice takes for shapes which most other tests leave to the kernels for few tokens or tiles.
+Each test asserts first that the rule sends its shape there."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+from paper_2503_06564_amd import trdq, workloads as wl
+from test_gpu_parity import _linear_case
+
+pytestmark = pytest.mark.gpu
+
+
+def _direct(M, K, N, asym=False):
+    return gu.library_rule("_ZN4trdq4gemm18qgemm8_direct_tileEliib", M, K, N, asym)
+
+
+def _rows(M, K, N, asym=False):
+    return gu.library_rule("_ZN4trdq4gemm15tiled_rows_paysEliib", M, K, N, asym) & 1
+
+
+# whole panels and the remaining rows in two launches: rows of Y that are 8-byte aligned only (M % 256 below and above 128), and
+# many ragged tokens at a width that is no multiple of 144 (heads of 256- and of 128-token panels; 16 and 112 rows left)
+@pytest.mark.parametrize("M,K,N,pad", [(1500, 1152, 1136, 4), (2100, 640, 1040, 12), (14096, 384, 400, 0), (14192, 256, 528, 0)])
+def test_ragged_tokens_in_two_launches(oracle, M, K, N, pad):
+    assert _direct(M, K, N) == -1 and (pad % 8 != 0 or not _rows(M, K, N))
+    _linear_case(oracle, 15, M, K, N, 8, -1, ldy=N + pad)
+
+
+# the general fused kernel: panels of 64, 32 and 16 tokens (up to 12, 24 and 48 blocks) in each register form (3, 6, 9, 12 blocks per
+# lane row), last panel and last channel tile incomplete
+@pytest.mark.parametrize("M,K,N", [(1000, 384, 1168), (1001, 768, 1168), (1001, 1152, 1168), (1010, 1536, 1168), (1000, 1664, 400),
+                                   (999, 3072, 272), (1000, 3200, 400), (100, 4736, 272), (37, 6144, 144)])
+@pytest.mark.parametrize("form", ["w8", "w4", "asym"])
+def test_general_fused_kernel(oracle, M, K, N, form):
+    assert not gu.library_rule("_ZN4trdq22fused_takes_few_tokensElii", M, K, N) & 1
+    wbits = 4 if form == "w4" else 8
+    Xb, W, d, bias = wl.small_case(45, M, K, N, n_outliers=max(1, K // 144), outlier=40.0)
+    w = trdq.prepare_weights(gu.f32_to_dev(W), gu.f32_to_dev(d), wbits=wbits)
+    buf = torch.full((M + 1, N + 4), 7.0, dtype=torch.bfloat16, device=gu.dev())
+    Y = buf[:M, :N]
+    fused = trdq.linear_fused_asym if form == "asym" else trdq.linear_fused
+    fused(gu.bf16_to_dev(Xb), gu.f32_to_dev(d), w, Y, bias=gu.f32_to_dev(bias))
+    torch.cuda.synchronize()
+    assert (buf[M] == 7.0).all() and (buf[:, N:] == 7.0).all()
+    codes, _ = w.export()
+    if form == "asym":
+        ref = oracle.linear_asym(Xb, W, d, bias, exact_blas=True)
+    else:
+        ref = oracle.linear(Xb, W, d, bias, wbits=wbits, exact_blas=True)
+    gu.assert_y_close(gu.bf16_to_host(Y), ref["Y"], "Y (fused, oracle end to end)",
+                      *gu.narrow_code_masks(8, wbits, None, None, codes, ref["Wq"]))
+    w.close()
+
+
+# products with zero points: the 128 x 144 kernel whose two wave groups split K (an odd and an even number of units each), one
+# workgroup per tile, two per compute unit, and the ring kernel (rows of Y that are 8-byte aligned only)
+@pytest.mark.parametrize("M,K,N,pad", [(1280, 2432, 1152, 0), (1152, 4608, 1152, 0), (1024, 1280, 1152, 0), (4224, 640, 1152, 0),
+                                       (1408, 1152, 1136, 4), (1500, 1152, 1136, 4)])
+def test_products_with_zero_points(oracle, M, K, N, pad):
+    assert _direct(M, K, N, True) == -1 and (pad % 8 != 0 or not _rows(M, K, N, True))
+    Xb, W, d, bias = wl.small_case(42, M, K, N, n_outliers=max(1, K // 144), outlier=40.0)
+    w = trdq.prepare_weights(gu.f32_to_dev(W), gu.f32_to_dev(d))
+    Xq = torch.empty((M, K), dtype=torch.int8, device=gu.dev())
+    sx, zc = torch.empty(M, device=gu.dev()), torch.empty(M, dtype=torch.int32, device=gu.dev())
+    trdq.rotate_quant_asym(gu.bf16_to_dev(Xb), gu.f32_to_dev(d), Xq, sx, zc, warm=w)
+    buf = torch.empty((M + 1, N + pad), dtype=torch.bfloat16, device=gu.dev())
+    Y = buf[:M, :N]
+    acc = torch.full((M, N), -7, dtype=torch.int32, device=gu.dev())
+    for debug in (acc, None):
+        buf.fill_(7.0)
+        trdq.qgemm_asym(w, Xq, sx, zc, Y, bias=gu.f32_to_dev(bias), acc_debug=debug)
+    torch.cuda.synchronize()
+    assert (buf[M] == 7.0).all() and (buf[:, N:] == 7.0).all()
+    codes, scales = w.export()
+    q = Xq.cpu().numpy().astype(np.float64) + zc.cpu().numpy()[:, None]     # q - z, exact in float64 as the sums are
+    want = (q @ codes.astype(np.float64)).astype(np.int32)
+    assert np.array_equal(acc.cpu().numpy(), want), "int32 accumulators differ"
+    y = oracle.dequant(want, sx.cpu().numpy(), scales, bias)
+    gu.assert_y_same_codes(gu.bf16_to_host(Y), y, "Y (same codes)")
+    w.close()
