@@ -145,7 +145,7 @@ def _ptr(t):
     return t.ctypes.data
 
 
-_raw_stream = None      # () -> the current stream's hipStream_t, once torch is there
+_raw_stream = None      # (of a device index, the current stream's hipStream_t; the current device index), once torch is there
 
 
 def _stream(stream):
@@ -157,9 +157,9 @@ def _stream(stream):
     if _raw_stream is None:
         import torch
         torch.cuda.current_stream()                     # initialises torch's side, or raises its error
-        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
-        _raw_stream = (lambda: raw(device())) if raw else (lambda: torch.cuda.current_stream().cuda_stream)
-    return _raw_stream()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda _: torch.cuda.current_stream().cuda_stream)
+        _raw_stream = raw, torch.cuda.current_device
+    return _raw_stream[0](_raw_stream[1]())
 
 
 # ------------------------------------------------------------------ table

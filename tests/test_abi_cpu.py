@@ -323,6 +323,7 @@ def test_current_stream_without_the_private_lookup(monkeypatch):
     import torch
     streams = iter([5, 77, 78])
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=next(streams)))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
     monkeypatch.setattr(torch, "_C", types.SimpleNamespace())
     monkeypatch.setattr(trdq, "_raw_stream", None)
     assert trdq._stream(None) == 77 and trdq._stream(None) == 78
