@@ -294,7 +294,7 @@ trdq_status trdq_rotate_quant_dense(const void *X_dev, int64_t M, int64_t ldx, c
  * the activation side takes K <= 4608 (ERR_UNSUPPORTED beyond): 16-token workgroups up to K = 1536,
  * 8-token workgroups that run the second rotation twice (maxima, then codes) for wider rows.
  * trdq_rotate_quant_dense_rpr_ws is the same operation with a device workspace, which rows wider than
- * K = 1536 (and narrower rows from 16384 tokens on) use for a faster form (a workgroup per block with the
+ * K = 1536 (and narrower rows from 16384 tokens on) use for another form, for wide rows a faster one (a workgroup per block with the
  * rotation resident in LDS; the once-rotated values cross the permutation through the workspace as float32):
  * ws_dev holds at least trdq_rotate_quant_dense_rpr_ws_nbytes(M, K) bytes (4 (K + 1) roundup(M, 32); 0 for
  * M <= 0 and for K <= 1536 below 16384 tokens, and then ws_dev may be NULL), 16-byte aligned, and belongs to the call until it has finished on its stream;
@@ -480,7 +480,7 @@ trdq_status trdq_layer_set_group(trdq_layer *l, int g, const float *diag_dev, co
 /* Forward at sampling step `step`: looks up the group, then runs either the fused kernel
  * (fused > 0) or rotate_quant + qgemm through the caller's workspace (fused == 0):
  * Xq_ws_dev int8 [M, K] and sx_ws_dev float32 [M] (both may be NULL when fused > 0).
- * fused < 0 chooses: with the workspace the faster path by the library's measured rule (the fused kernel for few
+ * fused < 0 chooses: with the workspace by the library's measured rule (the fused kernel for few
  * tokens); without it (either pointer NULL) the fused kernel where one round of 16-token workgroups does (int8 weights,
  * K <= 1536), else ERR_NULL: the pair needs the workspace.
  * X_dev bf16 [M, K] dense; Y_dev bf16 [M, N] dense.

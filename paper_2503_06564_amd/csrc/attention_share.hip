@@ -32,12 +32,6 @@ __device__ __forceinline__ double wave_sum(double x)
 
 constexpr int kAhead = 4;                                             // 16-byte pieces of each operand in flight per lane
 
-// One workgroup's share of a segment: chunk `c` of `chunks`, in steps of its lanes x kAhead x 8 elements; the tail
-// (seg_len % 8) is taken element by element by the last chunk.  Lane 0..2 of the workgroup return the sums.
-// What bounds it is the memory: 5.3 TB/s read with one piece per lane in flight and a grid that was a few workgroups
-// more than one round (28 segments of 4096 x 1152: 74 chunks each, 2072 workgroups for 2048 places).
-// Figures there (28 segments), before and after: 104 -> 91 us as a whole (5.1 -> 5.8 TB/s), of which four pieces in flight
-// and the one round 7 and non-temporal loads 8; eight pieces in flight are no faster.
 // STREAM: non-temporal loads, for operands that together exceed the 256 MB memory-side cache (at 132 MB 25.8 against 25.6 us).
 template <bool STREAM>
 __device__ __forceinline__ uint4 load_piece(const uint16_t *p)
@@ -50,6 +44,12 @@ __device__ __forceinline__ uint4 load_piece(const uint16_t *p)
     }
 }
 
+// One workgroup's share of a segment: chunk `c` of `chunks`, in steps of its lanes x kAhead x 8 elements; the tail
+// (seg_len % 8) is taken element by element by the last chunk.  Lane 0..2 of the workgroup return the sums.
+// What bounds it is the memory: 5.3 TB/s read with one piece per lane in flight and a grid that was a few workgroups
+// more than one round (28 segments of 4096 x 1152: 74 chunks each, 2072 workgroups for 2048 places).
+// Figures there (28 segments), before and after: 104 -> 91 us as a whole (5.1 -> 5.8 TB/s), of which four pieces in flight
+// and the one round 7 and non-temporal loads 8; eight pieces in flight are no faster.
 template <bool STREAM>
 __device__ __forceinline__ double segment_sums(const uint16_t *__restrict__ a, const uint16_t *__restrict__ b, int64_t seg_len,
                                                int c, int chunks, double (*part)[3])

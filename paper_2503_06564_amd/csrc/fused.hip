@@ -280,10 +280,10 @@ __global__ __launch_bounds__(kThreads) void linear_fused_kernel(FusedArgs g)
 // on idle compute units is free, and fewer weight bytes per compute unit arrive sooner.  The arguments that the
 // first loads need are the ones delivered in registers at wave launch.
 //
-// Measured, back-to-back launches (an empty kernel: 2.2 us): 1152 -> 1152 int8 at 16 / 128 / 256 / 512 tokens
-// 4.8 / 5.4 / 6.2 / 7.1 us, against 9.8 / 10.0 / 10.2 / 11.1 for a form that split K over eight waves, rotated
+// Measured, launches replayed back to back (an empty kernel: 2.2 us): 1152 -> 1152 int8 at 16 / 128 / 256 / 512 tokens
+// 5.0 / 5.6 / 6.0 / 6.9 us, against 10.0 / 10.1 / 10.2 / 10.5 for a form that split K over eight waves, rotated
 // with lane exchanges (630 vector instructions per wave instead of 290), read row-major weights and passed the codes
-// through LDS, and 7.7-11.4 for the pair; int4 5.2 / 5.9 / 6.9 / 7.7; 4608 -> 1152 at 16 tokens 12.0 (int8), 12.9 (int4).
+// through LDS; int4 5.4 / 6.1 / 6.6 / 7.6; 4608 -> 1152 at 16 tokens 12.2 (int8), 12.9 (int4).
 constexpr int64_t kSmallMaxWorkgroups = 512;    // of the widest tile: at most two rounds
 constexpr int kSmallMaxBlocks = 36;
 
@@ -650,11 +650,13 @@ bool fused_takes_few_tokens(int64_t M, int K, int N)
     return K <= kSmallMaxBlocks * kBlock && small_workgroups(M, K, N) <= kSmallMaxWorkgroups;
 }
 
-// True where the fused kernel is the faster path: the few-token kernel in a single round of workgroups (two of
-// the small ones that one or two blocks make).  In a second round the repeated rotation costs more than the pair's
-// second launch, us: 1152 -> 4608 at 128 tokens 7.0 against 13.2 (256 workgroups), at 256 tokens 12.9 against 14.9;
-// 768 -> 3072 at 256 tokens (352) 11.0 against 10.7; 4608 -> 1152 at 64 tokens (144) 15.3 against 17.7, at 128 (288)
-// 28.2 against 18.7; 256 -> 512 at 2048 tokens (512) 6.4 against 7.7.
+// The layer's choice: the few-token kernel in a single round of workgroups (two of the small ones that one or two blocks
+// make).  In a second round the repeated rotation costs more than the pair's second launch.  us, fused against the pair: 1152 ->
+// 4608 at 128 tokens (256 workgroups) 6.9 / 8.7, at 256 12.0 / 11.3; 768 -> 3072 at 256 (352) 10.4 / 8.8; 256 -> 512 at 2048
+// (512) 6.2 / 7.0, at 4096 12.6 / 8.2; int4 1152 -> 4608 at 128 7.5 / 11.0, at 256 13.3 / 11.2.  Where a wave has two or three
+// blocks the line dates from a slower pair: it still holds at 1664 -> 1152 (64 tokens 7.0 / 7.2; int4 7.5 / 8.4) and for int4 up to
+// 3072 channels (2304 -> 1152 at 64 9.1 / 9.3), no longer for int8 from 2304 on (2304 -> 1152 at 16 tokens 7.8 / 7.0, 4608 ->
+// 1152 at 16 / 64 11.9 / 8.4, 14.3 / 9.2) and for int4 at 4608 (at 64 13.9 / 12.1).
 bool fused_pays(int64_t M, int K, int N)
 {
     return M > 0 && K % kBlock == 0 && K <= kSmallMaxBlocks * kBlock &&

@@ -960,8 +960,9 @@ bool tiled_rows_supports(const GemmArgs &a)
 }
 
 // Where this form is the faster one for row-major codes that the kernel for few tiles leaves (qgemm8_direct_tile < 0);
-// both sides measured on ten shapes from 256 -> 512 to 4608 -> 1152 at 130 ... 32768 tokens.  Against the tiled form the
-// half-line copies cost 12 % from 4096 tokens on (1152 -> 3456: 21.4 against 18.7 us), which puts it level with
+// both sides measured on ten shapes from 256 -> 512 to 4608 -> 1152 at 130 ... 32768 tokens.  Against the tiled form it
+// costs 12 % from 4096 tokens on (1152 -> 3456: 21.4 against 18.7 us; its half-line copies, its spills in the last two
+// k-steps -- 14 registers, 35 with zero points, against 7 -- or both: not measured apart), which puts it level with
 // the 128 x 144 and 256 x 256 kernels where tokens and channels are whole tiles; it wins where they are not, because the
 // others leave the remainder to the any-shape kernel, a second launch (or the whole product, below 1024 tokens or with
 // zero points), us, before and after: 1152 -> 3456 at 500 / 1500 / 5000 tokens 11.1 / 18.6 / 30.2 -> 8.4 / 12.6 / 26.3,
@@ -971,7 +972,8 @@ bool tiled_rows_supports(const GemmArgs &a)
 //     repeats a part 14000 tokens (1024 -> 2048 at 12000 34.6 -> 33.5, at 16000 39.7 -> 42.7).
 //   - Whole tiles: up to three quarters of the compute units have one (1152 -> 3456 at 1024 tokens 9.9 -> 9.5, 768 -> 2304 at
 //     1024 7.9 -> 6.8; 1152 -> 1152 at 4096, one each, 11.3 -> 11.6 with cold weights), for K < 1024 all of them, for long K
-//     half (4608 -> 1152 at 1024 19.6 -> 17.8, at 4096 24.4 -> 25.0).  Below K = 512, where the width is whole 128-channel
+//     half (4608 -> 1152 at 1024 19.6 -> 17.8, at 4096 24.4 -> 25.0).  (Not at every shape: 2048 -> 2304 at 1280 / 1536 tokens
+//     13.5 / 13.7 -> 13.9 / 14.1, -> 1152 at 2560 / 3072 12.7 / 13.1 -> 11.4 / 12.2.)  Below K = 512, where the width is whole 128-channel
 //     tiles too, the 128 x 128 kernel is the other one and has no K to walk: only at nearly one tile each (256 -> 2304 at
 //     512 / 1536 / 2048 tokens 4.5 / 5.4 / 6.3 -> 4.7 / 5.5 / 6.0; 128 -> 1152 at 1024 4.1 -> 4.5).  With zero points K < 1024
 //     only (768 -> 2304 at 1024 8.0 -> 7.5, 1152 -> 3456 9.9 -> 10.6).

@@ -7,12 +7,18 @@
 //
 // What bounds it is latency up to a few thousand tokens and the memory beyond.  The form before this one put the H_16 factor of
 // the rotation on the bf16 matrix pipe (the diagonal as three exact bf16 pieces): 241 vector instructions per 16 tokens and
-// block against 344 here, but its 166 registers left two waves per SIMD, its 16-token workgroups one per compute unit
-// at 4096 tokens, and a workgroup began by staging the pieces of the diagonal in LDS.  Here a wave needs 50 registers and no
-// table, so six to eight waves per SIMD cover each other's loads, exchange and stores, and the extra vector
-// work runs under the memory time.  us, that form and this one: 256 tokens x 1152 4.9 -> 3.0, 256 x 4608 10.8 -> 4.0, 4096 x 1152
-// 5.9 -> 4.6, 4096 x 4608 14.8 -> 12.5, 32768 x 1152 22.7 -> 20.7 (5.5 TB/s), 32768 x 4608 94 -> 80 (5.7 TB/s; a kernel that
-// only reads two bytes and writes one takes 72).  Codes that differ from float64's: 2.2e-6 of them against 2.6e-6 at K = 1152.
+// block against 344 here, but its 166 ... 198 registers left two or three waves per SIMD, its 16-token workgroups one per
+// compute unit at 4096 tokens, and a workgroup began by staging the pieces of the diagonal in LDS.  Here a wave needs 50
+// registers and no table, so six to eight waves per SIMD cover each other's loads, exchange and stores, and the extra vector
+// work runs under the memory time.  us, that form and this one, alone and back to back, inputs in the caches / behind the
+// memory-side one:
+//   rows          256 tokens x 1152  5.0 ->  3.0             4096 x 1152   5.7 ->  4.5 /  6.1 ->  5.4   32768 x 1152 22.5 -> 20.7 / 26.9 -> 23.4
+//                 256 x 4608        10.6 ->  3.9             4096 x 4608  14.7 -> 12.4 / 17.0 -> 14.9   32768 x 4608 95.9 -> 81.5 / 97.7 -> 81.6
+//   block-tiled   4096 x 1152        5.5 ->  4.5 /  5.9 ->  5.4   32768 x 1152 22.1 -> 20.9 / 26.1 -> 26.5
+//                 4096 x 4608       13.6 -> 12.6 / 15.9 -> 14.7   32768 x 4608 92.8 -> 84.7 / 92.3 -> 86.2
+// (a kernel that only reads two bytes and writes one: 2.8 / 4.0, 9.5 / 12.0 at 4096 tokens, 18.8 / 20.0, 74.3 / 74.5 at 32768).
+// Between the products of a transformer block, whose outputs are still being written back, it takes 7.2 and 13.5 us at 4096
+// tokens and 28.5 and 101 at 32768 (kernel trace).  Codes that differ from float64's: 2.2e-6 of them against 2.6e-6 at K = 1152.
 #include "device_utils.h"
 #include "rotate_lanes.h"
 #include "trdq_internal.h"

@@ -875,9 +875,13 @@ bool rotate_quant_dense_rpr_reads_frags32(int K) { return K / kBlock > 12; }
 
 // Rows wider than 12 blocks have a second form that goes through a workspace: the once-rotated values,
 // float32, channel-major, tokens rounded up to 32 (the first rotation writes whole groups of 32 tokens),
-// and behind them one row more for the tokens' maxima.  Narrower rows take it from 16384 tokens on, where
-// it is ahead of the 16-token kernel (95 against 110 us at 16384 x 1152, 167 against 213 us at 32768 x 1152;
-// 44 against 31 us at 4096 x 1152): that kernel streams both rotations' fragments from L2 for every 16 tokens.
+// and behind them one row more for the tokens' maxima.  Narrower rows take it from 16384 tokens on, a line from the time when
+// the 16-token kernel, which streams both rotations' fragments from L2 for every 16 tokens, had its second product on the
+// fp32 instruction (this form / that kernel: 95 / 110 us at 16384 x 1152, 167 / 213 at 32768).  Against the kernel of today it is
+// the better line for up to two blocks (256 channels at 16384 / 32768 / 65536 tokens 37 / 31, 43 / 54, 76 / 105); for wider
+// rows that kernel is ahead by up to 20 % at 16384 tokens (640 66 / 54, 1152 94 / 88, 1536 121 / 108), and from 24576 on the
+// two take turns within 10 % (1152 at 24576 / 28672 / 65536 123 / 125, 130 / 145, 319 / 326; 1536 164 / 157, 189 / 180,
+// 433 / 430).  The sizes from which callers need a workspace are part of the interface.
 static int64_t dense_ws_ldt(int64_t M) { return (M + 31) / 32 * 32; }
 
 size_t rotate_quant_dense_rpr_workspace_bytes(int64_t M, int K)
