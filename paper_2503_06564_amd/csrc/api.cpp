@@ -62,6 +62,9 @@ struct trdq_layer {
     int K = 0, N = 0, wbits = 0;
     std::vector<trdq_weights *> w;     // one per group (H_t depends on t), with its copy of the diagonal (null = ones)
     trdq_weights *spare = nullptr;     // the set that was replaced last: what the next replacement fills
+    // Whether somebody may read a replaced set after its replacement has returned: a graph that recorded a forward call, the
+    // holder of a handle from trdq_layer_weights, or kernels of a replacement that failed.
+    mutable std::atomic<bool> outside{false};
     std::vector<char> set;
 };
 
@@ -215,10 +218,10 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     return TRDQ_OK;
 }
 
-// Fills an allocated weight set from W_dev on `st` and waits for it.  perm_dev == nullptr: H_t(W) of Eq. 10 with
+// Fills an allocated weight set from W_dev on `st` and waits for it (wait_device: for everything on the device).  perm_dev == nullptr: H_t(W) of Eq. 10 with
 // one rotation; otherwise the full H_t(W) of Eq. 9 (rotation, P^T, rotation).  rot / rot2: dense blocks.
 trdq_status fill_weights(trdq_weights *w, const float *W_dev, const float *diag_dev, const int32_t *perm_dev,
-                         const trdq::Rotation *rot, const trdq::Rotation *rot2, hipStream_t st)
+                         const trdq::Rotation *rot, const trdq::Rotation *rot2, hipStream_t st, bool wait_device = false)
 {
     const int K = w->K, N = w->N;
     const float half = 0.08838834764831845f;            // 1 / sqrt(128)
@@ -246,7 +249,7 @@ trdq_status fill_weights(trdq_weights *w, const float *W_dev, const float *diag_
     } else {
         e = trdq::launch_prepare_quant(W_dev, diag_dev, nullptr, true, half, *w, amax, w->diag, st);
     }
-    const bool ok = e == hipSuccess && hipStreamSynchronize(st) == hipSuccess;
+    const bool ok = e == hipSuccess && (wait_device ? hipDeviceSynchronize() : hipStreamSynchronize(st)) == hipSuccess;
     if (!ok) (void)hipGetLastError();
     if (Wrot) (void)hipFree(Wrot);
     if (Wrot2) (void)hipFree(Wrot2);
@@ -257,7 +260,7 @@ trdq_status fill_weights(trdq_weights *w, const float *W_dev, const float *diag_
 trdq_status prepare_weights_impl(const float *W_dev, int K, int N, const float *diag_dev, const int32_t *perm_dev,
                                  int block, int wbits, void *stream, trdq_weights **out,
                                  const trdq::Rotation *rot = nullptr, const trdq::Rotation *rot2 = nullptr,
-                                 bool with_diag = false)
+                                 bool with_diag = false, bool wait_device = false)
 {
     if (!out) return TRDQ_ERR_NULL;
     *out = nullptr;
@@ -271,7 +274,7 @@ trdq_status prepare_weights_impl(const float *W_dev, int K, int N, const float *
     w->rotation = rot ? (rot2 ? trdq::kRotDenseRPR : trdq::kRotDense) : (perm_dev ? trdq::kRotHadamardRPR : trdq::kRotHadamard);
     trdq_status rc = hipGetDevice(&w->device) == hipSuccess ? TRDQ_OK : TRDQ_ERR_HIP;
     if (rc == TRDQ_OK) rc = alloc_weights(w, with_diag);
-    if (rc == TRDQ_OK) rc = fill_weights(w, W_dev, diag_dev, perm_dev, rot, rot2, static_cast<hipStream_t>(stream));
+    if (rc == TRDQ_OK) rc = fill_weights(w, W_dev, diag_dev, perm_dev, rot, rot2, static_cast<hipStream_t>(stream), wait_device);
     if (rc != TRDQ_OK) {
         (void)hipGetLastError();
         trdq_weights_destroy(w);
@@ -1069,23 +1072,34 @@ trdq_status trdq_layer_set_group(trdq_layer *l, int g, const float *diag_dev, co
     trdq_weights *&slot = l->w[(size_t)g];
     trdq_weights *w = nullptr;
     trdq_status rc;
+    // The one wait of a replacement: for its own kernels and for every call made before, on any stream, so that nothing reads
+    // the set that goes out of use.  (A wait before the first kernel and one after the last left the device idle twice:
+    // 192 us for the four linears of a block of width 1152 and a forward call of each, 150 with one.)
+    const bool retires = slot != nullptr;
     if (l->spare && l->spare->device == dev && (l->spare->diag != nullptr) == (diag_dev != nullptr)) {
-        // A set replaced earlier is filled (releasing one and allocating another cost 0.1-0.2 ms), once nothing reads it any
-        // more on any stream.  The group's own set is never written: launches made before go on with it, and it stays
-        // the group's set if this fails.
-        if (hipDeviceSynchronize() != hipSuccess) { (void)hipGetLastError(); return TRDQ_ERR_HIP; }
-        rc = fill_weights(l->spare, W_dev, diag_dev, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream));
-        if (rc != TRDQ_OK) return rc;
+        // A set replaced earlier is filled (releasing one and allocating another cost 0.1-0.2 ms).  Calls that read it were
+        // waited for when it was replaced.  The group's own set is never written: launches made before go on with it, and
+        // it stays the group's set if this fails.
+        if (l->outside.load(std::memory_order_relaxed) && hipDeviceSynchronize() != hipSuccess) {
+            (void)hipGetLastError();
+            return TRDQ_ERR_HIP;
+        }
+        rc = fill_weights(l->spare, W_dev, diag_dev, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream), retires);
+        if (rc != TRDQ_OK) {
+            l->outside.store(true, std::memory_order_relaxed);
+            return rc;
+        }
         w = l->spare;
         l->spare = nullptr;
     } else {
         rc = prepare_weights_impl(W_dev, l->K, l->N, diag_dev, nullptr, trdq::kBlock, l->wbits, stream, &w, nullptr, nullptr,
-                                  diag_dev != nullptr);
+                                  diag_dev != nullptr, retires);
         if (rc != TRDQ_OK) return rc;
     }
     if (slot) {
         trdq_weights_destroy(l->spare);      // (of another form: one spare set is kept)
         l->spare = slot;
+        if (slot->device != dev) l->outside.store(true, std::memory_order_relaxed);   // the wait was for another device
     }
     slot = w;
     l->set[(size_t)g] = 1;
@@ -1102,21 +1116,30 @@ trdq_status trdq_layer_forward(const trdq_layer *l, int step, const void *X_dev,
     if (!l->set[(size_t)g]) return TRDQ_ERR_MISMATCH;
     const trdq_weights *w = l->w[(size_t)g];
     const float *d = w->diag;
+    // a launch that a graph records may read the set after it has been replaced
+    auto launched = [&](trdq_status rc) {
+        if (rc != TRDQ_OK || M == 0 || l->outside.load(std::memory_order_relaxed)) return rc;
+        hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+        const bool known = hipStreamIsCapturing(static_cast<hipStream_t>(stream), &recording) == hipSuccess;
+        if (!known) (void)hipGetLastError();
+        if (!known || recording != hipStreamCaptureStatusNone) l->outside.store(true, std::memory_order_relaxed);
+        return rc;
+    };
     const bool have_ws = Xq_ws_dev && sx_ws_dev;
     if (fused > 0 || (fused < 0 && (have_ws ? trdq::fused_pays(M, l->K, l->N)
                                             : trdq::fused_needs_no_workspace(M, l->K, l->N, w->wbits))))
-        return trdq_linear_fused(X_dev, M, l->K, d, w, bias_dev, Y_dev, l->N, stream);
+        return launched(trdq_linear_fused(X_dev, M, l->K, d, w, bias_dev, Y_dev, l->N, stream));
     if (!have_ws) return TRDQ_ERR_NULL;
     // the workspace is private to the layer: block-tiled codes where the tiled product takes the shape
     // (M % 128 == 0 there, so the workspace size M * K is the same)
     if (trdq_qgemm_tiled_preferred(w, M) && aligned(Y_dev, 16)) {
         trdq_status rt = trdq_rotate_quant_tiled(X_dev, M, l->K, l->K, d, trdq::kBlock, Xq_ws_dev, sx_ws_dev, w, stream);
         if (rt != TRDQ_OK) return rt;
-        return trdq_qgemm_tiled(w, Xq_ws_dev, sx_ws_dev, M, bias_dev, Y_dev, l->N, nullptr, stream);
+        return launched(trdq_qgemm_tiled(w, Xq_ws_dev, sx_ws_dev, M, bias_dev, Y_dev, l->N, nullptr, stream));
     }
     trdq_status rc = trdq_rotate_quant_warm(X_dev, M, l->K, l->K, d, trdq::kBlock, Xq_ws_dev, sx_ws_dev, w, stream);
     if (rc != TRDQ_OK) return rc;
-    return trdq_qgemm(w, Xq_ws_dev, sx_ws_dev, M, bias_dev, Y_dev, l->N, nullptr, stream);
+    return launched(trdq_qgemm(w, Xq_ws_dev, sx_ws_dev, M, bias_dev, Y_dev, l->N, nullptr, stream));
 }
 
 trdq_status trdq_layer_weights(const trdq_layer *l, int g, const trdq_weights **w_out)
@@ -1124,6 +1147,7 @@ trdq_status trdq_layer_weights(const trdq_layer *l, int g, const trdq_weights **
     if (!l || !w_out) return TRDQ_ERR_NULL;
     if (g < 0 || g >= l->table.n_groups) return TRDQ_ERR_RANGE;
     if (!l->set[(size_t)g]) return TRDQ_ERR_MISMATCH;
+    l->outside.store(true, std::memory_order_relaxed);
     *w_out = l->w[(size_t)g];
     return TRDQ_OK;
 }

@@ -76,6 +76,49 @@ def test_replaced_set_is_left_alone(trdq):
     assert held[0][0].handle.value == held[2][0].handle.value == held[4][0].handle.value     # two sets take turns
 
 
+@pytest.mark.parametrize("recorded", [False, True])
+def test_calls_before_a_replacement_keep_their_set(trdq, recorded):
+    """Forward calls that wait on another stream, launched or replayed from a graph, give the outputs of the set they were
+    given, however many replacements follow at once."""
+    import torch
+    M, K, N = 1024, 384, 2304
+    layer = trdq.Layer(trdq.Table(4, 2), K, N, 8)
+    xb, W, d, _ = wl.small_case(3, M, K, N)
+    X, dd = bf16_to_dev(xb), f32_to_dev(d)
+    weights = [f32_to_dev((1.0 + i) * W) for i in range(4)]
+    ws = dict(Xq_ws=torch.empty((M, K), dtype=torch.int8, device="cuda"), sx_ws=torch.empty(M, device="cuda"))
+    want = []
+    for Wd in weights:
+        layer.set_group(1, dd, Wd)
+        Y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        layer.forward(3, X, Y, **ws)
+        torch.cuda.synchronize()
+        want.append(Y)
+    assert not torch.equal(want[2], want[3])
+    side, busy = torch.cuda.Stream(), torch.empty(1 << 28, device="cuda")
+    layer.set_group(1, dd, weights[0])
+    got = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    if recorded:
+        with torch.cuda.graph(graph, stream=side):
+            layer.forward(3, X, got, **ws, stream=side.cuda_stream)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(4):
+            busy.add_(1.0)                               # about a millisecond in front of the call
+        if recorded:
+            graph.replay()
+        else:
+            layer.forward(3, X, got, **ws, stream=side.cuda_stream)
+    for Wd in weights[1:]:
+        layer.set_group(1, dd, Wd)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want[0])
+    layer.forward(3, X, got, **ws)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want[3])
+
+
 @pytest.mark.parametrize("replaced_before", [0, 1, 2])
 def test_failed_replacement_keeps_the_group(trdq, replaced_before):
     """The preparation of a group ends with a wait for its stream, which a capturing stream refuses."""
