@@ -187,8 +187,7 @@ void trdq_table_destroy(trdq_table *t)
 namespace {
 
 // One device allocation per weight set (an allocation and its release cost 50-100 us each, more than the
-// kernels that fill it): codes, their block-tiled copy (symmetric sets), scales, column sums, the block maxima between the
-// two passes of a preparation that has no scratch matrix (8-bit codes after one Hadamard rotation), and the diagonal for a
+// kernels that fill it): codes, their block-tiled copy (symmetric sets), scales, column sums, and the diagonal for a
 // handle that keeps a copy.
 trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
 {
@@ -202,8 +201,6 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     const size_t at_scales = take((w4 ? (size_t)nb * N : (size_t)N) * sizeof(float));
     const size_t at_colsum = take((size_t)N * sizeof(float));          // int32 sums, or the scaled float ones of int4 codes
     const size_t at_zcw = asym ? take((size_t)N * sizeof(int32_t)) : 0;
-    const bool maxima = !asym && !w4 && w->rotation == trdq::kRotHadamard;
-    const size_t at_amax = maxima ? take((size_t)nb * N * sizeof(float)) : 0;
     const size_t at_diag = with_diag ? take((size_t)K * sizeof(float)) : 0;
     if (hipMalloc(&w->block, total) != hipSuccess) { w->block = nullptr; (void)hipGetLastError(); return TRDQ_ERR_ALLOC; }
     char *const base = static_cast<char *>(w->block);
@@ -213,7 +210,6 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     if (w4) w->colsumw = reinterpret_cast<float *>(base + at_colsum);
     else w->colsum = reinterpret_cast<int32_t *>(base + at_colsum);
     w->zcw = asym ? reinterpret_cast<int32_t *>(base + at_zcw) : nullptr;
-    w->amax = maxima ? reinterpret_cast<float *>(base + at_amax) : nullptr;
     w->diag = with_diag ? reinterpret_cast<float *>(base + at_diag) : nullptr;
     return TRDQ_OK;
 }
@@ -225,29 +221,27 @@ trdq_status fill_weights(trdq_weights *w, const float *W_dev, const float *diag_
 {
     const int K = w->K, N = w->N;
     const float half = 0.08838834764831845f;            // 1 / sqrt(128)
-    const size_t bytes = (size_t)K * N * sizeof(float), maxima = (size_t)(K / trdq::kBlock) * N * sizeof(float);
+    const size_t bytes = (size_t)K * N * sizeof(float);
     float *Wrot = nullptr, *Wrot2 = nullptr;            // rotated weights, where more than one kernel needs them
-    float *amax = w->amax;                              // block maxima: behind them, or the set's own
-    if (((rot || perm_dev) && hipMalloc(reinterpret_cast<void **>(&Wrot), bytes + maxima) != hipSuccess) ||
+    if (((rot || perm_dev) && hipMalloc(reinterpret_cast<void **>(&Wrot), bytes) != hipSuccess) ||
         (rot2 && hipMalloc(reinterpret_cast<void **>(&Wrot2), bytes) != hipSuccess)) {
         (void)hipGetLastError();
         if (Wrot) (void)hipFree(Wrot);
         return TRDQ_ERR_ALLOC;
     }
-    if (Wrot) amax = Wrot + (size_t)K * N;
     hipError_t e;
     if (rot) {
         // dense orthonormal blocks (nothing to normalise afterwards); Eq. 10 in full: rows gathered through the
         // permutation and rotated a second time
-        e = trdq::launch_prepare_rotate_dense(W_dev, K, N, rot->diag, nullptr, rot->R, Wrot, amax, st);
-        if (e == hipSuccess && rot2) e = trdq::launch_prepare_rotate_dense(Wrot, K, N, nullptr, perm_dev, rot2->R, Wrot2, amax, st);
-        if (e == hipSuccess) e = trdq::launch_prepare_quant(rot2 ? Wrot2 : Wrot, nullptr, nullptr, false, 1.0f, *w, amax, nullptr, st);
+        e = trdq::launch_prepare_rotate_dense(W_dev, K, N, rot->diag, nullptr, rot->R, Wrot, st);
+        if (e == hipSuccess && rot2) e = trdq::launch_prepare_rotate_dense(Wrot, K, N, nullptr, perm_dev, rot2->R, Wrot2, st);
+        if (e == hipSuccess) e = trdq::launch_prepare_quant(rot2 ? Wrot2 : Wrot, nullptr, nullptr, false, 1.0f, *w, nullptr, st);
     } else if (perm_dev) {
         // the Hadamard form of Eq. 9: two unnormalised rotations, 1/128
         e = trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, Wrot, st);
-        if (e == hipSuccess) e = trdq::launch_prepare_quant(Wrot, nullptr, perm_dev, true, 0.0078125f, *w, amax, nullptr, st);
+        if (e == hipSuccess) e = trdq::launch_prepare_quant(Wrot, nullptr, perm_dev, true, 0.0078125f, *w, nullptr, st);
     } else {
-        e = trdq::launch_prepare_quant(W_dev, diag_dev, nullptr, true, half, *w, amax, w->diag, st);
+        e = trdq::launch_prepare_quant(W_dev, diag_dev, nullptr, true, half, *w, w->diag, st);
     }
     const bool ok = e == hipSuccess && (wait_device ? hipDeviceSynchronize() : hipStreamSynchronize(st)) == hipSuccess;
     if (!ok) (void)hipGetLastError();
@@ -1116,9 +1110,10 @@ trdq_status trdq_layer_forward(const trdq_layer *l, int step, const void *X_dev,
     if (!l->set[(size_t)g]) return TRDQ_ERR_MISMATCH;
     const trdq_weights *w = l->w[(size_t)g];
     const float *d = w->diag;
-    // a launch that a graph records may read the set after it has been replaced
+    // a launch that a graph records may read the set after it has been replaced (the null stream is never recorded; asking
+    // costs 0.1 us)
     auto launched = [&](trdq_status rc) {
-        if (rc != TRDQ_OK || M == 0 || l->outside.load(std::memory_order_relaxed)) return rc;
+        if (rc != TRDQ_OK || M == 0 || !stream || l->outside.load(std::memory_order_relaxed)) return rc;
         hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
         const bool known = hipStreamIsCapturing(static_cast<hipStream_t>(stream), &recording) == hipSuccess;
         if (!known) (void)hipGetLastError();

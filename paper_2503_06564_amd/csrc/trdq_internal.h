@@ -31,7 +31,6 @@ struct Weights {
     int32_t *zcw = nullptr;      // asymmetric int8 weights (Eq. 1-3 per output channel): 128 - z_w [N]; codes hold q - 128
     float *colsumw = nullptr;    // int4 weights: 16 * sum_g s_w[g][n] * (sum of the codes of group g) [N]
     float *diag = nullptr;       // the handle's copy of the diagonal [K], if it keeps one
-    float *amax = nullptr;       // scratch of the preparation of 8-bit codes after one Hadamard rotation: block maxima [K/128, N]
     void *block = nullptr;       // the one device allocation that holds all of the above
     int device = 0;
 };
@@ -80,10 +79,9 @@ hipError_t launch_rotate_quant_rpr(const uint16_t *X, int64_t M, int K, int64_t 
 
 hipError_t launch_prepare_rotate(const float *W, int K, int N, const float *diag, float *Wrot, hipStream_t st);
 // Codes (both forms), scales and column sums of w from W: rotated on the way (rotate: divided by diag, rows read through
-// perm, row k of the input to the rotation = row perm[k], both optional; amax: scratch of K / 128 * N floats), or already rotated with its block maxima in amax.  norm: what undoes the
-// unnormalised butterflies (1/sqrt(128) per rotation applied).  diag_copy (optional) receives diag.
+// perm, row k of the input to the rotation = row perm[k], both optional), or already rotated.  norm: what undoes the unnormalised butterflies (1/sqrt(128) per rotation applied).  diag_copy (optional) receives diag.
 hipError_t launch_prepare_quant(const float *W, const float *diag, const int32_t *perm, bool rotate, float norm,
-                                const Weights &w, float *amax, float *diag_copy, hipStream_t st);
+                                const Weights &w, float *diag_copy, hipStream_t st);
 // asymmetric weight quantiser: lohi = scratch of 2 N floats; codes [N, K] = q - 128, scales [N], zcw [N] = 128 - z
 hipError_t launch_prepare_quant_asym(const float *Wrot, float *lohi, int K, int N, float norm, void *codes, float *scales,
                                      int32_t *zcw, hipStream_t st);
@@ -134,7 +132,7 @@ bool rotate_quant_dense_supports(int K);
 hipError_t launch_rotate_quant_dense(const uint16_t *X, int64_t M, int K, int64_t ldx, const void *pieces,
                                      int8_t *Xq, float *sx, hipStream_t st);
 hipError_t launch_prepare_rotate_dense(const float *W, int K, int N, const float *diag, const int32_t *perm,
-                                       const float *R, float *Wrot, float *amax, hipStream_t st);
+                                       const float *R, float *Wrot, hipStream_t st);
 size_t rotation_frags32_bytes(int K);
 bool rotate_quant_dense_rpr_reads_frags32(int K);    // whether the form without a workspace reads them for such rows
 hipError_t launch_rotation_frags32(const float *R, int K, void *frags, hipStream_t st);

@@ -30,6 +30,33 @@ def test_codes_and_scales(trdq, oracle, wbits, K, N, with_diag):
     assert not codes[:, N // 2].any() and not np.asarray(scales).reshape(-1, N)[:, N // 2].any()
 
 
+# 16 / 17 blocks: one or three to a wave; 48 / 49: kept in registers, or read twice; 2 ... 34 workgroups, whole groups of 32 or not
+@pytest.mark.parametrize("wbits", [8, 6, 4])
+@pytest.mark.parametrize("K,N", [(2048, 16), (2176, 272), (6144, 16), (6272, 32)])
+def test_codes_scales_and_sums_of_wide_rows(trdq, oracle, wbits, K, N):
+    """... with a diagonal that has entries beyond the range in which the kernel divides by reciprocals."""
+    import torch
+    _, W, d, _ = wl.small_case(37, 1, K, N)
+    for row, f in ((5, 1e-22), (K - 3, 1e21)):
+        d[row] *= f
+        W[row] *= np.float32(f)
+    w = trdq.prepare_weights(f32_to_dev(W), f32_to_dev(d), wbits=wbits)
+    codes, scales = w.export()
+    ref_codes, ref_scales = oracle.prepare_weights(W, d, 128, wbits)
+    assert_codes_close(codes, ref_codes, "weight codes")
+    assert_scales_close(scales, ref_scales, "weight scales")
+    if wbits == 4:
+        return
+    # the column sums, through the product that uses them: sum_k (code_x + zc) code_w
+    rng = np.random.default_rng(K)
+    Xq, zc = rng.integers(-128, 128, (20, K), dtype=np.int8), rng.integers(-127, 129, 20, dtype=np.int32)
+    acc = torch.empty((20, N), dtype=torch.int32, device="cuda")
+    trdq.qgemm_asym(w, torch.from_numpy(Xq).cuda(), torch.ones(20, device="cuda"), torch.from_numpy(zc).cuda(),
+                    torch.empty((20, N), dtype=torch.bfloat16, device="cuda"), acc_debug=acc)
+    torch.cuda.synchronize()
+    assert np.array_equal(acc.cpu().numpy(), (Xq.astype(np.int64) + zc[:, None]) @ codes.astype(np.int64))
+
+
 @pytest.mark.parametrize("wbits", [8, 4])
 def test_group_set_again(trdq, wbits):
     """A group that is replaced holds what a fresh layer would hold: same diagonal form, then the diagonal dropped, then
