@@ -92,8 +92,8 @@ trdq_status warm_range(const trdq_weights *next, int64_t M, bool tiled, const vo
     bytes = 0;
     if (!next || !next->codes) return TRDQ_OK;
     if (trdq_status rd = check_device(next->device); rd != TRDQ_OK) return rd;
-    warm = next->codes_tiled && (tiled || trdq::qgemm_reads_tiled_codes(*next, M, asym)) ? next->codes_tiled : next->codes;
-    bytes = (int64_t)next->N * next->K / (next->wbits == 4 ? 2 : 1);
+    warm = trdq::qgemm_reads_codes(*next, M, tiled, asym);
+    bytes = (int64_t)next->N * next->K / (next->wbits == 4 && warm != next->codes_wide ? 2 : 1);
     bytes -= bytes % 16;
     return TRDQ_OK;
 }
@@ -198,6 +198,7 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     size_t total = 0;
     auto take = [&](size_t bytes) { const size_t at = total; total += (bytes + 255) / 256 * 256; return at; };
     const size_t at_codes = take(code_bytes), at_tiled = tiled ? take(code_bytes) : 0;
+    const size_t at_wide = tiled && w4 ? take((size_t)K * N) : 0;
     const size_t at_scales = take((w4 ? (size_t)nb * N : (size_t)N) * sizeof(float));
     const size_t at_colsum = take((size_t)N * sizeof(float));          // int32 sums, or the scaled float ones of int4 codes
     const size_t at_zcw = asym ? take((size_t)N * sizeof(int32_t)) : 0;
@@ -206,6 +207,7 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     char *const base = static_cast<char *>(w->block);
     w->codes = base + at_codes;
     w->codes_tiled = tiled ? base + at_tiled : nullptr;
+    w->codes_wide = tiled && w4 ? base + at_wide : nullptr;
     w->scales = reinterpret_cast<float *>(base + at_scales);
     if (w4) w->colsumw = reinterpret_cast<float *>(base + at_colsum);
     else w->colsum = reinterpret_cast<int32_t *>(base + at_colsum);

@@ -180,7 +180,7 @@ __device__ __forceinline__ void rotate_column_block(float (&v)[16], int lane)
 template <int WBITS, bool ROTATE, int HOLD>
 __global__ __launch_bounds__(64 * kPcMostWaves) void prepare_columns_kernel(
     const float *__restrict__ W, int K, int N, const float *__restrict__ diag, const int32_t *__restrict__ perm,
-    float norm, float qmax, void *__restrict__ codes, void *__restrict__ tiled, float *__restrict__ scales,
+    float norm, float qmax, void *__restrict__ codes, void *__restrict__ tiled, void *__restrict__ wide, float *__restrict__ scales,
     int32_t *__restrict__ colsum, float *__restrict__ colsumw, float *__restrict__ diag_copy)
 {
     __shared__ float part[kPcMostWaves][kPcCols];
@@ -356,6 +356,10 @@ __global__ __launch_bounds__(64 * kPcMostWaves) void prepare_columns_kernel(
                 // units of 16 input channels (8 bytes), see qgemm_tiled.hip
                 *reinterpret_cast<uint2 *>(static_cast<uint8_t *>(tiled) + ((size_t)(n >> 4) * (K >> 6) + (k0 >> 6)) * 512 +
                                            (rg & 3) * 128 + (n & 15) * 8) = make_uint2(w[0], w[1]);
+                // 16 * code, one byte each, in the blocks of the int8 form; a word's low nibbles are its first four codes
+                *reinterpret_cast<uint4 *>(static_cast<int8_t *>(wide) + ((size_t)(n >> 4) * (K >> 6) + (k0 >> 6)) * 1024 +
+                                           (rg & 3) * 256 + (n & 15) * 16) =
+                    make_uint4((w[0] << 4) & 0xF0F0F0F0u, w[0] & 0xF0F0F0F0u, (w[1] << 4) & 0xF0F0F0F0u, w[1] & 0xF0F0F0F0u);
             }
             __syncthreads();
             if (wave == 0 && rg == 0)
@@ -520,7 +524,7 @@ hipError_t launch_prepare_quant(const float *W, const float *diag, const int32_t
     const float qmax = w.wbits == 4 ? 7.0f : w.qbits == 6 ? 31.0f : 127.0f;
     const int rounds = (nb + kPcMostWaves - 1) / kPcMostWaves;      // blocks of the busiest wave
     auto go = [&](auto kern, int nw) {
-        hipLaunchKernelGGL(kern, dim3(N / kPcCols), dim3(64 * nw), 0, st, W, K, N, diag, perm, norm, qmax, w.codes, w.codes_tiled,
+        hipLaunchKernelGGL(kern, dim3(N / kPcCols), dim3(64 * nw), 0, st, W, K, N, diag, perm, norm, qmax, w.codes, w.codes_tiled, w.codes_wide,
                            w.scales, w.colsum, w.colsumw, diag_copy);
         return hipGetLastError();
     };

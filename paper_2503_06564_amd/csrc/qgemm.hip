@@ -289,6 +289,7 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
         if (zc && !w.colsumw) return hipErrorInvalidValue;
         const int tile = variant < 0 ? qgemm4_direct_tile(M, w.K, w.N) : (variant < 11 ? variant - 8 : -1);
         if (tile >= 0) return launch_qgemm4_direct(a, acc_debug != nullptr, tile, st);
+        a.Wc = w.codes_wide;
         if ((variant == 11 || tiled4_rows_pays(M, w.K, w.N)) && tiled4_rows_supports(a))
             return launch_qgemm4_tiled_rows(a, acc_debug != nullptr, st);
     }
@@ -403,18 +404,21 @@ hipError_t launch_qgemm_tiled(const Weights &w, const int8_t *Xt, const float *s
     if (M == 0) return hipSuccess;
     if (!qgemm_tiled_supports(w, M, Y, ldy)) return hipErrorInvalidValue;
     GemmArgs a;
-    a.Xq = Xt; a.Wc = w.codes_tiled; a.sx = sx; a.sw = w.scales; a.bias = bias; a.Y = Y;
+    a.Xq = Xt; a.Wc = w.wbits == 4 ? w.codes_wide : w.codes_tiled; a.sx = sx; a.sw = w.scales; a.bias = bias; a.Y = Y;
     a.acc_debug = acc_debug; a.M = M; a.ldy = ldy; a.K = w.K; a.N = w.N;
     a.tiles_m = a.tiles_n = 0;
     return w.wbits == 4 ? launch_qgemm4_tiled(a, acc_debug != nullptr, st) : launch_qgemm8_tiled(a, acc_debug != nullptr, st);
 }
 
-bool qgemm_reads_tiled_codes(const Weights &w, int64_t M, bool asym)
+const void *qgemm_reads_codes(const Weights &w, int64_t M, bool tiled, bool asym)
 {
-    if (!w.codes_tiled) return false;
-    if (w.wbits == 4) return qgemm4_direct_tile(M, w.K, w.N) >= 0 || (!asym && tiled4_rows_pays(M, w.K, w.N));
-    return w.wbits == 8 &&
-           (qgemm8_direct_tile(M, w.K, w.N, asym) >= 0 || tiled_rows_pays(M, w.K, w.N, asym));
+    if (!w.codes_tiled) return w.codes;
+    if (w.wbits == 4) {
+        if (tiled) return w.codes_wide;
+        if (qgemm4_direct_tile(M, w.K, w.N) >= 0) return w.codes_tiled;
+        return !asym && tiled4_rows_pays(M, w.K, w.N) ? w.codes_wide : w.codes;
+    }
+    return tiled || qgemm8_direct_tile(M, w.K, w.N, asym) >= 0 || tiled_rows_pays(M, w.K, w.N, asym) ? w.codes_tiled : w.codes;
 }
 
 bool qgemm4_tiled_pays(int64_t M, int K, int N)

@@ -623,32 +623,32 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
 
 // ---- int4 weights on block-tiled operands ---------------------------------------------------------
 // Eq. 10's product with 4-bit weight codes and one scale per 128 input channels and output channel.
-// Activations as above (1 KB blocks).  Weights: the 8 packed bytes that hold 16 consecutive input
-// channels of one output channel (byte j of a 4-byte word = code(k0 + j) | code(k0 + 4 + j) << 4, as
-// in the row-major form) are the unit; a block is 16 output channels x 64 input channels = 512 bytes,
-// unit (n, q = k / 16) at ((n / 16) * (K / 64) + q / 4) * 512 + (q % 4) * 128 + (n % 16) * 8: lane order
-// again, 8 bytes per lane.  A lane widens its unit to 16 * code in registers (one shift-and-mask and
-// one mask per word), the matrix instruction is the int8 one, and after the two k-steps of a scale
-// group the int32 sums are folded into float accumulators with the group's scales; the factor 16
-// leaves with the token scale in the epilogue.
+// Activations as above (1 KB blocks).  Weights: 16 * code, one byte each, in the 1 KB blocks of the int8 form (the packed codes,
+// widened when the set is prepared: K * N more bytes per set), so that the operands are those of the int8 kernels.  After the
+// two k-steps of a scale group the int32 sums are folded into float accumulators with the group's scales; the factor 16 leaves
+// with the token scale in the epilogue.
 //
 // 128 x 128 tiles, four waves as 2 x 2 (64 x 64 wave tiles: 64 + 64 accumulator registers), two
-// workgroups per compute unit, a ring of five stages of 13 KB (8 activation blocks, 8 weight blocks, the
-// group's 128 scales).  Per wave and k-step four copies: two activation blocks, 1 KB of weight blocks
-// (two of them), 256 bytes of scales (waves 2 and 3 copy them a second time into a spare area, and
-// the scales travel with both k-steps of their group, so that every wave issues the same number of
-// requests per step; past the last k-step the last one is copied again, for the same reason).
-// The fold of group g is spread over the first k-step of group g + 1: tile by tile, the eight vector
-// instructions of a tile right before the matrix instruction that starts the tile's next sum from
-// zero, so that they run under the matrix instructions of the tiles before.
+// workgroups per compute unit, a ring of four stages of 16.5 KB (8 activation blocks, 8 weight blocks, the
+// group's 128 scales).  Per wave and k-step five copies: two activation blocks, two weight blocks, 256 bytes of scales
+// (waves 2 and 3 copy the same scales as 0 and 1, and they travel with both k-steps of their group, so that every wave
+// issues the same number of requests per step; past the last k-step the last one is copied again, for the same reason).
+// The fold of group g is spread over the first k-step of group g + 1: channel tile by channel tile, the vector
+// instructions of the tile's four sums in one run before the matrix instructions that start the next sums from zero.
+//
+// What bounds it is vector issue, two instructions per sum and group, and beyond 8192 tokens the power that sets the clock
+// (1.73 GHz in the loop).  Widening in the loop cost 1.5 vector instructions per matrix instruction: with packed codes in LDS,
+// and the folds between single matrix instructions, a workgroup's loop took 19100 cycles at K = 1152, now 17000.  us,
+// before and after: 1152 -> 3456 at 4096 / 16384 tokens 26.8 / 88.6 -> 26.0 / 84.5, 1152 -> 4608 at 16384 115.4 -> 110.7, 4608 ->
+// 1152 at 16384 106.1 -> 99.9, 768 -> 2304 at 2048 11.2 -> 10.2; 64-token tiles: 384 -> 2304 at 1024 6.1 -> 5.8.
 constexpr int kW4BM = 128, kW4BN = 128;
-constexpr int kW4NS = 5;
+constexpr int kW4NS = 4;
 constexpr int kW4XOff = 0;
 constexpr int w4_woff(int bm) { return bm * 64; }
-constexpr int w4_soff(int bm) { return bm * 64 + 4096; }
-constexpr int w4_stage(int bm) { return bm * 64 + 5120; }
+constexpr int w4_soff(int bm) { return bm * 64 + 8192; }
+constexpr int w4_stage(int bm) { return bm * 64 + 8192 + 512; }
 constexpr int w4_par_off(int bm) { return kW4NS * w4_stage(bm); }   // epilogue operands: [128 bias][pad][BM s_x]
-constexpr int w4_lds(int bm) { return w4_par_off(bm) + 2048; }      // 68608 B, with 64 tokens 48128 B
+constexpr int w4_lds(int bm) { return w4_par_off(bm) + 2048; }      // 69632 B, with 64 tokens 53248 B
 
 template <int BM, bool DEBUG, int FORM>
 __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kernel(GemmArgs g)
@@ -656,7 +656,7 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
     extern __shared__ __align__(16) int8_t smem[];
     constexpr int TM = BM / 32, TN = 4, NS = kW4NS;
     constexpr int XC = BM / 64;                       // activation blocks a wave copies per k-step
-    constexpr int P = XC + 2;                         // copies per wave and k-step
+    constexpr int P = XC + 3;                         // copies per wave and k-step
     constexpr int kW4WOff = w4_woff(BM), kW4SOff = w4_soff(BM), kW4Stage = w4_stage(BM), kW4ParOff = w4_par_off(BM);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)smem;
 #ifdef TRDQ_PROBE_PHASES
@@ -675,21 +675,19 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
     const int n0 = tile_n0<FORM>(g, tn, kW4BN);
 
     const int64_t xstride = (int64_t)KT * 1024;      // bytes from one 16-token group to the next
-    const int64_t wstride = (int64_t)KT * 512;       // ... one 16-channel group to the next
     constexpr int XSTEP = FORM == kBlocks ? 1024 : 64;  // bytes from one k-step of the activations to the next
     const int8_t *const xsrc = g.Xq + (m0 + 16 * XC * wave) * g.K;
-    const uint8_t *const wsrc = static_cast<const uint8_t *>(g.Wc) + (int64_t)(n0 / 16 + 2 * wave) * wstride;
+    const int8_t *const wsrc = static_cast<const int8_t *>(g.Wc) + (int64_t)(n0 / 16 + 2 * wave) * xstride;
     const uint32_t voffx = x_copy_off<FORM>(lane, g.K);
-    // the weight copy moves two blocks: lanes 0-31 the first, lanes 32-63 the one a channel group further
-    const uint32_t voffw = (uint32_t)((lane & 31) * 16) + (lane >= 32 ? (uint32_t)wstride : 0u);
+    const uint32_t voffw = (uint32_t)(lane * 16);
     const float *const ssrc = g.sw + n0 + (wave & 1) * 64;
     const uint32_t voffs = (uint32_t)(lane * 4);
     auto issue_one = [&](auto c_tag, int s, int st) {
         constexpr int c = decltype(c_tag)::value;
         const uint32_t sbase = lds0 + st * kW4Stage;
         if constexpr (c < XC) dma_1k(voffx, xsrc + c * xstride + (int64_t)s * XSTEP, sbase + kW4XOff + (XC * wave + c) * 1024);
-        else if constexpr (c == XC) dma_1k(voffw, wsrc + (int64_t)s * 512, sbase + kW4WOff + wave * 1024);
-        else copy_256_if(1, voffs, ssrc + (int64_t)(s >> 1) * g.N, sbase + kW4SOff + wave * 256);
+        else if constexpr (c < XC + 2) dma_1k(voffw, wsrc + (c - XC) * xstride + (int64_t)s * 1024, sbase + kW4WOff + (2 * wave + c - XC) * 1024);
+        else copy_256_if(1, voffs, ssrc + (int64_t)(s >> 1) * g.N, sbase + kW4SOff + (wave & 1) * 256);
     };
     auto issue = [&](int s, int st) {
         static_for_n<P>([&](auto c) { issue_one(c, s, st); });
@@ -715,12 +713,8 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
 #endif
 
     const int xfr = kW4XOff + (wm * TM) * 1024 + (FORM == kBlocks ? lane * 16 : x_frag_off<FORM>(l16, lg));
-    const int wfr = kW4WOff + (wn * TN) * 512 + lane * 8;
+    const int wfr = kW4WOff + (wn * TN) * 1024 + lane * 16;
     const int sfr = kW4SOff + (wn * 64 + lg * 4) * 4;
-    auto widen = [](uint2 p) {
-        return v4i{(int)((p.x << 4) & 0xF0F0F0F0u), (int)(p.x & 0xF0F0F0F0u),
-                   (int)((p.y << 4) & 0xF0F0F0F0u), (int)(p.y & 0xF0F0F0F0u)};
-    };
     v4i acc[TN][TM];
     v4f facc[TN][TM];
 #pragma unroll
@@ -728,11 +722,10 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
 #pragma unroll
         for (int b = 0; b < TM; ++b) { acc[a][b] = v4i{0, 0, 0, 0}; facc[a][b] = v4f{0.f, 0.f, 0.f, 0.f}; }
     v4i af[TN], bf[2][TM];
-    uint2 raw[TN];
     float4 sc[TN];
 #pragma unroll
     for (int a = 0; a < TN; ++a) {
-        af[a] = widen(*reinterpret_cast<const uint2 *>(smem + wfr + a * 512));
+        af[a] = *reinterpret_cast<const v4i *>(smem + wfr + a * 1024);
         sc[a] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
@@ -754,8 +747,6 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
         if constexpr (has_next) {
 #pragma unroll
             for (int b = 0; b < TM; ++b) bf[1 - HALF][b] = *reinterpret_cast<const v4i *>(nxt + xfr + b * 1024);
-#pragma unroll
-            for (int a = 0; a < TN; ++a) raw[a] = *reinterpret_cast<const uint2 *>(nxt + wfr + a * 512);
         }
         __builtin_amdgcn_sched_barrier(0);
         static_for_n<TN>([&](auto a_tag) {
@@ -774,13 +765,17 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
                         facc[a][b][2] += sc[a].z * (float)acc[a][b][2];
                         facc[a][b][3] += sc[a].w * (float)acc[a][b][3];
                     }
-                    acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[a], bf[HALF][b], v4i{0, 0, 0, 0}, 0, 0, 0);
-                } else {
-                    acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[a], bf[HALF][b], acc[a][b], 0, 0, 0);
                 }
             }
-            if constexpr (has_next) af[a] = widen(raw[a]);
-            if constexpr (a < P) issue_one(std::integral_constant<int, a>{}, kt + NS < KT ? kt + NS : KT - 1, st);
+            if constexpr (HALF == 0) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int bb = 0; bb < TM; ++bb) {
+                const int b = (a & 1) ? TM - 1 - bb : bb;
+                acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[a], bf[HALF][b], HALF == 0 ? v4i{0, 0, 0, 0} : acc[a][b], 0, 0, 0);
+            }
+            if constexpr (has_next) af[a] = *reinterpret_cast<const v4i *>(nxt + wfr + a * 1024);
+            issue_one(std::integral_constant<int, a>{}, kt + NS < KT ? kt + NS : KT - 1, st);
+            if constexpr (a == TN - 1 && P > TN) issue_one(std::integral_constant<int, P - 1>{}, kt + NS < KT ? kt + NS : KT - 1, st);
             __builtin_amdgcn_sched_barrier(0);
         });
         // The group's scales, once the fold of the group before is done, from the NEXT step's stage (they

@@ -26,6 +26,7 @@ struct Weights {
     void *codes = nullptr;
     float *scales = nullptr;
     void *codes_tiled = nullptr; // symmetric sets: the same codes in blocks of 16 channels x 64 k (1 KB; int4: 512 bytes), see qgemm_tiled.hip
+    void *codes_wide = nullptr;  // int4 sets: 16 * code as int8 in the 1 KB blocks of the int8 form, read by the product of many tokens
     int rotation = 0;            // which transform was folded in (kRot*): the activation side must apply the same one
     int32_t *colsum = nullptr;   // int8 weights: sum over k of the codes of every output channel [N]
     int32_t *zcw = nullptr;      // asymmetric int8 weights (Eq. 1-3 per output channel): 128 - z_w [N]; codes hold q - 128
@@ -65,8 +66,8 @@ hipError_t launch_rotate_quant(const uint16_t *X, int64_t M, int K, int64_t ldx,
 bool qgemm_tiled_supports(const Weights &w, int64_t M, const void *Y, int64_t ldy);
 hipError_t launch_qgemm_tiled(const Weights &w, const int8_t *Xt, const float *sx, int64_t M, const float *bias,
                               uint16_t *Y, int64_t ldy, int32_t *acc_debug, hipStream_t st);
-// whether the product of row-major codes reads the block-tiled copy of the weights for M tokens (built-in choice)
-bool qgemm_reads_tiled_codes(const Weights &w, int64_t M, bool asym = false);
+// the copy of the weight codes that the product of M tokens reads (built-in choice); tiled: the block-tiled product
+const void *qgemm_reads_codes(const Weights &w, int64_t M, bool tiled, bool asym = false);
 // measured choice between the two products for a layer object (true: the tiled pair is the faster one)
 bool qgemm_tiled_pays(int64_t M, int K, int N);
 bool qgemm4_tiled_pays(int64_t M, int K, int N);   // int4 weights
