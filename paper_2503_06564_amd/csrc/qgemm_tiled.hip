@@ -157,16 +157,21 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
     const int8_t *const ws8 = wsrc + 8 * gstride;     // the ninth weight block: wave 0 copies it
     // copy c (0 .. TM + 2) of this wave's share of k-step s into stage st: its TM activation blocks, two
     // weight blocks, and for wave 0 the ninth weight block
-    auto issue_one = [&](auto c_tag, int s, int st) {
+    auto issue_one = [&](auto c_tag, int s, int st, auto if_tag, bool on = true) {
         constexpr int c = decltype(c_tag)::value;
+        constexpr bool IF = decltype(if_tag)::value;    // requested only if `on`
         const uint32_t sbase = lds0 + st * STAGE;
         const int64_t so = (int64_t)s * 1024;
-        if constexpr (c < TM) dma_1k(voffx, xs[c] + (int64_t)s * XSTEP, sbase + (wave * TM + c) * 1024);
-        else if constexpr (c < TM + 2) dma_1k(voff, ws[c - TM] + so, sbase + (XB + wave + 4 * (c - TM)) * 1024);
-        else copy_1k_if(wave == 0, voff, ws8 + so, sbase + (XB + 8) * 1024);
+        auto copy = [&](uint32_t v, const int8_t *src, uint32_t to) {
+            if constexpr (IF) copy_1k_if(on, v, src, to);
+            else dma_1k(v, src, to);
+        };
+        if constexpr (c < TM) copy(voffx, xs[c] + (int64_t)s * XSTEP, sbase + (wave * TM + c) * 1024);
+        else if constexpr (c < TM + 2) copy(voff, ws[c - TM] + so, sbase + (XB + wave + 4 * (c - TM)) * 1024);
+        else copy_1k_if(wave == 0 && on, voff, ws8 + so, sbase + (XB + 8) * 1024);
     };
     auto issue = [&](int s, int st) {
-        static_for_n<TM + 3>([&](auto c) { issue_one(c, s, st); });
+        static_for_n<TM + 3>([&](auto c) { issue_one(c, s, st, std::integral_constant<bool, false>{}); });
     };
 
     // epilogue operands first (older than every tile copy, so the first wait covers them):
@@ -218,6 +223,12 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
     for (int b = 0; b < TM; ++b) bf[0][b] = *reinterpret_cast<const v4i *>(smem + (wave * TM + b) * 1024 + frox);
 
     int st = 0;
+    // WHOLE: the loop takes all but the last two steps, its last odd one requesting nothing.  Otherwise the last pair in which
+    // only the even step requests stands behind the loop, where tall tiles of row-major activations ran out of registers: 14
+    // spilled, 35 with zero points, behind full waits.  us, rows 1152 -> 3456 / 4608 at 4096 tokens 21.7 / 27.4 -> 21.2 / 26.4, 4608 at
+    // 16384 103 -> 98; the question on every odd copy makes it the slower one elsewhere (block-tiled 18.6 / 23.8 -> 19.1 / 24.7,
+    // short tiles 6.7 -> 7.1 at 1000 x 768 -> 2304).
+    constexpr bool WHOLE = BM == 256 && FORM != kBlocks;
     // One k-step on activation fragment set PAR.  REFILL: the next step exists; its fragments are read
     // while this step's matrix instructions run (after waiting for vmcnt(WAITN) and the barrier).
     // ISSUE: the step three ahead exists and is requested into this step's stage.
@@ -247,7 +258,9 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
             if constexpr (REFILL) af[a] = *reinterpret_cast<const v4i *>(nxt + (XB + a) * 1024);
             // the copies of the step three ahead go out one at a time between the matrix instructions
             // (bunched, they stall the wave at the compute unit's copy path)
-            if constexpr (ISSUE && a < TM + 3) issue_one(std::integral_constant<int, a>{}, kt + kNS, st);
+            if constexpr (ISSUE && a < TM + 3)
+                issue_one(std::integral_constant<int, a>{}, kt + kNS, st, std::integral_constant<bool, WHOLE && PAR == 1>{},
+                          !(WHOLE && PAR == 1) || kt + kNS < KT);
             if constexpr (REFILL) __builtin_amdgcn_sched_barrier(0);
         });
         st = nst;
@@ -257,7 +270,12 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
     using Yes = std::integral_constant<bool, true>;
     using No = std::integral_constant<bool, false>;
     using WP = std::integral_constant<int, PMIN>;
-    if (KT >= 4) {
+    if constexpr (WHOLE) {
+        for (int kt = 0; kt + 2 < KT; kt += 2) {
+            step(I0{}, Yes{}, Yes{}, WP{}, kt);
+            step(I1{}, Yes{}, Yes{}, WP{}, kt + 1);
+        }
+    } else if (KT >= 4) {
         int kt = 0;
         for (; kt + 4 < KT; kt += 2) {
             step(I0{}, Yes{}, Yes{}, WP{}, kt);
@@ -956,8 +974,7 @@ bool tiled_rows_supports(const GemmArgs &a)
 
 // Where this form is the faster one for row-major codes that the kernel for few tiles leaves (qgemm8_direct_tile < 0);
 // both sides measured on ten shapes from 256 -> 512 to 4608 -> 1152 at 130 ... 32768 tokens.  Against the tiled form it
-// costs 12 % from 4096 tokens on (1152 -> 3456: 21.4 against 18.7 us; its half-line copies, its spills in the last two
-// k-steps -- 14 registers, 35 with zero points, against 7 -- or both: not measured apart), which puts it level with
+// costs 12 % from 4096 tokens on (1152 -> 3456: 21.2 against 18.7 us; its half-line copies), which puts it near
 // the 128 x 144 and 256 x 256 kernels where tokens and channels are whole tiles; it wins where they are not, because the
 // others leave the remainder to the any-shape kernel, a second launch (or the whole product, below 1024 tokens or with
 // zero points), us, before and after: 1152 -> 3456 at 500 / 1500 / 5000 tokens 11.1 / 18.6 / 30.2 -> 8.4 / 12.6 / 26.3,
@@ -972,6 +989,10 @@ bool tiled_rows_supports(const GemmArgs &a)
 //     tiles too, the 128 x 128 kernel is the other one and has no K to walk: only at nearly one tile each (256 -> 2304 at
 //     512 / 1536 / 2048 tokens 4.5 / 5.4 / 6.3 -> 4.7 / 5.5 / 6.0; 128 -> 1152 at 1024 4.1 -> 4.5).  With zero points K < 1024
 //     only (768 -> 2304 at 1024 8.0 -> 7.5, 1152 -> 3456 9.9 -> 10.6).
+//     And from more than one to four tiles per compute unit, where a launch is one round of tall and short tiles, if every die
+//     gets whole bands of tall ones (M % 2048; with 12 panels at 3072 tokens 1152 -> 3456 / 4608 22.0 / 22.6 -> 20.0 / 25.0), below K =
+//     2304: 1152 -> 3456 / 4608 at 4096 tokens 22.3 / 27.8 -> 21.6 / 26.6, 1024 -> 2016 at 6144 20.2 -> 18.5, 640 -> 1296 at 8192 15.5 -> 14.0,
+//     1152 -> 1152 at 8192 16.3 -> 16.2, 768 -> 2304 at 4096 12.9 -> 13.0 (2304 -> 2304 at 4096 24.3 -> 25.2).
 //   - Zero points: the only other kernel that takes them at any shape is the any-shape one (768 -> 3072 at 4096 tokens
 //     23.2 -> 19.1, 1152 -> 4608 at 32700 tokens 268 -> 215).
 bool tiled_rows_pays(int64_t M, int K, int N, bool asym)
@@ -983,6 +1004,7 @@ bool tiled_rows_pays(int64_t M, int K, int N, bool asym)
         if (asym && K >= 1024) return false;
         const int64_t tiles = (M / 128) * (int64_t)(N / kBN), cus = num_cus();
         if (K < 512 && N % 128 == 0) return K >= 256 && tiles > cus * 7 / 8 && tiles <= cus;
+        if (!asym && K >= 512 && K < 2304 && M % 2048 == 0 && tiles > cus && tiles <= 4 * cus) return true;
         return tiles <= (K < 1024 ? cus : K < 2304 ? cus * 3 / 4 : cus / 2);
     }
     if (asym) return true;

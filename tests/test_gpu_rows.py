@@ -56,3 +56,32 @@ def test_edges(oracle, M, K, N, asym):
     assert np.array_equal(acc.cpu().numpy(), want), "int32 accumulators differ"
     y = oracle.dequant(want, sx.cpu().numpy(), scales, bias)
     gu.assert_y_same_codes(gu.bf16_to_host(Y), y, "Y (same codes)")
+
+
+# tall tiles with 2, 4, 6 and 18 k-steps: the loop over all but the last two of them empty, once round, and more
+@pytest.mark.parametrize("M,K,N", [(33000, 128, 288), (33000, 256, 288), (16500, 384, 576), (4096, 1152, 3456)])
+@pytest.mark.parametrize("asym", [False, True])
+def test_tall_tiles(M, K, N, asym):
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    w = trdq.prepare_weights(0.02 * torch.randn(K, N, generator=g, device="cuda"), None)
+    Xq = torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    sx, bd = torch.rand(M, generator=g, device="cuda"), torch.randn(N, generator=g, device="cuda")
+    zc = torch.randint(-127, 129, (M,), generator=g, device="cuda", dtype=torch.int32)
+    Y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    acc = torch.full((M, N), -7, dtype=torch.int32, device="cuda")
+    for debug in (acc, None):
+        Y.fill_(7.0)
+        if asym:
+            trdq.qgemm_asym(w, Xq, sx, zc, Y, bias=bd, acc_debug=debug)
+        else:
+            trdq.qgemm(w, Xq, sx, Y, bias=bd, acc_debug=debug)
+    codes, scales = w.export()
+    q = Xq.float() + (zc.float()[:, None] if asym else 0.0)          # sums below 2^24: exact in float32
+    want = q @ torch.from_numpy(codes.astype(np.float32)).cuda()
+    if K > 256:                                                       # (beyond: in float64)
+        want = q.double() @ torch.from_numpy(codes.astype(np.float64)).cuda()
+    assert torch.equal(acc, want.int())
+    y = acc.double() * sx.double()[:, None] * torch.from_numpy(scales.reshape(1, N).astype(np.float64)).cuda() + bd.double()
+    # bf16 rounds to 2^-9 of the value; the float32 epilogue adds at most 4 * 2^-24 of the product's and the bias' size
+    off = (Y.double() - y).abs() - 2.0 ** -8 * y.abs()
+    assert (off <= 2.0 ** -21 * (y.abs() + 2.0 * bd.double().abs())).all()
