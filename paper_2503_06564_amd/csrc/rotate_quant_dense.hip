@@ -198,23 +198,30 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_kernel(
 // (non-negative floats order like integers; sx cleared before), kSinkCodes repeats the products,
 // quantises and stores; a last kernel turns the maxima in sx into scales.
 //
-// The same kernel carries Eq. 10 with both rotations dense for wide rows, in three launches around a
-// workspace T of once-rotated values, float32, CHANNEL-major ([K][ldt], ldt = tokens rounded up to 32):
-//   kSinkRows          first rotation; the operands of the matrix instruction trade places, so that a lane
-//                      ends up with four consecutive tokens of one channel and stores them as 16 bytes of T;
-//   GATHER + kSinkMaxima / kSinkCodes
-//                      second rotation; a lane's operand element k of a k-step is T[perm[b*128 + k]][token]
-//                      (a 4-byte load; the 16 tokens of a lane row are 64 consecutive bytes; the 128 row
-//                      numbers wait in LDS), float32, so it is split exactly into three bf16 pieces like the
-//                      rotation itself, and the product takes the six piece pairs down to 2^-24 of |r||t|
-//                      (hi.hi, hi.mid, mid.hi, mid.mid, hi.lo, lo.hi), each rotation fragment read from LDS
-//                      once for all its pairs.
+// The same kernel carries Eq. 10 with both rotations dense, around a workspace T of float32 values, CHANNEL-major
+// ([K][ldt], ldt = tokens rounded up to 32):
+//   kSinkRows     first rotation; the operands of the matrix instruction trade places, so that a lane
+//                 ends up with four consecutive tokens of one channel and stores them as 16 bytes of T;
+//   kSinkInPlace  second rotation; a lane's operand element k of a k-step is T[perm[b*128 + k]][token]
+//                 (a 4-byte load; the 16 tokens of a lane row are 64 consecutive bytes; the 128 row
+//                 numbers wait in LDS), float32, so it is split exactly into three bf16 pieces like the
+//                 rotation itself, and the product takes the six piece pairs down to 2^-24 of |r||t|
+//                 (hi.hi, hi.mid, mid.hi, mid.mid, hi.lo, lo.hi), each rotation fragment read from LDS
+//                 once for all its pairs.  The results replace the values they were formed from: nobody else reads rows perm[b*128 ..]
+//                 of T, perm being a permutation, and a wave has read all 128 rows of its tokens before it stores.  Their maxima
+//                 per token are merged by atomic maxima.  A table that names a row twice (after clamping, entries are not
+//                 checked before) is noticed by the first rotation: the maxima carry a sign, and nothing is stored;
+//   dense_codes_kernel   streams T once, quantises, and turns channel-major values into rows of codes; maxima with a sign:
+//                 T still holds once-rotated values, and it forms the products first.
 // Here the token maxima have a row of their own behind T (amax_tok), cleared by the first rotation's first block,
 // and the first block of the codes launch writes the scales: no clearing or scaling kernels around the three.
+// (Until the results were kept, the second rotation ran twice, for the maxima and for the codes: 4096 x 1664 / 2304 / 4608 44 / 61 / 95
+// us, now 40 / 53 / 81, and 16384 x 4608 331, now 306.  Of the 81, traced, the first rotation has 32, the second 42, the codes 15; all nine
+// piece products make the second 49.)
 // (Tried and no faster, same box, 4096 and 32768 tokens of 4608 channels: rows of T written in permuted order
 // so that the second rotation reads consecutive rows; 16-byte loads of T with a change of layout through
 // LDS instead of the 4-byte ones; two accumulator chains instead of four.)
-enum DenseSink { kSinkMaxima = 0, kSinkCodes = 1, kSinkRows = 2 };
+enum DenseSink { kSinkMaxima = 0, kSinkCodes = 1, kSinkRows = 2, kSinkInPlace = 3 };
 
 // eight float32 -> their exact three-way split by truncation, each piece eight bf16 in operand order
 // (a byte permute takes the upper halves of two words: no masks for the packing)
@@ -237,17 +244,18 @@ __device__ __forceinline__ void split3_bf16(const float (&v)[8], v8bf &hi, v8bf 
     lo = l.v;
 }
 
-template <int SINK, int TT, bool GATHER>
+__device__ __forceinline__ int clamp_channel(int p, int K) { return p < 0 ? 0 : (p >= K ? K - 1 : p); }
+
+template <int SINK, int TT>
 __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
     const uint16_t *__restrict__ X, int64_t M, int nb, int64_t ldx, const uint4 *__restrict__ pieces,
-    float *__restrict__ amax_tok, float *__restrict__ scale_out, int8_t *__restrict__ Xq,
-    const float *__restrict__ Tin, const int32_t *__restrict__ perm, float *__restrict__ Tout, int64_t ldt)
+    float *__restrict__ amax_tok, int8_t *__restrict__ Xq, const int32_t *__restrict__ perm, float *T, int64_t ldt)
 {
     // one token tile of the float32 operand is requested a group ahead (like the bf16 one); two tiles are
     // requested at the top of their own group (no registers to hold both across the products), and the
     // wave that shares the SIMD covers the wait
+    constexpr bool GATHER = SINK == kSinkInPlace;
     constexpr bool AHEAD = GATHER && TT == 1;
-    static_assert(!(GATHER && SINK == kSinkRows), "the second rotation ends in maxima or codes");
     constexpr bool QUANT = SINK == kSinkCodes;
     extern __shared__ __align__(16) uint4 lds_pieces[];           // [12][8][64] fragments of this block
     const int K = nb * kBlock;
@@ -255,6 +263,17 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, g = lane >> 4;
+    constexpr int TABLE = SINK == kSinkRows ? 36 * kBlock / 512 : 1;              // K <= 4608, all requests in flight
+    int row[TABLE];
+    if constexpr (SINK == kSinkRows) {
+        if (b == 0) {
+#pragma unroll
+            for (int i = 0; i < TABLE; ++i) {
+                const int k = i * 512 + threadIdx.x;
+                row[i] = perm[k < K ? k : K - 1];
+            }
+        }
+    }
     {   // the block's pieces: all twelve requests of a lane in flight, then the LDS writes
         static_assert(kPiecesPerBlock % 512 == 0, "whole rounds of the workgroup");
         constexpr int ROUNDS = kPiecesPerBlock / 512;
@@ -264,14 +283,26 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
 #pragma unroll
         for (int i = 0; i < ROUNDS; ++i) lds_pieces[i * 512 + threadIdx.x] = tmp[i];
     }
-    // second rotation: the rows of T that are the block's 128 input channels, and behind them eight waves' worth
-    // of rows in which finished codes wait (64 x 8 words per token tile)
+    // second rotation: the rows of T that are the block's 128 input channels
     int *const rowtab = reinterpret_cast<int *>(lds_pieces + kPiecesPerBlock);
-    uint32_t *const code_lds = reinterpret_cast<uint32_t *>(rowtab + kBlock) + wave * (TT * 8 * 64);
+    // whether the table names a row twice: the sign of the first rotation's cleared maxima
+    uint32_t sign = 0;
     if constexpr (GATHER) {
-        if (threadIdx.x < kBlock) {
-            int p = perm[b * kBlock + threadIdx.x];
-            rowtab[threadIdx.x] = p < 0 ? 0 : (p >= K ? K - 1 : p);
+        if (threadIdx.x < kBlock) rowtab[threadIdx.x] = clamp_channel(perm[b * kBlock + threadIdx.x], K);
+        sign = __builtin_amdgcn_readfirstlane(__float_as_uint(amax_tok[0])) & 0x80000000u;
+    }
+    if constexpr (SINK == kSinkRows) {
+        if (b == 0) {                                             // of two entries with the same row one reads the other's number
+            uint16_t *const last = reinterpret_cast<uint16_t *>(lds_pieces + kPiecesPerBlock);      // [K]
+#pragma unroll
+            for (int i = 0; i < TABLE; ++i)
+                if (i * 512 + threadIdx.x < K) last[clamp_channel(row[i], K)] = (uint16_t)(i * 512 + threadIdx.x);
+            __syncthreads();
+            bool twice = false;
+#pragma unroll
+            for (int i = 0; i < TABLE; ++i)
+                if (i * 512 + threadIdx.x < K) twice |= last[clamp_channel(row[i], K)] != i * 512 + threadIdx.x;
+            sign = __builtin_amdgcn_readfirstlane(__syncthreads_or(twice)) ? 0x80000000u : 0u;
         }
     }
     __syncthreads();
@@ -296,7 +327,7 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
     // float32 source: rows of T (token-padded, so tokens past M read what the first rotation wrote for its
     // repeated rows); element e of k-step s is row rowtab[32 s + 8 g + e], token l16 of the tile
     auto gather_x = [&](float (&raw)[4][8], int64_t gr, int tt) {
-        const float *const tile = Tin + gr * TOK + tt * 16 + l16;
+        const float *const tile = T + gr * TOK + tt * 16 + l16;
         int g8 = 8 * g;
         asm volatile("" : "+v"(g8));                              // keeps the row-number reads inside the group loop
 #pragma unroll
@@ -337,26 +368,26 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
         } else {
             load_x(xnext, nxt);
         }
-        float inv[TT], amax[TT];
+        constexpr int NA = GATHER ? 4 : 1;                        // in place a lane holds four tokens of one channel
+        float inv[TT], amax[TT][NA];
         int64_t token[TT];
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
             token[tt] = gr * TOK + tt * 16 + l16;
-            amax[tt] = 0.0f;
             inv[tt] = 0.0f;
+#pragma unroll
+            for (int j = 0; j < NA; ++j) amax[tt][j] = 0.0f;
             if constexpr (QUANT) {
                 if (token[tt] < M) {
                     const float a = amax_tok[token[tt]];
                     inv[tt] = a > 0.0f ? 127.0f / a : 0.0f;
-                    if (scale_out != nullptr && b == 0 && g == 0) scale_out[token[tt]] = a / 127.0f;
                 }
             }
         }
         if constexpr (SINK == kSinkRows) {                        // the first block's workgroups clear the maxima
-            if (amax_tok != nullptr && b == 0 && lane < TOK) amax_tok[gr * TOK + lane] = 0.0f;
+            if (b == 0 && lane < TOK) amax_tok[gr * TOK + lane] = __uint_as_float(sign);
         }
-        // the codes of a finished tile wait in registers, or (second rotation, short of registers) in LDS
-        uint32_t code[QUANT && !GATHER ? TT : 1][8];
+        uint32_t code[QUANT ? TT : 1][8];
         int lane_off = lane;                                      // keeps the fragment reads inside this loop
         asm volatile("" : "+v"(lane_off));
         // what becomes of a finished tile t (acc[tt][j]: see the sinks above)
@@ -364,17 +395,22 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) {
                 if constexpr (SINK == kSinkCodes) {
-                    const uint32_t c = pack4_low_bytes(quant_bits(acc[tt][0], inv[tt]), quant_bits(acc[tt][1], inv[tt]),
-                                                       quant_bits(acc[tt][2], inv[tt]), quant_bits(acc[tt][3], inv[tt]));
-                    if constexpr (GATHER) code_lds[(tt * 8 + t) * 64 + lane] = c;
-                    else code[tt][t] = c;
-                } else if constexpr (SINK == kSinkMaxima)
-                    amax[tt] = fmaxf(amax[tt], fmaxf(fmaxf(fabsf(acc[tt][0]), fabsf(acc[tt][1])),
-                                                     fmaxf(fabsf(acc[tt][2]), fabsf(acc[tt][3]))));
-                else                                              // tokens 4 g .. 4 g + 3 of channel c(t, l16)
-                    *reinterpret_cast<float4 *>(Tout + (int64_t)(b * kBlock + 32 * (l16 >> 2) + 4 * t + (l16 & 3)) * ldt +
-                                                gr * TOK + tt * 16 + 4 * g) =
-                        make_float4(acc[tt][0], acc[tt][1], acc[tt][2], acc[tt][3]);
+                    code[tt][t] = pack4_low_bytes(quant_bits(acc[tt][0], inv[tt]), quant_bits(acc[tt][1], inv[tt]),
+                                                  quant_bits(acc[tt][2], inv[tt]), quant_bits(acc[tt][3], inv[tt]));
+                } else if constexpr (SINK == kSinkMaxima) {
+                    amax[tt][0] = fmaxf(amax[tt][0], fmaxf(fmaxf(fabsf(acc[tt][0]), fabsf(acc[tt][1])),
+                                                           fmaxf(fabsf(acc[tt][2]), fabsf(acc[tt][3]))));
+                } else {                                          // tokens 4 g .. 4 g + 3 of channel c(t, l16)
+                    const int c = 32 * (l16 >> 2) + 4 * t + (l16 & 3);
+                    if constexpr (GATHER) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) amax[tt][j] = fmaxf(amax[tt][j], fabsf(acc[tt][j]));
+                    }
+                    const int64_t row = GATHER ? rowtab[c] : b * kBlock + c;
+                    if (!GATHER || sign == 0)
+                        *reinterpret_cast<float4 *>(T + row * ldt + gr * TOK + tt * 16 + 4 * g) =
+                            make_float4(acc[tt][0], acc[tt][1], acc[tt][2], acc[tt][3]);
+                }
             }
         };
         if constexpr (GATHER) {
@@ -414,7 +450,8 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
 #pragma unroll
                         for (int tt = 0; tt < TT; ++tt) {
                             const v8bf x = bp == 2 ? xlo[tt][s] : (bp == 1 ? xmid[tt][s] : xcur[tt][s]);
-                            ch[tt][s % NCH] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, x, ch[tt][s % NCH], 0, 0, 0);
+                            // rows = tokens, columns = the tile's channels
+                            ch[tt][s % NCH] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, a.v, ch[tt][s % NCH], 0, 0, 0);
                         }
                     }
                 }
@@ -464,22 +501,27 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) {
             if constexpr (SINK == kSinkCodes) {
-                uint32_t c[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    if constexpr (GATHER) c[t] = code_lds[(tt * 8 + t) * 64 + lane];
-                    else c[t] = code[tt][t];
-                }
+                const uint32_t (&c)[8] = code[tt];
                 if (token[tt] < M) {
                     uint4 *dst = reinterpret_cast<uint4 *>(Xq + token[tt] * K + b * kBlock + 32 * g);
                     dst[0] = make_uint4(c[0], c[1], c[2], c[3]);
                     dst[1] = make_uint4(c[4], c[5], c[6], c[7]);
                 }
             } else if constexpr (SINK == kSinkMaxima) {
-                float m = fmaxf(amax[tt], __shfl_xor(amax[tt], 16));
+                float m = fmaxf(amax[tt][0], __shfl_xor(amax[tt][0], 16));
                 m = fmaxf(m, __shfl_xor(m, 32));
                 if (g == 0 && token[tt] < M)
                     atomicMax(reinterpret_cast<unsigned int *>(amax_tok + token[tt]), __float_as_uint(m));
+            } else if constexpr (SINK == kSinkInPlace) {
+                float m = 0.0f;                                   // lane j of a row merges token 4 g + j
+#pragma unroll
+                for (int j = 0; j < NA; ++j) {
+                    const float over = row16_max(amax[tt][j]);
+                    if (l16 == j) m = over;
+                }
+                const int64_t tok = gr * TOK + tt * 16 + 4 * g + l16;
+                if (l16 < 4 && tok < M)
+                    atomicMax(reinterpret_cast<unsigned int *>(amax_tok + tok), __float_as_uint(m) | sign);
             }
         }
         if constexpr (AHEAD) {
@@ -490,6 +532,63 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
 #pragma unroll
                 for (int s = 0; s < 4; ++s) xcur[tt][s] = xnext[tt][s];
         }
+    }
+}
+
+// Codes and scales of twice-rotated values that wait in the workspace: channel j of block b is row perm[b*128 + j].  A workgroup
+// takes 64 tokens of one block, a wave 32 of its channels (a row's 64 tokens are one 256-byte load), and the codes change layout
+// in LDS: 128 bytes of a token's row per eight lanes.
+__global__ __launch_bounds__(256) void dense_codes_kernel(const float *__restrict__ T, int64_t ldt, int64_t M, int K,
+                                                          const int32_t *__restrict__ perm, const uint4 *__restrict__ pieces,
+                                                          const float *__restrict__ amax_tok, int8_t *__restrict__ Xq,
+                                                          float *__restrict__ sx)
+{
+    __shared__ __align__(16) uint32_t codes[64][kBlock / 4 + 4];
+    const int b = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t tok0 = (int64_t)blockIdx.x * 64;
+    const int64_t token = tok0 + lane < M ? tok0 + lane : M - 1;
+    float v[32];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) v[j] = T[(int64_t)clamp_channel(perm[b * kBlock + 32 * wave + j], K) * ldt + token];
+    const float signed_max = amax_tok[token], a = fabsf(signed_max);
+    const float inv = a > 0.0f ? 127.0f / a : 0.0f;
+    if (b == 0 && wave == 0 && tok0 + lane < M) sx[token] = a / 127.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        codes[lane][8 * wave + j] = pack4_low_bytes(quant_bits(v[4 * j], inv), quant_bits(v[4 * j + 1], inv),
+                                                    quant_bits(v[4 * j + 2], inv), quant_bits(v[4 * j + 3], inv));
+    if (__builtin_amdgcn_readfirstlane(__float_as_uint(signed_max)) >> 31) {      // a channel was named twice: the products are still to come
+#pragma unroll 1
+        for (int j = 0; j < 8; ++j) {                             // channels 32 wave + 4 j .. + 3: tile j, rows 4 wave .. 4 wave + 3
+            float w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+            for (int k8 = 0; k8 < kBlock / 8; ++k8) {             // inputs 8 k8 .. 8 k8 + 7: k-step k8 / 4, lanes of group k8 mod 4
+                float in[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) in[e] = T[(int64_t)clamp_channel(perm[b * kBlock + 8 * k8 + e], K) * ldt + token];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint4 *const f = pieces + (size_t)b * kPiecesPerBlock + ((k8 >> 2) * 8 + j) * 64 + (k8 & 3) * 16 + 4 * wave + i;
+                    const uint4 hi = f[0], mid = f[4 * 8 * 64], lo = f[8 * 8 * 64];
+                    const uint32_t h[4] = {hi.x, hi.y, hi.z, hi.w}, m[4] = {mid.x, mid.y, mid.z, mid.w}, l[4] = {lo.x, lo.y, lo.z, lo.w};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const auto piece = [&](uint32_t two) { return __uint_as_float(e & 1 ? two & 0xFFFF0000u : two << 16); };
+                        w[i] = fmaf(in[e], piece(h[e >> 1]) + (piece(m[e >> 1]) + piece(l[e >> 1])), w[i]);
+                    }
+                }
+            }
+            codes[lane][8 * wave + j] = pack4_low_bytes(quant_bits(w[0], inv), quant_bits(w[1], inv), quant_bits(w[2], inv), quant_bits(w[3], inv));
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int id = i * 256 + threadIdx.x, t = id >> 3, c = id & 7;
+        if (tok0 + t < M)
+            *reinterpret_cast<uint4 *>(Xq + (tok0 + t) * K + b * kBlock + 16 * c) = *reinterpret_cast<const uint4 *>(&codes[t][4 * c]);
     }
 }
 
@@ -514,19 +613,19 @@ int dense_block_chunks(int64_t groups, int nb)
     return chunks < 1 ? 1 : (int)chunks;
 }
 
-template <int SINK, int TT, bool GATHER>
+template <int SINK, int TT>
 hipError_t launch_dense_block_pass(const uint16_t *X, int64_t M, int nb, int64_t ldx, const uint4 *pieces,
-                                   float *amax_tok, float *scale_out, int8_t *Xq, const float *Tin, const int32_t *perm, float *Tout, int64_t ldt,
-                                   hipStream_t st)
+                                   float *amax_tok, int8_t *Xq, const int32_t *perm, float *T, int64_t ldt, hipStream_t st)
 {
-    // behind the pieces: the second rotation's 128 row numbers and eight waves' parked codes
-    const size_t smem = (size_t)kPiecesPerBlock * 16 + (GATHER ? kBlock * sizeof(int) + 8 * TT * 8 * 64 * sizeof(uint32_t) : 0);
-    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(rotate_dense_block_kernel<SINK, TT, GATHER>), smem);
+    // behind the pieces: the second rotation's 128 row numbers; the first one's check of the table
+    const size_t smem = (size_t)kPiecesPerBlock * 16 + (SINK == kSinkInPlace ? kBlock * sizeof(int) :
+                                                        SINK == kSinkRows ? (size_t)nb * kBlock * sizeof(uint16_t) : 0);
+    if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(rotate_dense_block_kernel<SINK, TT>), smem);
         e != hipSuccess)
         return e;
     const int64_t groups = (M + 16 * TT - 1) / (16 * TT);
-    hipLaunchKernelGGL((rotate_dense_block_kernel<SINK, TT, GATHER>), dim3((unsigned)dense_block_chunks(groups, nb), nb),
-                       dim3(512), smem, st, X, M, nb, ldx, pieces, amax_tok, scale_out, Xq, Tin, perm, Tout, ldt);
+    hipLaunchKernelGGL((rotate_dense_block_kernel<SINK, TT>), dim3((unsigned)dense_block_chunks(groups, nb), nb),
+                       dim3(512), smem, st, X, M, nb, ldx, pieces, amax_tok, Xq, perm, T, ldt);
     return hipGetLastError();
 }
 
@@ -536,12 +635,10 @@ hipError_t launch_dense_blocks(const uint16_t *X, int64_t M, int nb, int64_t ldx
 {
     const unsigned mg = (unsigned)((M + 255) / 256);
     hipLaunchKernelGGL(dense_clear_kernel, dim3(mg), dim3(256), 0, st, sx, M);
-    if (hipError_t e = launch_dense_block_pass<kSinkMaxima, TT, false>(X, M, nb, ldx, pieces, sx, nullptr, Xq, nullptr, nullptr,
-                                                                       nullptr, 0, st);
+    if (hipError_t e = launch_dense_block_pass<kSinkMaxima, TT>(X, M, nb, ldx, pieces, sx, Xq, nullptr, nullptr, 0, st);
         e != hipSuccess)
         return e;
-    if (hipError_t e = launch_dense_block_pass<kSinkCodes, TT, false>(X, M, nb, ldx, pieces, sx, nullptr, Xq, nullptr, nullptr,
-                                                                      nullptr, 0, st);
+    if (hipError_t e = launch_dense_block_pass<kSinkCodes, TT>(X, M, nb, ldx, pieces, sx, Xq, nullptr, nullptr, 0, st);
         e != hipSuccess)
         return e;
     hipLaunchKernelGGL(dense_scale_kernel, dim3(mg), dim3(256), 0, st, sx, M);
@@ -873,15 +970,10 @@ bool rotate_quant_dense_supports(int K) { return K % kBlock == 0 && K / kBlock <
 bool rotate_quant_dense_rpr_supports(int K) { return K % kBlock == 0 && K / kBlock <= 36; }
 bool rotate_quant_dense_rpr_reads_frags32(int K) { return K / kBlock > 12; }
 
-// Rows wider than 12 blocks have a second form that goes through a workspace: the once-rotated values,
+// Rows wider than 12 blocks have a second form that goes through a workspace: the rotated values,
 // float32, channel-major, tokens rounded up to 32 (the first rotation writes whole groups of 32 tokens),
-// and behind them one row more for the tokens' maxima.  Narrower rows take it from 16384 tokens on, a line from the time when
-// the 16-token kernel, which streams both rotations' fragments from L2 for every 16 tokens, had its second product on the
-// fp32 instruction (this form / that kernel: 95 / 110 us at 16384 x 1152, 167 / 213 at 32768).  Against the kernel of today it is
-// the better line for up to two blocks (256 channels at 16384 / 32768 / 65536 tokens 37 / 31, 43 / 54, 76 / 105); for wider
-// rows that kernel is ahead by up to 20 % at 16384 tokens (640 66 / 54, 1152 94 / 88, 1536 121 / 108), and from 24576 on the
-// two take turns within 10 % (1152 at 24576 / 28672 / 65536 123 / 125, 130 / 145, 319 / 326; 1536 164 / 157, 189 / 180,
-// 433 / 430).  The sizes from which callers need a workspace are part of the interface.
+// and behind them one row more for the tokens' maxima.  Callers bring one for narrower rows, too, from 16384 tokens on: a line that
+// belongs to the interface; which form such a call runs is dense_ws_pays.
 static int64_t dense_ws_ldt(int64_t M) { return (M + 31) / 32 * 32; }
 
 size_t rotate_quant_dense_rpr_workspace_bytes(int64_t M, int K)
@@ -890,34 +982,44 @@ size_t rotate_quant_dense_rpr_workspace_bytes(int64_t M, int K)
     return ((size_t)K + 1) * (size_t)dense_ws_ldt(M) * sizeof(float);
 }
 
+// us, 16-token kernel / this form, at 16384, 24576 and 32768 tokens: 128 channels 27 / 30, 37 / 35, 48 / 37; 256 29 / 37, 40 / 39, 53 / 42; 384
+// 34 / 38, 48 / 55, 63 / 58; 640 49 / 55, 71 / 65, 93 / 85; 768 55 / 58, 79 / 82, 104 / 103; 896 63 / 62, 91 / 86, 120 / 110; 1152 91 / 85,
+// 123 / 108, 162 / 143; 1536 104 / 104, 153 / 149, 203 / 195 (and 128 / 113 at 20480).
+static bool dense_ws_pays(int64_t M, int nb) { return nb >= 9 || M >= 24576; }
+
+// Values of T at a time, 226 MB: most of them stay in the memory-side cache between the three launches (us, whole / in two parts:
+// 32768 x 1664, 218 MB, 226 / 237; 16384 x 3072, 201 MB, 200 / 208; 65536 x 896, 235 MB, 251 / 244; with nine products 16384 x 4608, 302 MB,
+// 351 / 331 and 32768 x 2304 347 / 319).
+constexpr int64_t kDenseWsValues = 54 << 20;
+
 hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K, int64_t ldx, const void *pieces1,
                                             const int32_t *perm, const void *pieces2, int8_t *Xq, float *sx,
                                             float *T, hipStream_t st)
 {
     if (M == 0) return hipSuccess;
     const int nb = K / kBlock;
-    const int64_t ldt = dense_ws_ldt(M);
-    float *const amax_tok = T + (size_t)K * ldt;
-    // first rotation (also clears the maxima); second rotation for the maxima; again for the codes and the scales
-    if (hipError_t e = launch_dense_block_pass<kSinkRows, 2, false>(X, M, nb, ldx, static_cast<const uint4 *>(pieces1),
-                                                                    amax_tok, nullptr, Xq, nullptr, nullptr, T, ldt, st);
-        e != hipSuccess)
-        return e;
-    const uint4 *const p2 = static_cast<const uint4 *>(pieces2);
-    // Two token tiles per fragment read halve the LDS traffic of the second rotation (4-5 % from 8192 tokens on);
-    // with fewer tokens a wave has too few groups of 32 for that to make up for the coarser split of the work.
-    if (M >= 8192) {
-        if (hipError_t e = launch_dense_block_pass<kSinkMaxima, 2, true>(X, M, nb, ldx, p2, amax_tok, nullptr, Xq, T, perm,
-                                                                         nullptr, ldt, st);
-            e != hipSuccess)
-            return e;
-        return launch_dense_block_pass<kSinkCodes, 2, true>(X, M, nb, ldx, p2, amax_tok, sx, Xq, T, perm, nullptr, ldt, st);
+    if (!dense_ws_pays(M, nb)) return launch_rotate_quant_dense_rpr(X, M, K, ldx, pieces1, perm, nullptr, pieces2, Xq, sx, st);
+    const uint4 *const p1 = static_cast<const uint4 *>(pieces1), *const p2 = static_cast<const uint4 *>(pieces2);
+    const int64_t parts = (M * K + kDenseWsValues - 1) / kDenseWsValues;
+    const int64_t share = ((M + parts - 1) / parts + 63) / 64 * 64;
+    for (int64_t m0 = 0; m0 < M; m0 += share) {
+        const int64_t m = M - m0 < share ? M - m0 : share, ldt = dense_ws_ldt(m);
+        const uint16_t *const x = X + m0 * ldx;
+        int8_t *const xq = Xq + m0 * K;
+        float *const amax_tok = T + (size_t)K * ldt;
+        // first rotation (also clears the maxima); second rotation in place, with the maxima; codes and scales
+        hipError_t e = launch_dense_block_pass<kSinkRows, 2>(x, m, nb, ldx, p1, amax_tok, xq, perm, T, ldt, st);
+        if (e != hipSuccess) return e;
+        // Two token tiles per fragment read halve the LDS traffic of the second rotation (4-5 % from 8192 tokens on);
+        // with fewer tokens a wave has too few groups of 32 for that to make up for the coarser split of the work.
+        e = m >= 8192 ? launch_dense_block_pass<kSinkInPlace, 2>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st)
+                      : launch_dense_block_pass<kSinkInPlace, 1>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(dense_codes_kernel, dim3((unsigned)((m + 63) / 64), nb), dim3(256), 0, st, T, ldt, m, K, perm, p2, amax_tok, xq,
+                           sx + m0);
+        if (e = hipGetLastError(); e != hipSuccess) return e;
     }
-    if (hipError_t e = launch_dense_block_pass<kSinkMaxima, 1, true>(X, M, nb, ldx, p2, amax_tok, nullptr, Xq, T, perm,
-                                                                     nullptr, ldt, st);
-        e != hipSuccess)
-        return e;
-    return launch_dense_block_pass<kSinkCodes, 1, true>(X, M, nb, ldx, p2, amax_tok, sx, Xq, T, perm, nullptr, ldt, st);
+    return hipSuccess;
 }
 
 hipError_t launch_rotate_quant_dense_rpr(const uint16_t *X, int64_t M, int K, int64_t ldx, const void *pieces1,

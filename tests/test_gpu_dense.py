@@ -384,3 +384,46 @@ def test_second_rotation_keeps_float32_precision_for_sparse_blocks(K):
     assert np.abs(err).max() <= bound
     assert abs(err.mean()) <= bound * np.sqrt(2 * np.log(2e9) / M)
     rot1.close(); rot2.close()
+
+
+@pytest.mark.parametrize("M,K,parts", [(13001, 4608, 2), (12200, 4608, 1)])
+def test_dense_rpr_ws_in_parts(M, K, parts):
+    """Beyond 56.6 million values the workspace form takes the tokens in equal parts of whole 64: what the parts give alone."""
+    g = torch.Generator(device=dev()).manual_seed(M)
+    R = torch.randn(K // 128, 128, 128, generator=g, device=dev()) * 0.088
+    rot1, rot2 = trdq.Rotation(R, torch.rand(K, generator=g, device=dev()) + 0.5), trdq.Rotation(R)
+    perm = torch.randperm(K, generator=g, device=dev()).int()
+    X = torch.randn(M, K + 8, generator=g, device=dev()).bfloat16()[:, :K]           # rows that are further apart
+    ws = torch.full((trdq.rotate_quant_dense_rpr_ws_nbytes(M, K),), 0xFF, dtype=torch.uint8, device=dev())
+    out = []
+    share = (-(-M // parts) + 63) // 64 * 64 if parts > 1 else M
+    for step in (M, share):
+        Xq, sx = torch.full((M, K), 99, dtype=torch.int8, device=dev()), torch.full((M,), -1.0, device=dev())
+        for m in range(0, M, step):
+            trdq.rotate_quant_dense_rpr_ws(X[m:m + step], rot1, perm, rot2, Xq[m:m + step], sx[m:m + step], ws)
+        out.append((Xq, sx))
+    torch.cuda.synchronize()
+    assert (parts > 1) == (M * K > 54 << 20)
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]) and (out[0][1] > 0).all()
+    rot1.close(); rot2.close()
+
+
+@pytest.mark.parametrize("M,K", [(70, 1664), (8200, 1664), (24576, 256), (16400, 1152)])
+def test_dense_rpr_ws_with_channels_named_twice(M, K):
+    """A table that is no permutation (out-of-range entries are clamped) is the gather it says, as without a workspace, where a row of
+    T has one reader or none: codes within the one step that the two forms' rounding allows, scales within 128 * 2^-24."""
+    g = torch.Generator(device=dev()).manual_seed(M + K)
+    R = torch.randn(K // 128, 128, 128, generator=g, device=dev()) * 0.088
+    rot1, rot2 = trdq.Rotation(R, torch.rand(K, generator=g, device=dev()) + 0.5), trdq.Rotation(R)
+    perm = torch.randperm(K, generator=g, device=dev()).int()
+    perm[5], perm[K - 1], perm[K // 2], perm[3] = perm[130], perm[130], K + 7, -4
+    X = torch.randn(M, K, generator=g, device=dev()).bfloat16()
+    ws = torch.full((trdq.rotate_quant_dense_rpr_ws_nbytes(M, K),), 0xFF, dtype=torch.uint8, device=dev())
+    out = [(torch.full((M, K), 99, dtype=torch.int8, device=dev()), torch.full((M,), -1.0, device=dev())) for _ in range(2)]
+    trdq.rotate_quant_dense_rpr(X, rot1, perm, rot2, *out[0])
+    trdq.rotate_quant_dense_rpr_ws(X, rot1, perm, rot2, *out[1], ws)
+    torch.cuda.synchronize()
+    step = (out[0][0].short() - out[1][0].short()).abs()
+    assert step.max() <= 1 and (step != 0).float().mean() < 1e-3
+    assert ((out[0][1] - out[1][1]).abs() <= out[0][1] * 128 * 2.0 ** -24).all()
+    rot1.close(); rot2.close()
