@@ -16,6 +16,7 @@
 //                 256 x 4608        10.6 ->  3.9             4096 x 4608  14.7 -> 12.4 / 17.0 -> 14.9   32768 x 4608 95.9 -> 81.5 / 97.7 -> 81.6
 //   block-tiled   4096 x 1152        5.5 ->  4.5 /  5.9 ->  5.4   32768 x 1152 22.1 -> 20.9 / 26.1 -> 26.5
 //                 4096 x 4608       13.6 -> 12.6 / 15.9 -> 14.7   32768 x 4608 92.8 -> 84.7 / 92.3 -> 86.2
+// (block-tiled 32768 x 4608 since its input is read non-temporally: 79 / 82)
 // (a kernel that only reads two bytes and writes one: 2.8 / 4.0, 9.5 / 12.0 at 4096 tokens, 18.8 / 20.0, 74.3 / 74.5 at 32768).
 // Between the products of a transformer block, whose outputs are still being written back, it takes 7.2 and 13.5 us at 4096
 // tokens and 28.5 and 101 at 32768 (kernel trace).  Codes that differ from float64's: 2.2e-6 of them against 2.6e-6 at K = 1152.
@@ -27,12 +28,32 @@ namespace trdq {
 
 namespace {
 
+// From here on input and codes, three bytes per value, do not fit the memory-side cache of 256 MB together, and the input is read as
+// what nobody will read again, so that the codes stay for the product.  us, ordinary / non-temporal: 32768 x 4608 as rows 84 /
+// 77 on one input, 84 / 80 on several, block-tiled 89 / 79 and 88 / 82; 65536 x 2304 86 / 83, 86 / 87, 96 / 93, 96 / 94; the pass and
+// its product, 4608 -> 1152, at 24576 tokens 168 / 161, at 32768 230 / 210; layers in which each pass reads what the product
+// before it wrote, 1152 -> 4608 -> 1152 at 32768, 442 / 418.  Below, an input that the cache still holds
+// would come from memory instead: 16384 x 4608 38 / 42 and 32768 x 1152 21 / 23 on one input, 2304 -> 768 at 24576 with its product 84 / 87.
+constexpr int64_t kOnceValues = ((int64_t)256 << 20) / 3 + 1;
+
+// 16 bytes of the input; ONCE: non-temporal.  (A template: of a branch between the two loads the compiler makes one ordinary load.)
+template <bool ONCE>
+__device__ __forceinline__ uint4 load_in16(const uint16_t *p)
+{
+    if constexpr (ONCE) {
+        typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+        const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(p));
+        return make_uint4(v.x, v.y, v.z, v.w);
+    }
+    return *reinterpret_cast<const uint4 *>(p);
+}
+
 // QUADS: groups of four tokens per workgroup; SPW: most blocks per wave.
 // ASYM: the asymmetric quantiser (per-token minimum and maximum, zero point): codes q in 0..255 are stored as q - 128 so
 // that they stay int8 for the matrix instruction, and zc[i] = 128 - z_i is what the product's epilogue needs with the
 // weights' column sums.
 // tiled: Xq in 1 KB blocks of 16 tokens x 64 k, the 16-byte piece p of row r at p * 256 + r * 16.
-template <int QUADS, int SPW, bool ASYM>
+template <int QUADS, int SPW, bool ASYM, bool ONCE>
 __global__ __launch_bounds__(SPW <= 3 ? 768 : 576, SPW <= 3 ? 6 : 3) void rotate_quant_kernel(
     const uint16_t *__restrict__ X, int64_t M, int nb, int64_t ldx,
     const float *__restrict__ diag, int8_t *__restrict__ Xq, float *__restrict__ sx,
@@ -59,7 +80,7 @@ __global__ __launch_bounds__(SPW <= 3 ? 768 : 576, SPW <= 3 ? 6 : 3) void rotate
         for (int q = 0; q < QUADS; ++q) {
             int64_t token = m0 + q * 4 + t4;
             if (token >= M) token = M - 1;           // clamped: rotated like the others, never stored
-            raw[i][q] = *reinterpret_cast<const uint4 *>(X + token * ldx + b * kBlock + c_in);
+            raw[i][q] = load_in16<ONCE>(X + token * ldx + b * kBlock + c_in);
         }
         dg[i][0] = dg[i][1] = make_float4(1.f, 1.f, 1.f, 1.f);
         if (diag) {
@@ -202,7 +223,9 @@ hipError_t launch_spw(const uint16_t *X, int64_t M, int nb, int64_t ldx, const f
     const float sx_mul = 0.08838834764831845f / qmax;
     const size_t smem = sizeof(float) * (size_t)nw * 2 * TOK + 1024;                 // extremes, dump area
     const int64_t warm_chunks = (warm && warm_bytes < ((int64_t)1 << 32)) ? warm_bytes / 16 : 0;   // 32-bit byte offsets in the copy
-    auto kern = zc ? rotate_quant_kernel<QUADS, SPW, true> : rotate_quant_kernel<QUADS, SPW, false>;
+    const bool once = (int64_t)nb * kBlock * M >= kOnceValues;
+    auto kern = zc ? (once ? rotate_quant_kernel<QUADS, SPW, true, true> : rotate_quant_kernel<QUADS, SPW, true, false>)
+                   : (once ? rotate_quant_kernel<QUADS, SPW, false, true> : rotate_quant_kernel<QUADS, SPW, false, false>);
     hipLaunchKernelGGL(kern, dim3((unsigned)((M + TOK - 1) / TOK)), dim3(64 * nw), smem, st,
                        X, M, nb, ldx, diag, Xq, sx, zc, static_cast<const uint4 *>(warm), warm_chunks, qmax, sx_mul, (int)tiled);
     return hipGetLastError();

@@ -92,3 +92,32 @@ def test_many_tokens_like_few(M, K):
     m = M - 300
     trdq.rotate_quant_asym(X[m:], d, back[m:], want_s[m:], zc[:300])
     assert torch.equal(buf[m:M], back[m:]) and torch.equal(sx[m:M], want_s[m:]) and torch.equal(zc_all[m:], zc[:300])
+
+
+@pytest.mark.parametrize("M,K", [(19419, 4608), (19420, 4608), (699051, 128)])
+def test_inputs_about_the_size_of_the_memory_side_cache(M, K):
+    """One call on either side of the size from which the input is read non-temporally (89 478 486 values) against calls on parts of it:
+    the same codes, scales and zero points for every form, rows that are further apart than K included."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+    X = torch.randn(M, K + 8, generator=g, device="cuda", dtype=torch.float32).bfloat16()[:, :K]
+    diag = torch.rand(K, generator=g, device="cuda") + 0.5
+    part = 16 * (M // 64)
+    calls = [lambda x, q, s, z: trdq.rotate_quant(x, diag, q, s), lambda x, q, s, z: trdq.rotate_quant_asym(x, diag, q, s, z),
+             lambda x, q, s, z: trdq.rotate_quant_bits(x, diag, q, s, 6)]
+    for n, call in enumerate(calls):
+        out = []
+        for step in (M, part):
+            q = torch.full((M, K), 99, dtype=torch.int8, device="cuda")
+            s, z = torch.full((M,), -1.0, device="cuda"), torch.full((M,), -7, dtype=torch.int32, device="cuda")
+            for m in range(0, M, step):
+                call(X[m:m + step], q[m:m + step], s[m:m + step], z[m:m + step])
+            out.append((q, s, z))
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(*out)) and (out[0][1] > 0).all(), n
+        if n == 0:
+            tiled, s = torch.empty(trdq.xq_tiled_nbytes(M, K), dtype=torch.int8, device="cuda"), torch.empty(M, device="cuda")
+            trdq.rotate_quant_tiled(X, diag, tiled, s)
+            q = torch.empty_like(out[0][0])
+            trdq.xq_untile(tiled, M, K, q)
+            torch.cuda.synchronize()
+            assert torch.equal(q, out[0][0]) and torch.equal(s, out[0][1])
