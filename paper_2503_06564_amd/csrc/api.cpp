@@ -1123,7 +1123,7 @@ trdq_status trdq_layer_forward(const trdq_layer *l, int step, const void *X_dev,
         return rc;
     };
     const bool have_ws = Xq_ws_dev && sx_ws_dev;
-    if (fused > 0 || (fused < 0 && (have_ws ? trdq::fused_pays(M, l->K, l->N, w->wbits)
+    if (fused > 0 || (fused < 0 && (have_ws ? trdq::fused_pays(M, l->K, l->N)
                                             : trdq::fused_needs_no_workspace(M, l->K, l->N, w->wbits))))
         return launched(trdq_linear_fused(X_dev, M, l->K, d, w, bias_dev, Y_dev, l->N, stream));
     if (!have_ws) return TRDQ_ERR_NULL;

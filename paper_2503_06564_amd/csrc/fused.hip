@@ -653,17 +653,14 @@ bool fused_takes_few_tokens(int64_t M, int K, int N)
 // The layer's choice: the few-token kernel in a single round of workgroups (two of the small ones that one or two blocks
 // make).  In a second round the repeated rotation costs more than the pair's second launch.  us, fused against the pair: 1152 ->
 // 4608 at 128 tokens (256 workgroups) 6.9 / 8.7, at 256 12.0 / 11.3; 768 -> 3072 at 256 (352) 10.4 / 8.8; 256 -> 512 at 2048
-// (512) 6.2 / 7.0, at 4096 12.6 / 8.2; int4 1152 -> 4608 at 128 7.5 / 11.0, at 256 13.3 / 11.2.  A wave with two or three blocks rotates and
-// multiplies them in turn, while the pair splits K over more waves: int8 rows take the fused kernel up to 16 blocks (2048 ->
-// 1152 at 1 / 16 / 64 tokens 5.8 / 6.5, 6.8 / 7.0, 7.3 / 7.4; 2304 -> 1152 6.7 / 6.7, 7.8 / 7.1, 8.2 / 7.6; 4608 -> 1152 9.8 / 7.9,
-// 12.1 / 8.4, 14.6 / 9.2), int4 rows, whose product is the slower one in the pair, up to 24 (3072 -> 1152 at 16 / 64 tokens
-// 9.3 / 10.0, 10.1 / 9.9; 3328 -> 1152 11.7 / 10.6, 12.5 / 10.6) and beyond for up to four tokens (4608 -> 1152 at 4 / 8 / 16 tokens
-// 11.8 / 11.9, 12.4 / 12.1, 13.1 / 12.2).
-bool fused_pays(int64_t M, int K, int N, int wbits)
+// (512) 6.2 / 7.0, at 4096 12.6 / 8.2; int4 1152 -> 4608 at 128 7.5 / 11.0, at 256 13.3 / 11.2.  Where a wave has two or three
+// blocks the line dates from a slower pair: it still holds at 1664 -> 1152 (64 tokens 7.0 / 7.2; int4 7.5 / 8.4) and for int4 up to
+// 3072 channels (2304 -> 1152 at 64 9.1 / 9.3), no longer for int8 from 2304 on (2304 -> 1152 at 16 tokens 7.8 / 7.0, 4608 ->
+// 1152 at 16 / 64 11.9 / 8.4, 14.3 / 9.2) and for int4 at 4608 (at 64 13.9 / 12.1).
+bool fused_pays(int64_t M, int K, int N)
 {
-    if (M <= 0 || K % kBlock != 0 || K > kSmallMaxBlocks * kBlock) return false;
-    if (K > (wbits == 4 ? 24 : 16) * kBlock && !(wbits == 4 && M <= 4)) return false;
-    return small_workgroups(M, K, N) <= (int64_t)num_cus() * (K <= 2 * kBlock ? 2 : 1);
+    return M > 0 && K % kBlock == 0 && K <= kSmallMaxBlocks * kBlock &&
+           small_workgroups(M, K, N) <= (int64_t)num_cus() * (K <= 2 * kBlock ? 2 : 1);
 }
 
 // Where trdq_layer_forward takes the fused kernel for a caller that gave no workspace: a fixed range of shapes, so that

@@ -148,7 +148,7 @@ hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K,
                                             float *T, hipStream_t st);
 bool fused_supports(int K);
 bool fused_takes_few_tokens(int64_t M, int K, int N);    // which of the two fused kernels
-bool fused_pays(int64_t M, int K, int N, int wbits);
+bool fused_pays(int64_t M, int K, int N);
 bool fused_needs_no_workspace(int64_t M, int K, int N, int wbits);
 hipError_t launch_linear_fused(const Weights &w, const uint16_t *X, int64_t M, int64_t ldx,
                                const float *diag, const float *bias, uint16_t *Y, int64_t ldy,

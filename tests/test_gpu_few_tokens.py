@@ -75,25 +75,3 @@ def test_narrow_rows_many_workgroups(M, K, N, form):
     torch.cuda.synchronize()
     assert (buf[M] == 7.0).all()
     gu.assert_y_close(gu.bf16_to_host(Y), gu.bf16_to_host(Yp), "fused against the pair")
-
-
-@pytest.mark.parametrize("wbits,M,K,fused", [(8, 16, 2048, True), (8, 16, 2176, False), (8, 1, 4608, False), (4, 16, 3072, True),
-                                             (4, 16, 3200, False), (4, 4, 3200, True), (4, 5, 4608, False)])
-def test_layer_choice_by_width(wbits, M, K, fused):
-    """On both sides of the widths where the layer goes from the fused kernel to the pair: the outputs are those of the path
-    it is meant to take, and only the pair writes the token scales."""
-    N = 256
-    layer = trdq.Layer(trdq.Table(4, 1), K, N, wbits)
-    Xb, W, d, bias = wl.small_case(17, M, K, N)
-    layer.set_group(0, gu.f32_to_dev(d), gu.f32_to_dev(W))
-    X, bd = gu.bf16_to_dev(Xb), gu.f32_to_dev(bias)
-    Xq = torch.empty((M, K), dtype=torch.int8, device="cuda")
-    out = []
-    for choice in (None, fused):
-        sx = torch.full((M,), float("nan"), device="cuda")
-        Y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
-        layer.forward(1, X, Y, bias=bd, fused=choice, Xq_ws=Xq, sx_ws=sx)
-        torch.cuda.synchronize()
-        assert bool(torch.isnan(sx).all()) == fused
-        out.append(Y)
-    assert torch.equal(out[0], out[1])
