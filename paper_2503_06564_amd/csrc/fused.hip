@@ -656,7 +656,9 @@ bool fused_takes_few_tokens(int64_t M, int K, int N)
 // (512) 6.2 / 7.0, at 4096 12.6 / 8.2; int4 1152 -> 4608 at 128 7.5 / 11.0, at 256 13.3 / 11.2.  Where a wave has two or three
 // blocks the line dates from a slower pair: it still holds at 1664 -> 1152 (64 tokens 7.0 / 7.2; int4 7.5 / 8.4) and for int4 up to
 // 3072 channels (2304 -> 1152 at 64 9.1 / 9.3), no longer for int8 from 2304 on (2304 -> 1152 at 16 tokens 7.8 / 7.0, 4608 ->
-// 1152 at 16 / 64 11.9 / 8.4, 14.3 / 9.2) and for int4 at 4608 (at 64 13.9 / 12.1).
+// 1152 at 16 / 64 11.9 / 8.4, 14.3 / 9.2) and for int4 at 4608 (at 64 13.9 / 12.1).  Those are replays of a graph: launched by the
+// host one by one, a second launch costs 3 to 5 us (2176 -> 176 at 64 tokens 7.2 / 10.5; the four linears of a block of width
+// 1024 at one token 23 / 29), so the line stays.
 bool fused_pays(int64_t M, int K, int N)
 {
     return M > 0 && K % kBlock == 0 && K <= kSmallMaxBlocks * kBlock &&
