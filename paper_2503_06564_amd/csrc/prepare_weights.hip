@@ -212,11 +212,20 @@ __global__ __launch_bounds__(64 * kPcMostWaves) void prepare_columns_kernel(
     auto rotate = [&](int b, float (&v)[16]) {
         if (!ROTATE) return;
         if (diag) {
-            // v / d from r = 1 / d, which the wave forms once per row: q = v r, then q + (v - q d) r, which rounds like the
-            // division itself (its ten instructions a value were two fifths of the kernel)
+            // v / d from r = 1 / d, which the wave forms once per row: q = v r, then q + (v - q d) r (Markstein's correction;
+            // the division's ten instructions a value were two fifths of the kernel).  It rounds like the division while the
+            // quotient and the remainder v - q d stay normal numbers: |d| between 2^-64 and 2^64, v zero or between 2^-60 and 2^60.
+            // (An infinite quotient would become NaN, which the maximum below passes over.)  Other blocks are divided.
             const float d0 = diag[b * kBlock + lane], d1 = diag[b * kBlock + 64 + lane];
             auto plain = [](float d) { return fabsf(d) > 0x1p-64f && fabsf(d) < 0x1p64f; };
-            if (__all(plain(d0) && plain(d1))) {
+            float most = 0.0f;
+            uint32_t least = ~0u;                        // twice the bits (no sign) less one: a zero counts as the largest
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                most = fmaxf(most, fabsf(v[i]));
+                least = min(least, (__float_as_uint(v[i]) << 1) - 1);
+            }
+            if (__all(plain(d0) && plain(d1) && most < 0x1p60f && least >= (__float_as_uint(0x1p-60f) << 1) - 1)) {
                 float2 *const dr = recip[wave];
                 __builtin_amdgcn_wave_barrier();     // LDS serves a wave's requests in order
                 dr[lane] = make_float2(d0, 1.0f / d0);

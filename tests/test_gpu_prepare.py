@@ -57,6 +57,32 @@ def test_codes_scales_and_sums_of_wide_rows(trdq, oracle, wbits, K, N):
     assert np.array_equal(acc.cpu().numpy(), (Xq.astype(np.int64) + zc[:, None]) @ codes.astype(np.int64))
 
 
+# one block to a wave, three, and blocks read twice (int8); values[row 3 of a block, channel 5], the diagonal's entry there
+@pytest.mark.parametrize("wbits", [8, 6, 4])
+@pytest.mark.parametrize("K", [256, 2176, 6272])
+@pytest.mark.parametrize("value,entry", [(None, None), (np.inf, 0.5), (-np.inf, 2.0), (np.nan, 2.0), (3e38, 0.25), (1e25, 1e-19),
+                                         (1e-30, 1e14), (3e-39, 1.5), (-0.0, 3.0), (0.01, 1e-22)])
+def test_division_by_the_diagonal_is_a_float32_division(trdq, wbits, K, value, entry):
+    """Bit for bit what the quotients, rounded by the host, give without a diagonal: infinite, subnormal and overflowing ones too
+    (an infinite channel keeps its infinite scale).  Block 1 holds the value alone and with values of its own size."""
+    N = 32
+    _, W, d, _ = wl.small_case(41, 1, K, N)
+    if value is not None:
+        W[3, 5] = W[128 + 3, 5] = value
+        d[3] = d[128 + 3] = entry
+        if np.isfinite(value):
+            W[128:256, 7] *= np.float32(value)
+    with np.errstate(all="ignore"):
+        quotients = W / d[:, None]
+    assert quotients.dtype == np.float32
+    got = trdq.prepare_weights(f32_to_dev(W), f32_to_dev(d), wbits=wbits).export()
+    want = trdq.prepare_weights(f32_to_dev(quotients), None, wbits=wbits).export()
+    assert np.array_equal(got[0], want[0])
+    assert np.array_equal(got[1].view(np.uint32), want[1].view(np.uint32))
+    if np.isinf(quotients[3, 5]):
+        assert np.isinf(got[1].reshape(-1, N)[0, 5])
+
+
 @pytest.mark.parametrize("wbits", [8, 4])
 def test_group_set_again(trdq, wbits):
     """A group that is replaced holds what a fresh layer would hold: same diagonal form, then the diagonal dropped, then
