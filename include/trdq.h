@@ -471,8 +471,9 @@ trdq_status trdq_layer_create(const trdq_table *t, int K, int N, int wbits, trdq
 /* Prepare group g from W_dev [K, N] and diag_dev [K] (or NULL = ones; the diagonal is copied
  * to a device buffer the layer owns).  Replaces an earlier setting of the same group; if it fails, that
  * setting stays.  Returns when the weights are ready.  Calls that were enqueued before go on with the set they
- * were given: a replaced set is left as it is, the call that replaces it waits for the device, and the next replacement in
- * this layer, of whichever group, fills its memory (so a layer that has replaced a group holds one set more).  A graph that
+ * were given: a replaced set is left as it is, and the next replacement in this layer, of whichever group, fills its memory
+ * (so a layer that has replaced a group holds one set more), which nobody reads by then: a call that fills such a set waits
+ * for the device, a layer's first replacement for its stream only.  A graph that
  * recorded a forward call goes on reading the set it was recorded with.
  * No other call may run on the same layer object during this one. */
 trdq_status trdq_layer_set_group(trdq_layer *l, int g, const float *diag_dev, const float *W_dev,

@@ -62,6 +62,7 @@ struct trdq_layer {
     int K = 0, N = 0, wbits = 0;
     std::vector<trdq_weights *> w;     // one per group (H_t depends on t), with its copy of the diagonal (null = ones)
     trdq_weights *spare = nullptr;     // the set that was replaced last: what the next replacement fills
+    bool spare_read = false;           // whether calls made before its replacement may still read it
     // Whether somebody may read a replaced set after its replacement has returned: a graph that recorded a forward call, the
     // holder of a handle from trdq_layer_weights, or kernels of a replacement that failed.
     mutable std::atomic<bool> outside{false};
@@ -256,7 +257,7 @@ trdq_status fill_weights(trdq_weights *w, const float *W_dev, const float *diag_
 trdq_status prepare_weights_impl(const float *W_dev, int K, int N, const float *diag_dev, const int32_t *perm_dev,
                                  int block, int wbits, void *stream, trdq_weights **out,
                                  const trdq::Rotation *rot = nullptr, const trdq::Rotation *rot2 = nullptr,
-                                 bool with_diag = false, bool wait_device = false)
+                                 bool with_diag = false)
 {
     if (!out) return TRDQ_ERR_NULL;
     *out = nullptr;
@@ -270,7 +271,7 @@ trdq_status prepare_weights_impl(const float *W_dev, int K, int N, const float *
     w->rotation = rot ? (rot2 ? trdq::kRotDenseRPR : trdq::kRotDense) : (perm_dev ? trdq::kRotHadamardRPR : trdq::kRotHadamard);
     trdq_status rc = hipGetDevice(&w->device) == hipSuccess ? TRDQ_OK : TRDQ_ERR_HIP;
     if (rc == TRDQ_OK) rc = alloc_weights(w, with_diag);
-    if (rc == TRDQ_OK) rc = fill_weights(w, W_dev, diag_dev, perm_dev, rot, rot2, static_cast<hipStream_t>(stream), wait_device);
+    if (rc == TRDQ_OK) rc = fill_weights(w, W_dev, diag_dev, perm_dev, rot, rot2, static_cast<hipStream_t>(stream));
     if (rc != TRDQ_OK) {
         (void)hipGetLastError();
         trdq_weights_destroy(w);
@@ -1068,19 +1069,22 @@ trdq_status trdq_layer_set_group(trdq_layer *l, int g, const float *diag_dev, co
     trdq_weights *&slot = l->w[(size_t)g];
     trdq_weights *w = nullptr;
     trdq_status rc;
-    // The one wait of a replacement: for its own kernels and for every call made before, on any stream, so that nothing reads
-    // the set that goes out of use.  (A wait before the first kernel and one after the last left the device idle twice:
-    // 192 us for the four linears of a block of width 1152 and a forward call of each, 150 with one.)
-    const bool retires = slot != nullptr;
+    // Whether this call waits for every call made before, on any stream, so that nothing reads the set that goes out of use.
+    // One that fills a replaced set does, at its end, together with its own kernels; one that allocates (a layer's first
+    // replacement) waits for its stream only, and leaves the wait to the call that fills the set.  (A wait before the first
+    // kernel and one after the last left the device idle twice: 192 us for the four linears of a block of width 1152 and a forward
+    // call of each, 150 with one.)
+    bool waits = false;
     if (l->spare && l->spare->device == dev && (l->spare->diag != nullptr) == (diag_dev != nullptr)) {
-        // A set replaced earlier is filled (releasing one and allocating another cost 0.1-0.2 ms).  Calls that read it were
-        // waited for when it was replaced.  The group's own set is never written: launches made before go on with it, and
-        // it stays the group's set if this fails.
-        if (l->outside.load(std::memory_order_relaxed) && hipDeviceSynchronize() != hipSuccess) {
+        // A set replaced earlier is filled (releasing one and allocating another cost 0.1-0.2 ms), once nobody reads it any
+        // more.  The group's own set is never written: launches made before go on with it, and it stays the group's set if
+        // this fails.
+        if ((l->spare_read || l->outside.load(std::memory_order_relaxed)) && hipDeviceSynchronize() != hipSuccess) {
             (void)hipGetLastError();
             return TRDQ_ERR_HIP;
         }
-        rc = fill_weights(l->spare, W_dev, diag_dev, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream), retires);
+        waits = slot != nullptr;
+        rc = fill_weights(l->spare, W_dev, diag_dev, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream), waits);
         if (rc != TRDQ_OK) {
             l->outside.store(true, std::memory_order_relaxed);
             return rc;
@@ -1089,12 +1093,13 @@ trdq_status trdq_layer_set_group(trdq_layer *l, int g, const float *diag_dev, co
         l->spare = nullptr;
     } else {
         rc = prepare_weights_impl(W_dev, l->K, l->N, diag_dev, nullptr, trdq::kBlock, l->wbits, stream, &w, nullptr, nullptr,
-                                  diag_dev != nullptr, retires);
+                                  diag_dev != nullptr);
         if (rc != TRDQ_OK) return rc;
     }
     if (slot) {
         trdq_weights_destroy(l->spare);      // (of another form: one spare set is kept)
         l->spare = slot;
+        l->spare_read = !waits;
         if (slot->device != dev) l->outside.store(true, std::memory_order_relaxed);   // the wait was for another device
     }
     slot = w;

@@ -172,6 +172,68 @@ def test_calls_before_a_replacement_keep_their_set(trdq, recorded):
     assert torch.equal(got, want[3])
 
 
+@pytest.mark.parametrize("capturing", [False, True])
+def test_first_replacement_waits_for_its_own_stream_only(trdq, capturing):
+    """Long work on another stream does not hold it up, and a capture there (relaxed: allocations stay allowed) does not refuse
+    it; the replacements that follow leave the set that the other stream's call reads alone until it has ended."""
+    import ctypes as C
+
+    import torch
+    hip = trdq.lib()
+    M, K, N = 1024, 384, 2304
+    xb, W, d, _ = wl.small_case(5, M, K, N)
+    X, dd = bf16_to_dev(xb), f32_to_dev(d)
+    weights = [f32_to_dev((1.0 + i) * W) for i in range(3)]
+    ws = [dict(Xq_ws=torch.empty((M, K), dtype=torch.int8, device="cuda"), sx_ws=torch.empty(M, device="cuda")) for _ in range(2)]
+    want, got, after = (torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    layer = trdq.Layer(trdq.Table(4, 2), K, N, 8)
+    layer.set_group(1, dd, weights[0])
+    layer.forward(3, X, want, **ws[0])
+    side, busy, done = torch.cuda.Stream(), torch.empty(1 << 28, device="cuda"), torch.cuda.Event()
+
+    def occupy():
+        with torch.cuda.stream(side):
+            for _ in range(100):
+                busy.add_(1.0)                           # some 35 ms
+            done.record()
+
+    # a stream that does not share a hardware queue with `side`
+    for own in (torch.cuda.Stream() for _ in range(8)):
+        torch.cuda.synchronize()
+        occupy()
+        with torch.cuda.stream(own):
+            torch.zeros(1, device="cuda")
+        own.synchronize()
+        if not done.query():
+            break
+    else:
+        pytest.skip("every stream shares a hardware queue with the busy one")
+    torch.cuda.synchronize()
+    if capturing:
+        stream, graph = C.c_void_p(), C.c_void_p()
+        assert hip.hipStreamCreate(C.byref(stream)) == 0
+        assert hip.hipStreamBeginCapture(stream, 2) == 0
+        layer.set_group(1, dd, weights[1], stream=own.cuda_stream)
+        assert hip.hipStreamEndCapture(stream, C.byref(graph)) == 0
+        assert hip.hipGraphDestroy(graph) == 0 and hip.hipStreamDestroy(stream) == 0
+    else:
+        occupy()
+        layer.forward(3, X, got, **ws[1], stream=side.cuda_stream)
+        with torch.cuda.stream(side):
+            done.record()
+        layer.set_group(1, dd, weights[1], stream=own.cuda_stream)
+        assert not done.query()
+        layer.set_group(1, dd, weights[2], stream=own.cuda_stream)      # fills the set that the call on `side` reads
+        assert done.query()
+        assert torch.equal(got, want)
+    layer.forward(3, X, after, **ws[0])
+    fresh = trdq.Layer(trdq.Table(4, 2), K, N, 8)
+    fresh.set_group(1, dd, weights[1] if capturing else weights[2])
+    fresh.forward(3, X, want, **ws[0])
+    torch.cuda.synchronize()
+    assert torch.equal(after, want)
+
+
 @pytest.mark.parametrize("replaced_before", [0, 1, 2])
 def test_failed_replacement_keeps_the_group(trdq, replaced_before):
     """The preparation of a group ends with a wait for its stream, which a capturing stream refuses."""
