@@ -537,7 +537,12 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
 
 // Codes and scales of twice-rotated values that wait in the workspace: channel j of block b is row perm[b*128 + j].  A workgroup
 // takes 64 tokens of one block, a wave 32 of its channels (a row's 64 tokens are one 256-byte load), and the codes change layout
-// in LDS: 128 bytes of a token's row per eight lanes.
+// in LDS: 128 bytes of a token's row per eight lanes.  Maxima with a sign: a channel was named twice, and the products that
+// kSinkInPlace formed them from are formed again, 16 tokens and all channels of the block to a wave, in the same NCH chains.
+// (Multiplied out by the vector units, 128 gathers per channel, such a call took 152 us at 70 x 1664, 338 at 4096 x 1664 and 643 at 4096 x
+// 4608; now 24, 54
+// and 117, a permutation 19, 42 and 84.)
+template <int NCH>
 __global__ __launch_bounds__(256) void dense_codes_kernel(const float *__restrict__ T, int64_t ldt, int64_t M, int K,
                                                           const int32_t *__restrict__ perm, const uint4 *__restrict__ pieces,
                                                           const float *__restrict__ amax_tok, int8_t *__restrict__ Xq,
@@ -553,34 +558,47 @@ __global__ __launch_bounds__(256) void dense_codes_kernel(const float *__restric
 #pragma unroll
     for (int j = 0; j < 32; ++j) v[j] = T[(int64_t)clamp_channel(perm[b * kBlock + 32 * wave + j], K) * ldt + token];
     const float signed_max = amax_tok[token], a = fabsf(signed_max);
-    const float inv = a > 0.0f ? 127.0f / a : 0.0f;
     if (b == 0 && wave == 0 && tok0 + lane < M) sx[token] = a / 127.0f;
+    if (__builtin_amdgcn_readfirstlane(__float_as_uint(signed_max)) >> 31 == 0) {
+        const float inv = a > 0.0f ? 127.0f / a : 0.0f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-        codes[lane][8 * wave + j] = pack4_low_bytes(quant_bits(v[4 * j], inv), quant_bits(v[4 * j + 1], inv),
-                                                    quant_bits(v[4 * j + 2], inv), quant_bits(v[4 * j + 3], inv));
-    if (__builtin_amdgcn_readfirstlane(__float_as_uint(signed_max)) >> 31) {      // a channel was named twice: the products are still to come
+        for (int j = 0; j < 8; ++j)
+            codes[lane][8 * wave + j] = pack4_low_bytes(quant_bits(v[4 * j], inv), quant_bits(v[4 * j + 1], inv),
+                                                        quant_bits(v[4 * j + 2], inv), quant_bits(v[4 * j + 3], inv));
+    } else {
+        const int l16 = lane & 15, g = lane >> 4;
+        const int64_t mine = tok0 + 16 * wave + l16 < M ? tok0 + 16 * wave + l16 : M - 1;
+        const float most = fabsf(amax_tok[mine]);
+        const float inv = most > 0.0f ? 127.0f / most : 0.0f;
+        v8bf x[3][4];                                             // pieces of the gathered values: high, middle, low
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            float raw[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) raw[e] = T[(int64_t)clamp_channel(perm[b * kBlock + 32 * s + 8 * g + e], K) * ldt + mine];
+            split3_bf16(raw, x[0][s], x[1][s], x[2][s]);
+        }
 #pragma unroll 1
-        for (int j = 0; j < 8; ++j) {                             // channels 32 wave + 4 j .. + 3: tile j, rows 4 wave .. 4 wave + 3
-            float w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 1
-            for (int k8 = 0; k8 < kBlock / 8; ++k8) {             // inputs 8 k8 .. 8 k8 + 7: k-step k8 / 4, lanes of group k8 mod 4
-                float in[8];
+        for (int t = 0; t < 8; ++t) {
+            const uint4 *const f = pieces + (size_t)b * kPiecesPerBlock + t * 64 + lane;
+            v4f ch[NCH];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) in[e] = T[(int64_t)clamp_channel(perm[b * kBlock + 8 * k8 + e], K) * ldt + token];
+            for (int c = 0; c < NCH; ++c) ch[c] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint4 *const f = pieces + (size_t)b * kPiecesPerBlock + ((k8 >> 2) * 8 + j) * 64 + (k8 & 3) * 16 + 4 * wave + i;
-                    const uint4 hi = f[0], mid = f[4 * 8 * 64], lo = f[8 * 8 * 64];
-                    const uint32_t h[4] = {hi.x, hi.y, hi.z, hi.w}, m[4] = {mid.x, mid.y, mid.z, mid.w}, l[4] = {lo.x, lo.y, lo.z, lo.w};
+            for (int p = 2; p >= 0; --p) {
+                union { uint4 u; v8bf v; } r[4];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const auto piece = [&](uint32_t two) { return __uint_as_float(e & 1 ? two & 0xFFFF0000u : two << 16); };
-                        w[i] = fmaf(in[e], piece(h[e >> 1]) + (piece(m[e >> 1]) + piece(l[e >> 1])), w[i]);
-                    }
-                }
+                for (int s = 0; s < 4; ++s) r[s].u = f[(p * 4 + s) * 8 * 64];
+#pragma unroll
+                for (int bp = 2 - p; bp >= 0; --bp)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) ch[s % NCH] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r[s].v, x[bp][s], ch[s % NCH], 0, 0, 0);
             }
-            codes[lane][8 * wave + j] = pack4_low_bytes(quant_bits(w[0], inv), quant_bits(w[1], inv), quant_bits(w[2], inv), quant_bits(w[3], inv));
+            v4f acc;
+            if constexpr (NCH == 4) acc = (ch[0] + ch[1]) + (ch[2] + ch[3]);
+            else acc = ch[0] + ch[1];
+            codes[16 * wave + l16][8 * g + t] = pack4_low_bytes(quant_bits(acc[0], inv), quant_bits(acc[1], inv),
+                                                                quant_bits(acc[2], inv), quant_bits(acc[3], inv));
         }
     }
     __syncthreads();
@@ -1015,7 +1033,7 @@ hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K,
         e = m >= 8192 ? launch_dense_block_pass<kSinkInPlace, 2>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st)
                       : launch_dense_block_pass<kSinkInPlace, 1>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(dense_codes_kernel, dim3((unsigned)((m + 63) / 64), nb), dim3(256), 0, st, T, ldt, m, K, perm, p2, amax_tok, xq,
+        hipLaunchKernelGGL(m >= 8192 ? dense_codes_kernel<2> : dense_codes_kernel<4>, dim3((unsigned)((m + 63) / 64), nb), dim3(256), 0, st, T, ldt, m, K, perm, p2, amax_tok, xq,
                            sx + m0);
         if (e = hipGetLastError(); e != hipSuccess) return e;
     }
