@@ -992,7 +992,11 @@ bool tiled_rows_supports(const GemmArgs &a)
 //     And from more than one to four tiles per compute unit, where a launch is one round of tall and short tiles, if every die
 //     gets whole bands of tall ones (M % 2048; with 12 panels at 3072 tokens 1152 -> 3456 / 4608 22.0 / 22.6 -> 20.0 / 25.0), below K =
 //     2304: 1152 -> 3456 / 4608 at 4096 tokens 22.3 / 27.8 -> 21.6 / 26.6, 1024 -> 2016 at 6144 20.2 -> 18.5, 640 -> 1296 at 8192 15.5 -> 14.0,
-//     1152 -> 1152 at 8192 16.3 -> 16.2, 768 -> 2304 at 4096 12.9 -> 13.0 (2304 -> 2304 at 4096 24.3 -> 25.2).
+//     1152 -> 1152 at 8192 16.3 -> 16.2, 768 -> 2304 at 4096 12.9 -> 13.0 (2304 -> 2304 at 4096 24.3 -> 25.2).  But not where up to three
+//     tiles per compute unit need more tall ones than there are compute units: one with two of them then has the work of four
+//     tiles, while the 128 x 144 kernel has three (exactly three each: 768 -> 2304 at 6144 18.6 -> 20.5, 2048 -> 2304 32.6 -> 37.0,
+//     1152 -> 1152 at 12288 21.5 -> 24.1).  And where all tiles are short ones (up to two each) only below K = 1792: 1280 -> 2448 at
+//     2048 14.1 -> 13.2, 1536 -> 2016 at 4096 17.3 -> 16.8, 1792 -> 2448 at 2048 17.1 -> 17.9, 2176 -> 1152 at 8192 23.7 -> 24.5.
 //   - Zero points: the only other kernel that takes them at any shape is the any-shape one (768 -> 3072 at 4096 tokens
 //     23.2 -> 19.1, 1152 -> 4608 at 32700 tokens 268 -> 215).
 bool tiled_rows_pays(int64_t M, int K, int N, bool asym)
@@ -1004,7 +1008,11 @@ bool tiled_rows_pays(int64_t M, int K, int N, bool asym)
         if (asym && K >= 1024) return false;
         const int64_t tiles = (M / 128) * (int64_t)(N / kBN), cus = num_cus();
         if (K < 512 && N % 128 == 0) return K >= 256 && tiles > cus * 7 / 8 && tiles <= cus;
-        if (!asym && K >= 512 && K < 2304 && M % 2048 == 0 && tiles > cus && tiles <= 4 * cus) return true;
+        if (!asym && K >= 512 && K < 2304 && M % 2048 == 0 && tiles > cus && tiles <= 4 * cus) {
+            int n_big, nbn;
+            tiled_split(M, N, n_big, nbn);
+            return tiles <= 2 * cus ? K < 1792 : tiles > 3 * cus || n_big <= cus;
+        }
         return tiles <= (K < 1024 ? cus : K < 2304 ? cus * 3 / 4 : cus / 2);
     }
     if (asym) return true;

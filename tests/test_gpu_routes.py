@@ -27,6 +27,21 @@ def test_ragged_tokens_in_two_launches(oracle, M, K, N, pad):
     _linear_case(oracle, 15, M, K, N, 8, -1, ldy=N + pad)
 
 
+# whole 128 x 144 tiles, more than one per compute unit: one round of tall and short row-major tiles, unless three tiles per unit take
+# more tall ones than there are units (6144 x 2304: 264) or all of them are short and K is long
+@pytest.mark.parametrize("M,K,N,rows", [(4096, 1152, 3456, True), (6144, 768, 2160, True), (6144, 768, 2304, False), (12288, 1152, 1152, False),
+                                        (8192, 768, 2304, True), (8192, 1664, 1152, True), (8192, 1792, 1152, False), (4096, 2176, 2304, False)])
+def test_whole_tiles_in_one_round(M, K, N, rows):
+    assert bool(_rows(M, K, N)) == rows
+    g = torch.Generator(device="cuda").manual_seed(N)
+    w = trdq.prepare_weights(0.02 * torch.randn(K, N, generator=g, device="cuda"), None)
+    Xq = torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    acc, Y = torch.empty((M, N), dtype=torch.int32, device="cuda"), torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    trdq.qgemm(w, Xq, torch.ones(M, device="cuda"), Y, acc_debug=acc)
+    want = Xq.double() @ torch.from_numpy(w.export()[0].astype(np.float64)).cuda()
+    assert torch.equal(acc, want.int())
+
+
 # the general fused kernel: panels of 64, 32 and 16 tokens (up to 12, 24 and 48 blocks) in each register form (3, 6, 9, 12 blocks per
 # lane row), last panel and last channel tile incomplete
 @pytest.mark.parametrize("M,K,N", [(1000, 384, 1168), (1001, 768, 1168), (1001, 1152, 1168), (1010, 1536, 1168), (1000, 1664, 400),
