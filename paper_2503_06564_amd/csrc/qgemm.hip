@@ -289,7 +289,7 @@ hipError_t launch_qgemm(const Weights &w, const int8_t *Xq, const float *sx, con
         if (zc && !w.colsumw) return hipErrorInvalidValue;
         const int tile = variant < 0 ? qgemm4_direct_tile(M, w.K, w.N) : (variant < 11 ? variant - 8 : -1);
         if (tile >= 0) return launch_qgemm4_direct(a, acc_debug != nullptr, tile, st);
-        a.Wc = w.codes_wide;
+        if (tiled4_rows_reads_wide(M, w.N)) a.Wc = w.codes_wide;
         if ((variant == 11 || tiled4_rows_pays(M, w.K, w.N)) && tiled4_rows_supports(a))
             return launch_qgemm4_tiled_rows(a, acc_debug != nullptr, st);
     }
@@ -416,7 +416,8 @@ const void *qgemm_reads_codes(const Weights &w, int64_t M, bool tiled, bool asym
     if (w.wbits == 4) {
         if (tiled) return w.codes_wide;
         if (qgemm4_direct_tile(M, w.K, w.N) >= 0) return w.codes_tiled;
-        return !asym && tiled4_rows_pays(M, w.K, w.N) ? w.codes_wide : w.codes;
+        if (asym || !tiled4_rows_pays(M, w.K, w.N)) return w.codes;
+        return tiled4_rows_reads_wide(M, w.N) ? w.codes_wide : w.codes_tiled;
     }
     return tiled || qgemm8_direct_tile(M, w.K, w.N, asym) >= 0 || tiled_rows_pays(M, w.K, w.N, asym) ? w.codes_tiled : w.codes;
 }

@@ -642,7 +642,10 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
 // ---- int4 weights on block-tiled operands ---------------------------------------------------------
 // Eq. 10's product with 4-bit weight codes and one scale per 128 input channels and output channel.
 // Activations as above (1 KB blocks).  Weights: 16 * code, one byte each, in the 1 KB blocks of the int8 form (the packed codes,
-// widened when the set is prepared: K * N more bytes per set), so that the operands are those of the int8 kernels.  After the
+// widened when the set is prepared: K * N more bytes per set), so that the operands are those of the int8 kernels; PACKED: the
+// packed codes in blocks of 16 channels x 64 k (512 bytes): the 8 bytes that hold 16 consecutive k of a channel (byte j of a 4-byte
+// word = code(k0 + j) | code(k0 + 4 + j) << 4) are the unit, unit (n, q = k / 16) at ((n / 16) * (K / 64) + q / 4) * 512 + (q % 4) * 128 +
+// (n % 16) * 8, which a lane widens in registers (one shift-and-mask and one mask per word).  After the
 // two k-steps of a scale group the int32 sums are folded into float accumulators with the group's scales; the factor 16 leaves
 // with the token scale in the epilogue.
 //
@@ -653,29 +656,34 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
 // issues the same number of requests per step; past the last k-step the last one is copied again, for the same reason).
 // The fold of group g is spread over the first k-step of group g + 1: channel tile by channel tile, the vector
 // instructions of the tile's four sums in one run before the matrix instructions that start the next sums from zero.
+// Packed (64-token tiles only): a ring of five stages of 8.5 KB, three copies per wave and k-step, and each sum's fold right before
+// the matrix instruction that starts it again, under the ones before (in runs 1 to 10 % slower there).
 //
 // What bounds it is vector issue, two instructions per sum and group, and beyond 8192 tokens the power that sets the clock
 // (1.73 GHz in the loop).  Widening in the loop cost 1.5 vector instructions per matrix instruction: with packed codes in LDS,
 // and the folds between single matrix instructions, a workgroup's loop took 19100 cycles at K = 1152, now 17000.  us,
 // before and after: 1152 -> 3456 at 4096 / 16384 tokens 26.8 / 88.6 -> 26.0 / 84.5, 1152 -> 4608 at 16384 115.4 -> 110.7, 4608 ->
-// 1152 at 16384 106.1 -> 99.9, 768 -> 2304 at 2048 11.2 -> 10.2; 64-token tiles: 384 -> 2304 at 1024 6.1 -> 5.8.
+// 1152 at 16384 106.1 -> 99.9, 768 -> 2304 at 2048 11.2 -> 10.2; 64-token tiles: see tiled4_rows_reads_wide.
 constexpr int kW4BM = 128, kW4BN = 128;
-constexpr int kW4NS = 4;
 constexpr int kW4XOff = 0;
+constexpr int w4_stages(bool packed) { return packed ? 5 : 4; }
+constexpr int kW4MinK = 384;                          // a k-step more than the ring has stages, whole groups
 constexpr int w4_woff(int bm) { return bm * 64; }
-constexpr int w4_soff(int bm) { return bm * 64 + 8192; }
-constexpr int w4_stage(int bm) { return bm * 64 + 8192 + 512; }
-constexpr int w4_par_off(int bm) { return kW4NS * w4_stage(bm); }   // epilogue operands: [128 bias][pad][BM s_x]
-constexpr int w4_lds(int bm) { return w4_par_off(bm) + 2048; }      // 69632 B, with 64 tokens 53248 B
+constexpr int w4_soff(int bm, bool packed) { return bm * 64 + (packed ? 4096 : 8192); }
+constexpr int w4_stage(int bm, bool packed) { return w4_soff(bm, packed) + 512; }
+constexpr int w4_par_off(int bm, bool packed) { return w4_stages(packed) * w4_stage(bm, packed); }   // epilogue operands: [128 bias][pad][BM s_x]
+constexpr int w4_lds(int bm, bool packed) { return w4_par_off(bm, packed) + 2048; }     // 69632 B; with 64 tokens 53248, packed 45568 B
 
-template <int BM, bool DEBUG, int FORM>
+template <int BM, bool DEBUG, int FORM, bool PACKED>
 __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kernel(GemmArgs g)
 {
     extern __shared__ __align__(16) int8_t smem[];
-    constexpr int TM = BM / 32, TN = 4, NS = kW4NS;
+    constexpr int TM = BM / 32, TN = 4, NS = w4_stages(PACKED);
     constexpr int XC = BM / 64;                       // activation blocks a wave copies per k-step
-    constexpr int P = XC + 3;                         // copies per wave and k-step
-    constexpr int kW4WOff = w4_woff(BM), kW4SOff = w4_soff(BM), kW4Stage = w4_stage(BM), kW4ParOff = w4_par_off(BM);
+    constexpr int WC = PACKED ? 1 : 2;                // weight copies: two blocks, in one copy or two
+    constexpr int P = XC + WC + 1;                    // copies per wave and k-step
+    constexpr int WBLOCK = PACKED ? 512 : 1024;       // bytes of a weight block, 16 channels x 64 k
+    constexpr int kW4WOff = w4_woff(BM), kW4SOff = w4_soff(BM, PACKED), kW4Stage = w4_stage(BM, PACKED), kW4ParOff = w4_par_off(BM, PACKED);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)smem;
 #ifdef TRDQ_PROBE_PHASES
     const uint64_t clk_c0 = __builtin_readcyclecounter();
@@ -688,23 +696,25 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
     const int l16 = lane & 15, lg = lane >> 4;
     int tm, tn;
     tile_map(blockIdx.x, (int)((g.M + BM - 1) / BM), (g.N + kW4BN - 1) / kW4BN, tm, tn);
-    const int KT = g.K >> 6;                          // k-steps: even, at least NS
+    const int KT = g.K >> 6;                          // k-steps: even, more than NS
     const int64_t m0 = tile_m0(g, tm, BM);
     const int n0 = tile_n0<FORM>(g, tn, kW4BN);
 
     const int64_t xstride = (int64_t)KT * 1024;      // bytes from one 16-token group to the next
     constexpr int XSTEP = FORM == kBlocks ? 1024 : 64;  // bytes from one k-step of the activations to the next
     const int8_t *const xsrc = g.Xq + (m0 + 16 * XC * wave) * g.K;
-    const int8_t *const wsrc = static_cast<const int8_t *>(g.Wc) + (int64_t)(n0 / 16 + 2 * wave) * xstride;
+    const int64_t wstride = (int64_t)KT * WBLOCK;     // ... one 16-channel group to the next
+    const int8_t *const wsrc = static_cast<const int8_t *>(g.Wc) + (int64_t)(n0 / 16 + 2 * wave) * wstride;
     const uint32_t voffx = x_copy_off<FORM>(lane, g.K);
-    const uint32_t voffw = (uint32_t)(lane * 16);
+    // a packed copy moves two blocks: lanes 0-31 the first, lanes 32-63 the one a channel group further
+    const uint32_t voffw = PACKED ? (uint32_t)((lane & 31) * 16) + (lane >= 32 ? (uint32_t)wstride : 0u) : (uint32_t)(lane * 16);
     const float *const ssrc = g.sw + n0 + (wave & 1) * 64;
     const uint32_t voffs = (uint32_t)(lane * 4);
     auto issue_one = [&](auto c_tag, int s, int st) {
         constexpr int c = decltype(c_tag)::value;
         const uint32_t sbase = lds0 + st * kW4Stage;
         if constexpr (c < XC) dma_1k(voffx, xsrc + c * xstride + (int64_t)s * XSTEP, sbase + kW4XOff + (XC * wave + c) * 1024);
-        else if constexpr (c < XC + 2) dma_1k(voffw, wsrc + (c - XC) * xstride + (int64_t)s * 1024, sbase + kW4WOff + (2 * wave + c - XC) * 1024);
+        else if constexpr (c < XC + WC) dma_1k(voffw, wsrc + (c - XC) * wstride + (int64_t)s * WBLOCK, sbase + kW4WOff + (WC * wave + c - XC) * 1024);
         else copy_256_if(1, voffs, ssrc + (int64_t)(s >> 1) * g.N, sbase + kW4SOff + (wave & 1) * 256);
     };
     auto issue = [&](int s, int st) {
@@ -731,8 +741,11 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
 #endif
 
     const int xfr = kW4XOff + (wm * TM) * 1024 + (FORM == kBlocks ? lane * 16 : x_frag_off<FORM>(l16, lg));
-    const int wfr = kW4WOff + (wn * TN) * 1024 + lane * 16;
+    const int wfr = kW4WOff + (wn * TN) * WBLOCK + lane * (WBLOCK / 64);
     const int sfr = kW4SOff + (wn * 64 + lg * 4) * 4;
+    auto widen = [](uint2 p) {
+        return v4i{(int)((p.x << 4) & 0xF0F0F0F0u), (int)(p.x & 0xF0F0F0F0u), (int)((p.y << 4) & 0xF0F0F0F0u), (int)(p.y & 0xF0F0F0F0u)};
+    };
     v4i acc[TN][TM];
     v4f facc[TN][TM];
 #pragma unroll
@@ -740,10 +753,12 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
 #pragma unroll
         for (int b = 0; b < TM; ++b) { acc[a][b] = v4i{0, 0, 0, 0}; facc[a][b] = v4f{0.f, 0.f, 0.f, 0.f}; }
     v4i af[TN], bf[2][TM];
+    uint2 raw[PACKED ? TN : 1];                       // the next k-step's codes, widened where the ones before are used up
     float4 sc[TN];
 #pragma unroll
     for (int a = 0; a < TN; ++a) {
-        af[a] = *reinterpret_cast<const v4i *>(smem + wfr + a * 1024);
+        if constexpr (PACKED) af[a] = widen(*reinterpret_cast<const uint2 *>(smem + wfr + a * WBLOCK));
+        else af[a] = *reinterpret_cast<const v4i *>(smem + wfr + a * WBLOCK);
         sc[a] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
@@ -765,34 +780,41 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
         if constexpr (has_next) {
 #pragma unroll
             for (int b = 0; b < TM; ++b) bf[1 - HALF][b] = *reinterpret_cast<const v4i *>(nxt + xfr + b * 1024);
+            if constexpr (PACKED) {
+#pragma unroll
+                for (int a = 0; a < TN; ++a) raw[a] = *reinterpret_cast<const uint2 *>(nxt + wfr + a * WBLOCK);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
         static_for_n<TN>([&](auto a_tag) {
             constexpr int a = decltype(a_tag)::value;
-#pragma unroll
-            for (int b = 0; b < TM; ++b) {
-                if constexpr (HALF == 0) {
-                    if constexpr (fold_prev) {
-                        if constexpr (DEBUG) {
-                            const int64_t m = m_lane0 + b * 16;
-                            *reinterpret_cast<int4 *>(g.acc_debug + ((int64_t)((kt >> 1) - 1) * g.M + m) * g.N + n_lane + a * 16) =
-                                make_int4(acc[a][b][0] >> 4, acc[a][b][1] >> 4, acc[a][b][2] >> 4, acc[a][b][3] >> 4);
-                        }
-                        facc[a][b][0] += sc[a].x * (float)acc[a][b][0];
-                        facc[a][b][1] += sc[a].y * (float)acc[a][b][1];
-                        facc[a][b][2] += sc[a].z * (float)acc[a][b][2];
-                        facc[a][b][3] += sc[a].w * (float)acc[a][b][3];
+            auto fold = [&](int b) {
+                if constexpr (HALF == 0 && fold_prev) {
+                    if constexpr (DEBUG) {
+                        const int64_t m = m_lane0 + b * 16;
+                        *reinterpret_cast<int4 *>(g.acc_debug + ((int64_t)((kt >> 1) - 1) * g.M + m) * g.N + n_lane + a * 16) =
+                            make_int4(acc[a][b][0] >> 4, acc[a][b][1] >> 4, acc[a][b][2] >> 4, acc[a][b][3] >> 4);
                     }
+                    facc[a][b][0] += sc[a].x * (float)acc[a][b][0];
+                    facc[a][b][1] += sc[a].y * (float)acc[a][b][1];
+                    facc[a][b][2] += sc[a].z * (float)acc[a][b][2];
+                    facc[a][b][3] += sc[a].w * (float)acc[a][b][3];
                 }
+            };
+            if constexpr (!PACKED) {
+#pragma unroll
+                for (int b = 0; b < TM; ++b) fold(b);
+                if constexpr (HALF == 0) __builtin_amdgcn_sched_barrier(0);
             }
-            if constexpr (HALF == 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int bb = 0; bb < TM; ++bb) {
-                const int b = (a & 1) ? TM - 1 - bb : bb;
+                const int b = !PACKED && (a & 1) ? TM - 1 - bb : bb;
+                if constexpr (PACKED) fold(b);
                 acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[a], bf[HALF][b], HALF == 0 ? v4i{0, 0, 0, 0} : acc[a][b], 0, 0, 0);
             }
-            if constexpr (has_next) af[a] = *reinterpret_cast<const v4i *>(nxt + wfr + a * 1024);
-            issue_one(std::integral_constant<int, a>{}, kt + NS < KT ? kt + NS : KT - 1, st);
+            if constexpr (has_next && PACKED) af[a] = widen(raw[a]);
+            else if constexpr (has_next) af[a] = *reinterpret_cast<const v4i *>(nxt + wfr + a * WBLOCK);
+            if constexpr (a < P) issue_one(std::integral_constant<int, a>{}, kt + NS < KT ? kt + NS : KT - 1, st);
             if constexpr (a == TN - 1 && P > TN) issue_one(std::integral_constant<int, P - 1>{}, kt + NS < KT ? kt + NS : KT - 1, st);
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -1028,48 +1050,49 @@ hipError_t launch_qgemm8_tiled_rows(const GemmArgs &a, bool debug, hipStream_t s
 
 bool tiled4_supports(const GemmArgs &a)
 {
-    return a.M > 0 && a.M % kW4BM == 0 && a.N % kW4BN == 0 && a.K % 128 == 0 && a.K >= 64 * kW4NS + 64 && a.ldy % 8 == 0 &&
+    return a.M > 0 && a.M % kW4BM == 0 && a.N % kW4BN == 0 && a.K % 128 == 0 && a.K >= kW4MinK && a.ldy % 8 == 0 &&
            reinterpret_cast<uintptr_t>(a.Y) % 16 == 0 && !a.zc;
 }
 
 namespace {
 
-template <int BM, int FORM>
+template <int BM, int FORM, bool PACKED>
 hipError_t launch_w4(const GemmArgs &a, bool debug, hipStream_t st)
 {
     GemmArgs g = a;
     auto go = [&](auto kern) -> hipError_t {
-        if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), w4_lds(BM)); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(((a.M + BM - 1) / BM) * ((a.N + kW4BN - 1) / kW4BN))), dim3(kThreads), w4_lds(BM),
-                           st, g);
+        if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), w4_lds(BM, PACKED)); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(((a.M + BM - 1) / BM) * ((a.N + kW4BN - 1) / kW4BN))), dim3(kThreads),
+                           w4_lds(BM, PACKED), st, g);
         return hipGetLastError();
     };
 #ifdef TRDQ_PROBE_PHASES
     debug = false;                                    // the debug pointer receives time stamps instead
 #endif
-    return debug ? go(qgemm4_tiled_kernel<BM, true, FORM>) : go(qgemm4_tiled_kernel<BM, false, FORM>);
+    return debug ? go(qgemm4_tiled_kernel<BM, true, FORM, PACKED>) : go(qgemm4_tiled_kernel<BM, false, FORM, PACKED>);
 }
 
 }  // namespace
 
 hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st)
 {
-    return tiled4_supports(a) ? launch_w4<kW4BM, kBlocks>(a, debug, st) : hipErrorInvalidValue;
+    return tiled4_supports(a) ? launch_w4<kW4BM, kBlocks, false>(a, debug, st) : hipErrorInvalidValue;
 }
 
 bool tiled4_rows_supports(const GemmArgs &a)
 {
-    return a.M >= 64 && a.M <= (1 << 30) && a.N >= kW4BN && a.N % 16 == 0 && a.K % 128 == 0 && a.K >= 64 * kW4NS + 64 &&
+    return a.M >= 64 && a.M <= (1 << 30) && a.N >= kW4BN && a.N % 16 == 0 && a.K % 128 == 0 && a.K >= kW4MinK &&
            a.ldy % 8 == 0 && reinterpret_cast<uintptr_t>(a.Y) % 16 == 0 && !a.zc;
 }
 
 hipError_t launch_qgemm4_tiled_rows(const GemmArgs &a, bool debug, hipStream_t st)
 {
-    return tiled4_rows_supports(a) ? launch_w4<64, kRows>(a, debug, st) : hipErrorInvalidValue;
+    if (!tiled4_rows_supports(a)) return hipErrorInvalidValue;
+    return tiled4_rows_reads_wide(a.M, a.N) ? launch_w4<64, kRows, false>(a, debug, st) : launch_w4<64, kRows, true>(a, debug, st);
 }
 
 // Where the 64-token tiles on row-major codes are the fastest int4 product: up to three workgroups per compute unit, one
-// round (beyond, 128-token tiles do less widening and folding per product: 1152 -> 1152 at 6000 tokens, 846 tiles, 18.0
+// round (beyond, 128-token tiles read less per product: 1152 -> 1152 at 6000 tokens, 846 tiles, 18.0
 // against 16.6 us).  With one 128 x 128 tile per compute unit and one wave per SIMD every k-step waits for its barrier,
 // its LDS reads and its fold in turn; two or three workgroups of half the height fill those waits.  us, before and
 // after: 1024 -> 2048 at 1232 / 2048 / 3000 tokens 10.5 / 10.6 / 15.2 -> 9.1 / 10.2 / 12.9, 1152 -> 4608 at 1000 16.0 -> 13.5,
@@ -1077,7 +1100,20 @@ hipError_t launch_qgemm4_tiled_rows(const GemmArgs &a, bool debug, hipStream_t s
 // nothing here, the product being bound by its vector instructions.
 bool tiled4_rows_pays(int64_t M, int K, int N)
 {
-    return M >= 64 && N >= kW4BN && K >= 64 * kW4NS + 64 && ((M + 63) / 64) * ((N + kW4BN - 1) / kW4BN) <= 3 * (int64_t)num_cus();
+    return M >= 64 && N >= kW4BN && K >= kW4MinK && ((M + 63) / 64) * ((N + kW4BN - 1) / kW4BN) <= 3 * (int64_t)num_cus();
+}
+
+// Which copy of the codes they read.  Widened bytes spare a workgroup that shares its compute unit with at most one other the
+// instructions, packed ones halve what a die's L2 brings in, which grows with the channel tiles that run side by side and with
+// the rounds in which they do.  us, packed / widened: 4608 -> 1152 at 1344 tokens 23.4 / 19.7, at 3584 30.5 / 28.9, 1024 -> 2048 at 1280
+// 9.0 / 8.2, 3072 -> 3072 at 512 16.8 / 14.3, 4608 -> 4608 at 320 22.8 / 20.0; but there at 448 23.3 / 24.4, at 1344 45 / 62, 1152 -> 4608
+// at 576 9.9 / 11.9, 3072 -> 3072 at 1088 21.2 / 22.8, 1024 -> 2048 at 2048 9.9 / 10.9.  All linears of 24 blocks of width 1024 in turn,
+// passes included, at 4096 tokens 2934 / 2824.  Sets that come from memory without a pass that reads them before: 4608 -> 1152 at
+// 2304 29.7 / 25.9, 1024 -> 2048 at 1280 9.9 / 9.9, at 1600 10.2 / 10.5, 4608 -> 1152 at 3584 31.1 / 34.5.
+bool tiled4_rows_reads_wide(int64_t M, int N)
+{
+    const int64_t tiles_n = (N + kW4BN - 1) / kW4BN, tiles = (M + 63) / 64 * tiles_n, cus = num_cus();
+    return tiles <= 2 * cus && tiles * tiles_n <= 28 * cus;
 }
 
 hipError_t launch_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st)

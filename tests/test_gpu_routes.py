@@ -19,6 +19,10 @@ def _rows(M, K, N, asym=False):
     return gu.library_rule("_ZN4trdq4gemm15tiled_rows_paysEliib", M, K, N, asym) & 1
 
 
+def _rows4(M, K, N):
+    return not gu.library_rule("_ZN4trdq4gemm18qgemm4_direct_tileElii", M, K, N) >= 0 and gu.library_rule("_ZN4trdq4gemm16tiled4_rows_paysElii", M, K, N) & 1
+
+
 # whole panels and the remaining rows in two launches: rows of Y that are 8-byte aligned only (M % 256 below and above 128), and
 # many ragged tokens at a width that is no multiple of 144 (heads of 256- and of 128-token panels; 16 and 112 rows left)
 @pytest.mark.parametrize("M,K,N,pad", [(1500, 1152, 1136, 4), (2100, 640, 1040, 12), (14096, 384, 400, 0), (14192, 256, 528, 0)])
@@ -40,6 +44,56 @@ def test_whole_tiles_in_one_round(M, K, N, rows):
     trdq.qgemm(w, Xq, torch.ones(M, device="cuda"), Y, acc_debug=acc)
     want = Xq.double() @ torch.from_numpy(w.export()[0].astype(np.float64)).cuda()
     assert torch.equal(acc, want.int())
+
+
+# int4, 64-token tiles of row-major codes: widened codes with few channel tiles side by side, packed ones beyond (the last tile of
+# either kind ragged both ways)
+@pytest.mark.parametrize("M,K,N,wide", [(1000, 1664, 1296, True), (2010, 384, 1168, True), (700, 512, 2320, True), (448, 512, 4608, False),
+                                        (1000, 384, 3440, False), (3000, 640, 2000, False)])
+def test_int4_copy_of_the_codes(M, K, N, wide):
+    assert _rows4(M, K, N)
+    assert bool(gu.library_rule("_ZN4trdq4gemm22tiled4_rows_reads_wideEli", M, N, 0) & 1) == wide
+    g = torch.Generator(device="cuda").manual_seed(N)
+    w = trdq.prepare_weights(0.02 * torch.randn(K, N, generator=g, device="cuda"), None, wbits=4)
+    Xq = torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    sx, bias = torch.rand(M, generator=g, device="cuda"), torch.randn(N, generator=g, device="cuda")
+    acc = torch.empty((K // 128, M, N), dtype=torch.int32, device="cuda")
+    Y, ring = (torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    trdq.qgemm(w, Xq, sx, Y, bias=bias, acc_debug=acc)
+    codes = torch.from_numpy(w.export()[0].astype(np.float64)).cuda()
+    want = torch.stack([Xq[:, k:k + 128].double() @ codes[k:k + 128] for k in range(0, K, 128)])
+    assert torch.equal(acc, want.int())
+    trdq.qgemm(w, Xq, sx, Y.fill_(7.0), bias=bias)
+    try:
+        trdq.qgemm_set_variant(6)                     # the ring kernel; the folds keep its order
+        trdq.qgemm(w, Xq, sx, ring, bias=bias)
+    finally:
+        trdq.qgemm_set_variant(-1)
+    assert torch.equal(Y, ring)
+
+
+def test_int4_many_channel_tiles_are_no_slower_than_the_ring_kernel():
+    """... which the widened codes made them: 62 us against 45 at 1344 x 4608 -> 4608, packed 44.  1.2 leaves room for a busy device."""
+    M, K, N = 1344, 4608, 4608
+    assert _rows4(M, K, N)
+    w = trdq.prepare_weights(0.02 * torch.randn(K, N, device="cuda"), None, wbits=4)
+    Xq = torch.randint(-127, 128, (M, K), device="cuda", dtype=torch.int8)
+    sx, Y = torch.ones(M, device="cuda"), torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = {}
+    try:
+        for rep in range(8):
+            for variant in (-1, 6):
+                trdq.qgemm_set_variant(variant)
+                start.record()
+                for _ in range(20):
+                    trdq.qgemm(w, Xq, sx, Y)
+                end.record()
+                torch.cuda.synchronize()
+                best[variant] = min(best.get(variant, 1e9), start.elapsed_time(end))
+    finally:
+        trdq.qgemm_set_variant(-1)
+    assert best[-1] < 1.2 * best[6], best
 
 
 # the general fused kernel: panels of 64, 32 and 16 tokens (up to 12, 24 and 48 blocks) in each register form (3, 6, 9, 12 blocks per
