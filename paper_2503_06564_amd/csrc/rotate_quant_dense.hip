@@ -1000,10 +1000,12 @@ size_t rotate_quant_dense_rpr_workspace_bytes(int64_t M, int K)
     return ((size_t)K + 1) * (size_t)dense_ws_ldt(M) * sizeof(float);
 }
 
-// us, 16-token kernel / this form, at 16384, 24576 and 32768 tokens: 128 channels 27 / 30, 37 / 35, 48 / 37; 256 29 / 37, 40 / 39, 53 / 42; 384
-// 34 / 38, 48 / 55, 63 / 58; 640 49 / 55, 71 / 65, 93 / 85; 768 55 / 58, 79 / 82, 104 / 103; 896 63 / 62, 91 / 86, 120 / 110; 1152 91 / 85,
-// 123 / 108, 162 / 143; 1536 104 / 104, 153 / 149, 203 / 195 (and 128 / 113 at 20480).
-static bool dense_ws_pays(int64_t M, int nb) { return nb >= 9 || M >= 24576; }
+// us, 16-token kernel / this form, at 24576, 28672 and 32768 tokens: 128 channels 36 / 28, 41 / 30, 47 / 33; 256 40 / 41, 47 / 42, 53 / 43; 384
+// 47.5 / 57.6, 55.0 / 58.8, 62.6 / 61.2 and at 30720 63 / 60 (a block's workgroups have 680 waves for 768 groups of 32 tokens, so that most
+// wait for a second round); 512 59.5 / 61.8, 67 / 66, 77 / 70; 640 74 / 69, 86 / 86, 96 / 89; 768 83.5 / 87.0, 95 / 92, 108 / 108, at 26624 94 / 89;
+// 896 96 / 92, 110 / 110, 128 / 115; 1024 105 / 99, 124 / 115, 140 / 122; at 16384 128 27 / 30, 640 49 / 55, 896 63 / 62, 1152 91 / 85, 1536
+// 104 / 104.
+static bool dense_ws_pays(int64_t M, int nb) { return nb >= 9 || M >= (nb == 3 ? 30000 : 24576); }
 
 // Values of T at a time, 226 MB: most of them stay in the memory-side cache between the three launches (us, whole / in two parts:
 // 32768 x 1664, 218 MB, 226 / 237; 16384 x 3072, 201 MB, 200 / 208; 65536 x 896, 235 MB, 251 / 244; with nine products 16384 x 4608, 302 MB,
@@ -1026,14 +1028,18 @@ hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K,
         int8_t *const xq = Xq + m0 * K;
         float *const amax_tok = T + (size_t)K * ldt;
         // first rotation (also clears the maxima); second rotation in place, with the maxima; codes and scales
-        hipError_t e = launch_dense_block_pass<kSinkRows, 2>(x, m, nb, ldx, p1, amax_tok, xq, perm, T, ldt, st);
+        // Two token tiles per fragment read halve the LDS traffic (second rotation: 4-5 % from 8192 tokens on), but where a launch's 2048
+        // waves have hardly a group of 32 tokens each, groups of 16 halve the chain.  us, two / one: 128 channels at 24576 / 32768 tokens
+        // 34 / 28, 36 / 33 (beyond, groups of 16 are a second round: 40960 38 / 40), 256 at 28672 43.5 / 41.8; first rotation: 1664 at 1000
+        // 27.5 / 24.1, 4608 at 500 30.9 / 27.6.
+        const bool few = m * nb <= (nb == 1 ? 32768 : 65536), two = m >= 8192 && !few;
+        hipError_t e = few ? launch_dense_block_pass<kSinkRows, 1>(x, m, nb, ldx, p1, amax_tok, xq, perm, T, ldt, st)
+                           : launch_dense_block_pass<kSinkRows, 2>(x, m, nb, ldx, p1, amax_tok, xq, perm, T, ldt, st);
         if (e != hipSuccess) return e;
-        // Two token tiles per fragment read halve the LDS traffic of the second rotation (4-5 % from 8192 tokens on);
-        // with fewer tokens a wave has too few groups of 32 for that to make up for the coarser split of the work.
-        e = m >= 8192 ? launch_dense_block_pass<kSinkInPlace, 2>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st)
+        e = two ? launch_dense_block_pass<kSinkInPlace, 2>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st)
                       : launch_dense_block_pass<kSinkInPlace, 1>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(m >= 8192 ? dense_codes_kernel<2> : dense_codes_kernel<4>, dim3((unsigned)((m + 63) / 64), nb), dim3(256), 0, st, T, ldt, m, K, perm, p2, amax_tok, xq,
+        hipLaunchKernelGGL(two ? dense_codes_kernel<2> : dense_codes_kernel<4>, dim3((unsigned)((m + 63) / 64), nb), dim3(256), 0, st, T, ldt, m, K, perm, p2, amax_tok, xq,
                            sx + m0);
         if (e = hipGetLastError(); e != hipSuccess) return e;
     }

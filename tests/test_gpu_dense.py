@@ -198,11 +198,11 @@ def test_rotate_quant_dense_rpr_matches_oracle(oracle, M, K):
     rot1.close(); rot2.close()
 
 
-# the workspace form: block-resident kernels around float32 once-rotated values (K > 1536, and narrower rows from
-# 16384 tokens on); otherwise it is the plain call.  13 blocks and 36, token counts around the 16- and 32-token groups and beyond one round of workgroups.
-# (from 8192 tokens on the second rotation takes two token tiles per fragment read)
+# the workspace form: block-resident kernels around float32 rotated values (K > 1536, narrower rows from 16384 or 24576 tokens on);
+# otherwise it is the call without a workspace, which 300 x 1152, 16400 x 384 and 16384 x 128 are.  1, 9, 13 and 36 blocks, token counts
+# around the groups of 16 and of 32 tokens (of 32 for both rotations from 8230 x 1664 on) and beyond one round of workgroups.
 @pytest.mark.parametrize("M,K", [(1, 1664), (40, 1664), (9, 2304), (33, 2304), (70, 4608), (263, 4608), (1100, 2304),
-                                 (300, 1152), (0, 2304), (8230, 1664), (8192, 2304), (16400, 384), (16384, 128)])
+                                 (300, 1152), (0, 2304), (8230, 1664), (8192, 2304), (16400, 384), (16384, 128), (24580, 128), (16390, 1152)])
 def test_rotate_quant_dense_rpr_ws_matches_oracle(oracle, M, K):
     say(f"rotate_quant_dense_rpr_ws M={M} K={K}")
     Xb, _, d, _ = wl.small_case(74, max(M, 1), K, 16, n_outliers=max(1, K // 144), outlier=40.0)
@@ -383,6 +383,63 @@ def test_second_rotation_keeps_float32_precision_for_sparse_blocks(K):
     bound = 5 * 2.0 ** -24
     assert np.abs(err).max() <= bound
     assert abs(err.mean()) <= bound * np.sqrt(2 * np.log(2e9) / M)
+    rot1.close(); rot2.close()
+
+
+@pytest.mark.parametrize("M,K,form", [(24576, 128, "workspace"), (24577, 128, "workspace"), (40977, 128, "workspace"), (24599, 256, "workspace"),
+                                      (32801, 256, "workspace"), (24576, 384, "tokens"), (30001, 384, "workspace"), (16400, 1152, "workspace"),
+                                      (16385, 1536, "workspace"), (1001, 1664, "workspace"), (2521, 3328, "workspace")])
+def test_dense_rpr_ws_against_the_form_without_a_workspace(M, K, form):
+    """Real permutations, through the workspace in groups of 16 and of 32 tokens, and the narrow rows that the 16-token kernel takes: codes
+    within the one step that the two forms' rounding allows, scales within 128 * 2^-24."""
+    g = torch.Generator(device=dev()).manual_seed(M + K)
+    R = torch.randn(K // 128, 128, 128, generator=g, device=dev()) * 0.088
+    rot1, rot2 = trdq.Rotation(R, torch.rand(K, generator=g, device=dev()) + 0.5), trdq.Rotation(R)
+    perm = torch.randperm(K, generator=g, device=dev()).int()
+    X = torch.randn(M, K, generator=g, device=dev()).bfloat16()
+    ws = torch.full((trdq.rotate_quant_dense_rpr_ws_nbytes(M, K),), 0xFF, dtype=torch.uint8, device=dev())
+    out = [(torch.full((M, K), 99, dtype=torch.int8, device=dev()), torch.full((M,), -1.0, device=dev())) for _ in range(2)]
+    trdq.rotate_quant_dense_rpr(X, rot1, perm, rot2, *out[0])
+    trdq.rotate_quant_dense_rpr_ws(X, rot1, perm, rot2, *out[1], ws)
+    torch.cuda.synchronize()
+    assert bool((ws != 0xFF).any()) == (form == "workspace")
+    step = (out[0][0].short() - out[1][0].short()).abs()
+    assert step.max() <= 1 and (step != 0).float().mean() < 1e-3
+    assert ((out[0][1] - out[1][1]).abs() <= out[0][1] * 128 * 2.0 ** -24).all() and (out[0][1] > 0).all()
+    rot1.close(); rot2.close()
+
+
+@pytest.mark.parametrize("K,most", [(128, 0.87), (384, 1.1)])
+def test_dense_rpr_ws_of_narrow_rows_pays(K, most):
+    """... against the call without a workspace: at 24576 tokens of 128 channels 0.78 of its time (0.93 with groups of 32 tokens), of 384
+    the same kernel (through the workspace 1.2)."""
+    M = 24576
+    g = torch.Generator(device=dev()).manual_seed(3)
+    R = torch.randn(K // 128, 128, 128, generator=g, device=dev()) * 0.088
+    rot1, rot2 = trdq.Rotation(R, torch.rand(K, generator=g, device=dev()) + 0.5), trdq.Rotation(R)
+    perm = torch.randperm(K, generator=g, device=dev()).int()
+    X = torch.randn(M, K, generator=g, device=dev()).bfloat16()
+    ws = torch.empty((trdq.rotate_quant_dense_rpr_ws_nbytes(M, K),), dtype=torch.uint8, device=dev())
+    Xq, sx = torch.empty((M, K), dtype=torch.int8, device=dev()), torch.empty((M,), device=dev())
+    calls = {"plain": lambda: trdq.rotate_quant_dense_rpr(X, rot1, perm, rot2, Xq, sx),
+             "ws": lambda: trdq.rotate_quant_dense_rpr_ws(X, rot1, perm, rot2, Xq, sx, ws)}
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best, graphs = {}, {}
+    for name, call in calls.items():
+        call()
+        torch.cuda.synchronize()
+        graphs[name] = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graphs[name]):
+            for _ in range(20):
+                call()
+    for rep in range(12):
+        for name, graph in graphs.items():
+            start.record()
+            graph.replay()
+            end.record()
+            torch.cuda.synchronize()
+            best[name] = min(best.get(name, 1e9), start.elapsed_time(end))
+    assert best["ws"] < most * best["plain"], best
     rot1.close(); rot2.close()
 
 
