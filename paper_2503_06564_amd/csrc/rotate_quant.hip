@@ -28,13 +28,14 @@ namespace trdq {
 
 namespace {
 
-// From here on input and codes, three bytes per value, do not fit the memory-side cache of 256 MB together, and the input is read as
-// what nobody will read again, so that the codes stay for the product.  us, ordinary / non-temporal: 32768 x 4608 as rows 84 /
-// 77 on one input, 84 / 80 on several, block-tiled 89 / 79 and 88 / 82; 65536 x 2304 86 / 83, 86 / 87, 96 / 93, 96 / 94; the pass and
-// its product, 4608 -> 1152, at 24576 tokens 168 / 161, at 32768 230 / 210; layers in which each pass reads what the product
-// before it wrote, 1152 -> 4608 -> 1152 at 32768, 442 / 418.  Below, an input that the cache still holds
-// would come from memory instead: 16384 x 4608 38 / 42 and 32768 x 1152 21 / 23 on one input, 2304 -> 768 at 24576 with its product 84 / 87.
-constexpr int64_t kOnceValues = ((int64_t)256 << 20) / 3 + 1;
+// From here on (in values; zero points: their own line) the input is read as what nobody will read again, so that more of the codes stay
+// for the product in the memory-side cache of 256 MB.  us on one input, ordinary / non-temporal: 113 M values 24576 x 4608 as rows 59.2 / 57.0,
+// block-tiled 61.7 / 57.8, with zero points 59.5 / 57.6, 49152 x 2304 62.2 / 62.2, 67.1 / 65.3, 67.7 / 69.0; 151 M 32768 x 4608 79.7 / 73.9,
+// 84.0 / 75.6, 79.7 / 75.4, 65536 x 2304 83.5 / 81.7, 90.1 / 85.4, 89.6 / 89.5; the pass and its product, 4608 -> 1152, at 24576 tokens
+// 168 / 161, at 32768 230 / 210.  With fewer values an input that the cache still holds would come from memory: 90 M 38912 x 2304
+// 44.1 / 48.9, 45.8 / 52.6, 49.9 / 52.9, 22400 x 4096 45.4 / 47.8, 45.8 / 48.5, 19420 x 4608 45.0 / 46.5, 44.1 / 47.2.  (Layers in which
+// each pass reads what the product before it wrote gain below, too: 1152 -> 4608 -> 1152 at 24576 352 / 300.)
+constexpr int64_t kOnceValues = (int64_t)108 << 20, kOnceValuesAsym = (int64_t)144 << 20;
 
 // 16 bytes of the input; ONCE: non-temporal.  (A template: of a branch between the two loads the compiler makes one ordinary load.)
 template <bool ONCE>
@@ -212,6 +213,12 @@ __global__ __launch_bounds__(SPW <= 3 ? 768 : 576, SPW <= 3 ? 6 : 3) void rotate
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+}  // namespace
+
+bool rotate_quant_reads_once(int64_t M, int K, bool asym) { return M * K >= (asym ? kOnceValuesAsym : kOnceValues); }
+
+namespace {
+
 template <int QUADS, int SPW>
 hipError_t launch_spw(const uint16_t *X, int64_t M, int nb, int64_t ldx, const float *diag,
                       int8_t *Xq, float *sx, int32_t *zc, const void *warm, int64_t warm_bytes, hipStream_t st,
@@ -223,7 +230,7 @@ hipError_t launch_spw(const uint16_t *X, int64_t M, int nb, int64_t ldx, const f
     const float sx_mul = 0.08838834764831845f / qmax;
     const size_t smem = sizeof(float) * (size_t)nw * 2 * TOK + 1024;                 // extremes, dump area
     const int64_t warm_chunks = (warm && warm_bytes < ((int64_t)1 << 32)) ? warm_bytes / 16 : 0;   // 32-bit byte offsets in the copy
-    const bool once = (int64_t)nb * kBlock * M >= kOnceValues;
+    const bool once = rotate_quant_reads_once(M, nb * kBlock, zc != nullptr);
     auto kern = zc ? (once ? rotate_quant_kernel<QUADS, SPW, true, true> : rotate_quant_kernel<QUADS, SPW, true, false>)
                    : (once ? rotate_quant_kernel<QUADS, SPW, false, true> : rotate_quant_kernel<QUADS, SPW, false, false>);
     hipLaunchKernelGGL(kern, dim3((unsigned)((M + TOK - 1) / TOK)), dim3(64 * nw), smem, st,

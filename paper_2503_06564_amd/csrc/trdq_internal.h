@@ -58,6 +58,7 @@ struct Table {
 // kernel reads once and discards, to pull it into the memory-side cache for the next kernel.
 // zc: null (symmetric quantiser), or where the asymmetric quantiser writes 128 - z_i per token.
 // tiled: Xq is written in 1 KB blocks of 16 tokens x 64 k (block (m / 16, k / 64) at ((m / 16) * K / 64 + k / 64) * 1024)
+bool rotate_quant_reads_once(int64_t M, int K, bool asym);   // whether that pass reads its input non-temporally
 hipError_t launch_rotate_quant(const uint16_t *X, int64_t M, int K, int64_t ldx, const float *diag,
                                int8_t *Xq, float *sx, int32_t *zc, const void *warm, int64_t warm_bytes, hipStream_t st,
                                int abits = 8,    // symmetric codes in +-(2^(abits-1) - 1); K <= 4608 unless 8

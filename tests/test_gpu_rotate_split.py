@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2503_06564_amd import trdq, workloads as wl
-from gpu_util import CODE_FRAC, assert_scales_close, bf16_to_dev, dev, f32_to_dev
+from gpu_util import CODE_FRAC, assert_scales_close, bf16_to_dev, dev, f32_to_dev, library_rule
 
 pytestmark = pytest.mark.gpu
 
@@ -94,12 +94,15 @@ def test_many_tokens_like_few(M, K):
     assert torch.equal(buf[m:M], back[m:]) and torch.equal(sx[m:M], want_s[m:]) and torch.equal(zc_all[m:], zc[:300])
 
 
-@pytest.mark.parametrize("M,K", [(19419, 4608), (19420, 4608), (699051, 128)])
-def test_inputs_about_the_size_of_the_memory_side_cache(M, K):
-    """One call on either side of the size from which the input is read non-temporally (89 478 486 values) against calls on parts of it:
-    the same codes, scales and zero points for every form, rows that are further apart than K included."""
+@pytest.mark.parametrize("M,K,once", [(24575, 4608, "none"), (24576, 4608, "symmetric"), (884735, 128, "none"), (884736, 128, "symmetric"),
+                                      (32767, 4608, "symmetric"), (32768, 4608, "all")])
+def test_inputs_about_the_size_of_the_memory_side_cache(M, K, once):
+    """Calls on either side of the sizes from which the input is read non-temporally (108 * 2^20 values, with zero points 144 * 2^20) against
+    calls on parts of it: the same codes, scales and zero points for every form, rows that are further apart than K included."""
+    rule = "_ZN4trdq23rotate_quant_reads_onceElib"
+    assert (library_rule(rule, M, K, False) & 1, library_rule(rule, M, K, True) & 1) == (once != "none", once == "all")
     g = torch.Generator(device="cuda").manual_seed(M)
-    X = torch.randn(M, K + 8, generator=g, device="cuda", dtype=torch.float32).bfloat16()[:, :K]
+    X = torch.randn(M, K + 8, generator=g, device="cuda", dtype=torch.bfloat16)[:, :K]
     diag = torch.rand(K, generator=g, device="cuda") + 0.5
     part = 16 * (M // 64)
     calls = [lambda x, q, s, z: trdq.rotate_quant(x, diag, q, s), lambda x, q, s, z: trdq.rotate_quant_asym(x, diag, q, s, z),
