@@ -188,8 +188,9 @@ void trdq_table_destroy(trdq_table *t)
 namespace {
 
 // One device allocation per weight set (an allocation and its release cost 50-100 us each, more than the
-// kernels that fill it): codes, their block-tiled copy (symmetric sets), scales, column sums, and the diagonal for a
-// handle that keeps a copy.
+// kernels that fill it): codes, their block-tiled copy (symmetric sets), widened codes (int4), scales, column sums, the block maxima
+// between the two passes of a preparation that has no scratch matrix (8-bit codes of very long rows after one Hadamard rotation),
+// and the diagonal for a handle that keeps a copy.
 trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
 {
     const int K = w->K, N = w->N, nb = K / trdq::kBlock;
@@ -203,6 +204,8 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     const size_t at_scales = take((w4 ? (size_t)nb * N : (size_t)N) * sizeof(float));
     const size_t at_colsum = take((size_t)N * sizeof(float));          // int32 sums, or the scaled float ones of int4 codes
     const size_t at_zcw = asym ? take((size_t)N * sizeof(int32_t)) : 0;
+    const bool maxima = !asym && !w4 && w->rotation == trdq::kRotHadamard && trdq::prepare_takes_pair(K, N, w->wbits, false);
+    const size_t at_amax = maxima ? take((size_t)nb * N * sizeof(float)) : 0;
     const size_t at_diag = with_diag ? take((size_t)K * sizeof(float)) : 0;
     if (hipMalloc(&w->block, total) != hipSuccess) { w->block = nullptr; (void)hipGetLastError(); return TRDQ_ERR_ALLOC; }
     char *const base = static_cast<char *>(w->block);
@@ -213,6 +216,7 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     if (w4) w->colsumw = reinterpret_cast<float *>(base + at_colsum);
     else w->colsum = reinterpret_cast<int32_t *>(base + at_colsum);
     w->zcw = asym ? reinterpret_cast<int32_t *>(base + at_zcw) : nullptr;
+    w->amax = maxima ? reinterpret_cast<float *>(base + at_amax) : nullptr;
     w->diag = with_diag ? reinterpret_cast<float *>(base + at_diag) : nullptr;
     return TRDQ_OK;
 }
@@ -224,27 +228,30 @@ trdq_status fill_weights(trdq_weights *w, const float *W_dev, const float *diag_
 {
     const int K = w->K, N = w->N;
     const float half = 0.08838834764831845f;            // 1 / sqrt(128)
-    const size_t bytes = (size_t)K * N * sizeof(float);
+    const bool maxima = w->wbits != 4 && trdq::prepare_takes_pair(K, N, w->wbits, perm_dev && !rot);
+    const size_t bytes = (size_t)K * N * sizeof(float), more = maxima ? bytes / trdq::kBlock : 0;
     float *Wrot = nullptr, *Wrot2 = nullptr;            // rotated weights, where more than one kernel needs them
-    if (((rot || perm_dev) && hipMalloc(reinterpret_cast<void **>(&Wrot), bytes) != hipSuccess) ||
+    float *amax = w->amax;                              // block maxima: behind them, or the set's own
+    if (((rot || perm_dev) && hipMalloc(reinterpret_cast<void **>(&Wrot), bytes + more) != hipSuccess) ||
         (rot2 && hipMalloc(reinterpret_cast<void **>(&Wrot2), bytes) != hipSuccess)) {
         (void)hipGetLastError();
         if (Wrot) (void)hipFree(Wrot);
         return TRDQ_ERR_ALLOC;
     }
+    if (Wrot) amax = Wrot + (size_t)K * N;
     hipError_t e;
     if (rot) {
         // dense orthonormal blocks (nothing to normalise afterwards); Eq. 10 in full: rows gathered through the
         // permutation and rotated a second time
         e = trdq::launch_prepare_rotate_dense(W_dev, K, N, rot->diag, nullptr, rot->R, Wrot, st);
         if (e == hipSuccess && rot2) e = trdq::launch_prepare_rotate_dense(Wrot, K, N, nullptr, perm_dev, rot2->R, Wrot2, st);
-        if (e == hipSuccess) e = trdq::launch_prepare_quant(rot2 ? Wrot2 : Wrot, nullptr, nullptr, false, 1.0f, *w, nullptr, st);
+        if (e == hipSuccess) e = trdq::launch_prepare_quant(rot2 ? Wrot2 : Wrot, nullptr, nullptr, false, 1.0f, *w, amax, nullptr, st);
     } else if (perm_dev) {
         // the Hadamard form of Eq. 9: two unnormalised rotations, 1/128
         e = trdq::launch_prepare_rotate(W_dev, K, N, diag_dev, Wrot, st);
-        if (e == hipSuccess) e = trdq::launch_prepare_quant(Wrot, nullptr, perm_dev, true, 0.0078125f, *w, nullptr, st);
+        if (e == hipSuccess) e = trdq::launch_prepare_quant(Wrot, nullptr, perm_dev, true, 0.0078125f, *w, amax, nullptr, st);
     } else {
-        e = trdq::launch_prepare_quant(W_dev, diag_dev, nullptr, true, half, *w, w->diag, st);
+        e = trdq::launch_prepare_quant(W_dev, diag_dev, nullptr, true, half, *w, amax, w->diag, st);
     }
     const bool ok = e == hipSuccess && (wait_device ? hipDeviceSynchronize() : hipStreamSynchronize(st)) == hipSuccess;
     if (!ok) (void)hipGetLastError();

@@ -17,12 +17,20 @@ constexpr int kCols = 64;          // output channels per workgroup
 constexpr int kPrepThreads = 256;
 
 // A workgroup holds one 128-row block of 64 columns: wave q the rows 32 q .. 32 q + 31, a lane one column.
-// Loads the block into v, divided by the diagonal.
+// Loads the block into v, row k through perm (clamped to the matrix) when a permutation is given -- the
+// P^T factor of Eq. 9 in front of the second rotation --, divided by the diagonal.
 __device__ __forceinline__ void load_block(const float *__restrict__ W, int K, int N, const float *__restrict__ diag,
-                                           int b, int q, int n, bool col_ok, float (&v)[32])
+                                           const int32_t *__restrict__ perm, int b, int q, int n, bool col_ok, float (&v)[32])
 {
 #pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = col_ok ? W[(size_t)(b * kBlock + 32 * q + i) * N + n] : 0.0f;
+    for (int i = 0; i < 32; ++i) {
+        int row = b * kBlock + 32 * q + i;
+        if (perm) {
+            row = perm[row];
+            row = row < 0 ? 0 : (row >= K ? K - 1 : row);
+        }
+        v[i] = col_ok ? W[(size_t)row * N + n] : 0.0f;
+    }
     if (diag) {
 #pragma unroll
         for (int i = 0; i < 32; ++i) v[i] = v[i] / diag[b * kBlock + 32 * q + i];
@@ -67,7 +75,7 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_rotate_kernel(
     const int n = blockIdx.x * kCols + c;
     const bool col_ok = n < N;
     float v[32];
-    load_block(W, K, N, diag, b, q, n, col_ok, v);
+    load_block(W, K, N, diag, nullptr, b, q, n, col_ok, v);
     rotate_block(v, q, c, tile);
     if (!col_ok) return;
 #pragma unroll
@@ -118,6 +126,143 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_rotate_dense_kernel(
     for (int jj = 0; jj < 32; ++jj) Wrot[(size_t)(b * kBlock + 32 * q + jj) * N + n] = acc[jj];
 }
 
+// The symmetric quantiser as a kernel for the block maxima (8 bits) and one for the codes, a workgroup to 128 rows of 64
+// columns: for the rows and sets that the one kernel below is slower for (prepare_takes_pair).
+// First pass of the 8-bit quantiser: amax[b, n] = the largest magnitude of the rotated block.  Also clears the
+// column sums that the second pass adds to, and copies the diagonal for a handle that keeps one.
+template <bool ROTATE>
+__global__ __launch_bounds__(kPrepThreads) void prepare_absmax_kernel(
+    const float *__restrict__ W, int K, int N, const float *__restrict__ diag,
+    const int32_t *__restrict__ perm, float *__restrict__ amax, int32_t *__restrict__ colsum,
+    float *__restrict__ diag_copy)
+{
+    __shared__ float tile[kBlock][kCols];
+    __shared__ float part[4][kCols];
+    const int b = blockIdx.y, c = threadIdx.x % kCols, q = __builtin_amdgcn_readfirstlane(threadIdx.x / kCols);
+    const int n = blockIdx.x * kCols + c;
+    const bool col_ok = n < N;
+    float v[32];
+    load_block(W, K, N, ROTATE ? diag : nullptr, ROTATE ? perm : nullptr, b, q, n, col_ok, v);
+    if (diag_copy && blockIdx.x == 0 && threadIdx.x < kBlock)
+        diag_copy[b * kBlock + threadIdx.x] = diag[b * kBlock + threadIdx.x];
+    if (ROTATE) rotate_block(v, q, c, tile);
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) m = fmaxf(m, fabsf(v[i]));
+    part[q][c] = m;
+    __syncthreads();
+    if (q == 0 && col_ok) {
+        amax[(size_t)b * N + n] = fmaxf(fmaxf(part[0][c], part[1][c]), fmaxf(part[2][c], part[3][c]));
+        if (b == 0) colsum[n] = 0;
+    }
+}
+
+// Codes of one 128-row block of 64 columns, in the layouts and by the rounding of the kernel below; int4 codes find their maximum here.
+// A lane ends with 32 consecutive codes of one channel: two 16-byte pieces of its row (a 128-byte line per channel from the
+// four waves), 256 consecutive bytes over 16 lanes in the tiled form.
+template <int WBITS, bool ROTATE>
+__global__ __launch_bounds__(kPrepThreads) void prepare_quant_kernel(
+    const float *__restrict__ W, int K, int N, const float *__restrict__ diag, const int32_t *__restrict__ perm,
+    const float *__restrict__ amax, float norm, float qmax, void *__restrict__ codes, void *__restrict__ tiled, void *__restrict__ wide,
+    float *__restrict__ scales, int32_t *__restrict__ colsum, float *__restrict__ diag_copy)
+{
+    __shared__ float tile[kBlock][kCols];
+    __shared__ float part[4][kCols];
+    const int nb = K / kBlock;
+    const int b = blockIdx.y, c = threadIdx.x % kCols, q = __builtin_amdgcn_readfirstlane(threadIdx.x / kCols);
+    const int n = blockIdx.x * kCols + c;
+    const bool col_ok = n < N;
+    float v[32];
+    load_block(W, K, N, ROTATE ? diag : nullptr, ROTATE ? perm : nullptr, b, q, n, col_ok, v);
+    float a = 0.0f;
+    if (WBITS == 8) {
+        if (col_ok)
+            for (int bb = q; bb < nb; bb += 4) a = fmaxf(a, amax[(size_t)bb * N + n]);
+    } else if (diag_copy && blockIdx.x == 0 && threadIdx.x < kBlock) {
+        diag_copy[b * kBlock + threadIdx.x] = diag[b * kBlock + threadIdx.x];
+    }
+    if (ROTATE) rotate_block(v, q, c, tile);
+    if (WBITS == 4) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) a = fmaxf(a, fabsf(v[i]));
+    }
+    part[q][c] = a;
+    __syncthreads();
+    a = fmaxf(fmaxf(part[0][c], part[1][c]), fmaxf(part[2][c], part[3][c]));
+    if (q == 0 && col_ok) {
+        if (WBITS == 4) scales[(size_t)b * N + n] = a * (norm / qmax);
+        else if (b == 0) scales[n] = a * (norm / qmax);
+    }
+    const float inv = a > 0.0f ? qmax / a : 0.0f;
+    uint32_t u[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) u[i] = quant_bits(v[i], inv);
+    const int k0 = b * kBlock + 32 * q;                // the lane's first input channel
+    const size_t block = (size_t)(n >> 4) * (K >> 6) + (k0 >> 6);
+    if (WBITS == 8) {
+        int t = 0;
+#pragma unroll
+        for (int i = 0; i < 32; ++i) t += (int)(int8_t)(u[i] & 0xFF);
+        __syncthreads();
+        part[q][c] = __int_as_float(t);
+        __syncthreads();
+        if (q == 0 && col_ok)
+            atomicAdd(colsum + n, __float_as_int(part[0][c]) + __float_as_int(part[1][c]) +
+                                      __float_as_int(part[2][c]) + __float_as_int(part[3][c]));
+        if (!col_ok) return;
+        int8_t *const out = static_cast<int8_t *>(codes) + (size_t)n * K + k0;
+        int8_t *const blk = static_cast<int8_t *>(tiled) + block * 1024 + ((k0 & 63) >> 4) * 256 + (n & 15) * 16;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            uint32_t w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                w[j] = pack4_low_bytes(u[16 * p + 4 * j], u[16 * p + 4 * j + 1], u[16 * p + 4 * j + 2], u[16 * p + 4 * j + 3]);
+            const uint4 piece = make_uint4(w[0], w[1], w[2], w[3]);
+            *reinterpret_cast<uint4 *>(out + 16 * p) = piece;
+            *reinterpret_cast<uint4 *>(blk + 256 * p) = piece;
+        }
+    } else {
+        if (!col_ok) return;
+        // 8 consecutive k -> 4 bytes: byte j = code(k0+j) & 0xF | (code(k0+4+j) & 0xF) << 4
+        uint32_t w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t lo = pack4_low_bytes(u[8 * j], u[8 * j + 1], u[8 * j + 2], u[8 * j + 3]);
+            const uint32_t hi = pack4_low_bytes(u[8 * j + 4], u[8 * j + 5], u[8 * j + 6], u[8 * j + 7]);
+            w[j] = (lo & 0x0F0F0F0Fu) | ((hi << 4) & 0xF0F0F0F0u);
+        }
+        *reinterpret_cast<uint4 *>(static_cast<uint8_t *>(codes) + (size_t)n * (K / 2) + k0 / 2) =
+            make_uint4(w[0], w[1], w[2], w[3]);
+        uint8_t *const blk = static_cast<uint8_t *>(tiled) + block * 512 + ((k0 & 63) >> 4) * 128 + (n & 15) * 8;
+        uint8_t *const bytes = static_cast<uint8_t *>(wide) + block * 1024 + ((k0 & 63) >> 4) * 256 + (n & 15) * 16;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            *reinterpret_cast<uint2 *>(blk + 128 * p) = make_uint2(w[2 * p], w[2 * p + 1]);
+            *reinterpret_cast<uint4 *>(bytes + 256 * p) = make_uint4((w[2 * p] << 4) & 0xF0F0F0F0u, w[2 * p] & 0xF0F0F0F0u,
+                                                                     (w[2 * p + 1] << 4) & 0xF0F0F0F0u, w[2 * p + 1] & 0xF0F0F0F0u);
+        }
+    }
+}
+
+// int4 weights: colsumw[n] = 16 * sum_g s_w[g][n] * (sum over the 128 codes of group g), one wave per
+// output channel; a lane sums the two codes of a byte per group.
+__global__ __launch_bounds__(64) void weight_colsumw4_kernel(const uint8_t *__restrict__ codes, const float *__restrict__ scales,
+                                                             int K, int N, float *__restrict__ colsumw)
+{
+    const int n = blockIdx.x, lane = threadIdx.x;
+    const uint8_t *row = codes + (size_t)n * (K / 2);
+    float t = 0.0f;
+    for (int g = 0; g < K / kBlock; ++g) {
+        const uint32_t b = row[g * 64 + lane];
+        int s = (int)((b & 0xF) ^ 8) - 8 + (int)(((b >> 4) & 0xF) ^ 8) - 8;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        t += scales[(size_t)g * N + n] * (float)s;
+    }
+    if (lane == 0) colsumw[n] = 16.0f * t;
+}
+
 // The symmetric quantiser, rotation included.  A workgroup owns eight output channels for the whole K: a wave takes a
 // 128-row block of them (the blocks wave, wave + nw, ...), a lane 16 rows of one channel, so the rotation stays inside the
 // wave (four stages in the lane, three across lanes), the column maximum crosses the waves through LDS, and W is read once.
@@ -126,8 +271,7 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_rotate_dense_kernel(
 // norm undoes the unnormalised butterflies: 1/sqrt(128) after one rotation, 1/128 after two.
 //   code = rint(w * qmax / amax)   (ties to even; amax == 0 -> 0)
 // ROTATE: W is rotated here (rows through perm, divided by diag, both optional); otherwise it holds rotated values.
-// HOLD (8 bits): blocks that a wave keeps in registers between the maximum and the codes: 1 up to 16 blocks, 3 up to 48;
-// 0: wider, each block is read and rotated a second time.
+// HOLD (8 bits): blocks that a wave keeps in registers between the maximum and the codes: 1 up to 16 blocks, 3 up to 48.
 // A lane's 16 codes are one 16-byte piece of both layouts; eight channels and eight pieces make 128-byte runs in each.
 // A line of W is shared by four workgroups, which therefore run on the same die.
 // What bounds it is the chain of one block through a wave (of three at K = 4608), then the 128-byte lines that four workgroups
@@ -282,25 +426,17 @@ __global__ __launch_bounds__(64 * kPcMostWaves) void prepare_columns_kernel(
                                        (rg & 3) * 256 + (n & 15) * 16) = piece;
             return t;
         };
-        float v[HOLD ? HOLD : 1][16];
+        float v[HOLD][16];
         float a = 0.0f;
-        if constexpr (HOLD > 0) {
 #pragma unroll
-            for (int i = 0; i < HOLD; ++i)
-                if (wave + nw * i < nb) load(wave + nw * i, v[i]);
+        for (int i = 0; i < HOLD; ++i)
+            if (wave + nw * i < nb) load(wave + nw * i, v[i]);
 #pragma unroll
-            for (int i = 0; i < HOLD; ++i)
-                if (wave + nw * i < nb) {
-                    rotate(wave + nw * i, v[i]);
-                    a = lane_max(v[i], a);
-                }
-        } else {
-            for (int b = wave; b < nb; b += nw) {
-                load(b, v[0]);
-                rotate(b, v[0]);
-                a = lane_max(v[0], a);
+        for (int i = 0; i < HOLD; ++i)
+            if (wave + nw * i < nb) {
+                rotate(wave + nw * i, v[i]);
+                a = lane_max(v[i], a);
             }
-        }
         a = over_rows(a);
         if (rg == 0) part[wave][c] = a;
         __syncthreads();
@@ -308,17 +444,9 @@ __global__ __launch_bounds__(64 * kPcMostWaves) void prepare_columns_kernel(
         if (wave == 0 && rg == 0) scales[n] = a * (norm / qmax);
         const float inv = a > 0.0f ? qmax / a : 0.0f;
         int t = 0;
-        if constexpr (HOLD > 0) {
 #pragma unroll
-            for (int i = 0; i < HOLD; ++i)
-                if (wave + nw * i < nb) t += store(wave + nw * i, v[i], inv);
-        } else {
-            for (int b = wave; b < nb; b += nw) {
-                load(b, v[0]);
-                rotate(b, v[0]);
-                t += store(b, v[0], inv);
-            }
-        }
+        for (int i = 0; i < HOLD; ++i)
+            if (wave + nw * i < nb) t += store(wave + nw * i, v[i], inv);
         t = sum_rows(t);
         if (rg == 0) sums[wave][c] = t;
         __syncthreads();
@@ -525,12 +653,42 @@ hipError_t launch_prepare_rotate_dense(const float *W, int K, int N, const float
     return hipGetLastError();
 }
 
+// Where the pair is the faster form: rows so long that a wave of the one kernel would read and rotate its blocks twice or that come
+// through a table, and int4 sets so large that its 32-byte pieces of W's lines bound it.  us of a set's replacement, pair / one kernel:
+// 8 bits 6272 x 128 30 / 34, 9216 x 4608 134 / 143, 18432 x 128 39 / 84, but 6144 x 1152 44 / 35; int4 4608 x 16384 157 / 214, 9216 x 4608
+// 102 / 116, 6272 x 4608 75 / 82, 2176 x 16384 77 / 79, but 4608 x 4608 64 / 63, 2048 x 16384 73 / 71; through a table, a set made anew, 4608 x 16 36 / 44, 4608 x 4608 417 / 451
+// (int4 664 / 691), but 1152 x 4608 100 / 97.
+bool prepare_takes_pair(int K, int N, int wbits, bool gathered)
+{
+    const int nb = K / kBlock;
+    if (gathered && nb > kPcMostWaves) return true;
+    return wbits == 4 ? (int64_t)K * N > (int64_t)(K > 4096 ? 24 : 32) << 20 : nb > 3 * kPcMostWaves;
+}
+
 hipError_t launch_prepare_quant(const float *W, const float *diag, const int32_t *perm, bool rotate, float norm,
-                                const Weights &w, float *diag_copy, hipStream_t st)
+                                const Weights &w, float *amax, float *diag_copy, hipStream_t st)
 {
     const int K = w.K, N = w.N, nb = K / kBlock;
     if (!diag) diag_copy = nullptr;
     const float qmax = w.wbits == 4 ? 7.0f : w.qbits == 6 ? 31.0f : 127.0f;
+    if (prepare_takes_pair(K, N, w.wbits, perm != nullptr)) {
+        const dim3 grid((N + kCols - 1) / kCols, nb), threads(kPrepThreads);
+        if (w.wbits == 4) {
+            hipLaunchKernelGGL((rotate ? prepare_quant_kernel<4, true> : prepare_quant_kernel<4, false>), grid, threads, 0, st, W, K, N, diag, perm,
+                               nullptr, norm, qmax, w.codes, w.codes_tiled, w.codes_wide, w.scales, nullptr, diag_copy);
+            if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+            hipLaunchKernelGGL(weight_colsumw4_kernel, dim3(N), dim3(64), 0, st, static_cast<const uint8_t *>(w.codes), w.scales, K, N,
+                               w.colsumw);
+            return hipGetLastError();
+        }
+        if (!amax) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((rotate ? prepare_absmax_kernel<true> : prepare_absmax_kernel<false>), grid, threads, 0, st, W, K, N, diag, perm, amax,
+                           w.colsum, diag_copy);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        hipLaunchKernelGGL((rotate ? prepare_quant_kernel<8, true> : prepare_quant_kernel<8, false>), grid, threads, 0, st, W, K, N, diag, perm,
+                           amax, norm, qmax, w.codes, w.codes_tiled, nullptr, w.scales, w.colsum, nullptr);
+        return hipGetLastError();
+    }
     const int rounds = (nb + kPcMostWaves - 1) / kPcMostWaves;      // blocks of the busiest wave
     auto go = [&](auto kern, int nw) {
         hipLaunchKernelGGL(kern, dim3(N / kPcCols), dim3(64 * nw), 0, st, W, K, N, diag, perm, norm, qmax, w.codes, w.codes_tiled, w.codes_wide,
@@ -542,11 +700,8 @@ hipError_t launch_prepare_quant(const float *W, const float *diag, const int32_t
         return rotate ? go(prepare_columns_kernel<4, true, 0>, nw) : go(prepare_columns_kernel<4, false, 0>, nw);
     }
     if (rounds == 1) return rotate ? go(prepare_columns_kernel<8, true, 1>, nb) : go(prepare_columns_kernel<8, false, 1>, nb);
-    if (rounds <= 3) {
-        const int nw = (nb + 2) / 3;
-        return rotate ? go(prepare_columns_kernel<8, true, 3>, nw) : go(prepare_columns_kernel<8, false, 3>, nw);
-    }
-    return rotate ? go(prepare_columns_kernel<8, true, 0>, kPcMostWaves) : go(prepare_columns_kernel<8, false, 0>, kPcMostWaves);
+    const int nw = (nb + 2) / 3;
+    return rotate ? go(prepare_columns_kernel<8, true, 3>, nw) : go(prepare_columns_kernel<8, false, 3>, nw);
 }
 
 }  // namespace trdq

@@ -32,6 +32,7 @@ struct Weights {
     int32_t *zcw = nullptr;      // asymmetric int8 weights (Eq. 1-3 per output channel): 128 - z_w [N]; codes hold q - 128
     float *colsumw = nullptr;    // int4 weights: 16 * sum_g s_w[g][n] * (sum of the codes of group g) [N]
     float *diag = nullptr;       // the handle's copy of the diagonal [K], if it keeps one
+    float *amax = nullptr;       // scratch of the preparation of 8-bit codes of very long rows: block maxima [K/128, N]
     void *block = nullptr;       // the one device allocation that holds all of the above
     int device = 0;
 };
@@ -81,9 +82,11 @@ hipError_t launch_rotate_quant_rpr(const uint16_t *X, int64_t M, int K, int64_t 
 
 hipError_t launch_prepare_rotate(const float *W, int K, int N, const float *diag, float *Wrot, hipStream_t st);
 // Codes (both forms), scales and column sums of w from W: rotated on the way (rotate: divided by diag, rows read through
-// perm, row k of the input to the rotation = row perm[k], both optional), or already rotated.  norm: what undoes the unnormalised butterflies (1/sqrt(128) per rotation applied).  diag_copy (optional) receives diag.
+// perm, row k of the input to the rotation = row perm[k], both optional), or already rotated.  amax: K / 128 * N floats of scratch where
+// prepare_takes_pair for 8-bit codes.  norm: what undoes the unnormalised butterflies (1/sqrt(128) per rotation applied).  diag_copy (optional) receives diag.
 hipError_t launch_prepare_quant(const float *W, const float *diag, const int32_t *perm, bool rotate, float norm,
-                                const Weights &w, float *diag_copy, hipStream_t st);
+                                const Weights &w, float *amax, float *diag_copy, hipStream_t st);
+bool prepare_takes_pair(int K, int N, int wbits, bool gathered);
 // asymmetric weight quantiser: lohi = scratch of 2 N floats; codes [N, K] = q - 128, scales [N], zcw [N] = 128 - z
 hipError_t launch_prepare_quant_asym(const float *Wrot, float *lohi, int K, int N, float norm, void *codes, float *scales,
                                      int32_t *zcw, hipStream_t st);

@@ -30,9 +30,10 @@ def test_codes_and_scales(trdq, oracle, wbits, K, N, with_diag):
     assert not codes[:, N // 2].any() and not np.asarray(scales).reshape(-1, N)[:, N // 2].any()
 
 
-# 16 / 17 blocks: one or three to a wave; 48 / 49: kept in registers, or read twice; 2 ... 34 workgroups, whole groups of 32 or not
+# 16 / 17 blocks: one or three to a wave; 48 / 49: kept in registers, or a kernel for the maxima before; 2 ... 34 workgroups,
+# whole groups of 32 or not
 @pytest.mark.parametrize("wbits", [8, 6, 4])
-@pytest.mark.parametrize("K,N", [(2048, 16), (2176, 272), (6144, 16), (6272, 32)])
+@pytest.mark.parametrize("K,N", [(2048, 16), (2176, 272), (6144, 16), (6272, 32), (6272, 80)])
 def test_codes_scales_and_sums_of_wide_rows(trdq, oracle, wbits, K, N):
     """... with a diagonal that has entries beyond the range in which the kernel divides by reciprocals."""
     import torch
@@ -57,7 +58,56 @@ def test_codes_scales_and_sums_of_wide_rows(trdq, oracle, wbits, K, N):
     assert np.array_equal(acc.cpu().numpy(), (Xq.astype(np.int64) + zc[:, None]) @ codes.astype(np.int64))
 
 
-# one block to a wave, three, and blocks read twice (int8); values[row 3 of a block, channel 5], the diagonal's entry there
+# large int4 sets: a kernel of their own for the codes, one for the sums; the codes of a part of the columns by the other kernel
+@pytest.mark.parametrize("with_diag", [True, False])
+def test_large_int4_sets(trdq, with_diag):
+    import torch
+    K, N, part = 2176, 15440, 1040                       # K * N just beyond 2^25, neither whole workgroups
+    assert K * N > 1 << 25
+    g = torch.Generator(device="cuda").manual_seed(3)
+    W = 0.02 * torch.randn(K, N, generator=g, device="cuda")
+    W[:, 7] = 0.0
+    d = torch.rand(K, generator=g, device="cuda") + 0.5 if with_diag else None
+    big, small = trdq.prepare_weights(W, d, wbits=4), trdq.prepare_weights(W[:, :part].contiguous(), d, wbits=4)
+    codes, scales = big.export()
+    want = small.export()
+    assert np.array_equal(codes[:, :part], want[0]) and np.array_equal(scales[:, :part], want[1])
+    last = trdq.prepare_weights(W[:, N - 48:].contiguous(), d, wbits=4).export()
+    assert np.array_equal(codes[:, N - 48:], last[0]) and np.array_equal(scales[:, N - 48:], last[1])
+    # packed blocks, widened blocks and column sums, through the products that read them
+    Xq = torch.randint(-127, 128, (640, K), generator=g, device="cuda", dtype=torch.int8)
+    sx, zc = torch.rand(640, generator=g, device="cuda"), torch.randint(-50, 50, (640,), generator=g, device="cuda", dtype=torch.int32)
+    for M in (3, 128, 640):
+        y, y_part = torch.empty((M, N), dtype=torch.bfloat16, device="cuda"), torch.empty((M, part), dtype=torch.bfloat16, device="cuda")
+        for asym in (False, True):
+            for w, out in ((big, y), (small, y_part)):
+                if asym:
+                    trdq.qgemm_asym(w, Xq[:M], sx[:M], zc[:M], out)
+                else:
+                    trdq.qgemm(w, Xq[:M], sx[:M], out)
+            assert torch.equal(y[:, :part], y_part), (M, asym)
+
+
+def test_preparation_of_very_long_rows_takes_little_longer(trdq):
+    """18432 rows against 6144, 128 channels: 1.45 times (in one kernel 3 times, the wall clock of a replacement)."""
+    import time
+
+    import torch
+    best = {}
+    layers = {}
+    for K in (6144, 18432):
+        W = 0.02 * torch.randn(K, 128, device="cuda")
+        layers[K] = trdq.Layer(trdq.Table(1, 1), K, 128, 8), torch.ones(K, device="cuda"), W
+    for rep in range(40):
+        for K, (layer, d, W) in layers.items():
+            torch.cuda.synchronize()
+            start = time.perf_counter()
+            layer.set_group(0, d, W)
+            best[K] = min(best.get(K, 1.0), time.perf_counter() - start)
+    assert best[18432] < 2.2 * best[6144], best
+
+
+# one block to a wave, three, and the two kernels of longer rows (int8); values[row 3 of a block, channel 5], the diagonal's entry there
 @pytest.mark.parametrize("wbits", [8, 6, 4])
 @pytest.mark.parametrize("K", [256, 2176, 6272])
 @pytest.mark.parametrize("value,entry", [(None, None), (np.inf, 0.5), (-np.inf, 2.0), (np.nan, 2.0), (3e38, 0.25), (1e25, 1e-19),
