@@ -116,7 +116,9 @@ trdq_status trdq_weights_export_packed(const trdq_weights *w, uint8_t *packed_ho
 
 /* Bytes of the weight format (codes + scales): K*N + 4N for wbits 8, K*N/2 + 4*(K/128)*N for wbits 4.
  * A symmetric set holds its codes a second time, block-tiled (another K*N resp. K*N/2 bytes of device
- * memory, not part of this figure): the form of trdq_qgemm_tiled, and what the kernels for few tokens read. */
+ * memory, not part of this figure): the form of trdq_qgemm_tiled (wbits 8), and what the kernels for few tokens read.
+ * A set of wbits 4 with K >= 384 and N >= 128 holds them a third time, widened to bytes (K*N more, so as many bytes as a set of
+ * wbits 8): the form of trdq_qgemm_tiled (wbits 4), and of trdq_qgemm at medium token counts. */
 trdq_status trdq_weights_nbytes(const trdq_weights *w, int64_t *nbytes_out);
 
 void trdq_weights_destroy(trdq_weights *w);

@@ -188,7 +188,7 @@ void trdq_table_destroy(trdq_table *t)
 namespace {
 
 // One device allocation per weight set (an allocation and its release cost 50-100 us each, more than the
-// kernels that fill it): codes, their block-tiled copy (symmetric sets), widened codes (int4), scales, column sums, the block maxima
+// kernels that fill it): codes, their block-tiled copy (symmetric sets), widened codes (int4 sets of shapes that a product reads them of), scales, column sums, the block maxima
 // between the two passes of a preparation that has no scratch matrix (8-bit codes of very long rows after one Hadamard rotation),
 // and the diagonal for a handle that keeps a copy.
 trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
@@ -200,7 +200,8 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     size_t total = 0;
     auto take = [&](size_t bytes) { const size_t at = total; total += (bytes + 255) / 256 * 256; return at; };
     const size_t at_codes = take(code_bytes), at_tiled = tiled ? take(code_bytes) : 0;
-    const size_t at_wide = tiled && w4 ? take((size_t)K * N) : 0;
+    const bool wide = w4 && trdq::qgemm4_takes_wide(K, N);
+    const size_t at_wide = wide ? take((size_t)K * N) : 0;
     const size_t at_scales = take((w4 ? (size_t)nb * N : (size_t)N) * sizeof(float));
     const size_t at_colsum = take((size_t)N * sizeof(float));          // int32 sums, or the scaled float ones of int4 codes
     const size_t at_zcw = asym ? take((size_t)N * sizeof(int32_t)) : 0;
@@ -211,7 +212,7 @@ trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
     char *const base = static_cast<char *>(w->block);
     w->codes = base + at_codes;
     w->codes_tiled = tiled ? base + at_tiled : nullptr;
-    w->codes_wide = tiled && w4 ? base + at_wide : nullptr;
+    w->codes_wide = wide ? base + at_wide : nullptr;
     w->scales = reinterpret_cast<float *>(base + at_scales);
     if (w4) w->colsumw = reinterpret_cast<float *>(base + at_colsum);
     else w->colsum = reinterpret_cast<int32_t *>(base + at_colsum);

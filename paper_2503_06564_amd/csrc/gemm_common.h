@@ -125,6 +125,7 @@ bool tiled_rows_pays(int64_t M, int K, int N, bool asym);
 hipError_t launch_qgemm8_tiled_rows(const GemmArgs &a, bool debug, hipStream_t st);
 hipError_t launch_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st);
 // int4 weights on block-tiled operands (qgemm_tiled.hip): a.Wc holds the widened codes
+bool tiled4_takes(int K, int N);                      // at some token count, with either tile
 bool tiled4_supports(const GemmArgs &a);
 hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st);
 // 64-token tiles on row-major activation codes, any M >= 64 and N >= 128; a.Wc holds the widened codes where

@@ -239,8 +239,8 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_quant_kernel(
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             *reinterpret_cast<uint2 *>(blk + 128 * p) = make_uint2(w[2 * p], w[2 * p + 1]);
-            *reinterpret_cast<uint4 *>(bytes + 256 * p) = make_uint4((w[2 * p] << 4) & 0xF0F0F0F0u, w[2 * p] & 0xF0F0F0F0u,
-                                                                     (w[2 * p + 1] << 4) & 0xF0F0F0F0u, w[2 * p + 1] & 0xF0F0F0F0u);
+            if (wide) *reinterpret_cast<uint4 *>(bytes + 256 * p) = make_uint4((w[2 * p] << 4) & 0xF0F0F0F0u, w[2 * p] & 0xF0F0F0F0u,
+                                                                               (w[2 * p + 1] << 4) & 0xF0F0F0F0u, w[2 * p + 1] & 0xF0F0F0F0u);
         }
     }
 }
@@ -494,9 +494,10 @@ __global__ __launch_bounds__(64 * kPcMostWaves) void prepare_columns_kernel(
                 *reinterpret_cast<uint2 *>(static_cast<uint8_t *>(tiled) + ((size_t)(n >> 4) * (K >> 6) + (k0 >> 6)) * 512 +
                                            (rg & 3) * 128 + (n & 15) * 8) = make_uint2(w[0], w[1]);
                 // 16 * code, one byte each, in the blocks of the int8 form; a word's low nibbles are its first four codes
-                *reinterpret_cast<uint4 *>(static_cast<int8_t *>(wide) + ((size_t)(n >> 4) * (K >> 6) + (k0 >> 6)) * 1024 +
-                                           (rg & 3) * 256 + (n & 15) * 16) =
-                    make_uint4((w[0] << 4) & 0xF0F0F0F0u, w[0] & 0xF0F0F0F0u, (w[1] << 4) & 0xF0F0F0F0u, w[1] & 0xF0F0F0F0u);
+                if (wide)
+                    *reinterpret_cast<uint4 *>(static_cast<int8_t *>(wide) + ((size_t)(n >> 4) * (K >> 6) + (k0 >> 6)) * 1024 +
+                                               (rg & 3) * 256 + (n & 15) * 16) =
+                        make_uint4((w[0] << 4) & 0xF0F0F0F0u, w[0] & 0xF0F0F0F0u, (w[1] << 4) & 0xF0F0F0F0u, w[1] & 0xF0F0F0F0u);
             }
             __syncthreads();
             if (wave == 0 && rg == 0)

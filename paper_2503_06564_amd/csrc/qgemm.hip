@@ -414,13 +414,15 @@ const void *qgemm_reads_codes(const Weights &w, int64_t M, bool tiled, bool asym
 {
     if (!w.codes_tiled) return w.codes;
     if (w.wbits == 4) {
-        if (tiled) return w.codes_wide;
+        if (tiled) return w.codes_wide ? w.codes_wide : w.codes_tiled;      // none: a shape that the tiled product refuses
         if (qgemm4_direct_tile(M, w.K, w.N) >= 0) return w.codes_tiled;
         if (asym || !tiled4_rows_pays(M, w.K, w.N)) return w.codes;
         return tiled4_rows_reads_wide(M, w.N) ? w.codes_wide : w.codes_tiled;
     }
     return tiled || qgemm8_direct_tile(M, w.K, w.N, asym) >= 0 || tiled_rows_pays(M, w.K, w.N, asym) ? w.codes_tiled : w.codes;
 }
+
+bool qgemm4_takes_wide(int K, int N) { return tiled4_takes(K, N); }
 
 bool qgemm4_tiled_pays(int64_t M, int K, int N)
 {

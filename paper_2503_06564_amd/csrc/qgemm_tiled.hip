@@ -1048,9 +1048,11 @@ hipError_t launch_qgemm8_tiled_rows(const GemmArgs &a, bool debug, hipStream_t s
     return a.zc ? launch_form<kRowsAsym>(a, debug, st) : launch_form<kRows>(a, debug, st);
 }
 
+bool tiled4_takes(int K, int N) { return K % 128 == 0 && K >= kW4MinK && N % 16 == 0 && N >= kW4BN; }
+
 bool tiled4_supports(const GemmArgs &a)
 {
-    return a.M > 0 && a.M % kW4BM == 0 && a.N % kW4BN == 0 && a.K % 128 == 0 && a.K >= kW4MinK && a.ldy % 8 == 0 &&
+    return a.M > 0 && a.M % kW4BM == 0 && a.N % kW4BN == 0 && tiled4_takes(a.K, a.N) && a.ldy % 8 == 0 &&
            reinterpret_cast<uintptr_t>(a.Y) % 16 == 0 && !a.zc;
 }
 
@@ -1081,8 +1083,7 @@ hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st)
 
 bool tiled4_rows_supports(const GemmArgs &a)
 {
-    return a.M >= 64 && a.M <= (1 << 30) && a.N >= kW4BN && a.N % 16 == 0 && a.K % 128 == 0 && a.K >= kW4MinK &&
-           a.ldy % 8 == 0 && reinterpret_cast<uintptr_t>(a.Y) % 16 == 0 && !a.zc;
+    return a.M >= 64 && a.M <= (1 << 30) && tiled4_takes(a.K, a.N) && a.ldy % 8 == 0 && reinterpret_cast<uintptr_t>(a.Y) % 16 == 0 && !a.zc;
 }
 
 hipError_t launch_qgemm4_tiled_rows(const GemmArgs &a, bool debug, hipStream_t st)
@@ -1100,7 +1101,7 @@ hipError_t launch_qgemm4_tiled_rows(const GemmArgs &a, bool debug, hipStream_t s
 // nothing here, the product being bound by its vector instructions.
 bool tiled4_rows_pays(int64_t M, int K, int N)
 {
-    return M >= 64 && N >= kW4BN && K >= kW4MinK && ((M + 63) / 64) * ((N + kW4BN - 1) / kW4BN) <= 3 * (int64_t)num_cus();
+    return M >= 64 && tiled4_takes(K, N) && ((M + 63) / 64) * ((N + kW4BN - 1) / kW4BN) <= 3 * (int64_t)num_cus();
 }
 
 // Which copy of the codes they read.  Widened bytes spare a workgroup that shares its compute unit with at most one other the

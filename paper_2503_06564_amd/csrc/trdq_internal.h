@@ -26,7 +26,7 @@ struct Weights {
     void *codes = nullptr;
     float *scales = nullptr;
     void *codes_tiled = nullptr; // symmetric sets: the same codes in blocks of 16 channels x 64 k (1 KB; int4: 512 bytes), see qgemm_tiled.hip
-    void *codes_wide = nullptr;  // int4 sets: 16 * code as int8 in the 1 KB blocks of the int8 form, read by the product of many tokens
+    void *codes_wide = nullptr;  // int4 sets where qgemm4_takes_wide: 16 * code as int8 in the 1 KB blocks of the int8 form
     int rotation = 0;            // which transform was folded in (kRot*): the activation side must apply the same one
     int32_t *colsum = nullptr;   // int8 weights: sum over k of the codes of every output channel [N]
     int32_t *zcw = nullptr;      // asymmetric int8 weights (Eq. 1-3 per output channel): 128 - z_w [N]; codes hold q - 128
@@ -54,12 +54,14 @@ struct Table {
     int32_t *map = nullptr;
 };
 
+// whether launch_rotate_quant reads its input non-temporally
+bool rotate_quant_reads_once(int64_t M, int K, bool asym);
+
 // Kernel launchers (defined in the .hip files).  All return hipError_t of the launch.
 // warm / warm_bytes: optional device range (16-byte aligned, a multiple of 16 bytes) that the
 // kernel reads once and discards, to pull it into the memory-side cache for the next kernel.
 // zc: null (symmetric quantiser), or where the asymmetric quantiser writes 128 - z_i per token.
 // tiled: Xq is written in 1 KB blocks of 16 tokens x 64 k (block (m / 16, k / 64) at ((m / 16) * K / 64 + k / 64) * 1024)
-bool rotate_quant_reads_once(int64_t M, int K, bool asym);   // whether that pass reads its input non-temporally
 hipError_t launch_rotate_quant(const uint16_t *X, int64_t M, int K, int64_t ldx, const float *diag,
                                int8_t *Xq, float *sx, int32_t *zc, const void *warm, int64_t warm_bytes, hipStream_t st,
                                int abits = 8,    // symmetric codes in +-(2^(abits-1) - 1); K <= 4608 unless 8
@@ -73,6 +75,8 @@ const void *qgemm_reads_codes(const Weights &w, int64_t M, bool tiled, bool asym
 // measured choice between the two products for a layer object (true: the tiled pair is the faster one)
 bool qgemm_tiled_pays(int64_t M, int K, int N);
 bool qgemm4_tiled_pays(int64_t M, int K, int N);   // int4 weights
+// whether an int4 product of some token count reads the widened codes of such a set
+bool qgemm4_takes_wide(int K, int N);
 hipError_t launch_xq_untile(const int8_t *Xt, int8_t *Xq, int64_t M, int K, hipStream_t st);
 // Full transform of Eq. 9 (rotation, permutation, rotation) and per-token quantisation.
 bool rotate_quant_rpr_supports(int K);

@@ -88,6 +88,48 @@ def test_large_int4_sets(trdq, with_diag):
             assert torch.equal(y[:, :part], y_part), (M, asym)
 
 
+@pytest.mark.parametrize("K,N,copies", [(256, 131072, 2), (65536, 112, 2), (384, 32768, 4)])
+def test_memory_of_int4_sets(trdq, K, N, copies):
+    """Packed rows and packed blocks, and as many bytes again for widened codes where a product reads them."""
+    import torch
+    W = torch.zeros(K, N, device="cuda")
+    trdq.prepare_weights(W, None, wbits=4).close()       # what the runtime takes for a first launch
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    w = trdq.prepare_weights(W, None, wbits=4)
+    used = free - torch.cuda.mem_get_info()[0]
+    want = copies * K * N // 2 + 4 * (K // 128 + 1) * N
+    assert abs(used - want) <= 4 << 20, (used, want)     # whole pages of 2 MB
+    Xq, sx = torch.ones((64, K), dtype=torch.int8, device="cuda"), torch.ones(64, device="cuda")
+    Y = torch.empty((64, N), dtype=torch.bfloat16, device="cuda")
+    trdq.rotate_quant_tiled(torch.ones((64, K), dtype=torch.bfloat16, device="cuda")[:, :min(K, 4608)].contiguous(), None,
+                            torch.empty(64 * min(K, 4608), dtype=torch.int8, device="cuda"), sx, warm=w)
+    trdq.qgemm(w, Xq, sx, Y)
+    assert not Y.float().any()
+
+
+@pytest.mark.parametrize("wbits", [8, 4])
+def test_products_of_a_set_that_was_replaced(trdq, wbits):
+    """Every copy of the codes follows a replacement that fills a set again: few tokens, 64-token tiles on either copy, block-tiled."""
+    import torch
+    K, N = 384, 1152
+    g = torch.Generator(device="cuda").manual_seed(5)
+    layer, fresh = trdq.Layer(trdq.Table(1, 1), K, N, wbits), trdq.Layer(trdq.Table(1, 1), K, N, wbits)
+    for _ in range(4):
+        W, d = 0.02 * torch.randn(K, N, generator=g, device="cuda"), torch.rand(K, generator=g, device="cuda") + 0.5
+        layer.set_group(0, d, W)
+    fresh.set_group(0, d, W)
+    for M in (3, 100, 1000, 4600, 6016):
+        X = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+        Xq, sx = torch.empty((M, K), dtype=torch.int8, device="cuda"), torch.empty(M, device="cuda")
+        got, want = (torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        for fused in (True, False):
+            layer.forward(0, X, got, fused=fused, Xq_ws=Xq, sx_ws=sx)
+            fresh.forward(0, X, want, fused=fused, Xq_ws=Xq, sx_ws=sx)
+            assert torch.equal(got, want), (M, fused)
+    assert trdq.qgemm_tiled_preferred(layer.weights(0), 6016)
+
+
 def test_preparation_of_very_long_rows_takes_little_longer(trdq):
     """18432 rows against 6144, 128 channels: 1.45 times (in one kernel 3 times, the wall clock of a replacement)."""
     import time
