@@ -3,9 +3,9 @@
 // Offline, once per time-step group.
 //
 // What bounds it: W is read (4 bytes an element) and the codes are written twice (row-major and
-// block-tiled), 6 bytes an element, 32 MB for a 1152 x 4608 set; the rest of a set's preparation is the
+// block-tiled; int4 a third time, widened), 6 bytes an element, 32 MB for a 1152 x 4608 set; the rest of a set's preparation is the
 // host's: device allocations and the final synchronisation.  One Hadamard rotation goes without a float32 scratch matrix:
-// one kernel reads W, rotates, finds the maxima, and writes codes, scales and column sums.
+// one kernel reads W, rotates, finds the maxima, and writes codes, scales and column sums (two for some sets: prepare_takes_pair).
 #include "device_utils.h"
 #include "trdq_internal.h"
 
@@ -130,7 +130,6 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_rotate_dense_kernel(
 // columns: for the rows and sets that the one kernel below is slower for (prepare_takes_pair).
 // First pass of the 8-bit quantiser: amax[b, n] = the largest magnitude of the rotated block.  Also clears the
 // column sums that the second pass adds to, and copies the diagonal for a handle that keeps one.
-template <bool ROTATE>
 __global__ __launch_bounds__(kPrepThreads) void prepare_absmax_kernel(
     const float *__restrict__ W, int K, int N, const float *__restrict__ diag,
     const int32_t *__restrict__ perm, float *__restrict__ amax, int32_t *__restrict__ colsum,
@@ -142,10 +141,10 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_absmax_kernel(
     const int n = blockIdx.x * kCols + c;
     const bool col_ok = n < N;
     float v[32];
-    load_block(W, K, N, ROTATE ? diag : nullptr, ROTATE ? perm : nullptr, b, q, n, col_ok, v);
+    load_block(W, K, N, diag, perm, b, q, n, col_ok, v);
     if (diag_copy && blockIdx.x == 0 && threadIdx.x < kBlock)
         diag_copy[b * kBlock + threadIdx.x] = diag[b * kBlock + threadIdx.x];
-    if (ROTATE) rotate_block(v, q, c, tile);
+    rotate_block(v, q, c, tile);
     float m = 0.0f;
 #pragma unroll
     for (int i = 0; i < 32; ++i) m = fmaxf(m, fabsf(v[i]));
@@ -277,8 +276,8 @@ __global__ __launch_bounds__(64) void weight_colsumw4_kernel(const uint8_t *__re
 // What bounds it is the chain of one block through a wave (of three at K = 4608), then the 128-byte lines that four workgroups
 // share.  The form before (workgroups of 64 channels x 128 rows, one kernel for the maxima and one that read and rotated W
 // again for the codes) took 8.2 + 9.7 us for a 1152 x 1152 int8 set, 7.8 + 9.3 for 1152 x 3456, 9.4 + 11.4 for 1152 x 4608 and
-// 8.2 + 9.7 for 4608 x 1152; this one 6.4, 8.7, 12.6 and 16.3 (int4, one kernel and one for the sums: 6.8 + 6.8, 10.2 + 5.8,
-// 11.3 + 6.5 and 11.8 + 11.6; now 7.4, 12.2, 16.2 and 16.9).
+// 8.2 + 9.7 for 4608 x 1152; this one 6.5, 8.3, 12.9 and 16.7 (int4, one kernel and one for the sums, without widened codes: 6.8 + 6.8,
+// 10.2 + 5.8, 11.3 + 6.5 and 11.8 + 11.6; now, with them, 6.8, 11.3, 17.0 and 18.2).
 constexpr int kPcCols = 8;
 constexpr int kPcMostWaves = 16;
 
@@ -682,12 +681,11 @@ hipError_t launch_prepare_quant(const float *W, const float *diag, const int32_t
                                w.colsumw);
             return hipGetLastError();
         }
-        if (!amax) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((rotate ? prepare_absmax_kernel<true> : prepare_absmax_kernel<false>), grid, threads, 0, st, W, K, N, diag, perm, amax,
-                           w.colsum, diag_copy);
+        if (!amax || !rotate) return hipErrorInvalidValue;           // (dense blocks end at 36 of them)
+        hipLaunchKernelGGL(prepare_absmax_kernel, grid, threads, 0, st, W, K, N, diag, perm, amax, w.colsum, diag_copy);
         if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-        hipLaunchKernelGGL((rotate ? prepare_quant_kernel<8, true> : prepare_quant_kernel<8, false>), grid, threads, 0, st, W, K, N, diag, perm,
-                           amax, norm, qmax, w.codes, w.codes_tiled, nullptr, w.scales, w.colsum, nullptr);
+        hipLaunchKernelGGL((prepare_quant_kernel<8, true>), grid, threads, 0, st, W, K, N, diag, perm, amax, norm, qmax, w.codes,
+                           w.codes_tiled, nullptr, w.scales, w.colsum, nullptr);
         return hipGetLastError();
     }
     const int rounds = (nb + kPcMostWaves - 1) / kPcMostWaves;      // blocks of the busiest wave

@@ -88,6 +88,26 @@ def test_large_int4_sets(trdq, with_diag):
             assert torch.equal(y[:, :part], y_part), (M, asym)
 
 
+# values that are quantised without a rotation of the kernel's own: one block to a wave, three, and the kernel of large int4 sets
+@pytest.mark.parametrize("K,N,wbits", [(2048, 48, 8), (4608, 16, 8), (4608, 80, 4), (2176, 15440, 4)])
+def test_quantiser_alone(trdq, K, N, wbits):
+    """Identity blocks pass the values on bit for bit: codes and scales are the float32 quantiser's, rounded in float64 on the GPU."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(K)
+    W = torch.randn(K, N, generator=g, device="cuda")
+    W[:, 3] = 0.0
+    rot = trdq.Rotation(torch.eye(128, device="cuda").repeat(K // 128, 1, 1))
+    codes, scales = trdq.prepare_weights_dense(W, rot, wbits=wbits).export()
+    most = 7.0 if wbits == 4 else 127.0
+    blocks = W.view(K // 128, 128, N) if wbits == 4 else W.view(1, K, N)
+    a = blocks.abs().amax(dim=1, keepdim=True)
+    inv = torch.where(a > 0, torch.full_like(a, most) / a, torch.zeros_like(a))     # (a number / a tensor is a reciprocal, then a product)
+    want = (blocks.double() * inv.double()).round().clamp(-most, most).view(K, N)
+    assert np.array_equal(codes, want.to(torch.int8).cpu().numpy())
+    assert np.array_equal(scales.reshape(-1, N), a.view(-1, N).cpu().numpy() * (np.float32(1.0) / np.float32(most)))
+    rot.close()
+
+
 @pytest.mark.parametrize("K,N,copies", [(256, 131072, 2), (65536, 112, 2), (384, 32768, 4)])
 def test_memory_of_int4_sets(trdq, K, N, copies):
     """Packed rows and packed blocks, and as many bytes again for widened codes where a product reads them."""
