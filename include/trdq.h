@@ -297,7 +297,8 @@ trdq_status trdq_rotate_quant_dense(const void *X_dev, int64_t M, int64_t ldx, c
  * 8-token workgroups that run the second rotation twice (maxima, then codes) for wider rows.
  * trdq_rotate_quant_dense_rpr_ws is the same operation with a device workspace, which rows wider than
  * K = 1536 (and narrower rows from 16384 tokens on, where it pays) use for another, faster form (a workgroup per block with the
- * rotation resident in LDS; the rotated values wait in the workspace as float32, the second rotation's in place of the first's):
+ * rotation resident in LDS; the rotated values wait in the workspace as float32, the second rotation's in place of the first's; a
+ * table that names a channel twice takes up to 1.4 times as long as a permutation):
  * ws_dev holds at least trdq_rotate_quant_dense_rpr_ws_nbytes(M, K) bytes (4 (K + 1) roundup(M, 32); 0 for
  * M <= 0 and for K <= 1536 below 16384 tokens, and then ws_dev may be NULL), 16-byte aligned, and belongs to the call until it has finished on its stream;
  * nothing in it needs to be kept or cleared between calls.  ERR_NULL without it, ERR_SHAPE if it is too
