@@ -188,9 +188,9 @@ void trdq_table_destroy(trdq_table *t)
 namespace {
 
 // One device allocation per weight set (an allocation and its release cost 50-100 us each, more than the
-// kernels that fill it): codes, their block-tiled copy (symmetric sets), widened codes (int4 sets of shapes that a product reads them of), scales, column sums, the block maxima
-// between the two passes of a preparation that has no scratch matrix (8-bit codes of very long rows after one Hadamard rotation),
-// and the diagonal for a handle that keeps a copy.
+// kernels that fill it): codes, their block-tiled copy (symmetric sets), widened codes (int4 sets of shapes that a product
+// reads them of), scales, column sums, the block maxima between the two passes of a preparation that has no scratch matrix
+// (8-bit codes of very long rows after one Hadamard rotation), and the diagonal for a handle that keeps a copy.
 trdq_status alloc_weights(trdq_weights *w, bool with_diag, bool asym = false)
 {
     const int K = w->K, N = w->N, nb = K / trdq::kBlock;

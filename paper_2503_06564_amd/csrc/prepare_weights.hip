@@ -238,8 +238,9 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_quant_kernel(
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             *reinterpret_cast<uint2 *>(blk + 128 * p) = make_uint2(w[2 * p], w[2 * p + 1]);
-            if (wide) *reinterpret_cast<uint4 *>(bytes + 256 * p) = make_uint4((w[2 * p] << 4) & 0xF0F0F0F0u, w[2 * p] & 0xF0F0F0F0u,
-                                                                               (w[2 * p + 1] << 4) & 0xF0F0F0F0u, w[2 * p + 1] & 0xF0F0F0F0u);
+            if (wide)
+                *reinterpret_cast<uint4 *>(bytes + 256 * p) = make_uint4((w[2 * p] << 4) & 0xF0F0F0F0u, w[2 * p] & 0xF0F0F0F0u,
+                                                                         (w[2 * p + 1] << 4) & 0xF0F0F0F0u, w[2 * p + 1] & 0xF0F0F0F0u);
         }
     }
 }
@@ -653,11 +654,11 @@ hipError_t launch_prepare_rotate_dense(const float *W, int K, int N, const float
     return hipGetLastError();
 }
 
-// Where the pair is the faster form: rows so long that a wave of the one kernel would read and rotate its blocks twice or that come
-// through a table, and int4 sets so large that its 32-byte pieces of W's lines bound it.  us of a set's replacement, pair / one kernel:
-// 8 bits 6272 x 128 30 / 34, 9216 x 4608 134 / 143, 18432 x 128 39 / 84, but 6144 x 1152 44 / 35; int4 4608 x 16384 157 / 214, 9216 x 4608
-// 102 / 116, 6272 x 4608 75 / 82, 2176 x 16384 77 / 79, but 4608 x 4608 64 / 63, 2048 x 16384 73 / 71; through a table, a set made anew, 4608 x 16 36 / 44, 4608 x 4608 417 / 451
-// (int4 664 / 691), but 1152 x 4608 100 / 97.
+// Where the pair is the faster form: rows so long that a wave of the one kernel would read and rotate its blocks twice or that
+// come through a table, and int4 sets so large that its 32-byte pieces of W's lines bound it.  us of a set's replacement, pair / one
+// kernel: 8 bits 6272 x 128 30 / 34, 9216 x 4608 134 / 143, 18432 x 128 39 / 84, but 6144 x 1152 44 / 35; int4 4608 x 16384 157 / 214,
+// 9216 x 4608 102 / 116, 6272 x 4608 75 / 82, 2176 x 16384 77 / 79, but 4608 x 4608 64 / 63, 2048 x 16384 73 / 71; through a table, a set
+// made anew, 4608 x 16 36 / 44, 4608 x 4608 417 / 451 (int4 664 / 691), but 1152 x 4608 100 / 97.
 bool prepare_takes_pair(int K, int N, int wbits, bool gathered)
 {
     const int nb = K / kBlock;

@@ -539,9 +539,8 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
 // takes 64 tokens of one block, a wave 32 of its channels (a row's 64 tokens are one 256-byte load), and the codes change layout
 // in LDS: 128 bytes of a token's row per eight lanes.  Maxima with a sign: a channel was named twice, and the products that
 // kSinkInPlace formed them from are formed again, 16 tokens and all channels of the block to a wave, in the same NCH chains.
-// (Multiplied out by the vector units, 128 gathers per channel, such a call took 152 us at 70 x 1664, 338 at 4096 x 1664 and 643 at 4096 x
-// 4608; now 24, 54
-// and 117, a permutation 19, 42 and 84.)
+// (Multiplied out by the vector units, 128 gathers per channel, such a call took 152 us at 70 x 1664, 338 at 4096 x 1664 and 643 at
+// 4096 x 4608; now 24, 54 and 117, a permutation 19, 42 and 84.)
 template <int NCH>
 __global__ __launch_bounds__(256) void dense_codes_kernel(const float *__restrict__ T, int64_t ldt, int64_t M, int K,
                                                           const int32_t *__restrict__ perm, const uint4 *__restrict__ pieces,
@@ -1039,8 +1038,8 @@ hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K,
         e = two ? launch_dense_block_pass<kSinkInPlace, 2>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st)
                       : launch_dense_block_pass<kSinkInPlace, 1>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(two ? dense_codes_kernel<2> : dense_codes_kernel<4>, dim3((unsigned)((m + 63) / 64), nb), dim3(256), 0, st, T, ldt, m, K, perm, p2, amax_tok, xq,
-                           sx + m0);
+        hipLaunchKernelGGL(two ? dense_codes_kernel<2> : dense_codes_kernel<4>, dim3((unsigned)((m + 63) / 64), nb), dim3(256), 0, st,
+                           T, ldt, m, K, perm, p2, amax_tok, xq, sx + m0);
         if (e = hipGetLastError(); e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -94,7 +94,8 @@ def test_many_tokens_like_few(M, K):
     assert torch.equal(buf[m:M], back[m:]) and torch.equal(sx[m:M], want_s[m:]) and torch.equal(zc_all[m:], zc[:300])
 
 
-@pytest.mark.parametrize("M,K,once", [(24575, 4608, "none"), (24576, 4608, "symmetric"), (884735, 128, "none"), (884736, 128, "symmetric"),
+@pytest.mark.parametrize("M,K,once", [(19419, 4608, "none"), (19420, 4608, "none"), (699051, 128, "none"), (24575, 4608, "none"),
+                                      (24576, 4608, "symmetric"), (884735, 128, "none"), (884736, 128, "symmetric"),
                                       (32767, 4608, "symmetric"), (32768, 4608, "all")])
 def test_inputs_about_the_size_of_the_memory_side_cache(M, K, once):
     """Calls on either side of the sizes from which the input is read non-temporally (108 * 2^20 values, with zero points 144 * 2^20) against
