@@ -904,6 +904,238 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
 #endif
 }
 
+// ---- more than one round of 128 x 128 tiles: a workgroup walks a list of them --------------------
+// The loop and the arithmetic of qgemm4_tiled_kernel.  With a workgroup per tile a slot of a compute unit stands 0.7 us without one
+// between two tiles, and the new one waits 2 us for its first operands, of 14 us at K = 1152 (time stamps, 16384 tokens 1152 ->
+// 4608).  Here the ring never drains: the last k-steps of a tile request the first ones of the next, which land under the
+// epilogue; the output is laid out beside the ring, so that no barrier stands between two tiles.  Stages, copies and fragments as
+// above.  What bounds it is the loop: without copies 3 % faster, without LDS reads or stores not at all, without folds 17 %.
+// us, before and after: 1152 -> 1152 / 3456 / 4608 at 16384 tokens 33.3 / 86.9 / 110.9 -> 31.2 / 86.6 / 109.7, 4608 -> 1152 101.3 ->
+// 98.0, 768 -> 3072 at 8192 29.1 -> 27.9, 384 -> 1536 at 32768 36.8 -> 33.7.  Up to one round it is the slower form: the next tile's
+// place and the wait for its unused copies cost 0.6 us (4096 tokens 1152 -> 1152 14.1 -> 14.6, 384 -> 1152 7.6 -> 8.3).
+// (The same for the int8 kernel, tall tiles: 2 to 6 % slower.  Its lists drift apart, and with them what a die's L2 shares.)
+constexpr int kW4ListStage = 8192 + 8192 + 512;       // 8 activation blocks, 8 weight blocks, the group's 128 scales
+constexpr int kW4ListStages = 4;
+constexpr int kW4ListPar = kW4ListStages * kW4ListStage;          // [128 bias][pad][128 s_x][pad]
+constexpr int kW4ListRow = 64 * 2 + 16;               // a wave's 64 channels of one token, padded
+constexpr int kW4ListStg = kW4ListPar + 2048;
+constexpr int kW4ListLds = kW4ListStg + 4 * 16 * kW4ListRow;      // 78848 B: two workgroups per compute unit
+
+template <bool DEBUG>
+__global__ __launch_bounds__(kThreads, 2) void qgemm4_list_kernel(GemmArgs g, int stride)
+{
+    extern __shared__ __align__(16) int8_t smem[];
+    constexpr int TM = 4, TN = 4, NS = kW4ListStages;
+    constexpr int P = 5;                              // copies per wave and k-step: two activation blocks, two weight blocks, scales
+    constexpr int XOFF = 0, WOFF = 8192, SOFF = 16384;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t *)smem;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave & 1, wn = wave >> 1;
+    const int l16 = lane & 15, lg = lane >> 4;
+    const int tiles_m = (int)(g.M / kW4BM), tiles_n = g.N / kW4BN, ntiles = tiles_m * tiles_n;
+    const int KT = g.K >> 6;                          // k-steps: even, more than NS
+    auto locate = [&](int id, int64_t &m, int &n) {
+        int tm, tn, rows = tiles_m, cols = tiles_n;
+        asm volatile("" : "+s"(rows), "+s"(cols));    // the map's divisors anew for every tile: kept, they take the sums' registers
+        tile_map(id, rows, cols, tm, tn);
+        m = (int64_t)__builtin_amdgcn_readfirstlane(tm) * kW4BM;
+        n = __builtin_amdgcn_readfirstlane(tn) * kW4BN;
+    };
+    int id = blockIdx.x;
+    int64_t m0, m1;                                   // first token and channel of this tile and of the next one
+    int n0, n1;
+    locate(id, m0, n0);
+
+    // The copies run ahead of the products, over the end of a tile into the next one: where the next k-step to be copied
+    // lies, and how many of its tile are left.
+    const int64_t gstride = (int64_t)KT * 1024;       // bytes from one 16-row group to the next
+    const int8_t *xp, *wp, *xnext, *wnext;                  // ... and the tile after it
+    const float *sp, *snext;
+    int left = KT;
+    auto aim = [&](int64_t m, int n) {
+        xnext = g.Xq + (m / 16 + 2 * wave) * gstride;
+        wnext = static_cast<const int8_t *>(g.Wc) + (int64_t)(n / 16 + 2 * wave) * gstride;
+        snext = g.sw + n + (wave & 1) * 64;
+    };
+    const uint32_t voff = (uint32_t)(lane * 16), voffs = (uint32_t)(lane * 4);
+    auto copy = [&](auto c_tag, int stage) {          // stage: byte offset in the ring
+        constexpr int c = decltype(c_tag)::value;
+        const uint32_t to = lds0 + stage;
+        if constexpr (c < 2) dma_1k(voff, xp + c * gstride, to + XOFF + (2 * wave + c) * 1024);
+        else if constexpr (c < 4) dma_1k(voff, wp + (c - 2) * gstride, to + WOFF + (2 * wave + c - 2) * 1024);
+        else copy_256_if(1, voffs, sp, to + SOFF + (wave & 1) * 256);
+    };
+    auto advance = [&]() {
+        xp += 1024;
+        wp += 1024;
+        sp += (int64_t)(left & 1) * g.N;              // both steps of a group bring its scales
+        // (selects that stay selects: with a branch in the step the compiler moves the folds behind it)
+        asm("s_cmp_eq_u32 %3, 1\n\ts_cselect_b64 %0, %4, %0\n\ts_cselect_b64 %1, %5, %1\n\t"
+            "s_cselect_b64 %2, %6, %2\n\ts_cselect_b32 %3, %7, %3\n\ts_sub_i32 %3, %3, 1"
+            : "+&s"(xp), "+&s"(wp), "+&s"(sp), "+&s"(left) : "s"(xnext), "s"(wnext), "s"(snext), "s"(KT + 1) : "scc");
+    };
+
+    if (wave == 0 && g.bias == nullptr)               // no bias: zeros, so that the epilogue needs no branch
+        *reinterpret_cast<uint4 *>(smem + kW4ListPar + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
+    aim(m0, n0);
+    xp = xnext;
+    wp = wnext;
+    sp = snext;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        static_for_n<P>([&](auto c) { copy(c, s * kW4ListStage); });
+        advance();
+    }
+    wait_vmcnt<(NS - 1) * P>();
+    __syncthreads();
+
+    const int xfr = XOFF + wm * TM * 1024 + lane * 16;
+    const int wfr = WOFF + wn * TN * 1024 + lane * 16;
+    const int sfr = SOFF + (wn * 64 + lg * 4) * 4;
+    v4i af[TN], bf[2][TM];
+    float4 sc[TN];
+#pragma unroll
+    for (int a = 0; a < TN; ++a) {
+        af[a] = *reinterpret_cast<const v4i *>(smem + wfr + a * 1024);
+        sc[a] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int b = 0; b < TM; ++b) bf[0][b] = *reinterpret_cast<const v4i *>(smem + xfr + b * 1024);
+
+    int st = 0;                                       // byte offset of this step's stage
+    bool first = true;                                // no tile before: no stores among the requests
+    for (;;) {
+        const bool more = id + stride < ntiles;
+        v4i acc[TN][TM];
+        v4f facc[TN][TM];
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b) facc[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
+        auto fold = [&](int a, int b, int group) {
+            asm volatile("" : "+v"(acc[a][b]));       // folds stay where they are written: the compiler moves them into the step before
+            if constexpr (DEBUG) {
+                const int64_t m = m0 + wm * 64 + b * 16 + l16;
+                *reinterpret_cast<int4 *>(g.acc_debug + ((int64_t)group * g.M + m) * g.N + n0 + wn * 64 + a * 16 + lg * 4) =
+                    make_int4(acc[a][b][0] >> 4, acc[a][b][1] >> 4, acc[a][b][2] >> 4, acc[a][b][3] >> 4);
+            }
+            facc[a][b][0] += sc[a].x * (float)acc[a][b][0];
+            facc[a][b][1] += sc[a].y * (float)acc[a][b][1];
+            facc[a][b][2] += sc[a].z * (float)acc[a][b][2];
+            facc[a][b][3] += sc[a].w * (float)acc[a][b][3];
+        };
+        // One k-step.  HALF 0 starts the sums of a scale group (folding the group before, tile by tile, with
+        // the scales read one group earlier) and ends by reading the new group's scales; HALF 1 continues the sums.
+        auto step = [&](auto half_tag, auto fold_tag, int kt) {
+            constexpr int HALF = decltype(half_tag)::value;
+            constexpr bool FOLD = decltype(fold_tag)::value;
+            const int nst = st == (NS - 1) * kW4ListStage ? 0 : st + kW4ListStage;
+            const int8_t *const nxt = smem + nst;
+            // The next step's blocks have landed.  In a tile's first two steps the stores of the tile before are younger
+            // than they are (requests retire in order).
+            if (!FOLD && kt < 2 && !first) wait_vmcnt<(NS - 2) * P + 2 * TM>();
+            else wait_vmcnt<(NS - 2) * P>();
+            __syncthreads();
+#pragma unroll
+            for (int b = 0; b < TM; ++b) bf[1 - HALF][b] = *reinterpret_cast<const v4i *>(nxt + xfr + b * 1024);
+            __builtin_amdgcn_sched_barrier(0);
+            static_for_n<TN>([&](auto a_tag) {
+                constexpr int a = decltype(a_tag)::value;
+                if constexpr (FOLD) {
+#pragma unroll
+                    for (int b = 0; b < TM; ++b) fold(a, b, (kt >> 1) - 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int bb = 0; bb < TM; ++bb) {
+                    const int b = a & 1 ? TM - 1 - bb : bb;
+                    acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[a], bf[HALF][b], HALF == 0 ? v4i{0, 0, 0, 0} : acc[a][b], 0, 0, 0);
+                }
+                af[a] = *reinterpret_cast<const v4i *>(nxt + wfr + a * 1024);
+                copy(a_tag, st);
+                if constexpr (a == TN - 1) copy(std::integral_constant<int, P - 1>{}, st);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            advance();
+            // The group's scales, once the fold of the group before is done, from the NEXT step's stage (they
+            // travel with both steps of the group): that stage is not given away before the next barrier,
+            // this step's is being refilled by the other waves already.
+            if constexpr (HALF == 0) {
+#pragma unroll
+                for (int a = 0; a < TN; ++a) sc[a] = *reinterpret_cast<const float4 *>(nxt + sfr + a * 64);
+            }
+            st = nst;
+        };
+        using H0 = std::integral_constant<int, 0>;
+        using H1 = std::integral_constant<int, 1>;
+        using Yes = std::integral_constant<bool, true>;
+        using No = std::integral_constant<bool, false>;
+        step(H0{}, No{}, 0);
+        // Every wave is past the epilogue of the tile before: wave 0 requests this tile's biases, wave 1 its token scales
+        // (half a copy each).  They are there long before the last of at least six k-steps.
+        {
+            const uint32_t v32 = (uint32_t)((lane & 31) * 16);
+            copy_1k_if(wave == 0 && g.bias != nullptr, v32, g.bias ? g.bias + n0 : g.sw, lds0 + kW4ListPar);
+            copy_1k_if(wave == 1, v32, g.sx + m0, lds0 + kW4ListPar + 1024);
+        }
+        locate(more ? id + stride : id, m1, n1);          // past the end: the last tile again, unused
+        aim(m1, n1);
+        step(H1{}, No{}, 1);
+        int kt = 2;
+        do {
+            step(H0{}, Yes{}, kt);
+            step(H1{}, No{}, kt + 1);
+            kt += 2;
+        } while (kt < KT);
+        if (!more) wait_vmcnt<0>();                   // the unused copies: nobody may get their part of the LDS before
+        // the last group's fold
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b) fold(a, b, (KT >> 1) - 1);
+
+        // ---- epilogue: y = (s_x / 16) * facc + bias -> bf16, one 16-token tile at a time through the wave's staging rows
+        // (the lane index anew: kept over the loop, what follows from it takes the registers of the sums)
+        int zero = 0;
+        asm volatile("" : "+s"(zero));
+        const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (uint32_t)zero));
+        const int l16_e = lane_e & 15, lg_e = lane_e >> 4;
+        const float *const par = reinterpret_cast<const float *>(smem + kW4ListPar);
+        int8_t *const stg = smem + kW4ListStg + wave * (16 * kW4ListRow);
+        float4 bi_r[TN];
+#pragma unroll
+        for (int a = 0; a < TN; ++a) bi_r[a] = *reinterpret_cast<const float4 *>(par + wn * 64 + a * 16 + lg_e * 4);
+#pragma unroll
+        for (int b = 0; b < TM; ++b) {
+            const float sxm = par[256 + wm * 64 + b * 16 + l16_e] * 0.0625f;
+#pragma unroll
+            for (int a = 0; a < TN; ++a) {
+                uint2 o;
+                o.x = pack_bf16x2(sxm * facc[a][b][0] + bi_r[a].x, sxm * facc[a][b][1] + bi_r[a].y);
+                o.y = pack_bf16x2(sxm * facc[a][b][2] + bi_r[a].z, sxm * facc[a][b][3] + bi_r[a].w);
+                *reinterpret_cast<uint2 *>(stg + l16_e * kW4ListRow + (a * 16 + lg_e * 4) * 2) = o;
+            }
+            __builtin_amdgcn_wave_barrier();
+            // 16 rows x 128 bytes = 128 pieces of 16 bytes: two per lane
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int q = i * 64 + lane_e;
+                const int row = q >> 3, c = q & 7;
+                const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * kW4ListRow + c * 16);
+                store_out16(g.Y + (m0 + wm * 64 + b * 16 + row) * g.ldy + n0 + wn * 64 + c * 8, v);
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (!more) break;
+        id += stride;
+        m0 = m1;
+        n0 = n1;
+        first = false;
+    }
+}
+
 // 16 bytes per thread from the block form to the row-major form [M, K]
 __global__ void untile_kernel(const int8_t *__restrict__ Xt, int8_t *__restrict__ Xq, int64_t M, int K)
 {
@@ -1078,7 +1310,18 @@ hipError_t launch_w4(const GemmArgs &a, bool debug, hipStream_t st)
 
 hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st)
 {
-    return tiled4_supports(a) ? launch_w4<kW4BM, kBlocks, false>(a, debug, st) : hipErrorInvalidValue;
+    if (!tiled4_supports(a)) return hipErrorInvalidValue;
+    const int64_t tiles = (a.M / kW4BM) * (a.N / kW4BN), slots = 2 * (int64_t)num_cus();
+#ifdef TRDQ_PROBE_PHASES
+    return launch_w4<kW4BM, kBlocks, false>(a, debug, st);        // the kernel that records time stamps
+#endif
+    if (tiles <= slots || tiles > 0x3fffffff) return launch_w4<kW4BM, kBlocks, false>(a, debug, st);
+    auto go = [&](auto kern) -> hipError_t {
+        if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), kW4ListLds); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)slots), dim3(kThreads), kW4ListLds, st, a, (int)slots);
+        return hipGetLastError();
+    };
+    return debug ? go(qgemm4_list_kernel<true>) : go(qgemm4_list_kernel<false>);
 }
 
 bool tiled4_rows_supports(const GemmArgs &a)

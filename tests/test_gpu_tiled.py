@@ -142,6 +142,31 @@ def test_qgemm_tiled_int4_matches_oracle(oracle, M, K, N, with_bias):
     w.close()
 
 
+# more 128 x 128 tiles than two per compute unit: one workgroup with a second tile, the fewest k-steps, one channel tile, an odd number
+# of scale groups with most lists of one length, several rounds
+@pytest.mark.parametrize("M,K,N,ldy", [(7296, 384, 1152, 1152), (66560, 384, 128, 136), (9216, 896, 1152, 1152), (16384, 640, 2304, 2320)])
+def test_qgemm_tiled_int4_lists(M, K, N, ldy):
+    say(f"qgemm_tiled int4 lists M={M} K={K} N={N} ldy={ldy}")
+    gen = torch.Generator(device=dev()).manual_seed(M + K)
+    X = torch.randn((M, K), generator=gen, device=dev()).to(torch.bfloat16)
+    w = trdq.prepare_weights(0.02 * torch.randn((K, N), generator=gen, device=dev()), None, wbits=4)
+    Xt = torch.empty((trdq.xq_tiled_nbytes(M, K),), dtype=torch.int8, device=dev())
+    Xq = torch.empty((M, K), dtype=torch.int8, device=dev())
+    sx = torch.empty((M,), dtype=torch.float32, device=dev())
+    trdq.rotate_quant_tiled(X, None, Xt, sx)
+    trdq.xq_untile(Xt, M, K, Xq)
+    for bias in (None, torch.randn(N, generator=gen, device=dev())):
+        Y = torch.full((M, ldy), 7.0, dtype=torch.bfloat16, device=dev())
+        Y_rows = torch.full((M, N), 7.0, dtype=torch.bfloat16, device=dev())
+        trdq.qgemm_tiled(w, Xt, sx, Y[:, :N], bias=bias)
+        trdq.qgemm(w, Xq, sx, Y_rows, bias=bias)
+        torch.cuda.synchronize()
+        # the row-major kernels fold in the same order: the same bits; nothing beside the rows
+        assert torch.equal(Y[:, :N], Y_rows)
+        assert bool((Y[:, N:] == 7.0).all())
+    w.close()
+
+
 def test_qgemm_tiled_int4_refuses_what_it_does_not_take():
     _, W, d, _ = wl.small_case(76, 4, 256, 128)
     w = trdq.prepare_weights(f32_to_dev(W), f32_to_dev(d), wbits=4)              # two scale groups: too short
