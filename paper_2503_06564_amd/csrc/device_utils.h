@@ -136,17 +136,4 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-// 16-byte store of finished output, non-temporal: the lines leave a die's L2 while the product runs.  Kept there, up to 32 MB of
-// them are written back when the kernel ends and the next one starts behind that.  us, before and after: a block's four linears on
-// inputs of their own, width 1152, at 4096 / 32768 tokens 120 -> 113 / 650 -> 626, int4 at 16384 429 -> 413; 1152 -> 4608 -> 1152, each
-// reading what the other wrote, at 4096 / 16384 / 32768 tokens 66.9 -> 66.6 / 212.7 -> 211.9 / 417.9 -> 408.5, with an elementwise pass
-// between 78.4 -> 78.8 / 263.6 -> 255.8 / 514 -> 490; what loses is one product that writes the same buffer again and again (1152 -> 4608 at
-// 4096 31.7 -> 32.4).  For whole rows of at least 128 bytes only: the codes of rotate_quant, in runs of 64 to 128 bytes, are
-// slower so (the block at 4096 tokens 113 -> 117), and so is writing through (sc1: 125).
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void store_out16(void *p, uint4 v)
-{
-    __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t *>(p));
-}
-
 }  // namespace trdq

@@ -105,6 +105,35 @@ __device__ __forceinline__ void wait_vmcnt()
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
+// ---- output rows -----------------------------------------------------------------------------------
+// Stored non-temporally, the lines of an output leave a die's L2 while the product runs.  Kept there, up to 32 MB of them are
+// written back when the kernel ends, and the next one starts behind that.  A line that two workgroups share costs memory two
+// partial writes then; so whole lines of a workgroup's row segment only, where the kernel writes much per product.
+// us, ordinary stores and these, products and their passes on inputs of their own (600 MB in turn): int4 (segments of
+// 128 bytes) 384 -> 1024 / 4608 at 4096 tokens 10.9 / 22.7 -> 10.1 / 19.6, 1152 -> 4608 at 16384 134 -> 129; int8 (288 bytes) 256 -> 1152 at
+// 6000 12.7 -> 11.4, 1152 -> 1152 at 9368 30.8 -> 28.2.  Writing through instead (sc1) is slower than either (a block's four linears
+// of width 1152 at 4096 tokens 119 / 113 / 125), and so are non-temporal codes of rotate_quant, in runs of 64 to 128 bytes (117).
+// Where the output is read at once: 1152 -> 4608 -> 1152 at 4096 / 32768 tokens 66.9 / 418 -> 66.6 / 408, with an elementwise pass between
+// 78.4 / 514 -> 78.8 / 490; one product that writes the same buffer again and again 31.7 -> 32.4.
+//
+// 16 bytes of an output row
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_out16(uint16_t *p, uint4 v)
+{
+    __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t *>(p));
+}
+// 16-byte piece c of a row segment of BYTES bytes, non-temporal only if its whole line lies in the segment (assembly: the compiler
+// joins two stores that differ by the hint only)
+template <int BYTES>
+__device__ __forceinline__ void store_whole_lines(uint16_t *seg, int c, uint4 v)
+{
+    uint16_t *const p = seg + c * 8;
+    const uint32_t line = (uint32_t)(c * 16) - ((uint32_t)(uintptr_t)p & 127u);      // where the piece's line begins in the segment
+    const u32x4_t w = {v.x, v.y, v.z, v.w};
+    if (line <= (uint32_t)(BYTES - 128)) asm volatile("global_store_dwordx4 %0, %1, off nt" :: "v"(p), "v"(w) : "memory");
+    else *reinterpret_cast<u32x4_t *>(p) = w;
+}
+
 // Direct-to-LDS int8 kernels (qgemm_dma.hip).  variant indexes the table in that file.
 int dma_num_variants();
 hipError_t launch_qgemm8_dma(const GemmArgs &a, bool debug, int variant, hipStream_t st);

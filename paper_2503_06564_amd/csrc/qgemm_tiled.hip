@@ -45,6 +45,8 @@ constexpr int tiled_lds(bool asym) { return kParOff + par_bytes(asym); }   // 79
 // Where the activations are: kBlocks: the block-tiled form, whole tiles.  kRows: row-major [M, K], any M and N from one
 // tile on.  kRowsAsym: the same with zero points.
 enum { kBlocks = 0, kRows = 1, kRowsAsym = 2 };
+// Which lines of the output are stored non-temporally, see tiled_lines.
+enum { kNoLines = 0, kWholeLines = 1, kAllLines = 2 };
 
 template <int... Is, class F>
 __device__ __forceinline__ void static_for_seq(std::integer_sequence<int, Is...>, F &&f)
@@ -119,7 +121,7 @@ __device__ __forceinline__ int x_frag_off(int r, int p)
 // ahead, then 9 x TM matrix instructions on the fragments in registers while the next step's
 // fragments are read: a weight fragment's registers are refilled as soon as its TM instructions
 // have issued, the activation fragments alternate between two sets.
-template <int BM, bool DEBUG, int FORM>
+template <int BM, bool DEBUG, int FORM, int LINES>
 __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8_t *smem)
 {
     constexpr int TM = BM / 64;
@@ -340,7 +342,10 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
             if (id < 16 * LPR) {
                 const int row = id / LPR, c = id - row * LPR;
                 const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * ROWB + c * 16);
-                store_out16(g.Y + (m_wave + b * 16 + row) * g.ldy + n0 + c * 8, v);
+                uint16_t *const seg = g.Y + (m_wave + b * 16 + row) * g.ldy + n0;
+                if constexpr (LINES == kAllLines) store_out16(seg + c * 8, v);
+                else if constexpr (LINES == kWholeLines) store_whole_lines<kBN * 2>(seg, c, v);
+                else *reinterpret_cast<uint4 *>(seg + c * 8) = v;
             }
         }
         __builtin_amdgcn_wave_barrier();
@@ -359,7 +364,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
 #endif
 }
 
-template <bool DEBUG, int FORM>
+template <bool DEBUG, int FORM, int LINES>
 __global__ __launch_bounds__(kThreads, 2) void qgemm8_tiled_kernel(GemmArgs g, int n_big, int nbn)
 {
     extern __shared__ __align__(16) int8_t smem[];
@@ -368,10 +373,10 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm8_tiled_kernel(GemmArgs g, i
     int tm, tn;
     if (id < n_big) {
         tile_map(id, (int)((g.M + 255) / 256), nbn, tm, tn);
-        run_tile<256, DEBUG, FORM>(g, tm, tn, smem);
+        run_tile<256, DEBUG, FORM, LINES>(g, tm, tn, smem);
     } else {
         tile_map(id - n_big, (int)((g.M + 127) / 128), tiles_n - nbn, tm, tn);
-        run_tile<128, DEBUG, FORM>(g, tm, tn + nbn, smem);
+        run_tile<128, DEBUG, FORM, LINES>(g, tm, tn + nbn, smem);
     }
 }
 
@@ -1172,6 +1177,16 @@ void tiled_split(int64_t M, int N, int &n_big, int &nbn)
     n_big = (int)(p256 * nbn);
 }
 
+// Which lines of its segments of 288 bytes a workgroup stores non-temporally (gemm_common.h), us for all / whole ones / none: from 1024
+// input channels on all (the block of width 1152 at 32768 tokens 647 / 659 / 661), below up to 16 MB of output (768 -> 1152 at 6000 17.1 /
+// 18.1 / 19.1), beyond whole ones (256 -> 4608 at 4096 / 16384 20.8 / 17.3 / 17.4 and 63.3 / 48.4 / 49.8, 768 -> 2304 at 4096 18.5 / 18.1 / 18.9).
+// Outputs of a few MB gain nothing: below 8 MB none (256 -> 288 at 6000 / 9368 9.1 / 10.3 all, 8.9 / 10.0 none).
+int tiled_lines(int64_t M, int K, int N)
+{
+    const int64_t values = M * N;
+    return values < (4 << 20) ? kNoLines : K < 1024 && values > (8 << 20) ? kWholeLines : kAllLines;
+}
+
 // The kernel that splits K inside the workgroup: two pairs, four stages for an even number of
 // k-steps per pair and three for an odd one (the main loop takes the steps two at a time).
 bool tiled_ksplit_applies(const GemmArgs &a)
@@ -1212,7 +1227,12 @@ hipError_t launch_form(const GemmArgs &a, bool debug, hipStream_t st)
 #ifdef TRDQ_PROBE_PHASES
     debug = false;                                    // the debug pointer receives time stamps instead
 #endif
-    return debug ? go(qgemm8_tiled_kernel<true, FORM>) : go(qgemm8_tiled_kernel<false, FORM>);
+    if (debug) return go(qgemm8_tiled_kernel<true, FORM, kAllLines>);
+    switch (tiled_lines(a.M, a.K, a.N)) {
+        case kAllLines: return go(qgemm8_tiled_kernel<false, FORM, kAllLines>);
+        case kWholeLines: return go(qgemm8_tiled_kernel<false, FORM, kWholeLines>);
+        default: return go(qgemm8_tiled_kernel<false, FORM, kNoLines>);
+    }
 }
 
 hipError_t launch_qgemm8_tiled(const GemmArgs &a, bool debug, hipStream_t st)

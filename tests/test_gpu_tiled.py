@@ -167,6 +167,34 @@ def test_qgemm_tiled_int4_lists(M, K, N, ldy):
     w.close()
 
 
+# outputs stored with no, all or only the whole 128-byte lines of a tile's rows non-temporal, at every place of a row in its line
+@pytest.mark.parametrize("M,K,N", [(3968, 256, 1008), (4096, 256, 2304), (8192, 384, 1152), (4224, 1024, 2016)])
+@pytest.mark.parametrize("pad,shift", [(0, 0), (8, 0), (64, 24), (40, 56)])
+def test_output_lines(M, K, N, pad, shift):
+    say(f"output lines M={M} K={K} N={N} pad={pad} shift={shift}")
+    gen = torch.Generator(device=dev()).manual_seed(M + N)
+    X = torch.randn((M, K), generator=gen, device=dev()).to(torch.bfloat16)
+    w = trdq.prepare_weights(0.02 * torch.randn((K, N), generator=gen, device=dev()), None, wbits=8)
+    Xt = torch.empty((trdq.xq_tiled_nbytes(M, K),), dtype=torch.int8, device=dev())
+    Xq = torch.empty((M, K), dtype=torch.int8, device=dev())
+    sx = torch.empty((M,), dtype=torch.float32, device=dev())
+    trdq.rotate_quant_tiled(X, None, Xt, sx)
+    trdq.xq_untile(Xt, M, K, Xq)
+    ldy = N + pad
+    buf = torch.full((M * ldy + 64,), 7.0, dtype=torch.bfloat16, device=dev())
+    Y = buf[shift:shift + M * ldy].view(M, ldy)
+    acc = torch.empty((M, N), dtype=torch.int32, device=dev())
+    want = torch.empty((M, N), dtype=torch.bfloat16, device=dev())
+    trdq.qgemm_tiled(w, Xt, sx, want, acc_debug=acc)     # the kernel that also leaves its integer sums
+    for call in (lambda: trdq.qgemm_tiled(w, Xt, sx, Y[:, :N]), lambda: trdq.qgemm(w, Xq, sx, Y[:, :N])):
+        buf.fill_(7.0)
+        call()
+        torch.cuda.synchronize()
+        assert torch.equal(Y[:, :N], want)
+        assert bool((Y[:, N:] == 7.0).all()) and bool((buf[:shift] == 7.0).all()) and bool((buf[shift + M * ldy:] == 7.0).all())
+    w.close()
+
+
 def test_qgemm_tiled_int4_refuses_what_it_does_not_take():
     _, W, d, _ = wl.small_case(76, 4, 256, 128)
     w = trdq.prepare_weights(f32_to_dev(W), f32_to_dev(d), wbits=4)              # two scale groups: too short
