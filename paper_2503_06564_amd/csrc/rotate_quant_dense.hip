@@ -211,6 +211,8 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_kernel(
 //                 of T, perm being a permutation, and a wave has read all 128 rows of its tokens before it stores.  Their maxima
 //                 per token are merged by atomic maxima.  A table that names a row twice (after clamping, entries are not
 //                 checked before) is noticed by the first rotation: the maxima carry a sign, and nothing is stored;
+//   kSinkWholeRow  second rotation of rows of one block: the maximum of a token is the wave's own, so that codes and scales
+//                 (in amax_tok's place) follow at once and T is only read; a row named twice is no matter then;
 //   dense_codes_kernel   streams T once, quantises, and turns channel-major values into rows of codes; maxima with a sign:
 //                 T still holds once-rotated values, and it forms the products first.
 // Here the token maxima have a row of their own behind T (amax_tok), cleared by the first rotation's first block,
@@ -221,7 +223,7 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_kernel(
 // (Tried and no faster, same box, 4096 and 32768 tokens of 4608 channels: rows of T written in permuted order
 // so that the second rotation reads consecutive rows; 16-byte loads of T with a change of layout through
 // LDS instead of the 4-byte ones; two accumulator chains instead of four.)
-enum DenseSink { kSinkMaxima = 0, kSinkCodes = 1, kSinkRows = 2, kSinkInPlace = 3 };
+enum DenseSink { kSinkMaxima = 0, kSinkCodes = 1, kSinkRows = 2, kSinkInPlace = 3, kSinkWholeRow = 4 };
 
 // eight float32 -> their exact three-way split by truncation, each piece eight bf16 in operand order
 // (a byte permute takes the upper halves of two words: no masks for the packing)
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
     // one token tile of the float32 operand is requested a group ahead (like the bf16 one); two tiles are
     // requested at the top of their own group (no registers to hold both across the products), and the
     // wave that shares the SIMD covers the wait
-    constexpr bool GATHER = SINK == kSinkInPlace;
+    constexpr bool GATHER = SINK == kSinkInPlace || SINK == kSinkWholeRow;
     constexpr bool AHEAD = GATHER && TT == 1;
     constexpr bool QUANT = SINK == kSinkCodes;
     extern __shared__ __align__(16) uint4 lds_pieces[];           // [12][8][64] fragments of this block
@@ -289,7 +291,7 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
     uint32_t sign = 0;
     if constexpr (GATHER) {
         if (threadIdx.x < kBlock) rowtab[threadIdx.x] = clamp_channel(perm[b * kBlock + threadIdx.x], K);
-        sign = __builtin_amdgcn_readfirstlane(__float_as_uint(amax_tok[0])) & 0x80000000u;
+        if constexpr (SINK == kSinkInPlace) sign = __builtin_amdgcn_readfirstlane(__float_as_uint(amax_tok[0])) & 0x80000000u;
     }
     if constexpr (SINK == kSinkRows) {
         if (b == 0) {                                             // of two entries with the same row one reads the other's number
@@ -368,7 +370,7 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
         } else {
             load_x(xnext, nxt);
         }
-        constexpr int NA = GATHER ? 4 : 1;                        // in place a lane holds four tokens of one channel
+        constexpr int NA = SINK == kSinkInPlace ? 4 : 1;                        // in place a lane holds four tokens of one channel
         float inv[TT], amax[TT][NA];
         int64_t token[TT];
 #pragma unroll
@@ -388,6 +390,7 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
             if (b == 0 && lane < TOK) amax_tok[gr * TOK + lane] = __uint_as_float(sign);
         }
         uint32_t code[QUANT ? TT : 1][8];
+        float whole[SINK == kSinkWholeRow ? TT : 1][8][4];
         int lane_off = lane;                                      // keeps the fragment reads inside this loop
         asm volatile("" : "+v"(lane_off));
         // what becomes of a finished tile t (acc[tt][j]: see the sinks above)
@@ -400,6 +403,12 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
                 } else if constexpr (SINK == kSinkMaxima) {
                     amax[tt][0] = fmaxf(amax[tt][0], fmaxf(fmaxf(fabsf(acc[tt][0]), fabsf(acc[tt][1])),
                                                            fmaxf(fabsf(acc[tt][2]), fabsf(acc[tt][3]))));
+                } else if constexpr (SINK == kSinkWholeRow) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        whole[tt][t][j] = acc[tt][j];
+                        amax[tt][0] = fmaxf(amax[tt][0], fabsf(acc[tt][j]));
+                    }
                 } else {                                          // tokens 4 g .. 4 g + 3 of channel c(t, l16)
                     const int c = 32 * (l16 >> 2) + 4 * t + (l16 & 3);
                     if constexpr (GATHER) {
@@ -450,8 +459,11 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
 #pragma unroll
                         for (int tt = 0; tt < TT; ++tt) {
                             const v8bf x = bp == 2 ? xlo[tt][s] : (bp == 1 ? xmid[tt][s] : xcur[tt][s]);
-                            // rows = tokens, columns = the tile's channels
-                            ch[tt][s % NCH] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, a.v, ch[tt][s % NCH], 0, 0, 0);
+                            // in place: rows = tokens, columns = the tile's channels
+                            if constexpr (SINK == kSinkWholeRow)
+                                ch[tt][s % NCH] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, x, ch[tt][s % NCH], 0, 0, 0);
+                            else
+                                ch[tt][s % NCH] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, a.v, ch[tt][s % NCH], 0, 0, 0);
                         }
                     }
                 }
@@ -512,6 +524,13 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
                 m = fmaxf(m, __shfl_xor(m, 32));
                 if (g == 0 && token[tt] < M)
                     atomicMax(reinterpret_cast<unsigned int *>(amax_tok + token[tt]), __float_as_uint(m));
+            } else if constexpr (SINK == kSinkWholeRow) {
+                float m = fmaxf(amax[tt][0], __shfl_xor(amax[tt][0], 16));
+                m = fmaxf(m, __shfl_xor(m, 32));
+                if (token[tt] < M) {
+                    if (g == 0) amax_tok[token[tt]] = m / 127.0f;
+                    store_codes_dense(whole[tt], m > 0.0f ? 127.0f / m : 0.0f, Xq + token[tt] * K + 32 * g);
+                }
             } else if constexpr (SINK == kSinkInPlace) {
                 float m = 0.0f;                                   // lane j of a row merges token 4 g + j
 #pragma unroll
@@ -635,7 +654,7 @@ hipError_t launch_dense_block_pass(const uint16_t *X, int64_t M, int nb, int64_t
                                    float *amax_tok, int8_t *Xq, const int32_t *perm, float *T, int64_t ldt, hipStream_t st)
 {
     // behind the pieces: the second rotation's 128 row numbers; the first one's check of the table
-    const size_t smem = (size_t)kPiecesPerBlock * 16 + (SINK == kSinkInPlace ? kBlock * sizeof(int) :
+    const size_t smem = (size_t)kPiecesPerBlock * 16 + (SINK == kSinkInPlace || SINK == kSinkWholeRow ? kBlock * sizeof(int) :
                                                         SINK == kSinkRows ? (size_t)nb * kBlock * sizeof(uint16_t) : 0);
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(rotate_dense_block_kernel<SINK, TT>), smem);
         e != hipSuccess)
@@ -1035,6 +1054,11 @@ hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K,
         hipError_t e = few ? launch_dense_block_pass<kSinkRows, 1>(x, m, nb, ldx, p1, amax_tok, xq, perm, T, ldt, st)
                            : launch_dense_block_pass<kSinkRows, 2>(x, m, nb, ldx, p1, amax_tok, xq, perm, T, ldt, st);
         if (e != hipSuccess) return e;
+        if (nb == 1) {
+            // (in place and a launch for the codes: 24576 / 32768 tokens 27.0 / 31.6, now 17.6 / 18.4)
+            if (e = launch_dense_block_pass<kSinkWholeRow, 1>(x, m, nb, ldx, p2, sx + m0, xq, perm, T, ldt, st); e != hipSuccess) return e;
+            continue;
+        }
         e = two ? launch_dense_block_pass<kSinkInPlace, 2>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st)
                       : launch_dense_block_pass<kSinkInPlace, 1>(x, m, nb, ldx, p2, amax_tok, xq, perm, T, ldt, st);
         if (e != hipSuccess) return e;
