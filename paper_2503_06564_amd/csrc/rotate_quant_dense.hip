@@ -51,12 +51,39 @@ __global__ __launch_bounds__(256) void rotation_pieces_kernel(const float *__res
     pieces[base + (size_t)2 * 4 * 8 * 64 * 8 + off] = (uint16_t)(lo >> 16);
 }
 
+// The fragments of one block, read through a buffer descriptor: the lane's offset is the only vector register of their
+// addresses, and fragment f = (piece * 4 + k-step) * 8 + tile is an offset that all lanes share.  As pointers the addresses
+// of a block took so many registers that a longer ring was spilled (the kernel of both rotations spilled as it was).
+struct PieceReader {
+    __amdgpu_buffer_rsrc_t rsrc;
+    int lane_off;
+    __device__ __forceinline__ PieceReader(const uint4 *pieces, int b, int lane)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint4 *>(pieces + (size_t)b * kPiecesPerBlock), 0,
+                                                 kPiecesPerBlock * 16, 0x00027000)), lane_off(lane * 16)
+    {
+        // (the offset passes through an empty assembly statement: where a wave keeps its block for every
+        // token group the fragment loads would otherwise be hoisted out of the group loop, all 96 of them)
+        asm volatile("" : "+v"(lane_off));
+    }
+    __device__ __forceinline__ v8bf operator()(int f) const
+    {
+        return __builtin_bit_cast(v8bf, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off + (f & 3) * 1024, (f >> 2) * 4096, 0));
+    }
+};
+
 // One block of one token group: out[tt][t][j] = rotated channel 32 g + 4 t + j of token tile tt's
 // token l16 (this lane), amax[tt] = running maximum of |out|.  The A fragments (three pieces x four
-// k-steps per tile) are requested one chunk ahead of the products; the scheduling barriers keep the
+// k-steps per tile) go through a ring of RING chunks of six (half a tile: k-steps and pieces in the order they are
+// multiplied, smallest piece first), RING - 1 chunks ahead of the products; the scheduling barriers keep the
 // compiler from requesting all 96 at once (which would not fit the register file) and from sinking
 // the requests to just before their use (which would expose every load's latency).
-template <int TT>
+// What bounds it is the compute unit's path from L2, 64 bytes a clock, that every block's 96 KB come through once per token group
+// (1152 channels, both rotations: 11.5 of 16 us).  us, pointers and a ring of two / descriptor and four, with the second rotation's first
+// chunk requested before the barrier, pass alone: one rotation 4096 x 1152 12.65 / 12.4, 8192 x 1152 (ring of two) 16.6 / 15.65; both 100 x 512
+// 9.6 / 8.9, 1000 x 1152 19.15 / 18.3, 4096 x 768 16.3 / 15.3, x 1152 22.5 / 21.4, x 1536 28.0 / 26.3, 16384 x 896 64.2 / 60.7; behind a
+// 48 MB copy 4096 x 1152 1.5 less.  (A ring of two in the first rotation is 0.3 slower there; chunks of four and
+// rings of three and four of them in the second one are no faster, or slower behind the copy.)
+template <int TT, int RING>
 __device__ __forceinline__ void rotate_block_dense(const uint16_t *__restrict__ X, int64_t M, int64_t ldx,
                                                    const uint4 *__restrict__ pieces, int b, int64_t tok0, int lane,
                                                    float (&out)[TT][8][4], float (&amax)[TT])
@@ -69,31 +96,23 @@ __device__ __forceinline__ void rotate_block_dense(const uint16_t *__restrict__ 
         int64_t token = tok0 + tt * 16 + l16;
         if (token >= M) token = M - 1;                  // a repeated row: its results are not stored
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            union { uint4 u; v8bf v; } ld;
-            ld.u = *reinterpret_cast<const uint4 *>(X + token * ldx + b * kBlock + 32 * s + 8 * g);
-            xf[tt][s] = ld.v;
-        }
+        for (int s = 0; s < 4; ++s)
+            xf[tt][s] = *reinterpret_cast<const v8bf *>(X + token * ldx + b * kBlock + 32 * s + 8 * g);
     }
-    // (the offset passes through an empty assembly statement: where a wave keeps its block for every
-    // token group the fragment loads would otherwise be hoisted out of the group loop, all 96 of them)
-    int lane_off = lane;
-    asm volatile("" : "+v"(lane_off));
-    const uint4 *pb = pieces + (size_t)b * kPiecesPerBlock + lane_off;
-    // The 96 fragments go through a two-deep ring of chunks of six (half a tile: k-steps and pieces in the
-    // order they are multiplied, smallest piece first): chunk i + 1 is requested, then chunk i multiplied.
+    const PieceReader piece(pieces, b, lane);
     constexpr int CH = 6, NCH = 12 / CH;
-    uint4 fa[2][CH];
-    auto request = [&](uint4 (&f)[CH], int i) {          // chunk i: tile i / NCH, fragments q = 11 - CH (i % NCH) - e
+    v8bf fa[RING][CH];
+    auto request = [&](v8bf (&f)[CH], int i) {          // chunk i: tile i / NCH, fragments q = 11 - CH (i % NCH) - e
         const int t = i / NCH, q0 = 11 - CH * (i % NCH);
 #pragma unroll
-        for (int e = 0; e < CH; ++e) f[e] = pb[((q0 - e) * 8 + t) * 64];      // q = piece * 4 + k-step
+        for (int e = 0; e < CH; ++e) f[e] = piece((q0 - e) * 8 + t);          // q = piece * 4 + k-step
     };
-    request(fa[0], 0);
+#pragma unroll
+    for (int i = 0; i < RING - 1; ++i) request(fa[i], i);
     v4f acc[TT];
 #pragma unroll
     for (int i = 0; i < 8 * NCH; ++i) {
-        if (i + 1 < 8 * NCH) request(fa[(i + 1) & 1], i + 1);
+        if (i + RING - 1 < 8 * NCH) request(fa[(i + RING - 1) % RING], i + RING - 1);
         __builtin_amdgcn_sched_barrier(0);      // the requests go out before this chunk's products, not after them
         const int t = i / NCH, q0 = 11 - CH * (i % NCH);
         if (i % NCH == 0) {
@@ -101,13 +120,10 @@ __device__ __forceinline__ void rotate_block_dense(const uint16_t *__restrict__ 
             for (int tt = 0; tt < TT; ++tt) acc[tt] = v4f{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
-        for (int e = 0; e < CH; ++e) {
-            union { uint4 u; v8bf v; } a;
-            a.u = fa[i & 1][e];
+        for (int e = 0; e < CH; ++e)
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
-                acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, xf[tt][(q0 - e) & 3], acc[tt], 0, 0, 0);
-        }
+                acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i % RING][e], xf[tt][(q0 - e) & 3], acc[tt], 0, 0, 0);
         if (i % NCH == NCH - 1) {
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
@@ -157,7 +173,7 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_kernel(
         float amax[TT];
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) amax[tt] = 0.0f;
-        if (wave < nb) rotate_block_dense<TT>(X, M, ldx, pieces, wave, tok0, lane, out, amax);
+        if (wave < nb) rotate_block_dense<TT, TT == 1 ? 4 : 2>(X, M, ldx, pieces, wave, tok0, lane, out, amax);
         // token maximum: over the four lane groups, then over the waves
         float *const am = amax_s + parity * nw * TOK;
 #pragma unroll
@@ -736,11 +752,22 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_rpr_kernel(
         const int64_t tok0 = tg * 16;
         float out[1][8][4];
         float unused[1] = {0.0f};
-        rotate_block_dense<1>(X, M, ldx, pieces1, b, tok0, lane, out, unused);
+        rotate_block_dense<1, 4>(X, M, ldx, pieces1, b, tok0, lane, out, unused);
 #pragma unroll
         for (int t = 0; t < 8; ++t)
             *reinterpret_cast<float4 *>(T + l16 * LDT + b * kBlock + 32 * g + 4 * t) =
                 make_float4(out[0][t][0], out[0][t][1], out[0][t][2], out[0][t][3]);
+        // the second rotation's fragments as in rotate_block_dense: chunks of six, smallest piece first; the first ones
+        // are on their way while the workgroup waits for its rows
+        constexpr int CH = 6, NCH = 12 / CH, RING = 2;
+        const PieceReader piece(pieces2, b, lane);
+        v8bf fa2[RING][CH];
+        auto request2 = [&](v8bf (&f)[CH], int i) {
+#pragma unroll
+            for (int e = 0; e < CH; ++e) f[e] = piece((11 - CH * (i % NCH) - e) * 8 + i / NCH);
+        };
+#pragma unroll
+        for (int i = 0; i < RING - 1; ++i) request2(fa2[i], i);
         __syncthreads();
         // the second rotation's operands: element e of k-step s is input channel 32 s + 8 g + e of the block
         v8bf xh[4], xm[4], xl[4];
@@ -752,42 +779,29 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_rpr_kernel(
             split3_bf16(v, xh[s], xm[s], xl[s]);
         }
         float amax = 0.0f;
-        int lane_off = lane;                 // as in rotate_block_dense: keep the loads inside the group loop
-        asm volatile("" : "+v"(lane_off));
-        const uint4 *fb = pieces2 + (size_t)b * kPiecesPerBlock + lane_off;
-        // the fragments as in rotate_block_dense: chunks of six (half a tile), smallest piece first, one chunk ahead
-        constexpr int CH = 6;
-        uint4 fa2[2][CH];
-        auto request2 = [&](uint4 (&f)[CH], int i) {
-#pragma unroll
-            for (int e = 0; e < CH; ++e) f[e] = fb[((11 - CH * (i & 1) - e) * 8 + (i >> 1)) * 64];
-        };
-        request2(fa2[0], 0);
         v4f acc[4];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (i + 1 < 16) request2(fa2[(i + 1) & 1], i + 1);
+        for (int i = 0; i < 8 * NCH; ++i) {
+            if (i + RING - 1 < 8 * NCH) request2(fa2[(i + RING - 1) % RING], i + RING - 1);
             __builtin_amdgcn_sched_barrier(0);
-            if ((i & 1) == 0) acc[0] = acc[1] = acc[2] = acc[3] = v4f{0.f, 0.f, 0.f, 0.f};
+            if (i % NCH == 0) acc[0] = acc[1] = acc[2] = acc[3] = v4f{0.f, 0.f, 0.f, 0.f};
             // Every piece product, in four chains by k-step: those of the high pieces, which have 16 bits and whose sums are
             // nearly exact, and the others, smallest first, 2^-8 their size.
             auto multiply = [&](const v8bf (&x)[4], bool high) {
 #pragma unroll
                 for (int e = 0; e < CH; ++e) {
-                    const int q = 11 - CH * (i & 1) - e, s = q & 3, c = (high && q < 4 ? 2 : 0) + (s & 1);
-                    union { uint4 u; v8bf v; } f;
-                    f.u = fa2[i & 1][e];
-                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, x[s], acc[c], 0, 0, 0);
+                    const int q = 11 - CH * (i % NCH) - e, s = q & 3, c = (high && q < 4 ? 2 : 0) + (s & 1);
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa2[i % RING][e], x[s], acc[c], 0, 0, 0);
                 }
             };
             multiply(xl, false);
             multiply(xm, false);
             multiply(xh, true);
-            if (i & 1) {
+            if (i % NCH == NCH - 1) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    out[0][i >> 1][j] = (acc[2][j] + acc[3][j]) + (acc[0][j] + acc[1][j]);
-                    amax = fmaxf(amax, fabsf(out[0][i >> 1][j]));
+                    out[0][i / NCH][j] = (acc[2][j] + acc[3][j]) + (acc[0][j] + acc[1][j]);
+                    amax = fmaxf(amax, fabsf(out[0][i / NCH][j]));
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -881,7 +895,7 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_rpr_wide_kernel(
         for (int b = wave; b < nb; b += nw) {
             float out[1][8][4];
             float unused[1] = {0.0f};
-            rotate_block_dense<1>(X, M, ldx, pieces1, b, tok0, lane, out, unused);   // tokens tok0 .. tok0 + 15 (clamped to M - 1)
+            rotate_block_dense<1, 2>(X, M, ldx, pieces1, b, tok0, lane, out, unused);   // tokens tok0 .. tok0 + 15 (clamped to M - 1)
             if (l16 < 8) {
 #pragma unroll
                 for (int t = 0; t < 8; ++t)
@@ -935,7 +949,7 @@ __global__ __launch_bounds__(256) void channel_absmax_dense_kernel(const uint16_
     for (int64_t tg = (int64_t)blockIdx.x * 4 + wave; tg < groups; tg += (int64_t)gridDim.x * 4) {
         float out[1][8][4];
         float unused[1] = {0.0f};
-        rotate_block_dense<1>(X, M, ldx, pieces, b, tg * 16, lane, out, unused);   // rows past M repeat the last token
+        rotate_block_dense<1, 2>(X, M, ldx, pieces, b, tg * 16, lane, out, unused);   // rows past M repeat the last token
 #pragma unroll
         for (int t = 0; t < 8; ++t)
 #pragma unroll
