@@ -123,14 +123,15 @@ __device__ __forceinline__ void store_out16(uint16_t *p, uint4 v)
     __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t *>(p));
 }
 // 16-byte piece c of a row segment of BYTES bytes, non-temporal only if its whole line lies in the segment (assembly: the compiler
-// joins two stores that differ by the hint only)
+// joins two stores that differ by the hint only; a vector instruction may write the registers of a 16-byte store two wait states
+// behind it, which the compiler sees to for its own stores only)
 template <int BYTES>
 __device__ __forceinline__ void store_whole_lines(uint16_t *seg, int c, uint4 v)
 {
     uint16_t *const p = seg + c * 8;
     const uint32_t line = (uint32_t)(c * 16) - ((uint32_t)(uintptr_t)p & 127u);      // where the piece's line begins in the segment
     const u32x4_t w = {v.x, v.y, v.z, v.w};
-    if (line <= (uint32_t)(BYTES - 128)) asm volatile("global_store_dwordx4 %0, %1, off nt" :: "v"(p), "v"(w) : "memory");
+    if (line <= (uint32_t)(BYTES - 128)) asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" :: "v"(p), "v"(w) : "memory");
     else *reinterpret_cast<u32x4_t *>(p) = w;
 }
 
