@@ -71,6 +71,23 @@ struct PieceReader {
     }
 };
 
+// The workgroups of a die (every eighth one) read one line each per thread of the pieces that all of them are about to walk, 1.7 MB for
+// both rotations of 1152 channels.  They walk them side by side: after other kernels every chunk of every wave waited for memory, and
+// the few in flight were the same ones for all.  us, before and after, calls and their products on inputs of their own: both
+// rotations in a block of width 1152 at 4096 tokens 276.4 / 263.8 (another card 283.6 / 274.3), 8192 x 1152 50.4 / 49.4, 1000 x 1152 24.5 / 24.1; one rotation
+// in the block 197.3 / 192.4 (203.8 / 201.1), 4096 x 1152 19.4 / 18.8.  With less than four workgroups to a die the lines are too few to help and
+// cost 0.1 us (100 x 512 10.8 / 10.9).  The value is of no use but has to be kept until it is there: touched(), behind the first products.
+__device__ __forceinline__ uint32_t touch_pieces(const uint4 *first, const uint4 *second, int nb)
+{
+    if (gridDim.x < 32) return 0;
+    const uint32_t each = (uint32_t)nb * (kPiecesPerBlock / 8), most = (second ? 2 : 1) * each - 1;       // 128-byte lines
+    uint32_t line = (blockIdx.x >> 3) * blockDim.x + threadIdx.x;
+    line = line < most ? line : most;
+    const uint4 *const p = line < each ? first + line * 8 : second + (line - each) * 8;
+    return reinterpret_cast<const uint32_t *>(p)[0];
+}
+__device__ __forceinline__ void touched(uint32_t v) { asm volatile("" :: "v"(v)); }
+
 // One block of one token group: out[tt][t][j] = rotated channel 32 g + 4 t + j of token tile tt's
 // token l16 (this lane), amax[tt] = running maximum of |out|.  The A fragments (three pieces x four
 // k-steps per tile) go through a ring of RING chunks of six (half a tile: k-steps and pieces in the order they are
@@ -166,6 +183,7 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_kernel(
     constexpr int TOK = 16 * TT;
     const int64_t groups = (M + TOK - 1) / TOK;
     int parity = 0;
+    const uint32_t line = touch_pieces(pieces, nullptr, nb);
 
     for (int64_t tg = blockIdx.x; tg < groups; tg += gridDim.x) {
         const int64_t tok0 = tg * TOK;
@@ -174,6 +192,7 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_kernel(
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) amax[tt] = 0.0f;
         if (wave < nb) rotate_block_dense<TT, TT == 1 ? 4 : 2>(X, M, ldx, pieces, wave, tok0, lane, out, amax);
+        touched(line);
         // token maximum: over the four lane groups, then over the waves
         float *const am = amax_s + parity * nw * TOK;
 #pragma unroll
@@ -236,6 +255,8 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_kernel(
 // (Until the results were kept, the second rotation ran twice, for the maxima and for the codes: 4096 x 1664 / 2304 / 4608 44 / 61 / 95
 // us, now 40 / 53 / 81, and 16384 x 4608 331, now 306.  Of the 81, traced, the first rotation has 32, the second 42, the codes 15; all nine
 // piece products make the second 49.)
+// (Tried: the codes' reads of T non-temporal: 4096 x 4608 107.7 -> 103.9 in a stream of calls and 119 -> 123 on new inputs; the first
+// rotation's reads of X: 107.7 -> 115.0.)
 // (Tried and no faster, same box, 4096 and 32768 tokens of 4608 channels: rows of T written in permuted order
 // so that the second rotation reads consecutive rows; 16-byte loads of T with a change of layout through
 // LDS instead of the 4-byte ones; two accumulator chains instead of four.)
@@ -742,17 +763,18 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_rpr_kernel(
     const int b = wave;                                  // nw == nb
 
     // where the second rotation's inputs sit in a row of T: input channel k of block b is channel perm[b*128 + k]
-    for (int k = lane; k < kBlock; k += 64) {
-        const int p = perm[b * kBlock + k];
-        srcs[b * kBlock + k] = p < 0 ? 0 : (p >= K ? K - 1 : p);
-    }
-    __builtin_amdgcn_wave_barrier();     // a wave only reads its own entries (LDS serves a wave's requests in order)
+    // (requested here, into LDS behind the first rotation, which would wait for them otherwise)
+    const int src0 = perm[b * kBlock + lane], src1 = perm[b * kBlock + 64 + lane];
+    const uint32_t line = touch_pieces(pieces1, pieces2, nb);
     int parity = 0;
     for (int64_t tg = blockIdx.x; tg < groups; tg += gridDim.x) {
         const int64_t tok0 = tg * 16;
         float out[1][8][4];
         float unused[1] = {0.0f};
         rotate_block_dense<1, 4>(X, M, ldx, pieces1, b, tok0, lane, out, unused);
+        touched(line);
+        srcs[b * kBlock + lane] = clamp_channel(src0, K);           // a wave only reads its own entries
+        srcs[b * kBlock + 64 + lane] = clamp_channel(src1, K);
 #pragma unroll
         for (int t = 0; t < 8; ++t)
             *reinterpret_cast<float4 *>(T + l16 * LDT + b * kBlock + 32 * g + 4 * t) =
