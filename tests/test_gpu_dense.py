@@ -519,3 +519,28 @@ def test_dense_rpr_ws_with_a_channel_named_twice_takes_little_longer():
             best[name] = min(best.get(name, 1e9), start.elapsed_time(end))
     assert best["twice"] < 3.0 * best["permutation"], best
     rot1.close(); rot2.close()
+
+
+# rows of one block, which the second rotation quantises: whole groups of tokens and a ragged last one
+@pytest.mark.parametrize("M", [24576, 24593])
+def test_dense_rpr_ws_one_block_with_channels_named_twice(M):
+    """A table that names channels twice and out of range, against the call without a workspace: codes within the one step that the two
+    forms' rounding allows, scales within 128 * 2^-24."""
+    say(f"rotate_quant_dense_rpr_ws one block, channels named twice, M={M}")
+    K = 128
+    g = torch.Generator(device=dev()).manual_seed(M)
+    R = torch.randn(1, K, K, generator=g, device=dev()) * 0.088
+    rot1, rot2 = trdq.Rotation(R, torch.rand(K, generator=g, device=dev()) + 0.5), trdq.Rotation(R)
+    perm = torch.randperm(K, generator=g, device=dev()).int()
+    perm[5], perm[K - 1], perm[K // 2], perm[3] = perm[30], perm[30], K + 7, -4
+    X = torch.randn(M, K, generator=g, device=dev()).bfloat16()
+    ws = torch.full((trdq.rotate_quant_dense_rpr_ws_nbytes(M, K),), 0xFF, dtype=torch.uint8, device=dev())
+    out = [(torch.empty((M, K), dtype=torch.int8, device=dev()), torch.empty((M,), device=dev())) for _ in range(2)]
+    trdq.rotate_quant_dense_rpr(X, rot1, perm, rot2, *out[0])
+    trdq.rotate_quant_dense_rpr_ws(X, rot1, perm, rot2, *out[1], ws)
+    torch.cuda.synchronize()
+    assert bool((ws != 0xFF).any())
+    step = (out[0][0].short() - out[1][0].short()).abs()
+    assert step.max() <= 1 and (step != 0).float().mean() < 1e-3
+    assert ((out[0][1] - out[1][1]).abs() <= out[0][1] * 128 * 2.0 ** -24).all()
+    rot1.close(); rot2.close()
