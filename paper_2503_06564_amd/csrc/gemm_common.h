@@ -107,32 +107,48 @@ __device__ __forceinline__ void wait_vmcnt()
 
 // ---- output rows -----------------------------------------------------------------------------------
 // Stored non-temporally, the lines of an output leave a die's L2 while the product runs.  Kept there, up to 32 MB of them are
-// written back when the kernel ends, and the next one starts behind that.  A line that two workgroups share costs memory two
-// partial writes then; so whole lines of a workgroup's row segment only, where the kernel writes much per product.
-// us, ordinary stores and these, products and their passes on inputs of their own (600 MB in turn): int4 (segments of
-// 128 bytes) 384 -> 1024 / 4608 at 4096 tokens 10.9 / 22.7 -> 10.1 / 19.6, 1152 -> 4608 at 16384 134 -> 129; int8 (288 bytes) 256 -> 1152 at
-// 6000 12.7 -> 11.4, 1152 -> 1152 at 9368 30.8 -> 28.2.  Writing through instead (sc1) is slower than either (a block's four linears
-// of width 1152 at 4096 tokens 119 / 113 / 125), and so are non-temporal codes of rotate_quant, in runs of 64 to 128 bytes (117).
-// Where the output is read at once: 1152 -> 4608 -> 1152 at 4096 / 32768 tokens 66.9 / 418 -> 66.6 / 408, with an elementwise pass between
-// 78.4 / 514 -> 78.8 / 490; one product that writes the same buffer again and again 31.7 -> 32.4.
-//
-// 16 bytes of an output row
+// written back when the kernel ends, and the next one starts behind that.  A line that two waves share costs memory two partial
+// writes then, and whoever reads the output soon finds less of it in the caches.  So each kernel stores all, none or only the whole
+// lines of its waves' row segments so, chosen where it is launched.
+// Writing through instead (sc1) is slower than either (a block's four linears of width 1152 at 4096 tokens 119 ordinary / 113 / 125),
+// and so are non-temporal codes of rotate_quant, in runs of 64 to 128 bytes (117).
+enum { kNoLines = 0, kWholeLines = 1, kAllLines = 2 };
+
+// Kernels whose waves store segments of whole lines (128 or 256 bytes): all if the rows of the output begin at lines, else none.
+// us, ordinary / all, pass and product on inputs of their own, and with a pass behind them that reads the output.  Rows at lines: int4
+// 1152 -> 4608 at 4096 tokens 39.9 / 36.9 and 48.2 / 47.7, at 16384 128 / 122 and 172 / 173, 1024 -> 2048 at 1232 14.1 / 13.5 and 17.5 /
+// 17.2; int8 1152 -> 4608 at 16384 107 / 100 and 152 / 152, 512 -> 2064 at 32768 (rows of 2112) 77.1 / 67.4 and 134 / 122.  Rows of 16 bytes
+// more, which share their lines: int4 384 -> 1536 at 16384 29.4 / 34.2 and 49.0 / 56.0, 1152 -> 4608 at 4096 41.5 / 40.8 and 52.9 / 55.1; int8
+// 768 -> 3072 at 4096 24.8 / 25.8 and 34.8 / 38.5, 1152 -> 4608 at 16384 111 / 112 and 166 / 174, 512 -> 2064 at 32768 80.3 / 89.6 and
+// 121 / 138.
+inline int row_lines(const void *Y, int64_t ldy)
+{
+    return ldy % 64 == 0 && reinterpret_cast<uintptr_t>(Y) % 128 == 0 ? kAllLines : kNoLines;
+}
+
+// 16 bytes of an output row, non-temporal
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store_out16(uint16_t *p, uint4 v)
 {
     __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t *>(p));
 }
-// 16-byte piece c of a row segment of BYTES bytes, non-temporal only if its whole line lies in the segment (assembly: the compiler
-// joins two stores that differ by the hint only; a vector instruction may write the registers of a 16-byte store two wait states
-// behind it, which the compiler sees to for its own stores only)
-template <int BYTES>
-__device__ __forceinline__ void store_whole_lines(uint16_t *seg, int c, uint4 v)
+// 16-byte piece c of a row segment of BYTES bytes (whole lines in assembly: the compiler joins two stores that differ by the hint
+// only; a vector instruction may write the registers of a 16-byte store two wait states behind it, which the compiler sees to for
+// its own stores only)
+template <int BYTES, int LINES>
+__device__ __forceinline__ void store_piece(uint16_t *seg, int c, uint4 v)
 {
     uint16_t *const p = seg + c * 8;
-    const uint32_t line = (uint32_t)(c * 16) - ((uint32_t)(uintptr_t)p & 127u);      // where the piece's line begins in the segment
-    const u32x4_t w = {v.x, v.y, v.z, v.w};
-    if (line <= (uint32_t)(BYTES - 128)) asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" :: "v"(p), "v"(w) : "memory");
-    else *reinterpret_cast<u32x4_t *>(p) = w;
+    if constexpr (LINES == kAllLines) {
+        store_out16(p, v);
+    } else if constexpr (LINES == kWholeLines) {
+        const uint32_t line = (uint32_t)(c * 16) - ((uint32_t)(uintptr_t)p & 127u);      // where the piece's line begins in the segment
+        const u32x4_t w = {v.x, v.y, v.z, v.w};
+        if (line <= (uint32_t)(BYTES - 128)) asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" :: "v"(p), "v"(w) : "memory");
+        else *reinterpret_cast<u32x4_t *>(p) = w;
+    } else {
+        *reinterpret_cast<uint4 *>(p) = v;
+    }
 }
 
 // Direct-to-LDS int8 kernels (qgemm_dma.hip).  variant indexes the table in that file.

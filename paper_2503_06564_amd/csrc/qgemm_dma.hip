@@ -105,7 +105,7 @@ struct EpilogueOperands {
     }
 };
 
-template <int TN, int TM, bool DEBUG>
+template <int TN, int TM, bool DEBUG, int LINES>
 __device__ __forceinline__ void epilogue_w8_rows(const v4i (&acc)[TN][TM], const GemmArgs &g,
                                                  int64_t m_wave, int n_wave, int lane, int8_t *stage,
                                                  const EpilogueOperands<TN, TM> &eo)
@@ -145,7 +145,7 @@ __device__ __forceinline__ void epilogue_w8_rows(const v4i (&acc)[TN][TM], const
         const int row = id / LPR, c = id % LPR;
         if (CHUNKS % 64 == 0 || id < CHUNKS) {
             const uint4 v = *reinterpret_cast<const uint4 *>(stage + row * ROWB + c * 16);
-            store_out16(g.Y + (m_wave + row) * g.ldy + n_wave + c * 8, v);
+            store_piece<WN * 2, LINES>(g.Y + (m_wave + row) * g.ldy + n_wave, c, v);
         }
     }
 }
@@ -359,7 +359,7 @@ __device__ __forceinline__ void interleave_hint()
 // step 1; while one feeds the matrix cores the other is being filled.  At the end of tile kt
 // the workgroup waits for tile kt+1, passes the barrier (which also retires every read of
 // tile kt's stage), refills that stage with tile kt+NS and starts reading tile kt+1.
-template <int BM, int BN, int NS, int WGM, int WGN, bool DEBUG, bool ASYM = false>
+template <int BM, int BN, int NS, int WGM, int WGN, bool DEBUG, bool ASYM, int LINES>
 __global__ __launch_bounds__(WGM * WGN * 64) void qgemm8_pipe_kernel(GemmArgs g)
 {
     constexpr int NW = WGM * WGN;                     // waves per workgroup
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void qgemm8_pipe_kernel(GemmArgs g)
     if constexpr (kRowsEpilogue) {
         // every wave is done with the ring: reuse it as the epilogue's staging space
         __syncthreads();
-        epilogue_w8_rows<TN, TM, DEBUG>(acc, g, m0 + wm * WM, n0 + wn * WN, lane, smem + wave * (WM * (WN * 2 + 16)), eo);
+        epilogue_w8_rows<TN, TM, DEBUG, LINES>(acc, g, m0 + wm * WM, n0 + wn * WN, lane, smem + wave * (WM * (WN * 2 + 16)), eo);
     } else {
         epilogue_w8<TN, TM, DEBUG, true>(acc, g, m0 + wm * WM + l16, n0 + wn * WN + lg * 4);
     }
@@ -656,7 +656,7 @@ __global__ __launch_bounds__(2 * kThreads) void qgemm8_pipe2_kernel(GemmArgs g)
                 own[a][b] = (kg == 0 ? acc[a][b] : acc[a][TMH + b]) + o;
             }
     }
-    epilogue_w8_rows<TN, TMH, DEBUG>(own, g, m_own, n0 + wn * WN, lane, ring + XCH + wave * STG, eo);
+    epilogue_w8_rows<TN, TMH, DEBUG, kAllLines>(own, g, m_own, n0 + wn * WN, lane, ring + XCH + wave * STG, eo);
 }
 
 // ---- persistent software-pipelined kernel -------------------------------------------------------
@@ -853,7 +853,7 @@ __global__ __launch_bounds__(kThreads) void qgemm8_persist_kernel(GemmArgs g)
 // is zc * colsum_g[n]; scaled and summed over the groups it is zc * cw[n] with the per-channel float
 // cw[n] = 16 * sum_g s_w[g][n] * colsum_g[n] prepared with the weights, so it costs one multiply-add
 // per output in the epilogue.
-template <int BM, int BN, int NS, int WGM, int WGN, bool DEBUG, bool ASYM = false>
+template <int BM, int BN, int NS, int WGM, int WGN, bool DEBUG, bool ASYM, int LINES>
 __global__ __launch_bounds__(kThreads) void qgemm4_ring_kernel(GemmArgs g)
 {
     static_assert(WGM * WGN == 4, "four waves per workgroup");
@@ -1032,7 +1032,7 @@ __global__ __launch_bounds__(kThreads) void qgemm4_ring_kernel(GemmArgs g)
         for (int i = 0; i < WM / RPI; ++i) {
             const int row = i * RPI + r0;
             const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * ROWB + c * 16);
-            store_out16(g.Y + (m0 + wm * WM + row) * g.ldy + n0 + wn * WN + c * 8, v);
+            store_piece<WN * 2, LINES>(g.Y + (m0 + wm * WM + row) * g.ldy + n0 + wn * WN, c, v);
         }
     }
 }
@@ -1053,13 +1053,18 @@ template <int BM, int BN, int NS, int WGM, int WGN>
 hipError_t launch_ring4(const GemmArgs &a, bool debug, hipStream_t st)
 {
     const size_t smem = (size_t)NS * (BM * 128 + BN * 64 + 1024);
+    static_assert(BN / WGN % 64 == 0, "segments of whole lines");
+    const bool lines = row_lines(a.Y, a.ldy) == kAllLines;
+    auto go = [&](auto kern) { return launch_kernel(kern, a, BM, BN, smem, st); };
     if (a.zc) {
         if (!a.colsumw) return hipErrorInvalidValue;
-        if (debug) return launch_kernel(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, true, true>, a, BM, BN, smem, st);
-        return launch_kernel(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, false, true>, a, BM, BN, smem, st);
+        if (debug) return go(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, true, true, kNoLines>);
+        return lines ? go(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, false, true, kAllLines>)
+                     : go(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, false, true, kNoLines>);
     }
-    if (debug) return launch_kernel(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, true>, a, BM, BN, smem, st);
-    return launch_kernel(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, false>, a, BM, BN, smem, st);
+    if (debug) return go(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, true, false, kNoLines>);
+    return lines ? go(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, false, false, kAllLines>)
+                 : go(qgemm4_ring_kernel<BM, BN, NS, WGM, WGN, false, false, kNoLines>);
 }
 
 // the kernel that takes every shape with asymmetric activations (ring, 128 x 128 x 64, four stages)
@@ -1091,14 +1096,17 @@ hipError_t launch_pipe(const GemmArgs &a, bool debug, hipStream_t st)
         // asymmetric activations: built for the 128 x 144 tiles only; a block of LDS per wave for the zero-point operands
         if constexpr (BM == 128 && BN == 144 && NW == 4) {
             const size_t smem_z = smem + NW * kZpBlock;
-            if (debug) return launch_kernel(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, true, true>, a, BM, BN, smem_z, st, NW * 64);
-            return launch_kernel(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, true>, a, BM, BN, smem_z, st, NW * 64);
+            if (debug) return launch_kernel(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, true, true, kNoLines>, a, BM, BN, smem_z, st, NW * 64);
+            return launch_kernel(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, true, kAllLines>, a, BM, BN, smem_z, st, NW * 64);
         } else {
             return launch_ring_asym(a, debug, st);
         }
     }
-    if (debug) return launch_kernel(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, true>, a, BM, BN, smem, st, NW * 64);
-    return launch_kernel(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false>, a, BM, BN, smem, st, NW * 64);
+    auto go = [&](auto kern) { return launch_kernel(kern, a, BM, BN, smem, st, NW * 64); };
+    if (debug) return go(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, true, false, kNoLines>);
+    if constexpr (BN / WGN % 64 == 0)
+        if (row_lines(a.Y, a.ldy) == kNoLines) return go(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, false, kNoLines>);
+    return go(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, false, kAllLines>);
 }
 
 template <int BM, int BN, int NS, int WGM, int WGN>

@@ -45,8 +45,6 @@ constexpr int tiled_lds(bool asym) { return kParOff + par_bytes(asym); }   // 79
 // Where the activations are: kBlocks: the block-tiled form, whole tiles.  kRows: row-major [M, K], any M and N from one
 // tile on.  kRowsAsym: the same with zero points.
 enum { kBlocks = 0, kRows = 1, kRowsAsym = 2 };
-// Which lines of the output are stored non-temporally, see tiled_lines.
-enum { kNoLines = 0, kWholeLines = 1, kAllLines = 2 };
 
 template <int... Is, class F>
 __device__ __forceinline__ void static_for_seq(std::integer_sequence<int, Is...>, F &&f)
@@ -342,10 +340,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs &g, int tm, int tn, int8
             if (id < 16 * LPR) {
                 const int row = id / LPR, c = id - row * LPR;
                 const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * ROWB + c * 16);
-                uint16_t *const seg = g.Y + (m_wave + b * 16 + row) * g.ldy + n0;
-                if constexpr (LINES == kAllLines) store_out16(seg + c * 8, v);
-                else if constexpr (LINES == kWholeLines) store_whole_lines<kBN * 2>(seg, c, v);
-                else *reinterpret_cast<uint4 *>(seg + c * 8) = v;
+                store_piece<kBN * 2, LINES>(g.Y + (m_wave + b * 16 + row) * g.ldy + n0, c, v);
             }
         }
         __builtin_amdgcn_wave_barrier();
@@ -679,7 +674,7 @@ constexpr int w4_stage(int bm, bool packed) { return w4_soff(bm, packed) + 512; 
 constexpr int w4_par_off(int bm, bool packed) { return w4_stages(packed) * w4_stage(bm, packed); }   // epilogue operands: [128 bias][pad][BM s_x]
 constexpr int w4_lds(int bm, bool packed) { return w4_par_off(bm, packed) + 2048; }     // 69632 B; with 64 tokens 53248, packed 45568 B
 
-template <int BM, bool DEBUG, int FORM, bool PACKED>
+template <int BM, bool DEBUG, int FORM, bool PACKED, int LINES>
 __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kernel(GemmArgs g)
 {
     extern __shared__ __align__(16) int8_t smem[];
@@ -891,7 +886,7 @@ __global__ __launch_bounds__(kThreads, BM == 64 ? 3 : 2) void qgemm4_tiled_kerne
             const int id = i * 64 + lane;
             const int row = id >> 3, c = id & 7;
             const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * ROWB + c * 16);
-            store_out16(g.Y + (m0 + wm * (BM / 2) + b * 16 + row) * g.ldy + n0 + wn * 64 + c * 8, v);
+            store_piece<128, LINES>(g.Y + (m0 + wm * (BM / 2) + b * 16 + row) * g.ldy + n0 + wn * 64, c, v);
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -926,7 +921,7 @@ constexpr int kW4ListRow = 64 * 2 + 16;               // a wave's 64 channels of
 constexpr int kW4ListStg = kW4ListPar + 2048;
 constexpr int kW4ListLds = kW4ListStg + 4 * 16 * kW4ListRow;      // 78848 B: two workgroups per compute unit
 
-template <bool DEBUG>
+template <bool DEBUG, int LINES>
 __global__ __launch_bounds__(kThreads, 2) void qgemm4_list_kernel(GemmArgs g, int stride)
 {
     extern __shared__ __align__(16) int8_t smem[];
@@ -1129,7 +1124,7 @@ __global__ __launch_bounds__(kThreads, 2) void qgemm4_list_kernel(GemmArgs g, in
                 const int q = i * 64 + lane_e;
                 const int row = q >> 3, c = q & 7;
                 const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * kW4ListRow + c * 16);
-                store_out16(g.Y + (m0 + wm * 64 + b * 16 + row) * g.ldy + n0 + wn * 64 + c * 8, v);
+                store_piece<128, LINES>(g.Y + (m0 + wm * 64 + b * 16 + row) * g.ldy + n0 + wn * 64, c, v);
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -1323,7 +1318,9 @@ hipError_t launch_w4(const GemmArgs &a, bool debug, hipStream_t st)
 #ifdef TRDQ_PROBE_PHASES
     debug = false;                                    // the debug pointer receives time stamps instead
 #endif
-    return debug ? go(qgemm4_tiled_kernel<BM, true, FORM, PACKED>) : go(qgemm4_tiled_kernel<BM, false, FORM, PACKED>);
+    if (debug) return go(qgemm4_tiled_kernel<BM, true, FORM, PACKED, kNoLines>);
+    return row_lines(a.Y, a.ldy) == kAllLines ? go(qgemm4_tiled_kernel<BM, false, FORM, PACKED, kAllLines>)
+                                                   : go(qgemm4_tiled_kernel<BM, false, FORM, PACKED, kNoLines>);
 }
 
 }  // namespace
@@ -1341,7 +1338,8 @@ hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st)
         hipLaunchKernelGGL(kern, dim3((unsigned)slots), dim3(kThreads), kW4ListLds, st, a, (int)slots);
         return hipGetLastError();
     };
-    return debug ? go(qgemm4_list_kernel<true>) : go(qgemm4_list_kernel<false>);
+    if (debug) return go(qgemm4_list_kernel<true, kNoLines>);
+    return row_lines(a.Y, a.ldy) == kAllLines ? go(qgemm4_list_kernel<false, kAllLines>) : go(qgemm4_list_kernel<false, kNoLines>);
 }
 
 bool tiled4_rows_supports(const GemmArgs &a)

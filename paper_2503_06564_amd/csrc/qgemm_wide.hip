@@ -96,7 +96,7 @@ __device__ __forceinline__ int acc_read()
 //   unit of a compute unit takes 16 clocks per instruction, and bunched copies stall the waves.
 // The copy stream runs on into the next tile of the workgroup; the block ends with vmcnt(0), so
 // the next tile's first four k-steps have landed when its block starts.
-template <bool DEBUG, bool FULL>
+template <bool DEBUG, bool FULL, int LINES>
 __global__ __launch_bounds__(kThreads) void qgemm8_wide_kernel(GemmArgs g)
 {
     extern __shared__ __align__(16) int8_t smem[];
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(kThreads) void qgemm8_wide_kernel(GemmArgs g)
                 const int64_t m = m_wave + b * 16 + row;
                 const int n = n_wave + c * 8;
                 if (FULL || (m < g.M && n < g.N))
-                    store_out16(g.Y + m * g.ldy + n_wave + c * 8, v);
+                    store_piece<256, LINES>(g.Y + m * g.ldy + n_wave, c, v);
             }
             __builtin_amdgcn_wave_barrier();          // ... and the next token tile's writes after these reads
         });
@@ -411,13 +411,13 @@ __global__ __launch_bounds__(kThreads) void qgemm8_wide_kernel(GemmArgs g)
     }
 }
 
-template <bool DEBUG, bool FULL>
+template <bool DEBUG, bool FULL, int LINES>
 hipError_t launch_wide(const GemmArgs &a, hipStream_t st)
 {
     GemmArgs g = a;
     g.tiles_m = (int)((g.M + kWideBM - 1) / kWideBM);
     g.tiles_n = (g.N + kWideBN - 1) / kWideBN;
-    auto kern = qgemm8_wide_kernel<DEBUG, FULL>;
+    auto kern = qgemm8_wide_kernel<DEBUG, FULL, LINES>;
     if (hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), kWideLds); e != hipSuccess) return e;
     int grid = num_cus();
     if (grid > g.tiles_m * g.tiles_n) grid = g.tiles_m * g.tiles_n;
@@ -439,8 +439,10 @@ hipError_t launch_qgemm8_wide(const GemmArgs &a, bool debug, hipStream_t st)
 {
     if (!wide_supports(a)) return hipErrorInvalidValue;
     const bool full = a.M % kWideBM == 0 && a.N % kWideBN == 0;
-    if (debug) return full ? launch_wide<true, true>(a, st) : launch_wide<true, false>(a, st);
-    return full ? launch_wide<false, true>(a, st) : launch_wide<false, false>(a, st);
+    if (debug) return full ? launch_wide<true, true, kNoLines>(a, st) : launch_wide<true, false, kNoLines>(a, st);
+    if (row_lines(a.Y, a.ldy) == kAllLines)
+        return full ? launch_wide<false, true, kAllLines>(a, st) : launch_wide<false, false, kAllLines>(a, st);
+    return full ? launch_wide<false, true, kNoLines>(a, st) : launch_wide<false, false, kNoLines>(a, st);
 }
 
 }  // namespace gemm

@@ -1,0 +1,90 @@
+"""Where a product's output rows lie in memory lines: the same bits wherever, and no great difference in time."""
+import pytest
+import torch
+
+from paper_2503_06564_amd import trdq
+
+pytestmark = pytest.mark.gpu
+
+
+def _operands(M, K, N, wbits):
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    w = trdq.prepare_weights(0.02 * torch.randn(K, N, generator=g, device="cuda"), None, wbits=wbits)
+    Xq = torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    return w, Xq, torch.rand(M, generator=g, device="cuda") + 0.5
+
+
+# rows that begin at 128-byte lines and rows that do not: int4 (64-token tiles, the ring kernel, with zero points), 128 x 128 tiles, 256 x 256
+# tiles (whole and ragged)
+@pytest.mark.parametrize("wbits,M,K,N,variant,asym", [(4, 1000, 384, 1168, -1, False), (4, 1100, 384, 1152, -1, False), (4, 512, 384, 1152, 6, False),
+                                                     (4, 512, 384, 1152, -1, True), (8, 1024, 512, 1152, 15, False), (8, 512, 512, 1152, 27, False),
+                                                     (8, 300, 512, 1168, 27, False)])
+@pytest.mark.parametrize("pad,shift", [(0, 0), (64, 64), (8, 0), (64, 24)])
+def test_output_rows_anywhere(wbits, M, K, N, variant, asym, pad, shift):
+    w, Xq, sx = _operands(M, K, N, wbits)
+    zc = torch.arange(M, device="cuda", dtype=torch.int32) % 100
+    ldy = N + pad
+    buf = torch.empty(M * ldy + 64, dtype=torch.bfloat16, device="cuda")
+    Y = buf[shift:shift + M * ldy].view(M, ldy)
+    want = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    acc = torch.empty((K // 128, M, N) if wbits == 4 else (M, N), dtype=torch.int32, device="cuda")
+    bias = torch.randn(N, device="cuda")
+
+    def product(y, debug=None):
+        if asym:
+            trdq.qgemm_asym(w, Xq, sx, zc, y, bias=bias, acc_debug=debug)
+        else:
+            trdq.qgemm(w, Xq, sx, y, bias=bias, acc_debug=debug)
+
+    try:
+        trdq.qgemm_set_variant(variant)
+        product(want, acc)                    # the kernel that also leaves its integer sums
+        buf.fill_(7.0)
+        product(Y[:, :N])
+        torch.cuda.synchronize()
+    finally:
+        trdq.qgemm_set_variant(-1)
+    assert torch.equal(Y[:, :N], want)
+    assert bool((Y[:, N:] == 7.0).all()) and bool((buf[:shift] == 7.0).all()) and bool((buf[shift + M * ldy:] == 7.0).all())
+    w.close()
+
+
+def _turns(calls, reps=8):
+    """Milliseconds of each call in turn with the others, the best of several runs."""
+    best = [1e9] * len(calls)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for _ in range(reps):
+        for i, call in enumerate(calls):
+            a.record()
+            for _ in range(12):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("wbits,M,K,N,beside,at", [(4, 16384, 384, 1536, 1544, 1600), (8, 32768, 512, 2064, 2064, 2112)])
+def test_rows_beside_lines_take_little_longer(wbits, M, K, N, beside, at):
+    """Products and a pass behind each that reads the output.  Rows at lines are stored non-temporally, others not: 38.3 / 39.0 us with int4 codes
+    and 108 / 111 with int8 ones (what cost there is is the reader's), both stored so 42.0 / 38.6 and 118 / 111."""
+    w, Xq, sx = _operands(M, K, N, wbits)
+    calls = []
+    for ldy in (beside, at):
+        Y = [torch.empty((M, ldy), dtype=torch.bfloat16, device="cuda")[:, :N] for _ in range(3)]
+        Z = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        if wbits == 4:
+            Xt = torch.empty(trdq.xq_tiled_nbytes(M, K), dtype=torch.int8, device="cuda").zero_()
+            product = lambda y: trdq.qgemm_tiled(w, Xt, sx, y)
+        else:
+            product = lambda y: trdq.qgemm(w, Xq, sx, y)
+
+        def call(product=product, Y=Y, Z=Z):
+            for y in Y:
+                product(y)
+                torch.mul(y, 1.5, out=Z)
+        calls.append(call)
+    t = _turns(calls)
+    print(f"int{wbits} {M} x {K} -> {N}: rows beside lines {t[0] / 36 * 1e3:.1f} us, at lines {t[1] / 36 * 1e3:.1f} us")
+    assert t[0] < 1.05 * t[1], t
+    w.close()
