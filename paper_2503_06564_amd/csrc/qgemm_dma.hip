@@ -10,6 +10,8 @@
 // Two kernels: `ring` (simple: one barrier per k-tile, fragments read right before use) and
 // `pipe` (fragments double-buffered in registers so LDS reads of the next k-step overlap the
 // matrix instructions of the current one; one workgroup of four waves per compute unit).
+#include <type_traits>
+
 #include "gemm_common.h"
 
 namespace trdq {
@@ -500,7 +502,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void qgemm8_pipe_kernel(GemmArgs g)
 // independent instruction streams on every SIMD, which overlap each other's copy issue, LDS reads
 // and barriers the way a second resident workgroup would, without a second tile to give it.
 // Needs at least NS k-tiles per group.
-template <int BM, int BN, int NS, int WGM, int WGN, bool DEBUG, bool ASYM = false>
+template <int BM, int BN, int NS, int WGM, int WGN, bool DEBUG, bool ASYM, int LINES>
 __global__ __launch_bounds__(2 * kThreads) void qgemm8_pipe2_kernel(GemmArgs g)
 {
     static_assert(WGM * WGN == 4, "four waves per group");
@@ -656,7 +658,7 @@ __global__ __launch_bounds__(2 * kThreads) void qgemm8_pipe2_kernel(GemmArgs g)
                 own[a][b] = (kg == 0 ? acc[a][b] : acc[a][TMH + b]) + o;
             }
     }
-    epilogue_w8_rows<TN, TMH, DEBUG, kAllLines>(own, g, m_own, n0 + wn * WN, lane, ring + XCH + wave * STG, eo);
+    epilogue_w8_rows<TN, TMH, DEBUG, LINES>(own, g, m_own, n0 + wn * WN, lane, ring + XCH + wave * STG, eo);
 }
 
 // ---- persistent software-pipelined kernel -------------------------------------------------------
@@ -1037,6 +1039,23 @@ __global__ __launch_bounds__(kThreads) void qgemm4_ring_kernel(GemmArgs g)
     }
 }
 
+}  // namespace
+
+// Which lines of their segments of 288 bytes the kernels with 144 channels to a tile store non-temporally.  us, none / all / whole ones,
+// pass and product on inputs of their own, and with a pass behind them that reads the output.  Up to 16 MB all: 1152 -> 1152 at 5120
+// tokens 22.9 / 21.0 / 22.0 and 27.1 / 26.4 / 26.8, 512 -> 1152 at 6144 16.8 / 14.9 / 16.0 and 22.3 / 22.0 / 22.2.  Beyond, whole ones:
+// 1152 -> 4608 at 3072 29.8 / 29.2 / 28.5 and 37.4 / 38.5 / 37.2, with zero points 1152 -> 3456 at 4096 31.7 / 31.2 / 30.8 and
+// 38.5 / 39.7 / 38.5, at 16384 96.8 / 95.0 / 93.7 and 127 / 130 / 127.  Beyond 28 MB none for fewer than 640 input channels: 512 -> 2304
+// at 11264 32.3 / 32.6 / 32.0 and 47.2 / 48.8 / 48.1, with zero points 512 -> 4608 at 8192 40.7 / 40.6 / 39.5 and 61.2 / 64.2 / 63.7
+// (at 3072 21.5 / 21.2 / 20.7 and 30.4 / 32.3 / 30.9).
+int pipe144_lines(int64_t M, int K, int N)
+{
+    const int64_t values = M * N;
+    return values < (8 << 20) ? kAllLines : K < 640 && values >= (14 << 20) ? kNoLines : kWholeLines;
+}
+
+namespace {
+
 template <typename Kern>
 hipError_t launch_kernel(Kern kern, const GemmArgs &a, int BM, int BN, size_t smem, hipStream_t st,
                          int threads = kThreads)
@@ -1085,6 +1104,14 @@ hipError_t launch_ring(const GemmArgs &a, bool debug, hipStream_t st)
     return launch_kernel(qgemm8_ring_kernel<BM, BN, BK, NS, WGM, WGN, false>, a, BM, BN, smem, st);
 }
 
+template <class F>
+hipError_t with_lines(int lines, F &&launch)
+{
+    if (lines == kAllLines) return launch(std::integral_constant<int, kAllLines>{});
+    if (lines == kWholeLines) return launch(std::integral_constant<int, kWholeLines>{});
+    return launch(std::integral_constant<int, kNoLines>{});
+}
+
 template <int BM, int BN, int NS, int WGM, int WGN>
 hipError_t launch_pipe(const GemmArgs &a, bool debug, hipStream_t st)
 {
@@ -1097,16 +1124,26 @@ hipError_t launch_pipe(const GemmArgs &a, bool debug, hipStream_t st)
         if constexpr (BM == 128 && BN == 144 && NW == 4) {
             const size_t smem_z = smem + NW * kZpBlock;
             if (debug) return launch_kernel(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, true, true, kNoLines>, a, BM, BN, smem_z, st, NW * 64);
-            return launch_kernel(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, true, kAllLines>, a, BM, BN, smem_z, st, NW * 64);
+            return with_lines(pipe144_lines(a.M, a.K, a.N), [&](auto lines) {
+                return launch_kernel(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, true, decltype(lines)::value>, a, BM, BN, smem_z, st, NW * 64);
+            });
         } else {
             return launch_ring_asym(a, debug, st);
         }
     }
     auto go = [&](auto kern) { return launch_kernel(kern, a, BM, BN, smem, st, NW * 64); };
     if (debug) return go(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, true, false, kNoLines>);
-    if constexpr (BN / WGN % 64 == 0)
-        if (row_lines(a.Y, a.ldy) == kNoLines) return go(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, false, kNoLines>);
-    return go(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, false, kAllLines>);
+    if constexpr (BN / WGN % 64 == 0) {
+        // (fewer than 384 input channels into more than 28 MB, none / all, with a reader behind: 256 -> 2048 at 8192 tokens 28.2 / 29.4 us,
+        // 256 -> 1024 at 16384 29.5 / 30.0; 256 -> 1536 at 8192 and 384 -> 4096 at 4096 alike)
+        const bool lines = row_lines(a.Y, a.ldy) == kAllLines && (a.K >= 384 || a.M * a.N < (14 << 20));
+        return lines ? go(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, false, kAllLines>)
+                     : go(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, false, kNoLines>);
+    } else {
+        return with_lines(pipe144_lines(a.M, a.K, a.N), [&](auto lines) {
+            return go(qgemm8_pipe_kernel<BM, BN, NS, WGM, WGN, false, false, decltype(lines)::value>);
+        });
+    }
 }
 
 template <int BM, int BN, int NS, int WGM, int WGN>
@@ -1124,11 +1161,15 @@ hipError_t launch_pipe2(const GemmArgs &a, bool debug, hipStream_t st)
         return hipGetLastError();
     };
     if (a.zc) {
-        if (debug) return go(qgemm8_pipe2_kernel<BM, BN, NS, WGM, WGN, true, true>);
-        return go(qgemm8_pipe2_kernel<BM, BN, NS, WGM, WGN, false, true>);
+        if (debug) return go(qgemm8_pipe2_kernel<BM, BN, NS, WGM, WGN, true, true, kNoLines>);
+        return with_lines(pipe144_lines(a.M, a.K, a.N), [&](auto lines) {
+            return go(qgemm8_pipe2_kernel<BM, BN, NS, WGM, WGN, false, true, decltype(lines)::value>);
+        });
     }
-    if (debug) return go(qgemm8_pipe2_kernel<BM, BN, NS, WGM, WGN, true>);
-    return go(qgemm8_pipe2_kernel<BM, BN, NS, WGM, WGN, false>);
+    if (debug) return go(qgemm8_pipe2_kernel<BM, BN, NS, WGM, WGN, true, false, kNoLines>);
+    return with_lines(pipe144_lines(a.M, a.K, a.N), [&](auto lines) {
+        return go(qgemm8_pipe2_kernel<BM, BN, NS, WGM, WGN, false, false, decltype(lines)::value>);
+    });
 }
 
 template <int BM, int BN, int NS, int WGM, int WGN, int WGS_PER_CU>

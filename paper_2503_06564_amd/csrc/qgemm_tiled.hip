@@ -397,7 +397,7 @@ constexpr int kKsPairs = 2;
 template <int NS> constexpr int ks_par_off() { return kKsPairs * NS * kKsStage; }
 template <int NS> constexpr int ks_lds(bool asym) { return ks_par_off<NS>() + par_bytes(asym); }
 
-template <int NS, bool DEBUG, int FORM>
+template <int NS, bool DEBUG, int FORM, int LINES>
 __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(GemmArgs g)
 {
     constexpr int NG = kKsPairs;
@@ -619,7 +619,7 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
                 if (id < 16 * LPR) {
                     const int row = id / LPR, c = id - row * LPR;
                     const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * ROWB + c * 16);
-                    store_out16(g.Y + (m_own + row) * g.ldy + n0 + c * 8, v);
+                    store_piece<kBN * 2, LINES>(g.Y + (m_own + row) * g.ldy + n0, c, v);
                 }
             }
             __builtin_amdgcn_wave_barrier();
@@ -1189,6 +1189,14 @@ bool tiled_ksplit_applies(const GemmArgs &a)
     return a.K % 128 == 0 && a.K >= 1024 && ((a.M + 127) / 128) * (int64_t)((a.N + kBN - 1) / kBN) <= num_cus();
 }
 
+// Whether the output of row-major codes, of 9.4 MB at most, is stored non-temporally, all lines or none (of block-tiled ones: always).
+// us, none / all, pass and product on inputs of their own, and with a pass behind them that reads the output: block-tiled 1152 -> 1152 at
+// 4096 tokens 17.4 / 16.5 and 21.5 / 21.5, 4608 -> 1152 35.7 / 34.4 and 40.2 / 39.6, 2304 -> 1152 at 3072 21.0 / 20.2 and 24.1 / 24.1; row-
+// major 1152 -> 1152 at 4000 18.3 / 17.5 and 22.6 / 22.6, but 1152 -> 2304 at 1900 16.4 / 16.3 and 21.3 / 23.3, 2304 -> 2304 there 22.5 /
+// 21.7 and 27.3 / 28.6, 1152 -> 3456 at 1000 15.3 / 15.2 and 19.8 / 21.5, 4608 -> 1152 at 3000 34.5 / 33.8 and 38.8 / 39.6.  (Whole lines
+// only: as none.)
+bool ksplit_rows_lines(int64_t M, int K, int N) { return M * N >= 4500000; }
+
 template <int NS, int FORM>
 hipError_t launch_ksplit(const GemmArgs &a, bool debug, hipStream_t st)
 {
@@ -1202,7 +1210,10 @@ hipError_t launch_ksplit(const GemmArgs &a, bool debug, hipStream_t st)
 #ifdef TRDQ_PROBE_PHASES
     debug = false;                                    // the debug pointer receives time stamps instead
 #endif
-    return debug ? go(qgemm8_tiled_ksplit_kernel<NS, true, FORM>) : go(qgemm8_tiled_ksplit_kernel<NS, false, FORM>);
+    if (debug) return go(qgemm8_tiled_ksplit_kernel<NS, true, FORM, kNoLines>);
+    if constexpr (FORM != kBlocks)
+        if (!ksplit_rows_lines(a.M, a.K, a.N)) return go(qgemm8_tiled_ksplit_kernel<NS, false, FORM, kNoLines>);
+    return go(qgemm8_tiled_ksplit_kernel<NS, false, FORM, kAllLines>);
 }
 
 template <int FORM>
