@@ -168,7 +168,7 @@ def test_qgemm_tiled_int4_lists(M, K, N, ldy):
 
 
 # outputs stored with no, all or only the whole 128-byte lines of a tile's rows non-temporal, at every place of a row in its line
-@pytest.mark.parametrize("M,K,N", [(3968, 256, 1008), (4096, 256, 2304), (8192, 384, 1152), (4224, 1024, 2016)])
+@pytest.mark.parametrize("M,K,N", [(3968, 256, 1008), (4096, 384, 1152), (4096, 256, 2304), (8192, 384, 1152), (4224, 1024, 2016)])
 @pytest.mark.parametrize("pad,shift", [(0, 0), (8, 0), (64, 24), (40, 56)])
 def test_output_lines(M, K, N, pad, shift):
     say(f"output lines M={M} K={K} N={N} pad={pad} shift={shift}")
