@@ -304,8 +304,9 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
     const int l16 = lane & 15, g = lane >> 4;
     constexpr int TABLE = SINK == kSinkRows ? 36 * kBlock / 512 : 1;              // K <= 4608, all requests in flight
     int row[TABLE];
+    const bool clears = SINK == kSinkRows && b == 0 && amax_tok;  // (rows of one block: nobody reads the maxima)
     if constexpr (SINK == kSinkRows) {
-        if (b == 0) {
+        if (clears) {
 #pragma unroll
             for (int i = 0; i < TABLE; ++i) {
                 const int k = i * 512 + threadIdx.x;
@@ -331,7 +332,7 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
         if constexpr (SINK == kSinkInPlace) sign = __builtin_amdgcn_readfirstlane(__float_as_uint(amax_tok[0])) & 0x80000000u;
     }
     if constexpr (SINK == kSinkRows) {
-        if (b == 0) {                                             // of two entries with the same row one reads the other's number
+        if (clears) {                                             // of two entries with the same row one reads the other's number
             uint16_t *const last = reinterpret_cast<uint16_t *>(lds_pieces + kPiecesPerBlock);      // [K]
 #pragma unroll
             for (int i = 0; i < TABLE; ++i)
@@ -424,7 +425,7 @@ __global__ __launch_bounds__(512) void rotate_dense_block_kernel(
             }
         }
         if constexpr (SINK == kSinkRows) {                        // the first block's workgroups clear the maxima
-            if (b == 0 && lane < TOK) amax_tok[gr * TOK + lane] = __uint_as_float(sign);
+            if (clears && lane < TOK) amax_tok[gr * TOK + lane] = __uint_as_float(sign);
         }
         uint32_t code[QUANT ? TT : 1][8];
         float whole[SINK == kSinkWholeRow ? TT : 1][8][4];
@@ -1087,8 +1088,9 @@ hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K,
         // 34 / 28, 36 / 33 (beyond, groups of 16 are a second round: 40960 38 / 40), 256 at 28672 43.5 / 41.8; first rotation: 1664 at 1000
         // 27.5 / 24.1, 4608 at 500 30.9 / 27.6.
         const bool few = m * nb <= (nb == 1 ? 32768 : 65536), two = m >= 8192 && !few;
-        hipError_t e = few ? launch_dense_block_pass<kSinkRows, 1>(x, m, nb, ldx, p1, amax_tok, xq, perm, T, ldt, st)
-                           : launch_dense_block_pass<kSinkRows, 2>(x, m, nb, ldx, p1, amax_tok, xq, perm, T, ldt, st);
+        float *const cleared = nb == 1 ? nullptr : amax_tok;
+        hipError_t e = few ? launch_dense_block_pass<kSinkRows, 1>(x, m, nb, ldx, p1, cleared, xq, perm, T, ldt, st)
+                           : launch_dense_block_pass<kSinkRows, 2>(x, m, nb, ldx, p1, cleared, xq, perm, T, ldt, st);
         if (e != hipSuccess) return e;
         if (nb == 1) {
             // (in place and a launch for the codes: 24576 / 32768 tokens 27.0 / 31.6, now 17.6 / 18.4)

@@ -544,3 +544,25 @@ def test_dense_rpr_ws_one_block_with_channels_named_twice(M):
     assert step.max() <= 1 and (step != 0).float().mean() < 1e-3
     assert ((out[0][1] - out[1][1]).abs() <= out[0][1] * 128 * 2.0 ** -24).all()
     rot1.close(); rot2.close()
+
+
+@pytest.mark.parametrize("M", [24576, 40977])
+def test_dense_rpr_ws_one_block_leaves_the_maxima_alone(M):
+    """Rows of one block have their maxima in the wave that quantises them: the row behind the values is neither cleared nor written, and the
+    table is not looked through for channels named twice."""
+    say(f"rotate_quant_dense_rpr_ws one block, maxima, M={M}")
+    K = 128
+    g = torch.Generator(device=dev()).manual_seed(M)
+    rot1, rot2 = (trdq.Rotation(torch.randn(1, K, K, generator=g, device=dev()) * 0.088) for _ in range(2))
+    perm = torch.randperm(K, generator=g, device=dev()).int()
+    X = torch.randn(M, K, generator=g, device=dev()).bfloat16()
+    ws = torch.full((trdq.rotate_quant_dense_rpr_ws_nbytes(M, K),), 0xFF, dtype=torch.uint8, device=dev())
+    out = [(torch.empty((M, K), dtype=torch.int8, device=dev()), torch.empty((M,), device=dev())) for _ in range(2)]
+    trdq.rotate_quant_dense_rpr_ws(X, rot1, perm, rot2, *out[0], ws)
+    trdq.rotate_quant_dense_rpr(X, rot1, perm, rot2, *out[1])
+    torch.cuda.synchronize()
+    rows = ws.view(K + 1, -1)
+    assert bool((rows[K] == 0xFF).all()) and bool((rows[:K, :4 * M] != 0xFF).any())
+    step = (out[0][0].short() - out[1][0].short()).abs()
+    assert step.max() <= 1 and (step != 0).float().mean() < 1e-3
+    rot1.close(); rot2.close()
