@@ -73,14 +73,16 @@ struct PieceReader {
 
 // The workgroups of a die (every eighth one) read one line each per thread of the pieces that all of them are about to walk, 1.7 MB for
 // both rotations of 1152 channels.  They walk them side by side: after other kernels every chunk of every wave waited for memory, and
-// the few in flight were the same ones for all.  us, before and after, calls and their products on inputs of their own: both
-// rotations in a block of width 1152 at 4096 tokens 276.4 / 263.8 (another card 283.6 / 274.3), 8192 x 1152 50.4 / 49.4, 1000 x 1152 24.5 / 24.1; one rotation
-// in the block 197.3 / 192.4 (203.8 / 201.1), 4096 x 1152 19.4 / 18.8.  With less than four workgroups to a die the lines are too few to help and
-// cost 0.1 us (100 x 512 10.8 / 10.9).  The value is of no use but has to be kept until it is there: touched(), behind the first products.
+// the few in flight were the same ones for all.  us, before and after, both rotations in a block and its products, on inputs of their own: width
+// 1152 at 1000 / 4096 / 6000 tokens 153.0 / 263.0 / 405.4 -> 152.2 / 260.3 / 393.7 (4096 on other cards 276 -> 264, 284 -> 274), width
+// 384 at 512 / 6000 73.5 / 147.0 -> 74.2 / 144.6.  (Before one rotation alone it gains nothing in a block, 1152 at 4096 186.5 / 187.3, and
+// costs 0.1 to 0.3 of a call of 512 to 4096 tokens: 1000 x 1152 10.7 / 10.8, with its product 19.0 / 19.2.)  With less than four workgroups to
+// a die the lines are too few to help and cost 0.1 us (100 x 512 10.8 / 10.9).  The value is of no use but has to be kept until it is
+// there: touched(), behind the first products.
 __device__ __forceinline__ uint32_t touch_pieces(const uint4 *first, const uint4 *second, int nb)
 {
     if (gridDim.x < 32) return 0;
-    const uint32_t each = (uint32_t)nb * (kPiecesPerBlock / 8), most = (second ? 2 : 1) * each - 1;       // 128-byte lines
+    const uint32_t each = (uint32_t)nb * (kPiecesPerBlock / 8), most = 2 * each - 1;       // 128-byte lines
     uint32_t line = (blockIdx.x >> 3) * blockDim.x + threadIdx.x;
     line = line < most ? line : most;
     const uint4 *const p = line < each ? first + line * 8 : second + (line - each) * 8;
@@ -183,7 +185,6 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_kernel(
     constexpr int TOK = 16 * TT;
     const int64_t groups = (M + TOK - 1) / TOK;
     int parity = 0;
-    const uint32_t line = touch_pieces(pieces, nullptr, nb);
 
     for (int64_t tg = blockIdx.x; tg < groups; tg += gridDim.x) {
         const int64_t tok0 = tg * TOK;
@@ -192,7 +193,6 @@ __global__ __launch_bounds__(768) void rotate_quant_dense_kernel(
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) amax[tt] = 0.0f;
         if (wave < nb) rotate_block_dense<TT, TT == 1 ? 4 : 2>(X, M, ldx, pieces, wave, tok0, lane, out, amax);
-        touched(line);
         // token maximum: over the four lane groups, then over the waves
         float *const am = amax_s + parity * nw * TOK;
 #pragma unroll
