@@ -1353,7 +1353,7 @@ hipError_t launch_qgemm4_tiled(const GemmArgs &a, bool debug, hipStream_t st)
     if (!tiled4_supports(a)) return hipErrorInvalidValue;
     const int64_t tiles = (a.M / kW4BM) * (a.N / kW4BN), slots = 2 * (int64_t)num_cus();
 #ifdef TRDQ_PROBE_PHASES
-    return launch_w4<kW4BM, kBlocks, false>(a, debug, st);        // the kernel that records time stamps
+    if (debug && tiles > slots) return hipErrorInvalidValue;      // the kernel that takes them records no time stamps
 #endif
     if (tiles <= slots || tiles > 0x3fffffff) return launch_w4<kW4BM, kBlocks, false>(a, debug, st);
     auto go = [&](auto kern) -> hipError_t {

@@ -4,7 +4,8 @@ A build of the library with -DTRDQ_PROBE_PHASES makes every workgroup of the til
 (qgemm8_tiled_kernel, qgemm8_tiled_ksplit_kernel, qgemm4_tiled_kernel) record the constant-rate timer
 and the shader cycle counter at entry, after its first operands have landed, after its k-loop and at
 its end, plus the die and compute unit it ran on; the records land in the buffer that otherwise
-receives the integer sums.  This script prints, per shape: the span from the first entry to the last
+receives the integer sums.  (Int4 products of more than two 128 x 128 tiles per compute unit go to
+qgemm4_list_kernel, which records nothing: that build refuses them here.)  This script prints, per shape: the span from the first entry to the last
 exit, the mean length of the three phases, the shader clock during the k-loop (cycle counter /
 timer) per die, and the k-loop's length in cycles against the number of cycles its matrix
 instructions need (16 per instruction on the SIMD's one matrix pipe; with two workgroups per compute
@@ -20,9 +21,9 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 PROBE_LIB = os.path.join(HERE, "libtrdq_probe.so")
 # (weight bits, tokens, K, N): the four layers of a DiT-XL/2 block at 4096 tokens, one long-K and one many-round
-# int8 case, and the int4 kernel
+# int8 case, and the int4 kernel with one and with two tiles per compute unit
 CASES = [(8, 4096, 1152, 3456), (8, 4096, 1152, 1152), (8, 4096, 1152, 4608), (8, 4096, 4608, 1152),
-         (8, 4096, 4608, 4608), (8, 16384, 1152, 4608), (4, 4096, 1152, 4608), (4, 16384, 1152, 4608)]
+         (8, 4096, 4608, 4608), (8, 16384, 1152, 4608), (4, 4096, 1152, 1024), (4, 4096, 1152, 2048)]
 KERNEL = {1: "qgemm8_tiled_kernel", 2: "qgemm8_tiled_ksplit_kernel", 4: "qgemm4_tiled_kernel"}
 
 

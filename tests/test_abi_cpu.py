@@ -328,3 +328,10 @@ def test_current_stream_without_the_private_lookup(monkeypatch):
     monkeypatch.setattr(trdq, "_raw_stream", None)
     assert trdq._stream(None) == 77 and trdq._stream(None) == 78
     assert trdq._stream(9) == 9 and trdq._stream(types.SimpleNamespace(cuda_stream=11)) == 11
+
+
+def test_phase_probe_asks_for_kernels_that_record():
+    """int4 products of more than two 128 x 128 tiles for each of 256 compute units go to a kernel without time stamps."""
+    from paper_2503_06564_amd import probe_phases
+    int4 = [c for c in probe_phases.CASES if c[0] == 4]
+    assert int4 and all(M * N <= 512 * 128 * 128 for _, M, K, N in int4)
