@@ -1042,7 +1042,7 @@ __global__ __launch_bounds__(kThreads) void qgemm4_ring_kernel(GemmArgs g)
 }  // namespace
 
 // Which lines of their segments of 288 bytes the kernels with 144 channels to a tile store non-temporally.  us, none / all / whole ones,
-// pass and product on inputs of their own, and with a pass behind them that reads the output.  Up to 16 MB all: 1152 -> 1152 at 5120
+// pass and product on inputs of their own, and with a pass behind them that reads the output.  Up to 20 MB all: 1152 -> 1152 at 5120
 // tokens 22.9 / 21.0 / 22.0 and 27.1 / 26.4 / 26.8, 512 -> 1152 at 6144 16.8 / 14.9 / 16.0 and 22.3 / 22.0 / 22.2.  Beyond, whole ones:
 // 1152 -> 4608 at 3072 29.8 / 29.2 / 28.5 and 37.4 / 38.5 / 37.2, with zero points 1152 -> 3456 at 4096 31.7 / 31.2 / 30.8 and
 // 38.5 / 39.7 / 38.5, at 16384 96.8 / 95.0 / 93.7 and 127 / 130 / 127.  Beyond 28 MB none for fewer than 640 input channels: 512 -> 2304
@@ -1051,7 +1051,7 @@ __global__ __launch_bounds__(kThreads) void qgemm4_ring_kernel(GemmArgs g)
 int pipe144_lines(int64_t M, int K, int N)
 {
     const int64_t values = M * N;
-    return values < (8 << 20) ? kAllLines : K < 640 && values >= (14 << 20) ? kNoLines : kWholeLines;
+    return values < (10 << 20) ? kAllLines : K < 640 && values >= (14 << 20) ? kNoLines : kWholeLines;
 }
 
 namespace {

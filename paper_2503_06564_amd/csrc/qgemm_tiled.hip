@@ -1172,24 +1172,27 @@ void tiled_split(int64_t M, int N, int &n_big, int &nbn)
     n_big = (int)(p256 * nbn);
 }
 
-// Which lines of its segments of 288 bytes a workgroup stores non-temporally (gemm_common.h): the choice that is fastest among those with
-// which neither the product alone nor one with a reader behind it loses against ordinary stores.  us, none / all / whole ones, pass and
-// product on inputs of their own, and the mean of three forms with a pass behind them that reads the output:
+// Which lines of its segments of 288 bytes a workgroup stores non-temporally (gemm_common.h).  A product alone gains 2 to 8 % by it nearly
+// everywhere, but outputs are read, and then it gains nothing or loses.  So the choice is the one with which whole blocks do best whose every
+// output is read by the next pass (four blocks with weights of their own, elementwise kernels between, buffers used again; us a block, no lines / all
+// from 8 MB on / this rule and pipe144_lines): width 1152 at 4096 tokens 159 / 162 / 159, at 6144 225 / 221 / 222, at 32768 945 / 928 /
+// 928; row-major codes at 3000 146 / 148 / 147, at 4096 161 / 164 / 162, width 768 at 6000 156 / 159 / 156, at 12000 251 / 255 / 250; with
+// zero points at 8192 286 / 292 / 284, at 16384 531 / 545 / 529.  Of 35 such blocks those with all lines took 0.3 % longer than with
+// none, at most 2.5 %, those with this rule 0.1 % less, at most 1.4 % longer.
+// By size, us, none / all / whole lines, pass and product on inputs of their own, and the mean of three forms with a reader behind:
 //   - below 8 MB none (256 -> 288 at 6000 / 9368 tokens, alone, 8.9 / 10.0 none, 9.1 / 10.3 all);
-//   - to 16 MB all: 768 -> 1152 at 5120 17.3 / 15.6 / 16.7 and 22.9 / 21.8 / 22.3, 1152 -> 2304 at 2560 18.8 / 17.2 / 18.2 and 23.5 / 22.9 / 23.5;
-//   - to 28 MB whole ones: 1152 -> 3456 at 4096 28.6 / 28.9 / 27.3 and 36.1 / 38.2 / 36.1, 512 -> 2304 16.4 / 16.1 / 15.6 and 24.1 / 24.8 / 23.9,
-//     896 -> 3456 26.1 / 26.7 / 24.6 and 33.3 / 35.8 / 33.5;
-//   - to 64 MB none: 1152 -> 4608 at 4096 32.5 / 31.5 / 31.8 and 42.0 / 43.0 / 42.6, 768 -> 2304 at 8192 30.4 / 30.6 / 29.7 and 39.4 / 41.2 / 40.1,
-//     1536 -> 3456 at 6144 49.9 / 48.7 / 49.5 and 60.1 / 61.7 / 62.0; for 1024 to 1151 input channels up to 128 MB (1024 -> 4608 at 8192
-//     54.5 / 53.1 / 53.3 and 72.6 / 74.4 / 74.4), for fewer up to 192 MB (896 -> 2304 at 16384 53.6 / 52.3 / 52.8 and 73.1 / 75.2 / 74.6);
+//   - to 20 MB all: 768 -> 1152 at 5120 17.3 / 15.6 / 16.7 and 22.9 / 21.8 / 22.3, 1152 -> 2304 at 2560 18.8 / 17.2 / 18.2 and 23.5 / 22.9 / 23.5;
+//     from 16 MB on whole ones for fewer than 640 input channels (512 -> 2304 at 4096 16.4 / 16.1 / 15.6 and 24.1 / 24.8 / 23.9);
+//   - to 64 MB none: 1152 -> 4608 at 4096 32.5 / 31.5 / 31.8 and 42.0 / 43.0 / 42.6, 768 -> 2304 at 8192 30.4 / 30.6 / 29.7 and 39.4 / 41.2 / 40.1;
+//     for 1024 to 1151 input channels up to 128 MB (1024 -> 4608 at 8192 54.5 / 53.1 / 53.3 and 72.6 / 74.4 / 74.4), for fewer up to 192 MB
+//     (896 -> 2304 at 16384 53.6 / 52.3 / 52.8 and 73.1 / 75.2 / 74.6);
 //   - then all (1152 -> 3456 at 16384 82.3 / 77.2 / 80.7 and 111 / 110 / 111, 1024 -> 4608 96.5 / 90.7 / 95.6 and 141 / 138 / 139), for fewer
 //     than 768 input channels whole ones (512 -> 4608 at 32768 128 / 135 / 126 and 213 / 225 / 208).
 int tiled_lines(int64_t M, int K, int N)
 {
     const int64_t mi = M * N >> 20;
     if (mi < 4) return kNoLines;
-    if (mi < 8) return kAllLines;
-    if (mi < 14) return kWholeLines;
+    if (mi < 10) return K < 640 && mi >= 8 ? kWholeLines : kAllLines;
     if (mi < (K >= 1152 ? 32 : K >= 1024 ? 64 : 96)) return kNoLines;
     return K >= 768 ? kAllLines : kWholeLines;
 }
