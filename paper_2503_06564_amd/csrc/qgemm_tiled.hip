@@ -395,9 +395,16 @@ constexpr int kKsStage = (8 + kTN) * 1024;
 constexpr int kKsCopies = 9;                         // per wave and k-step
 constexpr int kKsPairs = 2;
 template <int NS> constexpr int ks_par_off() { return kKsPairs * NS * kKsStage; }
+// The output, 9.4 MB at most, of block-tiled codes is stored non-temporally, all lines, that of row-major ones ordinarily.  us, none / all, pass
+// and product on inputs of their own, and with a pass behind them that reads the output: block-tiled 1152 -> 1152 at 4096 tokens 17.4 / 16.5
+// and 21.5 / 21.5, 4608 -> 1152 35.7 / 34.4 and 40.2 / 39.6, 2304 -> 1152 at 3072 21.0 / 20.2 and 24.1 / 24.1; row-major 1152 -> 2304 at 1900
+// 16.4 / 16.3 and 21.3 / 23.3, 1152 -> 3456 at 1000 15.3 / 15.2 and 19.8 / 21.5, 4608 -> 1152 at 3000 34.5 / 33.8 and 38.8 / 39.6, at 4000
+// 39.5 / 38.8 and 43.9 / 44.0; a block of width 1152 whose outputs are read at 1500 tokens, none / all, 112 / 113, at 4000 170 / 171.  Either by the
+// size of the output: two kernels in a block, whose instructions are fetched in turn (1000 tokens 97.0, with one 95.6).
+template <int FORM> constexpr int kKsLines = FORM == kBlocks ? kAllLines : kNoLines;
 template <int NS> constexpr int ks_lds(bool asym) { return ks_par_off<NS>() + par_bytes(asym); }
 
-template <int NS, bool DEBUG, int FORM, int LINES>
+template <int NS, bool DEBUG, int FORM>
 __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(GemmArgs g)
 {
     constexpr int NG = kKsPairs;
@@ -619,7 +626,7 @@ __global__ __launch_bounds__(128 * kKsPairs) void qgemm8_tiled_ksplit_kernel(Gem
                 if (id < 16 * LPR) {
                     const int row = id / LPR, c = id - row * LPR;
                     const uint4 v = *reinterpret_cast<const uint4 *>(stg + row * ROWB + c * 16);
-                    store_piece<kBN * 2, LINES>(g.Y + (m_own + row) * g.ldy + n0, c, v);
+                    store_piece<kBN * 2, kKsLines<FORM>>(g.Y + (m_own + row) * g.ldy + n0, c, v);
                 }
             }
             __builtin_amdgcn_wave_barrier();
@@ -1204,14 +1211,6 @@ bool tiled_ksplit_applies(const GemmArgs &a)
     return a.K % 128 == 0 && a.K >= 1024 && ((a.M + 127) / 128) * (int64_t)((a.N + kBN - 1) / kBN) <= num_cus();
 }
 
-// Whether the output of row-major codes, of 9.4 MB at most, is stored non-temporally, all lines or none (of block-tiled ones: always).
-// us, none / all, pass and product on inputs of their own, and with a pass behind them that reads the output: block-tiled 1152 -> 1152 at
-// 4096 tokens 17.4 / 16.5 and 21.5 / 21.5, 4608 -> 1152 35.7 / 34.4 and 40.2 / 39.6, 2304 -> 1152 at 3072 21.0 / 20.2 and 24.1 / 24.1; row-
-// major 1152 -> 1152 at 4000 18.3 / 17.5 and 22.6 / 22.6, but 1152 -> 2304 at 1900 16.4 / 16.3 and 21.3 / 23.3, 2304 -> 2304 there 22.5 /
-// 21.7 and 27.3 / 28.6, 1152 -> 3456 at 1000 15.3 / 15.2 and 19.8 / 21.5, 4608 -> 1152 at 3000 34.5 / 33.8 and 38.8 / 39.6.  (Whole lines
-// only: as none.)
-bool ksplit_rows_lines(int64_t M, int K, int N) { return M * N >= 4500000; }
-
 template <int NS, int FORM>
 hipError_t launch_ksplit(const GemmArgs &a, bool debug, hipStream_t st)
 {
@@ -1225,10 +1224,7 @@ hipError_t launch_ksplit(const GemmArgs &a, bool debug, hipStream_t st)
 #ifdef TRDQ_PROBE_PHASES
     debug = false;                                    // the debug pointer receives time stamps instead
 #endif
-    if (debug) return go(qgemm8_tiled_ksplit_kernel<NS, true, FORM, kNoLines>);
-    if constexpr (FORM != kBlocks)
-        if (!ksplit_rows_lines(a.M, a.K, a.N)) return go(qgemm8_tiled_ksplit_kernel<NS, false, FORM, kNoLines>);
-    return go(qgemm8_tiled_ksplit_kernel<NS, false, FORM, kAllLines>);
+    return debug ? go(qgemm8_tiled_ksplit_kernel<NS, true, FORM>) : go(qgemm8_tiled_ksplit_kernel<NS, false, FORM>);
 }
 
 template <int FORM>

@@ -14,13 +14,6 @@ def test_pipelined_kernels(M, K, N, lines):
     assert gu.library_rule("_ZN4trdq4gemm13pipe144_linesElii", M, K, N) == lines
 
 
-# row-major codes, K split inside the workgroup: from 9 MB on
-@pytest.mark.parametrize("M,K,N,lines", [(4000, 1152, 1152, ALL), (2000, 2304, 2304, ALL), (1900, 1152, 2304, NONE), (1000, 1152, 3456, NONE),
-                                         (3000, 4608, 1152, NONE)])
-def test_k_split_rows(M, K, N, lines):
-    assert bool(gu.library_rule("_ZN4trdq4gemm17ksplit_rows_linesElii", M, K, N) & 1) == (lines == ALL)
-
-
 # tiled product: all lines from 8 to 20 MB (from 16 on whole ones for fewer than 640 input channels), none to 64 (128 for 1024 to 1151 input channels,
 # 192 for fewer), then all, or whole ones for fewer than 768
 @pytest.mark.parametrize("M,K,N,lines", [(6000, 256, 288, NONE), (9368, 256, 288, NONE), (5120, 768, 1152, ALL), (2560, 1152, 2304, ALL),
