@@ -97,11 +97,12 @@ __device__ __forceinline__ void touched(uint32_t v) { asm volatile("" :: "v"(v))
 // compiler from requesting all 96 at once (which would not fit the register file) and from sinking
 // the requests to just before their use (which would expose every load's latency).
 // What bounds it is the compute unit's path from L2, 64 bytes a clock, that every block's 96 KB come through once per token group
-// (1152 channels, both rotations: 11.5 of 16 us).  us, pointers and a ring of two / descriptor and four, with the second rotation's first
+// (1152 channels, both rotations: 11.5 of a call's 21.6 us).  us, pointers and a ring of two / descriptor and four, with the second rotation's first
 // chunk requested before the barrier, pass alone: one rotation 4096 x 1152 12.65 / 12.4, 8192 x 1152 (ring of two) 16.6 / 15.65; both 100 x 512
 // 9.6 / 8.9, 1000 x 1152 19.15 / 18.3, 4096 x 768 16.3 / 15.3, x 1152 22.5 / 21.4, x 1536 28.0 / 26.3, 16384 x 896 64.2 / 60.7; behind a
-// 48 MB copy 4096 x 1152 1.5 less.  (A ring of two in the first rotation is 0.3 slower there; chunks of four and
-// rings of three and four of them in the second one are no faster, or slower behind the copy.)
+// 48 MB copy 4096 x 1152 1.5 less.  (A ring of two in the first rotation is 0.3 slower there, and 1 % in
+// a block of one rotation, 512 tokens of width 1152 95.8 / 94.8; called again and again it is 0.2 faster, 1000 x 1152 10.5 / 10.7.  Chunks
+// of four and rings of three and four of them in the second one are no faster, or slower behind the copy.)
 template <int TT, int RING>
 __device__ __forceinline__ void rotate_block_dense(const uint16_t *__restrict__ X, int64_t M, int64_t ldx,
                                                    const uint4 *__restrict__ pieces, int b, int64_t tok0, int lane,
@@ -1093,7 +1094,7 @@ hipError_t launch_rotate_quant_dense_rpr_ws(const uint16_t *X, int64_t M, int K,
                            : launch_dense_block_pass<kSinkRows, 2>(x, m, nb, ldx, p1, cleared, xq, perm, T, ldt, st);
         if (e != hipSuccess) return e;
         if (nb == 1) {
-            // (in place and a launch for the codes: 24576 / 32768 tokens 27.0 / 31.6, now 17.6 / 18.4)
+            // (in place and a launch for the codes: 24576 / 32768 tokens 28.4 / 33.1, now 17.1 / 18.2)
             if (e = launch_dense_block_pass<kSinkWholeRow, 1>(x, m, nb, ldx, p2, sx + m0, xq, perm, T, ldt, st); e != hipSuccess) return e;
             continue;
         }
