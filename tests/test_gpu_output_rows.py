@@ -90,5 +90,5 @@ def test_rows_beside_lines_take_little_longer(wbits, M, K, N, beside, at):
         calls.append(call)
     t = _turns(calls)
     print(f"int{wbits} {M} x {K} -> {N}: rows beside lines {t[0] / 36 * 1e3:.1f} us, at lines {t[1] / 36 * 1e3:.1f} us")
-    assert t[0] < 1.05 * t[1], t
+    assert t[0] < 1.06 * t[1], t          # 0.98 to 1.01; stored alike 1.07 and 1.09
     w.close()
